@@ -216,18 +216,25 @@ def fc_cache_stitch(x_obj, x_bg, m_obj, m_bg, out, pixels: int, channels: int, s
                                 _stream(stream)), "fc_cache_stitch")
 
 
+def _source_codes(src, n: int):
+    """int(v) of each source code as n int32, the rest zero: (what holds them, their address)."""
+    if isinstance(src, np.ndarray) and src.dtype.kind == "i":
+        src = src.tolist()
+    if type(src) in (list, tuple) and len(src) == n:     # what can be walked again if it does not hold plain integers
+        try:
+            codes = array("i", src)                      # 1.3 us for 64 codes, the ctypes array below 7.2
+            return codes, codes.buffer_info()[0]
+        except (TypeError, OverflowError):
+            pass
+    codes = (C.c_int32 * n)(*[int(v) for v in src])
+    return codes, C.addressof(codes)
+
+
 def fc_cache_decompress(first, diff_base, n_base: int, alpha: float, extra, n_extra: int, src, frames: int,
                         frame_elems: int, out, stream=None) -> None:
-    try:
-        codes = array("i", src)                # 1.3 us for 64 frames, a ctypes array 7.4
-    except TypeError:
-        codes = array("i", map(int, src))
-    if len(codes) < max(frames, 1):
-        codes.extend([0] * (max(frames, 1) - len(codes)))
-    elif len(codes) > max(frames, 1):
-        raise IndexError("more source codes than frames")
+    held, codes = _source_codes(src, max(frames, 1))
     _check(_lib.fc_cache_decompress(_ptr(first), _ptr(diff_base), n_base, alpha, _ptr(extra), n_extra,
-                                    codes.buffer_info()[0], frames, frame_elems, _ptr(out), _stream(stream)),
+                                    codes, frames, frame_elems, _ptr(out), _stream(stream)),
            "fc_cache_decompress")
 
 

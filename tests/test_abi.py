@@ -1,9 +1,10 @@
 """Host-side checks of the C-ABI library: it loads, exports every declared symbol,
 and its host-only entry points agree with the oracle.  No GPU work is launched."""
+import array
+import ctypes
 import math
 import os
 import re
-import ctypes
 
 import numpy as np
 import pytest
@@ -135,3 +136,28 @@ def test_key_frame_selection_matches_oracle(fc):
     chain = np.array([[1.0, 0.995, 0.98], [0.995, 1.0, 0.995], [0.98, 0.995, 1.0]], dtype=np.float32)
     assert np.array_equal(fc.fc_cache_select_key_frames(chain, 0.99), [0, 2, 2])
     assert fc.fc_cache_workspace_bytes(0) >= 4096 and fc.fc_cache_workspace_bytes(64) >= 64 * 64 * 8
+
+
+@pytest.mark.parametrize("src", [
+    [0, 3, -1, 2], (0, 3, -1, 2), [0.0, 3.9, -1.0, 2.0], [np.int64(0), np.float32(3.0), -1, True],
+    np.array([0, 3, -1, 2]), np.array([0, 3, -1, 2], dtype=np.int8), np.array([0.0, 3.0, -1.0, 2.0]), b"\x00\x03\x01\x02",
+    bytearray(b"\x00\x03\x01\x02"), bytes(64), range(4), [2 ** 32 + 1, -2 ** 31, 2 ** 31, 0], ["0", "3", "-1", "2"], [0, 3], [],
+    array.array("b", [0, 3, -1, 2]), array.array("d", [0.0, 3.0, -1.0, 2.0]), np.array([2 ** 32 - 1, 1], dtype=np.uint32)])
+@pytest.mark.parametrize("once", [False, True])
+def test_decompress_source_codes(monkeypatch, src, once):
+    """Every iterable of numbers gives int(v) per frame, the rest zero, also one that can be walked only once."""
+    from paper_2501_04012_amd import binding
+    frames, seen = max(len(src), 4), {}
+
+    class Library:
+        def fc_cache_decompress(self, first, base, n_base, alpha, extra, n_extra, codes, frames, *rest):
+            address = codes if isinstance(codes, int) else ctypes.addressof(codes)
+            seen["codes"] = list((ctypes.c_int32 * frames).from_address(address))
+            return 0
+
+    monkeypatch.setattr(binding, "_lib", Library())
+    want = list((ctypes.c_int32 * frames)(*[int(v) for v in src]))
+    binding.fc_cache_decompress(None, None, 0, 1.0, None, 0, iter(src) if once else src, frames, 1, None, stream=1)
+    assert seen["codes"] == want
+    with pytest.raises(IndexError):
+        binding.fc_cache_decompress(None, None, 0, 1.0, None, 0, [0] * 5, 4, 1, None, stream=1)
