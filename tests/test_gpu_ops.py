@@ -420,6 +420,24 @@ def test_attention_fp32_matrix_cores(fc, G, nq, nk, d):
     assert np.isfinite(got).all() and rel_l2(got, want) < 2e-5, rel_l2(got, want)
 
 
+@pytest.mark.parametrize("bf,d", [(False, 8), (False, 32), (False, 72), (False, 128), (True, 32), (True, 96), (True, 128)])
+@pytest.mark.parametrize("nq,nk", [(20, 37), (40, 33), (300, 100), (600, 70), (130, 2100)])
+def test_attention_with_infinite_values(fc, bf, d, nq, nk):
+    """An infinite value makes its column infinite (a last key's too: key tiles that hang over the end repeat
+    it), a NaN its column NaN, and nothing else."""
+    torch = _torch()
+    q, k, v = _attn_inputs(2, nq, nk, d, 1.0, bf)
+    want = dit.attention(q.astype(np.float64), k.astype(np.float64), v.astype(np.float64))
+    v[0, nk - 1, 3], v[0, nk - 1, d - 1], v[0, 1, 5], v[0, nk // 2, 7] = np.inf, -np.inf, np.inf, np.nan
+    out = torch.empty((2, nq, d), dtype=torch.bfloat16 if bf else torch.float32, device="cuda:0")
+    fc.fc_op_attention(fc.FC_BF16 if bf else fc.FC_F32, dev(q, bf), dev(k, bf), dev(v, bf), out, 2, nq, nk, d, 0)
+    got = host(out)
+    want[0, :, 3], want[0, :, d - 1], want[0, :, 5], want[0, :, 7] = np.inf, -np.inf, np.inf, np.nan
+    finite = np.isfinite(want)
+    np.testing.assert_array_equal(got[~finite], want[~finite])
+    assert rel_l2(got[finite], want[finite]) < (4e-3 if bf else 2e-5)
+
+
 def test_attention_rows_are_convex_combinations(fc):
     """Property that holds at any size: with all-ones V every output is exactly 1
     (softmax rows sum to 1), also across a ragged last key tile."""
