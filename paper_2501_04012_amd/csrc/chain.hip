@@ -120,7 +120,9 @@ __device__ __forceinline__ bool attend(const float* qs, int nk, int lo, int hi, 
     acc[j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
   }
   if (half && h >= 2) q[HDT - 1] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-  float m = -1e30f, l = 0.0f, probe = 0.0f;               // probe: 0, or NaN once a value is not finite
+  // kNone: below every score, and finite: a lane may meet a tile without a key of its own first
+  constexpr float kNone = -__FLT_MAX__;
+  float m = kNone, l = 0.0f, probe = 0.0f;                // probe: 0, or NaN once a value is not finite
   for (int k0 = 0; k0 < nk; k0 += 16) {
     if (AHEAD) { if (k0 + 16 < nk) fetch(k0 + 16, nxt); }
     else if (k0 > 0) fetch(k0, cur);
@@ -133,11 +135,11 @@ __device__ __forceinline__ bool attend(const float* qs, int nk, int lo, int hi, 
       for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_16x16x4f32(cur.k[j][e], q[j][e], s, 0, 0, 0);
     const int key = k0 + 4 * h;
     bool in[4];
-    float mc = -1e30f;
+    float mc = kNone;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       in[e] = (unsigned)(key + e - lo) < (unsigned)(hi - lo);
-      mc = fmaxf(mc, in[e] ? s[e] : -1e30f);
+      mc = fmaxf(mc, in[e] ? s[e] : kNone);
     }
     const float mn = fmaxf(m, quad_max(mc)), corr = __builtin_amdgcn_exp2f(m - mn);
     m = mn;
