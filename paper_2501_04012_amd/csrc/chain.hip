@@ -450,13 +450,29 @@ hipError_t run_kind(const ChainArgs& a, hipStream_t s) {
 }
 }  // namespace
 
-// Where the chain is the faster form, step of four blocks against one launch per operator, us:
-//   by rows, 128 wide: 64 rows 277 against 318, 8192 475 against 661, 16384 1009 against 946; 64 wide: 64 rows 141 against 287, 16384 397 against 604; 32 wide: 32768 507 against 685
-//   by keys (a workgroup walks them alone, a wave per head): 64 wide and 528 keys 200 against 267, 128 wide and 528 keys
-//   436 against 369, 32 wide and 1024 keys 908 against 830, 16 wide and 2064 keys 833 against 603
-bool chain_fits(const ChainArgs& a, int keys) {
-  return a.D <= 4 * kThreadsPerRow && a.D % 16 == 0 && a.mlp <= 512 && a.mlp % 16 == 0 && (long long)a.rows * a.D <= 1 << 20 &&
-         keys <= 640 && keys * a.D <= 40960;
+// Where the chain is the faster form.  keys: of the longest self-attention; text: of the cross-attention, 0 in the
+// full-3D form, where text and video are one sequence.  A workgroup walks all keys of its rows alone, a wave per
+// head and eight heads at a time, and what it saves in launches shrinks with the width.  Steps of four blocks, us, chain
+// against one launch per operator:
+//   rows: 64 wide 134 against 274 at 16 and 408 against 630 at 3080; 128 wide 308 against 318 at 64, 16384 lose.
+//   full 3-D: 128 wide loses at 1 to 16 heads (4: 167 against 156 at 72 keys; 16: 214 against 160 at 152).  Up to eight
+//     heads the narrower ones win (112 wide, 7 heads: 0.90 to 0.99 of the time); above that 80 wide wins up to 390 keys
+//     (0.99; 512: 1.06), 96 up to 170 (164: 0.99; 264: 1.06), 112 hardly (24: 0.96; 72: 1.02).
+//   cross-attention: up to four heads win at any text tried (128 wide, 4: 0.91 at 4096); five to eight lose at
+//     128 wide from about 600 text keys (512: 1.03 and 0.95, 1024: 1.06 and 0.98 at 64 and 256 rows; 4096: 1.12) and
+//     at 64 wide above 2700 (0.96; 4096: 1.09); more than eight win while self-attention and text have fewer than 16 keys
+//     per column that is missing to 128 (80 wide: 664 keys 0.93; 96: 320 0.94, 664 1.07; 112: 244 1.00, 272 1.04; 128,
+//     16 heads: 80 1.03, 4096 rows but none else win).
+// Above 640 keys a lone head of 16 or 32 columns still wins (1032 keys: 160 against 286 us), but not every form has been
+// timed there.
+bool chain_fits(const ChainArgs& a, int keys, int text) {
+  const int missing = 128 - a.D;
+  if (missing < 0 || a.D % 16 != 0 || a.mlp > 512 || a.mlp % 16 != 0 || (long long)a.rows * a.D > 1 << 20 || keys > 640 ||
+      keys * a.D > 40960)
+    return false;
+  if (text == 0) return missing > 0 && (a.heads <= 8 || 6 * keys <= missing * missing);
+  if (a.heads > 8) return keys + (long long)text < 16 * missing;
+  return text <= (a.heads <= 4 ? 1 << 20 : missing > 0 ? 2560 : 512);    // 2^20: key offsets are 24-bit products
 }
 
 hipError_t launch_chain(const ChainArgs& args, hipStream_t s) {

@@ -333,7 +333,7 @@ struct ChainArgs {
   float *q_out, *k_out, *v_out;            // NEXT, eps NULL
   float* eps;                              // NEXT as the output head: [B, T, H, W, C]
 };
-bool chain_fits(const ChainArgs& a, int keys);           // keys: of the longest self-attention
+bool chain_fits(const ChainArgs& a, int keys, int text);  // keys of the longest self-attention; of the cross-attention (0: none)
 hipError_t launch_chain(const ChainArgs& a, hipStream_t s);
 
 // cache restore (cache.hip)

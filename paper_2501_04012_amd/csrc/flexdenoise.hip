@@ -628,8 +628,9 @@ int run_step(const Ctx& c, float* latent, const fc_schedule* sched, int step, fl
     HIP_TRY(launch_gemv(m->bf16, w.c, D, m->fmod.wt, m->fmod.b, w.fmod, 2 * D, 1, 0, 1, 0, 0, 0, c.s));
   }
 
-  const int keys = cf.attn_mode == FC_ATTN_FACTORIZED_CROSS ? std::max(m->S, cf.frames) : m->Ns;
-  rc = !m->bf16 && chain_fits(chain_base(c), keys) ? run_chains(c, latent) : run_layers(c, latent);
+  const bool fact = cf.attn_mode == FC_ATTN_FACTORIZED_CROSS;
+  const bool chain = !m->bf16 && chain_fits(chain_base(c), fact ? std::max(m->S, cf.frames) : m->Ns, fact ? cf.text_len : 0);
+  rc = chain ? run_chains(c, latent) : run_layers(c, latent);
   if (rc != FC_OK) return rc;
 
   const size_t n = (size_t)c.R * cf.frames * cf.height * cf.width * cf.channels;
