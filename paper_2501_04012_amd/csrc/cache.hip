@@ -130,15 +130,16 @@ hipError_t launch_alpha(const float* first_s, const float* keys_s, const float* 
 // sim[i][j] = sim[j][i] = <frame i, frame j> / (|frame i| |frame j|) in double, rounded once.  A workgroup
 // owns 4 x 4 pairs (J <= I): 16 dot products and the 8 norms from 8 frames' values, each read once and widened once,
 // where a workgroup per pair read two frames for every dot product (64 frames of 10 240: 26 us and 4 for the
-// division, now 9 in all).  Threads take every 512th run of V values in order, so a frame's norm is the same number in
-// whichever workgroup it is taken.
-constexpr int kSimTile = 4, kSimThreads = 512;
-template <int V>
+// division, now 9 in all).  Threads take the same values of every frame in order, so a frame's norm is the same number
+// in whichever workgroup it is taken.  Few workgroups wait for memory: a trip has four values of each of the eight
+// frames in flight, next to each other where frames are made of whole aligned 16-byte pieces, else 512 apart (32 frames
+// of 86 401: 201 us with one value a trip, 95 in two launches of a workgroup per pair, 67 now; of 86 400: 33).
+constexpr int kSimTile = 4, kSimThreads = 512, kSimValues = 4;
+template <bool VEC>
 __global__ __launch_bounds__(kSimThreads) void k_frame_similarity(const float* __restrict__ frames, int T, long long F,
                                                                   float* __restrict__ sim) {
   const int I = blockIdx.y, J = blockIdx.x;
   if (J > I) return;
-  typedef float vec __attribute__((ext_vector_type(V)));
   const float* row[2 * kSimTile];
 #pragma unroll
   for (int r = 0; r < kSimTile; ++r) {                    // rows past the end: the last one again, never stored
@@ -147,12 +148,9 @@ __global__ __launch_bounds__(kSimThreads) void k_frame_similarity(const float* _
   }
   constexpr int NACC = kSimTile * kSimTile + 2 * kSimTile;
   double acc[32] = {};                                    // 16 products, 8 norms, 8 unused
-  for (long long e = (long long)threadIdx.x * V; e < F; e += kSimThreads * V) {
-    vec x[2 * kSimTile];
+  auto add = [&](auto& x, int n) {                        // n values of every row
 #pragma unroll
-    for (int r = 0; r < 2 * kSimTile; ++r) x[r] = *(const vec*)(row[r] + e);
-#pragma unroll
-    for (int c = 0; c < V; ++c) {
+    for (int c = 0; c < n; ++c) {
       double d[2 * kSimTile];
 #pragma unroll
       for (int r = 0; r < 2 * kSimTile; ++r) d[r] = (double)x[r][c];
@@ -163,6 +161,26 @@ __global__ __launch_bounds__(kSimThreads) void k_frame_similarity(const float* _
 #pragma unroll
       for (int r = 0; r < 2 * kSimTile; ++r) acc[16 + r] = __builtin_fma(d[r], d[r], acc[16 + r]);
     }
+  };
+  constexpr long long kTrip = kSimThreads * kSimValues;
+  long long e = 0;
+  f32x4 x[2 * kSimTile];
+  for (; e + kTrip <= F; e += kTrip) {
+#pragma unroll
+    for (int r = 0; r < 2 * kSimTile; ++r) {
+      if constexpr (VEC) {
+        x[r] = *(const f32x4*)(row[r] + e + threadIdx.x * kSimValues);
+      } else {
+#pragma unroll
+        for (int c = 0; c < kSimValues; ++c) x[r][c] = row[r][e + c * kSimThreads + threadIdx.x];
+      }
+    }
+    add(x, kSimValues);
+  }
+  for (e += threadIdx.x; e < F; e += kSimThreads) {       // the last part of a trip, a value at a time
+#pragma unroll
+    for (int r = 0; r < 2 * kSimTile; ++r) x[r][0] = row[r][e];
+    add(x, 1);
   }
   // 32 sums over 64 lanes: a lane hands half of its sums to its partner and takes the other half, five
   // times; what is left of each sum is in two lanes
@@ -200,8 +218,8 @@ __global__ __launch_bounds__(kSimThreads) void k_frame_similarity(const float* _
 hipError_t launch_frame_similarity(const float* frames, int T, long long F, float* sim, hipStream_t s) {
   if (T == 0) return hipSuccess;
   const dim3 grid(ceil_div(T, kSimTile), ceil_div(T, kSimTile));
-  if (F % 4 == 0 && ((uintptr_t)frames & 15) == 0) k_frame_similarity<4><<<grid, kSimThreads, 0, s>>>(frames, T, F, sim);
-  else k_frame_similarity<1><<<grid, kSimThreads, 0, s>>>(frames, T, F, sim);
+  if (F % 4 == 0 && ((uintptr_t)frames & 15) == 0) k_frame_similarity<true><<<grid, kSimThreads, 0, s>>>(frames, T, F, sim);
+  else k_frame_similarity<false><<<grid, kSimThreads, 0, s>>>(frames, T, F, sim);
   return hipGetLastError();
 }
 
