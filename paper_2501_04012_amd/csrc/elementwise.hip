@@ -496,7 +496,8 @@ static hipError_t run_patch_f32(const float* latent, int R, int B, const float* 
   return hipGetLastError();
 }
 
-// impl 0: by shape; 1: general kernel; 2: matrix-core kernel (hipErrorInvalidValue if the shape does not fit it)
+// impl 0: by shape; 1: general kernel; 2: bf16-split matrix-core kernel (hipErrorInvalidValue if the shape does not fit
+// it); kPatchF32: by shape, in fp32 arithmetic
 hipError_t launch_patch_embed(const float* latent, int R, int B, const float* Wp, const float* bp,
                               const float* pos_sp, const float* pos_t, float* x, int T, int H, int W, int C,
                               int p, int D, int rows_per_b, int row_off, int impl, hipStream_t s) {
@@ -517,9 +518,9 @@ hipError_t launch_patch_embed(const float* latent, int R, int B, const float* Wp
     return hipGetLastError();
   }
   const int pd = p * p * C;
-  if (pd <= 16) return run_patch_f32<2>(latent, R, B, Wp, bp, pos_sp, pos_t, x, T, H, W, C, p, D, rows_per_b, row_off, s);
-  if (pd <= 32) return run_patch_f32<4>(latent, R, B, Wp, bp, pos_sp, pos_t, x, T, H, W, C, p, D, rows_per_b, row_off, s);
-  if (pd <= 64) return run_patch_f32<8>(latent, R, B, Wp, bp, pos_sp, pos_t, x, T, H, W, C, p, D, rows_per_b, row_off, s);
+  if (impl != 1 && pd <= 16) return run_patch_f32<2>(latent, R, B, Wp, bp, pos_sp, pos_t, x, T, H, W, C, p, D, rows_per_b, row_off, s);
+  if (impl != 1 && pd <= 32) return run_patch_f32<4>(latent, R, B, Wp, bp, pos_sp, pos_t, x, T, H, W, C, p, D, rows_per_b, row_off, s);
+  if (impl != 1 && pd <= 64) return run_patch_f32<8>(latent, R, B, Wp, bp, pos_sp, pos_t, x, T, H, W, C, p, D, rows_per_b, row_off, s);
   dim3 grid(ceil_div(N, PE_TOK), B);
   size_t sh = (size_t)PE_TOK * p * p * C * sizeof(float);
   k_patch_embed<<<grid, 256, sh, s>>>(latent, R, Wp, bp, pos_sp, pos_t, x, T, H, W, C, p, D, rows_per_b, row_off);

@@ -561,9 +561,9 @@ int run_layers(const Ctx& c, const float* latent) {
   const int text_rows = cf.attn_mode == FC_ATTN_FULL3D_CONCAT ? cf.text_len : 0;
   {
   ProfScope ps(c, PC_PATCH_EMBED);
-  // an fp32 model keeps fp32 arithmetic: the matrix-core kernel (bf16 high/low splits) is for bf16 models only
+  // an fp32 model keeps fp32 arithmetic: the kernel of bf16 high/low splits is for bf16 models only
   HIP_TRY(launch_patch_embed(latent, c.R, w.B, m->p_w, m->p_b, m->pos_sp, m->pos_t, w.x, cf.frames, cf.height,
-                             cf.width, cf.channels, cf.patch, D, m->Ns, text_rows, m->bf16 ? 0 : 1, c.s));
+                             cf.width, cf.channels, cf.patch, D, m->Ns, text_rows, m->bf16 ? 0 : kPatchF32, c.s));
   if (text_rows)
     HIP_TRY(launch_act_to_f32_rows(m->bf16, w.y, w.x, w.B * cf.text_len, D, cf.text_len, m->Ns, 0, c.R, c.use_cfg,
                                    c.s));

@@ -554,6 +554,19 @@ def test_patch_embed_kernels(fc, shape, impl):
         assert (got[b, :row_off] == -7.0).all() and (got[b, row_off + T * S:] == -7.0).all()
 
 
+def test_patch_embed_general_kernel_on_request(fc):
+    """impl 1 is the general kernel at any number of features.  It shows in the order of the sum: (x W + b) + positions
+    loses the product beside a bias of 1e8, (b + position) + x W does not."""
+    import torch
+    T, H, W, C, p, D = 2, 4, 6, 4, 2, 64
+    lat, Wp = torch.full((1, T, H, W, C), 0.5, device="cuda:0"), torch.full((16, D), 2.0 ** -5, device="cuda:0")
+    bp, pos_sp = torch.full((D,), 1e8, device="cuda:0"), torch.full((6, D), -1e8, device="cuda:0")
+    pos_t = torch.zeros(T, D, device="cuda:0")
+    for impl, want in ((1, 0.0), (0, 0.25)):
+        x = torch.full((1, 12, D), -7.0, device="cuda:0")
+        fc.fc_op_patch_embed(lat, 1, 1, Wp, bp, pos_sp, pos_t, x, T, H, W, C, p, D, 12, 0, impl)
+        assert (host(x) == want).all(), impl
+
 
 @pytest.mark.parametrize("T,H,W,C,p,D,R,B,row_off", [
     (3, 10, 14, 4, 2, 260, 2, 4, 3),      # 16 features, ragged positions (35) and columns, guidance copies
@@ -563,6 +576,8 @@ def test_patch_embed_kernels(fc, shape, impl):
     (1, 16, 18, 16, 2, 96, 2, 4, 5),      # 64 features, one frame
     (2, 6, 6, 5, 3, 32, 1, 2, 0),         # 45 features, unaligned
     (2, 8, 8, 8, 4, 68, 1, 2, 0),         # 128 features: the general kernel
+    (3, 12, 20, 8, 4, 132, 2, 4, 3),      # ... ragged tokens (45), requests and their guidance copies
+    (1, 9, 12, 9, 3, 1028, 3, 3, 2),      # 81 features, fewer tokens (12) than a workgroup takes, columns past a pass
 ])
 def test_patch_embed_fp32(fc, T, H, W, C, p, D, R, B, row_off):
     """impl 0 on shapes that stay in fp32: within (features + 3) 2^-24 of the sum of magnitudes."""
