@@ -426,17 +426,25 @@ __global__ __launch_bounds__(256, KS <= 2 ? 4 : 3) void k_patch_embed_f32(const 
       w[s][e] = f < pd ? Wp[(size_t)f * D + col] : 0.0f;
     }
   const size_t frame = (size_t)H * W * C;
+  // offsets of this lane's values in a patch: the divisions stay out of the frames' loop (45 features in runs of 15,
+  // 45 frames of 640 positions, 1536 wide: 237 -> 148 us; the general kernel 186 to 202)
+  constexpr int PIECES = VEC ? KS : 4 * KS;
+  size_t off[PIECES];
+#pragma unroll
+  for (int i = 0; i < PIECES; ++i) {
+    const int f = VEC ? 8 * i + 4 * lh : 8 * (i / 4) + 4 * lh + i % 4;
+    off[i] = tok_off + (f < pd ? (size_t)(f / run) * W * C + f % run : 0);
+  }
   auto fetch = [&](int bt, f32x4 (&dst)[KS]) {
-    const float* src = latent + (size_t)bt * frame + tok_off;                  // bt = b T + t, latents are [R, T, ...]
+    const float* src = latent + (size_t)bt * frame;                            // bt = b T + t, latents are [R, T, ...]
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
       const int f = 8 * s + 4 * lh;
       if constexpr (VEC) {
-        dst[s] = f < pd ? *(const f32x4*)(src + (size_t)(f / run) * W * C + f % run) : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        dst[s] = f < pd ? *(const f32x4*)(src + off[s]) : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
       } else {
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-          dst[s][e] = f + e < pd ? src[(size_t)((f + e) / run) * W * C + (f + e) % run] : 0.0f;
+        for (int e = 0; e < 4; ++e) dst[s][e] = f + e < pd ? src[off[4 * s + e]] : 0.0f;
       }
     }
   };
