@@ -904,8 +904,12 @@ __global__ __launch_bounds__(WR * WC * 64) void k_gemm_f32(const float* __restri
   const int nkt = (K + BK - 1) / BK;
   issue(0, 0);
   for (int kt = 0; kt < nkt; ++kt) {
-    wait_vm<0>();                                        // this K tile has landed
-    __builtin_amdgcn_s_barrier();                        // ... in every wave's part, and the other stage is read out
+    // This K tile has landed and this wave's reads of the other stage are in registers, whatever the scheduler has made
+    // of the multiplications that use them; after the barrier that holds for every wave, and the DMA may overwrite it.
+    __builtin_amdgcn_sched_barrier(0);
+    wait_vm_lgkm0<0>();
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
     if (kt + 1 < nkt) issue(kt + 1, (kt + 1) & 1);
     const unsigned char* st = smem + (kt & 1) * STAGE_BYTES;
 #pragma unroll
