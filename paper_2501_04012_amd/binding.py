@@ -130,17 +130,30 @@ def _ptr(t) -> Optional[int]:
 _current_stream = None       # () -> handle of torch's current stream on the current device
 
 
+def _forget_stream():
+    global _current_stream
+    _current_stream = None
+
+
+os.register_at_fork(after_in_child=_forget_stream)      # torch refuses the device in a forked child: ask it again there
+
+
 def _stream(stream) -> Optional[int]:
     if stream is not None:
         return getattr(stream, "cuda_stream", stream) or None
     global _current_stream
-    if _current_stream is None:
+    source = _current_stream
+    if source is None:
         import torch
         torch.cuda.init()
-        # the handle without a Stream object around it: 0.2 us a call instead of 3.6
-        device, raw = torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
-        _current_stream = lambda: raw(device())
-    return _current_stream() or None
+        # the handle without a Stream object around it: 0.2 us a call instead of 3.6; names torch does not promise
+        device, raw = getattr(torch._C, "_cuda_getDevice", None), getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if device and raw:
+            source = lambda: raw(device())
+        else:
+            source = lambda: torch.cuda.current_stream().cuda_stream
+        _current_stream = source
+    return source() or None
 
 
 def _cfg_struct(cfg: synth.ModelConfig) -> fc_model_config:

@@ -161,3 +161,31 @@ def test_decompress_source_codes(monkeypatch, src, once):
     assert seen["codes"] == want
     with pytest.raises(IndexError):
         binding.fc_cache_decompress(None, None, 0, 1.0, None, 0, [0] * 5, 4, 1, None, stream=1)
+
+
+@pytest.mark.parametrize("private", [True, False])
+def test_current_stream_handle(monkeypatch, private):
+    """With torch's own names for the device and the stream's handle, and without them."""
+    import torch
+    from paper_2501_04012_amd import binding
+    monkeypatch.setattr(torch.cuda, "init", lambda: None)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: type("S", (), {"cuda_stream": 3})())
+    if private:
+        monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 1, raising=False)
+        monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 10 + device, raising=False)
+    else:
+        monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(binding, "_current_stream", None)
+    assert binding._stream(None) == (11 if private else 3)
+    assert binding._stream(7) == 7 and binding._stream(0) is None
+
+
+def test_forked_child_asks_for_the_device_again(monkeypatch):
+    """torch raises in a child forked after the device was used; a handle kept from the parent would bypass that."""
+    from paper_2501_04012_amd import binding
+    monkeypatch.setattr(binding, "_current_stream", lambda: 5)
+    pid = os.fork()
+    if pid == 0:
+        os._exit(0 if binding._current_stream is None else 1)
+    assert os.waitstatus_to_exitcode(os.waitpid(pid, 0)[1]) == 0
+    assert binding._stream(None) == 5
