@@ -227,12 +227,13 @@ __global__ __launch_bounds__(kThreads) void k_chain(ChainArgs a) {
       const int run = a.p * a.C, n = e_pos - a.text_rows, t = a.by_S.div(n), s = n - t * a.S;
       const int ph = a.by_gw.div(s), pw = s - ph * a.by_gw.d;
       const float* src = a.latent + ((((size_t)(e_b < a.R ? e_b : e_b - a.R) * a.T + t) * a.H + (size_t)ph * a.p) * a.W + (size_t)pw * a.p) * a.C;
-      x4 = *(const f32x4*)(a.p_b + ec) + *(const f32x4*)(a.pos_sp + (size_t)s * D + ec);
+      const f32x4 pos = *(const f32x4*)(a.pos_sp + (size_t)s * D + ec) + *(const f32x4*)(a.pos_t + (size_t)t * D + ec);
+      x4 = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
       for (int dh = 0; dh < a.p; ++dh)
 #pragma unroll 4
         for (int f = 0; f < run; ++f)
           x4 += src[(size_t)dh * a.W * a.C + f] * *(const f32x4*)(a.p_w + (size_t)(dh * run + f) * D + ec);
-      x4 += *(const f32x4*)(a.pos_t + (size_t)t * D + ec);
+      x4 = (x4 + *(const f32x4*)(a.p_b + ec)) + pos;
     }
     *(f32x4*)(xt + er * ld + ec) = x4;
   }

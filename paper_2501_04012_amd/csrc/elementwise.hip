@@ -406,7 +406,7 @@ __global__ __launch_bounds__(256, KS <= 2 ? 4 : 3) void k_patch_embed_f32(const 
   const int s_l = s0 + li < S ? s0 + li : S - 1;          // rows past S are computed from a valid token, never stored
   const size_t tok_off = ((size_t)(s_l / gw) * p * W + (size_t)(s_l % gw) * p) * C;
   const int run = p * C;                                  // a patch row is a contiguous run of the latent
-  f32x16 base;
+  f32x16 pos;                                             // added last: (x W + b) + (spatial + temporal position)
   f32x4 w[KS];
   const bool col_in = col0 + li < D;
   const int col = col_in ? col0 + li : D - 1;             // columns past D: never stored
@@ -416,7 +416,7 @@ __global__ __launch_bounds__(256, KS <= 2 ? 4 : 3) void k_patch_embed_f32(const 
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const int tok = s0 + 8 * g + 4 * lh + e;
-      base[4 * g + e] = bias + pos_sp[(size_t)(tok < S ? tok : S - 1) * D + col];
+      pos[4 * g + e] = pos_sp[(size_t)(tok < S ? tok : S - 1) * D + col];
     }
 #pragma unroll
   for (int s = 0; s < KS; ++s)
@@ -463,25 +463,29 @@ __global__ __launch_bounds__(256, KS <= 2 ? 4 : 3) void k_patch_embed_f32(const 
     } else {
       fetch(bt, av);
     }
-    f32x16 acc = base;
+    f32x16 acc;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[i] = 0.0f;
 #pragma unroll
     for (int s = 0; s < KS; ++s)
 #pragma unroll
       for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av[s][e], w[s][e], acc, 0, 0, 0);
     const float pt = pos_t[(size_t)t * D + col];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[i] = (acc[i] + bias) + (pos[i] + pt);
     for (int b = b0; b < B; b += R) {
       float* xu = x + ((size_t)b * rows_per_b + row_off + (size_t)t * S + s0) * D + col0;
       if (whole) {
 #pragma unroll
         for (int g = 0; g < 4; ++g)
 #pragma unroll
-          for (int e = 0; e < 4; ++e) xu[(size_t)(8 * g + e) * D + lane_off] = acc[4 * g + e] + pt;
+          for (int e = 0; e < 4; ++e) xu[(size_t)(8 * g + e) * D + lane_off] = acc[4 * g + e];
       } else {
 #pragma unroll
         for (int g = 0; g < 4; ++g)
 #pragma unroll
           for (int e = 0; e < 4; ++e)
-            if (col_in && s0 + 8 * g + 4 * lh + e < S) xu[(size_t)(8 * g + e) * D + lane_off] = acc[4 * g + e] + pt;
+            if (col_in && s0 + 8 * g + 4 * lh + e < S) xu[(size_t)(8 * g + e) * D + lane_off] = acc[4 * g + e];
       }
     }
   }
