@@ -446,7 +446,10 @@ hipError_t run_chain(const ChainArgs& a, hipStream_t s) {
 template <int HDT>
 hipError_t run_kind(const ChainArgs& a, hipStream_t s) {
   if (a.step[CHAIN_XQ].w) return run_chain<HDT, CHAIN_SELF | CHAIN_CROSS | CHAIN_MLP>(a, s);
-  if (a.step[CHAIN_FC1].w) return run_chain<HDT, CHAIN_SELF | CHAIN_MLP>(a, s);
+  if (a.step[CHAIN_FC1].w) {                              // full 3-D: not at a width of 128 (chain_fits)
+    if constexpr (HDT < 8) return run_chain<HDT, CHAIN_SELF | CHAIN_MLP>(a, s);
+    else return hipErrorInvalidValue;
+  }
   return run_chain<HDT, CHAIN_SELF>(a, s);
 }
 }  // namespace
