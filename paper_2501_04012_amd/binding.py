@@ -231,11 +231,12 @@ def fc_cache_stitch(x_obj, x_bg, m_obj, m_bg, out, pixels: int, channels: int, s
 
 def _source_codes(src, n: int):
     """int(v) of each source code as n int32, the rest zero: (what holds them, their address)."""
-    if isinstance(src, np.ndarray) and src.dtype.kind == "i":
-        src = src.tolist()
-    if type(src) in (list, tuple) and len(src) == n:     # what can be walked again if it does not hold plain integers
+    kind = type(src)
+    if kind is np.ndarray and src.dtype.kind == "i":
+        src, kind = src.tolist(), list
+    if (kind is list or kind is tuple) and len(src) == n:    # what can be walked again if it does not hold plain integers
         try:
-            codes = array("i", src)                      # 1.3 us for 64 codes, the ctypes array below 7.2
+            codes = array("i", src)                          # 1.3 us for 64 codes, the ctypes array below 7.2
             return codes, codes.buffer_info()[0]
         except (TypeError, OverflowError):
             pass
