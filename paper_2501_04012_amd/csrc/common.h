@@ -295,7 +295,11 @@ hipError_t launch_cfg_ddim_noise(float* x, const float* eps_c, const float* eps_
 // scratch (optional, dev, 16-byte aligned): memory the product may use for split-K partial tiles
 // (fp32, at most 64 MB); without it every tile is computed whole
 hipError_t launch_gemm(int bf16, int mode, const void* A, const void* Wt, int M, int N, int K,
-                       const EpiParams& ep, hipStream_t s, void* scratch = nullptr, size_t scratch_bytes = 0);
+                       const EpiParams& ep, hipStream_t s, void* scratch = nullptr, size_t scratch_bytes = 0,
+                       const void* w_parts = nullptr);
+// w_parts (optional, fp32): the weights once more, split into bf16 parts (launch_split_weights, split_weights_bytes)
+size_t split_weights_bytes(int N, int K);
+hipError_t launch_split_weights(const float* Wt, void* out, int N, int K, hipStream_t s);
 hipError_t launch_attention(int bf16, const AttnParams& p, int impl, hipStream_t s);
 // out [KB * heads * kKeyNormChunks] (f32): per (key batch, head) and chunk of the k_tokens rows of
 // k [KB, heads, k_tokens, hd] (bf16), the largest Euclidean row norm (0 for an empty chunk)

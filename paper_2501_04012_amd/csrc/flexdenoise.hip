@@ -67,6 +67,7 @@ struct Profiler {
 struct Linear {           // weights [out, in] in the activation dtype, bias fp32
   void* wt = nullptr;
   float* b = nullptr;
+  void* parts = nullptr;  // fp32, where the products are large: the weights once more, split into bf16 parts
   int in = 0, out = 0;
 };
 
@@ -198,6 +199,11 @@ size_t layout_weights(fc_model* m, unsigned char* base) {
     L.wt = cv.take((size_t)in * out * es);
     L.b = (float*)cv.take((size_t)out * 4);
   };
+  // the products over all token rows of fp32 models that do not run as chains
+  auto lin_rows = [&](Linear& L, int in, int out) {
+    lin(L, in, out);
+    if (!m->bf16 && D > 128) L.parts = cv.take(split_weights_bytes(out, in));
+  };
   lin(m->t1, c.t_embed_dim, D);
   lin(m->t2, D, D);
   lin(m->y, c.text_dim, D);
@@ -209,19 +215,19 @@ size_t layout_weights(fc_model* m, unsigned char* base) {
   if (c.attn_mode == FC_ATTN_FACTORIZED_CROSS) lin(m->xkv, D, c.depth * 2 * D);
   for (int l = 0; l < c.depth; ++l) {
     Block& b = m->blocks[l];
-    lin(b.qkv[0], D, 3 * D);
-    lin(b.proj[0], D, D);
+    lin_rows(b.qkv[0], D, 3 * D);
+    lin_rows(b.proj[0], D, D);
     if (c.attn_mode == FC_ATTN_FACTORIZED_CROSS) {
-      lin(b.qkv[1], D, 3 * D);
-      lin(b.proj[1], D, D);
-      lin(b.xq, D, D);
+      lin_rows(b.qkv[1], D, 3 * D);
+      lin_rows(b.proj[1], D, D);
+      lin_rows(b.xq, D, D);
       b.xkv.in = D; b.xkv.out = 2 * D;                   // its rows of the product that serves all blocks
       b.xkv.wt = base ? (unsigned char*)m->xkv.wt + (size_t)l * 2 * D * D * es : nullptr;
       b.xkv.b = base ? m->xkv.b + (size_t)l * 2 * D : nullptr;
-      lin(b.xproj, D, D);
+      lin_rows(b.xproj, D, D);
     }
-    lin(b.fc1, D, M);
-    lin(b.fc2, M, D);
+    lin_rows(b.fc1, D, M);
+    lin_rows(b.fc2, M, D);
   }
   lin(m->fmod, D, 2 * D);
   lin(m->fout, D, m->pd);
@@ -331,7 +337,7 @@ int linear(const Ctx& c, int cat, int mode, const void* A, const Linear& L, int 
            void* scratch = nullptr, size_t scratch_bytes = 0) {
   ep.bias = L.b;
   ProfScope ps(c, cat);
-  HIP_TRY(launch_gemm(c.m->bf16, mode, A, L.wt, M, L.out, L.in, ep, c.s, scratch, scratch_bytes));
+  HIP_TRY(launch_gemm(c.m->bf16, mode, A, L.wt, M, L.out, L.in, ep, c.s, scratch, scratch_bytes, L.parts));
   return FC_OK;
 }
 
@@ -748,6 +754,7 @@ int fc_model_set_weights(fc_model* m, const float* blob, size_t n_floats) {
   };
   auto up_lin = [&](Linear& L) -> hipError_t {
     hipError_t e = up_matrix_t(L.wt, L.in, L.out);
+    if (e == hipSuccess && L.parts) e = launch_split_weights((const float*)L.wt, L.parts, L.out, L.in, nullptr);
     if (e != hipSuccess) return e;
     return up_f32(L.b, L.out);
   };

@@ -1,7 +1,7 @@
 // Linear layers: C[M,N] = A[M,K] * Wt[N,K]^T with fused epilogues.
 //   bf16: MFMA (v_mfma_f32_32x32x16_bf16) kernel, operands DMA'd into swizzled LDS tiles,
 //         fp32 accumulation.
-//   fp32: MFMA (v_mfma_f32_32x32x2_f32) kernels; a plain LDS-tiled FMA kernel for operands that
+//   fp32: MFMA kernels, on three bf16 parts of a value or (small products) v_mfma_f32_32x32x2_f32; a plain LDS-tiled FMA kernel for operands that
 //         are not made of whole aligned 16-byte chunks.
 // Both operands are contiguous along K ("TN" form): activations are [tokens, K]
 // and weights are stored [out, in].
@@ -836,17 +836,15 @@ static hipError_t run_skinny(const void* A, const void* Wt, int M, int N, int K,
   return run_skinny_waves<T, 4, MODE>((const T*)A, (const T*)Wt, M, N, K, ep, s);
 }
 
-// ---------------------------------------------------------------- fp32 on the matrix cores
-// v_mfma_f32_32x32x2_f32: exact fp32 products and sums at 256 FLOP per clock and CU.  Operand
+// ---------------------------------------------------------------- fp32 on the fp32 matrix cores
+// v_mfma_f32_32x32x2_f32: exact fp32 products and sums at 256 FLOP per clock and CU.  For products that are at most one
+// 64x64 tile to a CU (the dispatch): a slice of K is over sooner here than in the kernel below, which is built for
+// throughput (216 tiles of 500 x 1728 x 576: 16 us against 19).  Operand
 // lane (i, h) supplies row i, k = h, so four instructions consume one 16-byte chunk per lane (4
 // floats of K; instruction e contracts elements e of both halves' chunks): tiles, LDS layout,
 // DMA and fragment addressing are those of the bf16 kernels with 32 floats of K in a 128-byte
-// row.  An instruction takes 64 cycles, eight times a bf16 one per byte of operand, so nothing but the
-// matrix pipe bounds this kernel: plain double buffering, no pinned schedule, one 32x32
-// accumulator per wave (small tiles fill the chip more evenly, and more waves cover the barriers),
-// several workgroups per CU, and the column-form epilogue (a wave-store covers 32 consecutive
-// floats of a row).  125-131 TFLOP/s on large products, where the vendor's fp32 product reaches
-// 154 and the FMA kernel below 58-65 (4096 x 4608 x 1152: 669 -> 332 us; x 1152 x 4608: 911 -> 374).
+// row.  Plain double buffering, no pinned schedule, one 32x32 accumulator per wave, and the column-form epilogue
+// (a wave-store covers 32 consecutive floats of a row).
 // K need only be a whole number of chunks: past its end a lane's offset is moved out of the buffer
 // resource's range, which loads zero, as do rows past the end of an operand.
 template <int BM, int BN, int WR, int WC, typename Epi>
@@ -949,6 +947,252 @@ static hipError_t run_f32(const void* A, const void* Wt, int M, int N, int K, co
   const long long grid = ((long long)tiles_m * tiles_n + 255) / 256 * 256;
   if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
   k_gemm_f32<BM, BN, WR, WC, Epi><<<(unsigned)grid, WR * WC * 64, 0, s>>>((const float*)A, (const float*)Wt, M, N, K, tiles_m, tiles_n, epi);
+  return hipGetLastError();
+}
+
+// ---------------------------------------------------------------- fp32 on the bf16 matrix cores
+// An fp32 value is the sum of three bf16 values of 8 bits each (high, middle, low: exact), so an fp32 product
+// is nine bf16 products that the matrix cores form exactly and add in fp32.  Six of them are taken: what is
+// left out (middle x low twice, low x low) is at most 2^-23 of a product and of either sign, below what the fp32
+// additions round away.  Six bf16 instructions do what eight v_mfma_f32_32x32x2_f32 of twice the length do:
+// 2.7 times the rate of the fp32 matrix pipe, and with fewer roundings (six per 16 products instead of eight) the
+// smaller error: 0.84 to 0.88 of that kernel's against float64, over 24 shapes with K from 256 to 4608.
+//
+// A value is split once, on its way from global memory (registers, one slice of 16 of K ahead) to LDS, where a row
+// holds its three parts of a slice one after the other, 96 bytes: rows 24 banks apart, so that the 8 rows that a
+// ds_read_b128 takes at a time do not meet.  SPLIT_W: the weights have been split already (k_split_weights, once per
+// model) and come by DMA, two slices ahead, three stages.  Fragments are those of the bf16 kernels: lane (i, h) holds
+// row i, k = 8h .. 8h+7.  Of a slice's instructions the splitting (7.5 per value) is spread over the matrix
+// instructions; written as a block behind them it cost 10 %.
+// LDS bounds the small tiles (64x128: 580 cycles of reads and writes against 384 of matrix instructions per slice),
+// the power limit the large ones (1.2 PFLOP/s of bf16 products, as in the bf16 kernels).
+// us, fp32 matrix pipe, weights split on the way, and before: 4096 x 3456 x 1152 269, 205, 167; 4096 x 4608 x 1152 339, 254,
+// 212; 4096 x 1152 x 4608 372, 348, 291; 4096 x 1152 x 1152 116, 95, 79; 16000 x 256 x 256 24.6, 19, 18.
+// K need only be a whole number of 16-byte chunks: past its end a lane's offset is moved out of the buffer
+// resource's range, which loads zero, as do rows past the end of an operand.
+//
+// The high part is rounded from the value held to bf16's finite range: infinities, NaN and what rounding would
+// push to infinity go into the low part, whose one product is with the other operand's high part, so that they
+// come out as fp32 products would have them and not as inf - inf or inf * 0.
+typedef __attribute__((ext_vector_type(2))) unsigned u32x2;
+constexpr float kBf16Max = 3.3895313892515355e38f;       // largest finite bf16
+__device__ __forceinline__ unsigned pack_bf16(float x, float y) {
+  bf16x2 p;
+  p[0] = (bf16_t)x; p[1] = (bf16_t)y;
+  unsigned w = __builtin_bit_cast(unsigned, p);
+  asm("" : "+v"(w));                                     // else the first half is converted once more where it is used alone
+  return w;
+}
+__device__ __forceinline__ float bf16_lo(unsigned p) { return __builtin_bit_cast(float, p << 16); }
+__device__ __forceinline__ float bf16_hi(unsigned p) { return __builtin_bit_cast(float, p & 0xffff0000u); }
+
+// f(A) .. f(B - 1) as compile-time constants
+template <int A, int B, typename F>
+__device__ __forceinline__ void unrolled(F f) {
+  if constexpr (A < B) {
+    f(std::integral_constant<int, A>{});
+    unrolled<A + 1, B>(f);
+  }
+}
+
+template <int BM, int BN, int WR, int WC, int PER_SIMD, bool SPLIT_W, typename Epi>
+__global__ __launch_bounds__(WR * WC * 64, PER_SIMD) void k_gemm_f32_parts(const float* __restrict__ A, const void* __restrict__ Wt,
+                                                                     int M, int N, int K, int tiles_m, int tiles_n, Epi epi) {
+#if defined(__HIP_DEVICE_COMPILE__)   // buffer resources are a device-side type: the host pass sees an empty body
+  constexpr int NW = WR * WC, NT = NW * 64;
+  constexpr int WTM = BM / WR, WTN = BN / WC, TM = WTM / 32, TN = WTN / 32;
+  constexpr int LA = BM * 4 / NT, LB = SPLIT_W ? 0 : BN * 4 / NT;      // 16-byte chunks per thread and slice to be split
+  constexpr int WL = SPLIT_W ? BN * 96 / 1024 : 0, LD = (WL + NW - 1) / NW;   // wave-loads of split weights per slice, and per wave
+  static_assert(BM * 4 % NT == 0 && (SPLIT_W || BN * 4 % NT == 0) && BN % 32 == 0, "loads must divide among threads");
+  constexpr int ROWS = SPLIT_W ? BM : BM + BN;           // split on the way
+  constexpr int STAGE = ROWS * 96, W_STAGE = BN * 96;
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wr = wave / WC, wc = wave % WC;
+  const int li = lane & 31, lh = lane >> 5;
+  // workgroup -> tile: runs of 32 consecutive tiles per XCD, 8 tile rows before the next tile column
+  const int vb = blockIdx.x, local = vb >> 3;
+  const int t = ((local >> 5) * 8 + (vb & 7)) * 32 + (local & 31);
+  if (t >= tiles_m * tiles_n) return;
+  const int per_group = 8 * tiles_n, group = t / per_group, first_m = group * 8, gsz = min(tiles_m - first_m, 8);
+  const int bm0 = (first_m + (t % per_group) % gsz) * BM, bn0 = ((t % per_group) / gsz) * BN;
+  const int slices = (K + 15) / 16;
+
+  const auto ra = __builtin_amdgcn_make_buffer_rsrc((void*)(A + (size_t)bm0 * K), 0, (int)((unsigned)min(M - bm0, BM) * (unsigned)K * 4u), 0x00020000);
+  // split weights: [N / 32][slices][32 rows][3 parts][16] bf16, rows past N zero
+  const int w_blocks = min((N + 31) / 32 - bn0 / 32, BN / 32);
+  const auto rb = SPLIT_W ? __builtin_amdgcn_make_buffer_rsrc((void*)((const unsigned char*)Wt + (size_t)(bn0 / 32) * slices * 3072), 0, (int)((unsigned)w_blocks * (unsigned)slices * 3072u), 0x00020000)
+                          : __builtin_amdgcn_make_buffer_rsrc((void*)((const float*)Wt + (size_t)bn0 * K), 0, (int)((unsigned)min(N - bn0, BN) * (unsigned)K * 4u), 0x00020000);
+  // chunk tid + NT j of a slice: row (tid >> 2) + NT / 4 j, floats 4c .. 4c+3
+  const int row0 = tid >> 2, c = tid & 3;
+  f32x4 raw[2][LA + LB];                                 // of the next slice and of the one behind it
+  auto fetch = [&](f32x4 (&raw)[LA + LB], int j, int ks) {
+    const unsigned off = (unsigned)(row0 + NT / 4 * (j < LA ? j : j - LA)) * (unsigned)K * 4u + (unsigned)c * 16u;
+    raw[j] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(j < LA ? ra : rb, (int)(ks * 16 + c * 4 < K ? off : 0x80000000u), ks * 64, 0));
+  };
+  // split weights go to LDS as they lie: 1 KB a wave-load, three to a block of 32 rows; wave-load wave + NW j
+  const int wave_u = __builtin_amdgcn_readfirstlane(wave);
+  int w_off[LD > 0 ? LD : 1];
+#pragma unroll
+  for (int j = 0; j < LD; ++j)
+    w_off[j] = (wave_u + NW * j) / 3 * slices * 3072 + (wave_u + NW * j) % 3 * 1024 + lane * 16;
+  auto request = [&](int ks, int stage) {
+#pragma unroll
+    for (int j = 0; j < LD; ++j) {
+      if (WL % NW != 0 && wave_u + NW * j >= WL) break;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lds_void*)(smem + 2 * STAGE + stage * W_STAGE + (wave_u + NW * j) * 1024), 16, w_off[j], ks * 3072, 0, 0);
+    }
+  };
+  auto put = [&](int j, int stage, u32x2 h, u32x2 m, u32x2 l) {
+    const int row = j < LA ? row0 + NT / 4 * j : BM + row0 + NT / 4 * (j - LA);
+    unsigned char* dst = smem + stage * STAGE + row * 96 + c * 8;
+    *(u32x2*)dst = h;
+    *(u32x2*)(dst + 32) = m;
+    *(u32x2*)(dst + 64) = l;
+  };
+  // Step X of the splitting of slice ks: chunk X / 6, a pair of its values after the other in steps of 3, 5 and 7 vector
+  // instructions; behind the last the chunk is fetched for slice ks + 2.
+  float ra0 = 0.0f, ra1 = 0.0f, a0 = 0.0f, a1 = 0.0f;    // of the pair: what is left of the value held to range, and of the value
+  unsigned h0 = 0, m0 = 0, l0 = 0, h1 = 0, m1 = 0;
+  auto split_step = [&](auto step, auto par, int ks) {
+    constexpr int P = decltype(par)::value;                // ks & 1
+    constexpr int X = decltype(step)::value, j = X / 6, half = X % 6 / 3;
+    if constexpr (X % 3 == 0) {
+      a0 = raw[P][j][2 * half]; a1 = raw[P][j][2 * half + 1];
+      ra0 = __builtin_amdgcn_fmed3f(a0, -kBf16Max, kBf16Max); ra1 = __builtin_amdgcn_fmed3f(a1, -kBf16Max, kBf16Max);
+      (half ? h1 : h0) = pack_bf16(ra0, ra1);
+    } else if constexpr (X % 3 == 1) {
+      const unsigned h = half ? h1 : h0;
+      (half ? m1 : m0) = pack_bf16(ra0 - bf16_lo(h), ra1 - bf16_hi(h));
+      a0 -= bf16_lo(h); a1 -= bf16_hi(h);
+    } else {
+      const unsigned m = half ? m1 : m0, l = pack_bf16(a0 - bf16_lo(m), a1 - bf16_hi(m));
+      if constexpr (half == 0) {
+        l0 = l;
+      } else {
+        put(j, P, u32x2{h0, h1}, u32x2{m0, m1}, u32x2{l0, l});
+        fetch(raw[P], j, ks + 2);
+      }
+    }
+  };
+  constexpr int STEPS = 6 * (LA + LB), NM = 6 * TM * TN;
+
+  f32x16 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+  const int a_off = (wr * WTM + li) * 96 + lh * 16, b_off = ((SPLIT_W ? 0 : BM) + wc * WTN + li) * 96 + lh * 16;
+  using P0 = std::integral_constant<int, 0>; using P1 = std::integral_constant<int, 1>;
+#pragma unroll
+  for (int j = 0; j < LA + LB; ++j) fetch(raw[0], j, 0);
+#pragma unroll
+  for (int j = 0; j < LA + LB; ++j) fetch(raw[1], j, 1);
+  unrolled<0, STEPS>([&](auto x) { split_step(x, P0{}, 0); });
+  __builtin_amdgcn_sched_barrier(0);
+  request(0, 0);
+  request(1, 1);
+  int w_stage = 0;                                       // of three
+  wait_vm_lgkm0<WL / NW>();
+  __builtin_amdgcn_s_barrier();
+  // One slice.  Past the last one zeros are fetched and split, and weights requested that nothing reads: no branch parts
+  // the vector instructions from the matrix ones, and the number of loads in flight is the same throughout.
+  auto slice = [&](auto par, int ks) {
+    constexpr int P = decltype(par)::value;
+    __builtin_amdgcn_sched_barrier(0);
+    request(ks + 2, w_stage == 0 ? 2 : w_stage - 1);     // the stage read a slice ago
+    const unsigned char* sa = smem + P * STAGE;
+    const unsigned char* sb = SPLIT_W ? smem + 2 * STAGE + w_stage * W_STAGE : sa;
+    w_stage = w_stage == 2 ? 0 : w_stage + 1;
+    bf16x8 fa[3][TM], fb[3][TN];
+    constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};   // smallest products first
+    constexpr int RA[3] = {2, 0, 1}, RB[3] = {0, 2, 1};
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i) fa[RA[p]][i] = *(const bf16x8*)(sa + RA[p] * 32 + a_off + i * 3072);
+#pragma unroll
+      for (int j = 0; j < TN; ++j) fb[RB[p]][j] = *(const bf16x8*)(sb + RB[p] * 32 + b_off + j * 3072);
+    }
+    // The next slice's splitting, a few steps behind each matrix instruction, into the stage last read a slice ago.
+    unrolled<0, NM>([&](auto at) {
+      constexpr int R = decltype(at)::value, x = R / (TM * TN), i = R / TN % TM, j = R % TN;
+      __builtin_amdgcn_sched_barrier(0);
+      acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[PA[x]][i], fb[PB[x]][j], acc[i][j], 0, 0, 0);
+      unrolled<R * STEPS / NM, (R + 1) * STEPS / NM>([&](auto y) { split_step(y, std::integral_constant<int, P ^ 1>{}, ks + 1); });
+    });
+    __builtin_amdgcn_sched_barrier(0);
+    wait_vm_lgkm0<2 * (LA + LB) + WL / NW>();            // the next slice's weights have landed, those behind them may be on their way
+    __builtin_amdgcn_s_barrier();
+  };
+  for (int ks = 0; ks < slices; ks += 2) {
+    slice(P0{}, ks);
+    if (ks + 1 < slices) slice(P1{}, ks + 1);
+  }
+  wait_vm<0>();                                          // nothing is on its way to LDS when the workgroup ends
+#pragma unroll
+  for (int j = 0; j < TN; ++j) {
+    const auto col = epi.col(bn0 + wc * WTN + j * 32 + li);
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        float v[4] = {acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
+        epi.store4(col, bm0 + wr * WTM + i * 32 + g * 8 + lh * 4, v);
+      }
+  }
+#endif
+}
+
+// Split weights of a product, as k_gemm_f32_parts reads them: [N / 32][slices of 16][32 rows][3 parts][16] bf16, zero
+// past N and K.  Once per model.
+__global__ __launch_bounds__(256) void k_split_weights(const float* __restrict__ Wt, unsigned char* __restrict__ out, int N, int K, int slices) {
+  const long long i = (long long)blockIdx.x * 256 + threadIdx.x;       // a row's slice
+  const int row = (int)(i / slices), ks = (int)(i % slices);
+  if (row >= (N + 31) / 32 * 32) return;
+  unsigned h[8], m[8], l[8];
+#pragma unroll
+  for (int x = 0; x < 8; ++x) {
+    const int k = ks * 16 + 2 * x;
+    const float a = row < N && k < K ? Wt[(size_t)row * K + k] : 0.0f, b = row < N && k + 1 < K ? Wt[(size_t)row * K + k + 1] : 0.0f;
+    const float ca = __builtin_amdgcn_fmed3f(a, -kBf16Max, kBf16Max), cb = __builtin_amdgcn_fmed3f(b, -kBf16Max, kBf16Max);
+    h[x] = pack_bf16(ca, cb);
+    m[x] = pack_bf16(ca - bf16_lo(h[x]), cb - bf16_hi(h[x]));
+    l[x] = pack_bf16((a - bf16_lo(h[x])) - bf16_lo(m[x]), (b - bf16_hi(h[x])) - bf16_hi(m[x]));
+  }
+  unsigned* dst = (unsigned*)(out + ((size_t)(row / 32) * slices + ks) * 3072 + (row % 32) * 96);
+#pragma unroll
+  for (int x = 0; x < 8; ++x) { dst[x] = h[x]; dst[8 + x] = m[x]; dst[16 + x] = l[x]; }
+}
+
+size_t split_weights_bytes(int N, int K) { return (size_t)((N + 31) / 32) * ((K + 15) / 16) * 3072; }
+hipError_t launch_split_weights(const float* Wt, void* out, int N, int K, hipStream_t s) {
+  const int slices = (K + 15) / 16;
+  const long long blocks = ((long long)(N + 31) / 32 * 32 * slices + 255) / 256;
+  if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+  k_split_weights<<<(unsigned)blocks, 256, 0, s>>>(Wt, (unsigned char*)out, N, K, slices);
+  return hipGetLastError();
+}
+
+template <int BM, int BN, int WR, int WC, int PER_SIMD, bool SPLIT_W, int MODE>
+static hipError_t run_f32_parts(const void* A, const void* Wt, int M, int N, int K, const EpiParams& ep, hipStream_t s) {
+  using Epi = Epilogue<float, MODE>;
+  Epi epi = Epi::make(ep, M, N);
+  const int tiles_m = ceil_div(M, BM), tiles_n = ceil_div(N, BN);
+  const long long grid = ((long long)tiles_m * tiles_n + 255) / 256 * 256;
+  if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
+  constexpr size_t smem = (size_t)(SPLIT_W ? 2 * BM + 3 * BN : 2 * (BM + BN)) * 96;
+  auto kern = k_gemm_f32_parts<BM, BN, WR, WC, PER_SIMD, SPLIT_W, Epi>;
+  static bool attr_set = false;
+  if (!attr_set) {
+    hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    if (e != hipSuccess) return e;
+    attr_set = true;
+  }
+  kern<<<(unsigned)grid, WR * WC * 64, smem, s>>>((const float*)A, Wt, M, N, K, tiles_m, tiles_n, epi);
   return hipGetLastError();
 }
 
@@ -1072,25 +1316,35 @@ static hipError_t run_plain(const void* A, const void* Wt, int M, int N, int K, 
 
 // fp32 products.  The plain kernel keeps what is not made of whole aligned 16-byte chunks.
 template <int MODE>
-static hipError_t dispatch_f32(const void* A, const void* Wt, int M, int N, int K, const EpiParams& ep, hipStream_t s) {
+static hipError_t dispatch_f32(const void* A, const void* Wt, const void* w_parts, int M, int N, int K, const EpiParams& ep, hipStream_t s) {
   if (K % 4 != 0 || (((uintptr_t)A | (uintptr_t)Wt) & 15) != 0 || K >= kSkinnyMaxK) return run_plain<float, MODE>(A, Wt, M, N, K, ep, s);
   // Few tiles: one 32x32 tile per workgroup, K split over its waves (500 x 512 x 512: 8.6 us
   // against 13.6 with 64x64 tiles; at 192 of those, 500 x 1536 x 512, 18 against 14).
-  const long long t64 = (long long)ceil_div(M, 64) * ceil_div(N, 64), t128 = (long long)ceil_div(M, 64) * ceil_div(N, 128);
+  const long long t64 = (long long)ceil_div(M, 64) * ceil_div(N, 64);
   if ((t64 <= 128 || N < 32) && ceil_div(M, 32) <= 65535) return run_skinny<float, MODE>(A, Wt, M, N, K, ep, s);
-  // The matrix pipe of the CU that gets the most tiles bounds the launch: rounds of 256 tiles, and
-  // per round 64x128 takes 1.9 times a 64x64 one (4096 x 4608 x 1152: 332 against 353 us = 131 and
-  // 123 TFLOP/s, 4096 x 1152 x 1152: 112 against 107).  128x128, 64x96, 128x64 and 128x96 tiles were
-  // no faster than the better of the two at any size tried.
-  const double rounds64 = (double)((t64 + 255) / 256), rounds128 = (double)((t128 + 255) / 256);
-  if (1.9 * rounds128 <= rounds64) return run_f32<64, 128, 2, 4, MODE>(A, Wt, M, N, K, ep, s);
-  return run_f32<64, 64, 2, 2, MODE>(A, Wt, M, N, K, ep, s);
+  if (t64 <= 256) return run_f32<64, 64, 2, 2, MODE>(A, Wt, M, N, K, ep, s);
+  // The CU that gets the most tiles bounds the launch: rounds of 256 tiles times what a tile takes per slice of K, in
+  // tenths of a microsecond, measured where several tiles share a CU and (second figure) where one has it to itself.
+  auto estimate = [&](int bm, int bn, double shared, double alone) {
+    const long long rounds = ((long long)ceil_div(M, bm) * ceil_div(N, bn) + 255) / 256;
+    return rounds == 1 ? alone : rounds * shared;
+  };
+  if (w_parts && K < (1 << 18)) {                        // (K: 32-bit offsets into the split weights)
+    const double e64 = estimate(64, 64, 2.3, 4.2), e128 = estimate(64, 128, 3.7, 5.0), e192 = estimate(128, 192, 9.9, 12.0),
+                 e256 = estimate(256, 256, 22.0, 23.0);
+    if (e256 < e192 && e256 < e128 && e256 < e64) return run_f32_parts<256, 256, 4, 2, 2, true, MODE>(A, w_parts, M, N, K, ep, s);
+    if (e192 < e128 && e192 < e64) return run_f32_parts<128, 192, 2, 2, 2, true, MODE>(A, w_parts, M, N, K, ep, s);
+    if (e64 < e128) return run_f32_parts<64, 64, 2, 2, 4, true, MODE>(A, w_parts, M, N, K, ep, s);
+    return run_f32_parts<64, 128, 2, 2, 4, true, MODE>(A, w_parts, M, N, K, ep, s);
+  }
+  if (estimate(128, 128, 7.0, 9.0) < estimate(64, 64, 2.4, 4.7)) return run_f32_parts<128, 128, 2, 2, 2, false, MODE>(A, Wt, M, N, K, ep, s);
+  return run_f32_parts<64, 64, 2, 2, 4, false, MODE>(A, Wt, M, N, K, ep, s);
 }
 
 template <int MODE>
 static hipError_t dispatch_mode(int bf16, const void* A, const void* Wt, int M, int N, int K, const EpiParams& ep,
-                                void* scratch, size_t scratch_bytes, hipStream_t s) {
-  if (!bf16) return dispatch_f32<MODE>(A, Wt, M, N, K, ep, s);
+                                void* scratch, size_t scratch_bytes, const void* w_parts, hipStream_t s) {
+  if (!bf16) return dispatch_f32<MODE>(A, Wt, w_parts, M, N, K, ep, s);
   bool aligned = (((uintptr_t)A | (uintptr_t)Wt) & 15) == 0;
   // very few tiles (a request's text rows), or an N too narrow for the tile kernel (a 16-wide
   // output head): split K inside a workgroup instead.  Measured against the 128x128
@@ -1148,15 +1402,15 @@ static hipError_t dispatch_mode(int bf16, const void* A, const void* Wt, int M, 
 }
 
 hipError_t launch_gemm(int bf16, int mode, const void* A, const void* Wt, int M, int N, int K, const EpiParams& ep,
-                       hipStream_t s, void* scratch, size_t scratch_bytes) {
+                       hipStream_t s, void* scratch, size_t scratch_bytes, const void* w_parts) {
   if (M <= 0 || N <= 0 || K <= 0) return hipSuccess;
   switch (mode) {
-    case EPI_STORE: return dispatch_mode<EPI_STORE>(bf16, A, Wt, M, N, K, ep, scratch, scratch_bytes, s);
-    case EPI_GELU: return dispatch_mode<EPI_GELU>(bf16, A, Wt, M, N, K, ep, scratch, scratch_bytes, s);
-    case EPI_GATE: return dispatch_mode<EPI_GATE>(bf16, A, Wt, M, N, K, ep, scratch, scratch_bytes, s);
-    case EPI_HEADS: return dispatch_mode<EPI_HEADS>(bf16, A, Wt, M, N, K, ep, scratch, scratch_bytes, s);
-    case EPI_UNPATCH: return dispatch_mode<EPI_UNPATCH>(bf16, A, Wt, M, N, K, ep, scratch, scratch_bytes, s);
-    case EPI_LAYERS_KV: return dispatch_mode<EPI_LAYERS_KV>(bf16, A, Wt, M, N, K, ep, scratch, scratch_bytes, s);
+    case EPI_STORE: return dispatch_mode<EPI_STORE>(bf16, A, Wt, M, N, K, ep, scratch, scratch_bytes, w_parts, s);
+    case EPI_GELU: return dispatch_mode<EPI_GELU>(bf16, A, Wt, M, N, K, ep, scratch, scratch_bytes, w_parts, s);
+    case EPI_GATE: return dispatch_mode<EPI_GATE>(bf16, A, Wt, M, N, K, ep, scratch, scratch_bytes, w_parts, s);
+    case EPI_HEADS: return dispatch_mode<EPI_HEADS>(bf16, A, Wt, M, N, K, ep, scratch, scratch_bytes, w_parts, s);
+    case EPI_UNPATCH: return dispatch_mode<EPI_UNPATCH>(bf16, A, Wt, M, N, K, ep, scratch, scratch_bytes, w_parts, s);
+    case EPI_LAYERS_KV: return dispatch_mode<EPI_LAYERS_KV>(bf16, A, Wt, M, N, K, ep, scratch, scratch_bytes, w_parts, s);
   }
   return hipErrorInvalidValue;
 }

@@ -166,7 +166,8 @@ def test_linear_fp32(fc, M, N, K):
 @pytest.mark.parametrize("M,N,K", [
     (33, 31, 4), (31, 33, 12), (65, 200, 300), (500, 512, 512), (7, 2304, 768), (9000, 16, 36),   # one 32x32 tile per workgroup
     (700, 700, 4), (1025, 577, 100), (1500, 576, 576),                  # 64x64 tiles: ragged edges, K past whole K tiles
-    (4095, 1025, 132), (2048, 2048, 260)])                              # 64x128 tiles
+    (1100, 1030, 52), (2113, 520, 16),                                  # bf16 parts: 64x64 tiles
+    (4095, 1025, 132), (2048, 2048, 260)])                              # 128x128 tiles
 @pytest.mark.parametrize("epilogue", [0, 2])
 def test_linear_fp32_matrix_cores(fc, M, N, K, epilogue):
     """fp32 sums of K products in any order are within K 2^-24 of sum |a| |w| (here bounded by
@@ -187,6 +188,32 @@ def test_linear_fp32_matrix_cores(fc, M, N, K, epilogue):
     assert np.isnan(got[M]).all()                                       # nothing past the last row
     assert np.abs(got[:M] - want).max() <= bound
     assert rel_l2(got[:M], want) < 2e-6
+
+
+@pytest.mark.parametrize("M,N", [(1100, 1030), (4100, 1024)])
+def test_linear_fp32_in_parts_keeps_values_that_are_not_finite(fc, M, N):
+    """Infinities, NaN and the largest finite values leave exactly the marks that fp32 products leave."""
+    torch = _torch()
+    K = 40
+    rng = np.random.default_rng(M)
+    A = rng.standard_normal((M, K), dtype=np.float32)
+    W = rng.standard_normal((K, N), dtype=np.float32)
+    big = np.float32(np.finfo(np.float32).max)
+    A[3, 5], A[4, 7], A[9, 9], A[20, 11], A[21, 12] = np.inf, np.nan, -np.inf, big, -big
+    W[5, 2], W[5, 7], W[9, 8], W[30, 33], W[31, 40] = 0.0, 1.0, 1.5, np.inf, np.nan
+    W[11], W[12] = 0.25, 0.5
+    out = torch.empty((M, N), dtype=torch.float32, device="cuda:0")
+    fc.fc_op_linear(fc.FC_F32, dev(A), dev(W.T.copy()), dev(np.zeros(N, np.float32)), None, out, M, N, K, 0)
+    torch.cuda.synchronize()
+    got = host(out)
+    with np.errstate(invalid="ignore"):
+        want = A.astype(np.float64) @ W.astype(np.float64)
+    assert (np.isnan(got) == np.isnan(want)).all()
+    assert (got[np.isinf(want)] == want[np.isinf(want)]).all()
+    assert np.isfinite(got[np.isfinite(want)]).all()
+    for row, v in ((20, big * 0.25), (21, -big * 0.5)):
+        ok = np.isfinite(want[row])
+        assert np.abs(got[row][ok] / v - 1).max() < 1e-6
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
