@@ -64,7 +64,7 @@ EXPORTS = {
                        C.c_void_p],
     "fc_cache_frame_similarity": [C.c_void_p, C.c_int32, C.c_int64, C.c_void_p, C.c_void_p, C.c_size_t, C.c_void_p],
     "fc_cache_frame_similarity_noalloc": [C.c_void_p, C.c_int32, C.c_int64, C.c_void_p, C.c_void_p],
-    "fc_cache_select_key_frames": [C.POINTER(C.c_float), C.c_int32, C.c_float, C.POINTER(C.c_int32)],
+    "fc_cache_select_key_frames": [C.c_void_p, C.c_int32, C.c_float, C.c_void_p],
     "fc_profile_enable": [C.c_void_p, C.c_int32],
     "fc_profile_select": [C.c_void_p, C.c_int32],
     "fc_profile_categories": [],
@@ -113,6 +113,20 @@ _lib = None
 _lib = _load()
 
 
+def _load_fast():
+    """The cache calls as CPython functions (csrc/pycall.cpp): the library they call, and they."""
+    try:
+        from . import _pycall
+    except ImportError as e:
+        raise ImportError(f"{os.path.join(_HERE, '_pycall.so')} is not built: run `python -m paper_2501_04012_amd.build`") from e
+    _pycall.bind(*(C.cast(getattr(_lib, "fc_cache_" + n), C.c_void_p).value
+                   for n in ("stitch", "decompress", "alpha", "frame_similarity")))
+    return _lib, _pycall
+
+
+_fast_lib, _fast = _load_fast()
+
+
 def _check(status: int, where: str) -> None:
     if status != 0:
         raise FlexDenoiseError(status, where)
@@ -122,9 +136,12 @@ def _ptr(t) -> Optional[int]:
     """Device (or host) address of a torch tensor / numpy array / None."""
     if t is None:
         return None
-    if isinstance(t, np.ndarray):
-        return t.ctypes.data
-    return t.data_ptr()
+    try:
+        return t.data_ptr()                              # tensors first: most arguments are
+    except AttributeError:
+        if isinstance(t, np.ndarray):
+            return t.ctypes.data
+        raise
 
 
 _current_stream = None       # () -> handle of torch's current stream on the current device
@@ -224,7 +241,19 @@ def fc_denoise_resume_ex(model, latent, cond, null_cond, sched: synth.Schedule, 
                                      _stream(stream)), "fc_denoise_resume_ex")
 
 
+# The cache calls take plain arguments straight to native code; what that refuses (arrays, numpy scalars, other
+# iterables) is marshalled here.
+
 def fc_cache_stitch(x_obj, x_bg, m_obj, m_bg, out, pixels: int, channels: int, stream=None) -> None:
+    if _lib is _fast_lib:
+        try:
+            status = _fast.fc_cache_stitch(x_obj, x_bg, m_obj, m_bg, out, pixels, channels, _stream(stream))
+        except TypeError:
+            pass
+        else:
+            if status:
+                _check(status, "fc_cache_stitch")
+            return
     _check(_lib.fc_cache_stitch(_ptr(x_obj), _ptr(x_bg), _ptr(m_obj), _ptr(m_bg), _ptr(out), pixels, channels,
                                 _stream(stream)), "fc_cache_stitch")
 
@@ -246,6 +275,16 @@ def _source_codes(src, n: int):
 
 def fc_cache_decompress(first, diff_base, n_base: int, alpha: float, extra, n_extra: int, src, frames: int,
                         frame_elems: int, out, stream=None) -> None:
+    if _lib is _fast_lib:
+        try:
+            status = _fast.fc_cache_decompress(first, diff_base, n_base, alpha, extra, n_extra, src, frames, frame_elems,
+                                               out, _stream(stream))
+        except TypeError:
+            pass
+        else:
+            if status:
+                _check(status, "fc_cache_decompress")
+            return
     held, codes = _source_codes(src, max(frames, 1))
     _check(_lib.fc_cache_decompress(_ptr(first), _ptr(diff_base), n_base, alpha, _ptr(extra), n_extra,
                                     codes, frames, frame_elems, _ptr(out), _stream(stream)),
@@ -258,15 +297,34 @@ def fc_cache_workspace_bytes(frames: int) -> int:
 
 def fc_cache_alpha(first_s, keys_s, diff_base, n_base: int, frame_elems: int, alpha_out, workspace,
                    stream=None) -> None:
+    nbytes = workspace.numel() * workspace.element_size()
+    if _lib is _fast_lib:
+        try:
+            status = _fast.fc_cache_alpha(first_s, keys_s, diff_base, n_base, frame_elems, alpha_out, workspace, nbytes,
+                                          _stream(stream))
+        except TypeError:
+            pass
+        else:
+            if status:
+                _check(status, "fc_cache_alpha")
+            return
     _check(_lib.fc_cache_alpha(_ptr(first_s), _ptr(keys_s), _ptr(diff_base), n_base, frame_elems, _ptr(alpha_out),
-                               _ptr(workspace), workspace.numel() * workspace.element_size(), _stream(stream)),
-           "fc_cache_alpha")
+                               _ptr(workspace), nbytes, _stream(stream)), "fc_cache_alpha")
 
 
 def fc_cache_frame_similarity(frames_dev, frames: int, frame_elems: int, sim, workspace, stream=None) -> None:
-    _check(_lib.fc_cache_frame_similarity(_ptr(frames_dev), frames, frame_elems, _ptr(sim), _ptr(workspace),
-                                          workspace.numel() * workspace.element_size(), _stream(stream)),
-           "fc_cache_frame_similarity")
+    nbytes = workspace.numel() * workspace.element_size()
+    if _lib is _fast_lib:
+        try:
+            status = _fast.fc_cache_frame_similarity(frames_dev, frames, frame_elems, sim, workspace, nbytes, _stream(stream))
+        except TypeError:
+            pass
+        else:
+            if status:
+                _check(status, "fc_cache_frame_similarity")
+            return
+    _check(_lib.fc_cache_frame_similarity(_ptr(frames_dev), frames, frame_elems, _ptr(sim), _ptr(workspace), nbytes,
+                                          _stream(stream)), "fc_cache_frame_similarity")
 
 
 def fc_cache_frame_similarity_noalloc(frames_dev, frames: int, frame_elems: int, sim, stream=None) -> None:
@@ -280,13 +338,17 @@ def fc_bench_pipe_rates(operands, iters: int, mode_first: int, mode_second: int,
                                     _stream(stream)), "fc_bench_pipe_rates")
 
 
+def _array_address(a: np.ndarray) -> int:
+    return a.__array_interface__["data"][0]              # without a.ctypes, whose object alone takes 2 us
+
+
 def fc_cache_select_key_frames(sim_host: np.ndarray, threshold: float = 0.99) -> np.ndarray:
     sim_host = np.ascontiguousarray(sim_host, dtype=np.float32)
     T = sim_host.shape[0]
-    out = (C.c_int32 * max(T, 1))()
-    _check(_lib.fc_cache_select_key_frames(sim_host.ctypes.data_as(C.POINTER(C.c_float)), T, threshold, out),
+    out = np.empty(max(T, 1), dtype=np.int32)
+    _check(_lib.fc_cache_select_key_frames(_array_address(sim_host), T, threshold, _array_address(out)),
            "fc_cache_select_key_frames")
-    return np.array(out[:T], dtype=np.int64)
+    return out[:T].astype(np.int64)
 
 
 def fc_schedule_coefficients(sched: synth.Schedule, step: int):

@@ -1,4 +1,4 @@
-"""Builds libflexdenoise.so for gfx950 with hipcc, in-tree.
+"""Builds libflexdenoise.so for gfx950 with hipcc, and the CPython side of the binding, in-tree.
 
     python -m paper_2501_04012_amd.build [--force]
 """
@@ -7,6 +7,7 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -14,6 +15,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ_DIR = os.path.join(HERE, "_build")
 LIB_PATH = os.path.join(HERE, "libflexdenoise.so")
 SOURCES = ["flexdenoise.hip", "elementwise.hip", "gemm.hip", "attention.hip", "chain.hip", "cache.hip", "microbench.hip"]
+PYCALL_PATH = os.path.join(HERE, "_pycall.so")           # the cache calls as CPython functions (host only)
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -48,6 +50,10 @@ def build(force: bool = True, verbose: bool = False) -> str:
             print(log)
     objs = [o for o, _ in results]
     _run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB_PATH, *objs])
+    src = os.path.join(CSRC, "pycall.cpp")
+    if force or not os.path.exists(PYCALL_PATH) or os.path.getmtime(PYCALL_PATH) < max(os.path.getmtime(src), newest_hdr):
+        _run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+              "-I" + sysconfig.get_paths()["include"], src, "-o", PYCALL_PATH])
     return LIB_PATH
 
 

@@ -189,3 +189,47 @@ def test_forked_child_asks_for_the_device_again(monkeypatch):
         os._exit(0 if binding._current_stream is None else 1)
     assert os.waitstatus_to_exitcode(os.waitpid(pid, 0)[1]) == 0
     assert binding._stream(None) == 5
+
+
+@pytest.mark.parametrize("call,args,status", [
+    ("fc_cache_decompress", (None, None, 0, 1.0, None, 0, [0], 1, 4, None), -1),
+    ("fc_cache_decompress", ("t", None, 0, 1.0, None, 0, [1], 1, 4, "t"), -3),                 # a frame the entry does not hold
+    ("fc_cache_decompress", ("t", None, 0, 1.0, None, 0, [0] * 257, 257, 4, "t"), -6),
+    ("fc_cache_decompress", ("t", None, 0, 1.0, None, 0, [0], 1, 0, "t"), 0),                   # nothing to do: no launch
+    ("fc_cache_stitch", ("t", "t", None, None, "t", 4, 4), -1),
+    ("fc_cache_stitch", ("t", "t", "t", None, "t", 4, 0), -3),
+    ("fc_cache_stitch", ("t", "t", "t", "t", "t", 0, 4), 0),
+    ("fc_cache_alpha", ("t", "t", "t", 0, 4, "t", "t"), -3),
+    ("fc_cache_alpha", ("t", "t", "t", 1, 4, "t", "t"), -4),
+    ("fc_cache_frame_similarity", (None, 1, 4, "t", "t"), -1),
+    ("fc_cache_frame_similarity", ("t", 1, 4, "t", "t"), -4)])
+@pytest.mark.parametrize("native", [True, False])
+def test_cache_calls_by_both_routes(monkeypatch, call, args, status, native):
+    """The CPython route and the ctypes one give the same status for the same arguments."""
+    import torch
+    from paper_2501_04012_amd import binding
+    t = torch.zeros(16)
+    args = [t if isinstance(a, str) else a for a in args]
+    if not native:
+        monkeypatch.setattr(binding, "_fast_lib", None)
+    if status == 0:
+        getattr(binding, call)(*args, stream=1)
+        return
+    with pytest.raises(binding.FlexDenoiseError) as e:
+        getattr(binding, call)(*args, stream=1)
+    assert e.value.status == status and call in str(e.value)
+
+
+def test_native_route_leaves_other_arguments_to_ctypes():
+    import torch
+    from paper_2501_04012_amd import binding
+    t = torch.zeros(16)
+    plain = [t, None, 0, 1.0, None, 0, [0], 1, 0, t, None]
+    assert binding._fast.fc_cache_decompress(*plain) == 0
+    for at, other in ((0, np.zeros(4, np.float32)), (2, np.int64(0)), (2, False), (2, 2 ** 31), (3, 1), (3, np.float32(1)), (6, [0, 0]),
+                      (6, np.zeros(1, np.int64)), (6, [np.int64(0)]), (6, [2 ** 31]), (6, iter([0])), (7, 0), (8, 2 ** 63), (8, 0.0),
+                      (10, "x")):
+        with pytest.raises(TypeError):
+            binding._fast.fc_cache_decompress(*(plain[:at] + [other] + plain[at + 1:]))
+    with pytest.raises(TypeError):
+        binding._fast.fc_cache_decompress(*plain[:-1])
