@@ -13,7 +13,9 @@
 // workgroups.  Weights are the A operand and rows the B operand, so that a lane ends up with four
 // consecutive outputs of one row.  An operand lane (i, h) holds one 16-byte chunk of K and
 // instruction e contracts element e of the four chunks (any order of K will do as long as both
-// operands agree).  Weights come straight from global memory.
+// operands agree).  Weights come straight from global memory, laid out once per model in the order of the fragments
+// (launch_pack_chain): a load of 64 lanes is 1 KB in a row, where rows of the plain layout gave it 64 bytes of each of 16
+// (64 wide, six blocks full 3-D 123 -> 112 us; 128 wide, factorized 379 -> 351; 64 wide resume below 7.85 -> 7.61 ms).
 //
 // A workgroup is alone with its 16 rows, two waves to a SIMD, so what it takes is the instructions of
 // one wave after the other, 4 to 8 cycles each, and little of that is multiplication.  Hence: no
@@ -22,7 +24,7 @@
 // issued all the same), one kernel per kind of launch, and the first weights of a product on their way
 // before the stage in front of it begins (barriers wait for LDS only).
 //
-// 64 wide, 4 heads, 28 blocks, 4 requests with guidance (512 rows), ten steps: 17.2 -> 8.0 ms, of which a
+// 64 wide, 4 heads, 28 blocks, 4 requests with guidance (512 rows), ten steps: 17.2 -> 7.6 ms, of which a
 // spatial and a temporal launch take about 9 and 17 us.
 #include "common.h"
 
@@ -270,20 +272,20 @@ __global__ __launch_bounds__(kThreads) void k_chain(ChainArgs a) {
     }
     return s;
   };
-  auto fetch = [&](const ChainStep& p, unsigned lane_off, int t, int c, int c1, f32x4 (&r)[U]) {
-    const float* base = p.w + (size_t)(t * 16) * p.K;     // uniform
+  auto fetch = [&](const ChainStep& p, int t, int c, int c1, f32x4 (&r)[U]) {
+    const float* base = p.packed + (size_t)(t * (p.K >> 4) + c) * 256;     // uniform
 #pragma unroll
     for (int x = 0; x < U; ++x)
-      if (c + x < c1) r[x] = *(const f32x4*)(base + 16 * (c + x) + lane_off);
+      if (c + x < c1) r[x] = *(const f32x4*)(base + 256 * x + 4 * lane);
   };
-  auto ahead = [&](const ChainStep& p, unsigned lane_off, bool split) {
+  auto ahead = [&](const ChainStep& p, bool split) {
     Ahead f;
     const Share s = share(p.N, p.K, split);
-    if (s.t < s.nt) fetch(p, lane_off, s.t, s.c0, s.c1, f.w);
+    if (s.t < s.nt) fetch(p, s.t, s.c0, s.c1, f.w);
     __builtin_amdgcn_sched_barrier(0);
     return f;
   };
-  auto product = [&](const ChainStep& p, unsigned lane_off, bool split, Ahead& f, const float* in, auto gate_at, auto store) {
+  auto product = [&](const ChainStep& p, bool split, Ahead& f, const float* in, auto gate_at, auto store) {
     const Share s = share(p.N, p.K, split);
     const float* ap = in + 4 * h;
     for (int t = s.t; t < s.nt; t += kChainWaves) {
@@ -293,8 +295,8 @@ __global__ __launch_bounds__(kThreads) void k_chain(ChainArgs a) {
       const f32x4 gate = gate_at(n);
       for (int c = s.c0; c < s.c1; c += U) {
         f32x4 nx[U];
-        if (c + U < s.c1) fetch(p, lane_off, t, c + U, s.c1, nx);
-        else if (s.parts == 1 && t + kChainWaves < s.nt) fetch(p, lane_off, t + kChainWaves, s.c0, s.c1, nx);
+        if (c + U < s.c1) fetch(p, t, c + U, s.c1, nx);
+        else if (s.parts == 1 && t + kChainWaves < s.nt) fetch(p, t + kChainWaves, s.c0, s.c1, nx);
         __builtin_amdgcn_sched_barrier(0);                // the scheduler would move the loads to their use
 #pragma unroll
         for (int x = 0; x < U; ++x)
@@ -315,7 +317,6 @@ __global__ __launch_bounds__(kThreads) void k_chain(ChainArgs a) {
       store(n, v + bias, gate);
     }
   };
-  const unsigned off_d = i * D + 4 * h, off_m = i * a.mlp + 4 * h;     // of a lane in 16 weight rows
   auto no_gate = [](int) { return f32x4{1.0f, 1.0f, 1.0f, 1.0f}; };
   auto add = [&](int n, f32x4 v, f32x4 gate) { *(f32x4*)(xt + i * ld + n) += gate * v; };   // the residual; only this lane touches it
 
@@ -351,46 +352,46 @@ __global__ __launch_bounds__(kThreads) void k_chain(ChainArgs a) {
 
   if constexpr (KIND & CHAIN_SELF) {
     const ChainStep& p = a.step[CHAIN_PROJ];
-    Ahead f = ahead(p, off_d, false);
+    Ahead f = ahead(p, false);
     lds_barrier();
     attention(a.k, a.v, a.seq_len, a.by_len, a.seq_len, false);
     lds_barrier();
-    product(p, off_d, false, f, u + i * ld, [&](int n) { return *(const f32x4*)(p.gate + (unsigned)(my_alt + n)); }, add);
+    product(p, false, f, u + i * ld, [&](int n) { return *(const f32x4*)(p.gate + (unsigned)(my_alt + n)); }, add);
   }
   if constexpr (KIND & CHAIN_CROSS) {
     const ChainStep& pq = a.step[CHAIN_XQ];
-    Ahead f = ahead(pq, off_d, false);
+    Ahead f = ahead(pq, false);
     lds_barrier();
     layer_norm(nullptr, nullptr, 0);
     lds_barrier();
-    product(pq, off_d, false, f, u + i * ld, no_gate, [&](int n, f32x4 v, f32x4) { *(f32x4*)(o + i * ld + n) = v * a.qscale; });
+    product(pq, false, f, u + i * ld, no_gate, [&](int n, f32x4 v, f32x4) { *(f32x4*)(o + i * ld + n) = v * a.qscale; });
     const ChainStep& p = a.step[CHAIN_XPROJ];
-    f = ahead(p, off_d, false);
+    f = ahead(p, false);
     lds_barrier();
     attention(a.xk, a.xv, a.Ns, a.by_Ns, a.L, true);
     lds_barrier();
-    product(p, off_d, false, f, u + i * ld, no_gate, add);
+    product(p, false, f, u + i * ld, no_gate, add);
   }
   if constexpr (KIND & CHAIN_MLP) {
     const ChainStep& p1 = a.step[CHAIN_FC1];
-    Ahead f = ahead(p1, off_d, false);
+    Ahead f = ahead(p1, false);
     lds_barrier();
     layer_norm(p1.shift, p1.scale, e_alt);
     lds_barrier();
-    product(p1, off_d, false, f, u + i * ld, no_gate, [&](int n, f32x4 v, f32x4) {
+    product(p1, false, f, u + i * ld, no_gate, [&](int n, f32x4 v, f32x4) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[e] = gelu_tanh_f(v[e]);
       *(f32x4*)(hid + i * ldm + n) = v;
     });
     const ChainStep& p2 = a.step[CHAIN_FC2];
-    f = ahead(p2, off_m, true);
+    f = ahead(p2, true);
     lds_barrier();
-    product(p2, off_m, true, f, hid + i * ldm, [&](int n) { return *(const f32x4*)(p2.gate + (unsigned)(my_alt + n)); }, add);
+    product(p2, true, f, hid + i * ldm, [&](int n) { return *(const f32x4*)(p2.gate + (unsigned)(my_alt + n)); }, add);
   }
   // ---- the next self-attention's queries, keys and values, or the output head
   const ChainStep& p = a.step[CHAIN_NEXT];
   if (!a.eps) {
-    Ahead f = ahead(p, off_d, false);
+    Ahead f = ahead(p, false);
     lds_barrier();
     const f32x4 x4 = layer_norm(p.shift, p.scale, e_alt);
     if (e_in && idx0 + er <= last) *(f32x4*)(a.x_out + (unsigned)(e_row * D + ec)) = x4;
@@ -401,7 +402,7 @@ __global__ __launch_bounds__(kThreads) void k_chain(ChainArgs a) {
       out_row = b * a.N + s * a.T + t;
     }
     const bool mine = idx0 + i <= last;
-    product(p, off_d, false, f, u + i * ld, no_gate, [&](int n, f32x4 v, f32x4) {
+    product(p, false, f, u + i * ld, no_gate, [&](int n, f32x4 v, f32x4) {
       const int which = n >= 2 * D ? 2 : n >= D ? 1 : 0, c = n - which * D;     // D % 16 == 0: uniform but for c
       float* dst = which == 0 ? a.q_out : which == 1 ? a.k_out : a.v_out;
       if (which == 0) v *= a.qscale;
@@ -435,6 +436,12 @@ __global__ __launch_bounds__(kThreads) void k_chain(ChainArgs a) {
       }
     }
   }
+}
+
+__global__ __launch_bounds__(256) void k_pack_chain(const float* __restrict__ w, float* __restrict__ packed, int N, int K) {
+  const int x = blockIdx.x * 256 + threadIdx.x, lane = x & 63, c = (x >> 6) % (K >> 4), t = (x >> 6) / (K >> 4);
+  if (t * 16 >= N) return;
+  *(f32x4*)(packed + (size_t)x * 4) = *(const f32x4*)(w + (size_t)(t * 16 + (lane & 15)) * K + c * 16 + (lane >> 4) * 4);
 }
 
 template <int HDT, int KIND>
@@ -477,6 +484,12 @@ bool chain_fits(const ChainArgs& a, int keys, int text) {
   if (text == 0) return missing > 0 && (a.heads <= 8 || 6 * keys <= missing * missing);
   if (a.heads > 8) return keys + (long long)text < 16 * missing;
   return text <= (a.heads <= 4 ? 1 << 20 : missing > 0 ? 2560 : 512);    // 2^20: key offsets are 24-bit products
+}
+
+hipError_t launch_pack_chain(const float* w, float* packed, int N, int K, hipStream_t s) {
+  if (N % 16 != 0 || K % 16 != 0 || (long long)N * K > 1 << 28) return hipErrorInvalidValue;
+  k_pack_chain<<<ceil_div((long long)N * K / 4, 256), 256, 0, s>>>(w, packed, N, K);
+  return hipGetLastError();
 }
 
 hipError_t launch_chain(const ChainArgs& args, hipStream_t s) {

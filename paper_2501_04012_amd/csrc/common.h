@@ -312,6 +312,7 @@ bool attention_uses_key_norms(int bf16, const AttnParams& p);
 enum ChainStage : int { CHAIN_PROJ, CHAIN_XQ, CHAIN_XPROJ, CHAIN_FC1, CHAIN_FC2, CHAIN_NEXT, CHAIN_STEPS };
 struct ChainStep {
   const float *w, *bias;                   // [N, K], [N]
+  const float* packed;                     // w in fragment order (launch_pack_chain); NULL: the output head, which reads w
   int N, K;
   const float* gate;                       // PROJ, XPROJ, FC2: on what is added to the rows (NULL: 1)
   const float *shift, *scale;              // XQ, FC1, NEXT: of the LayerNorm in front (NULL: none)
@@ -338,6 +339,8 @@ struct ChainArgs {
   float *q_out, *k_out, *v_out;            // NEXT, eps NULL
   float* eps;                              // NEXT as the output head: [B, T, H, W, C]
 };
+// w [N, K], both multiples of 16, as [N / 16][K / 16][lane][4]: lane i + 16 h holds row i, columns 4 h .. 4 h + 3
+hipError_t launch_pack_chain(const float* w, float* packed, int N, int K, hipStream_t s);
 bool chain_fits(const ChainArgs& a, int keys, int text);  // keys of the longest self-attention; of the cross-attention (0: none)
 hipError_t launch_chain(const ChainArgs& a, hipStream_t s);
 

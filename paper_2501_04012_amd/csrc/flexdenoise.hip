@@ -67,7 +67,7 @@ struct Profiler {
 struct Linear {           // weights [out, in] in the activation dtype, bias fp32
   void* wt = nullptr;
   float* b = nullptr;
-  void* parts = nullptr;  // fp32, where the products are large: the weights once more, split into bf16 parts
+  void* parts = nullptr;  // fp32: the weights once more, split into bf16 parts or (chain) in fragment order
   int in = 0, out = 0;
 };
 
@@ -84,6 +84,7 @@ struct fc_model {
   int device = 0;
   bool has_weights = false;
   bool bf16 = false;
+  bool chain_shape = false;        // steps may run as chains, if their sizes fit too (chain_fits)
   int S = 0, N = 0, Ns = 0, pd = 0, hd = 0, nmod = 0;
   size_t esz = 4;                  // bytes per activation / weight element
 
@@ -199,10 +200,11 @@ size_t layout_weights(fc_model* m, unsigned char* base) {
     L.wt = cv.take((size_t)in * out * es);
     L.b = (float*)cv.take((size_t)out * 4);
   };
-  // the products over all token rows of fp32 models that do not run as chains
+  // the products over all token rows of fp32 models
   auto lin_rows = [&](Linear& L, int in, int out) {
     lin(L, in, out);
-    if (!m->bf16 && D > 128) L.parts = cv.take(split_weights_bytes(out, in));
+    if (m->chain_shape) L.parts = cv.take((size_t)in * out * es);
+    else if (!m->bf16) L.parts = cv.take(split_weights_bytes(out, in));
   };
   lin(m->t1, c.t_embed_dim, D);
   lin(m->t2, D, D);
@@ -337,7 +339,7 @@ int linear(const Ctx& c, int cat, int mode, const void* A, const Linear& L, int 
            void* scratch = nullptr, size_t scratch_bytes = 0) {
   ep.bias = L.b;
   ProfScope ps(c, cat);
-  HIP_TRY(launch_gemm(c.m->bf16, mode, A, L.wt, M, L.out, L.in, ep, c.s, scratch, scratch_bytes, L.parts));
+  HIP_TRY(launch_gemm(c.m->bf16, mode, A, L.wt, M, L.out, L.in, ep, c.s, scratch, scratch_bytes, c.m->chain_shape ? nullptr : L.parts));
   return FC_OK;
 }
 
@@ -505,7 +507,7 @@ int run_chains(const Ctx& c, const float* latent) {
   float* const sets[2][3] = {{(float*)w.q, (float*)w.k, (float*)w.v}, {(float*)w.u, (float*)w.p[0], (float*)w.p[1]}};
   int cur = 0;
   auto step = [](const Linear& L, const float* gate, const float* shift, const float* scale) {
-    return ChainStep{(const float*)L.wt, L.b, L.out, L.in, gate, shift, scale};
+    return ChainStep{(const float*)L.wt, L.b, (const float*)L.parts, L.out, L.in, gate, shift, scale};
   };
   auto next_qkv = [&](ChainArgs& a, int l, int br) {
     const float* mv = w.mod + ((size_t)l * m->nmod + (size_t)br * 3) * D;
@@ -635,7 +637,7 @@ int run_step(const Ctx& c, float* latent, const fc_schedule* sched, int step, fl
   }
 
   const bool fact = cf.attn_mode == FC_ATTN_FACTORIZED_CROSS;
-  const bool chain = !m->bf16 && chain_fits(chain_base(c), fact ? std::max(m->S, cf.frames) : m->Ns, fact ? cf.text_len : 0);
+  const bool chain = m->chain_shape && chain_fits(chain_base(c), fact ? std::max(m->S, cf.frames) : m->Ns, fact ? cf.text_len : 0);
   rc = chain ? run_chains(c, latent) : run_layers(c, latent);
   if (rc != FC_OK) return rc;
 
@@ -706,6 +708,7 @@ int fc_model_create(const fc_model_config* cfg, fc_model** out) {
   m->device = dev;
   m->bf16 = c.dtype == FC_BF16;
   m->esz = m->bf16 ? 2 : 4;
+  m->chain_shape = !m->bf16 && c.hidden <= 128 && c.hidden % 16 == 0 && c.mlp_dim <= 512 && c.mlp_dim % 16 == 0;
   m->S = (c.height / c.patch) * (c.width / c.patch);
   m->N = c.frames * m->S;
   m->Ns = m->N + (c.attn_mode == FC_ATTN_FULL3D_CONCAT ? c.text_len : 0);
@@ -754,7 +757,9 @@ int fc_model_set_weights(fc_model* m, const float* blob, size_t n_floats) {
   };
   auto up_lin = [&](Linear& L) -> hipError_t {
     hipError_t e = up_matrix_t(L.wt, L.in, L.out);
-    if (e == hipSuccess && L.parts) e = launch_split_weights((const float*)L.wt, L.parts, L.out, L.in, nullptr);
+    if (e == hipSuccess && L.parts)
+      e = m->chain_shape ? launch_pack_chain((const float*)L.wt, (float*)L.parts, L.out, L.in, nullptr)
+                         : launch_split_weights((const float*)L.wt, L.parts, L.out, L.in, nullptr);
     if (e != hipSuccess) return e;
     return up_f32(L.b, L.out);
   };
