@@ -4,6 +4,7 @@
 // and the two reductions of the compressing side that define what is expanded (Eq. 2's
 // least-squares coefficient, the frame cosine similarities the key frames are chosen by).
 // All of it moves each byte once: the kernels are bound by HBM.
+#include <type_traits>
 #include "common.h"
 
 namespace fc {
@@ -130,11 +131,29 @@ hipError_t launch_alpha(const float* first_s, const float* keys_s, const float* 
 // sim[i][j] = sim[j][i] = <frame i, frame j> / (|frame i| |frame j|) in double, rounded once.  A workgroup
 // owns 4 x 4 pairs (J <= I): 16 dot products and the 8 norms from 8 frames' values, each read once and widened once,
 // where a workgroup per pair read two frames for every dot product (64 frames of 10 240: 26 us and 4 for the
-// division, now 9 in all).  Threads take the same values of every frame in order, so a frame's norm is the same number
+// division, now 6.6 in all).  Threads take the same values of every frame in order, so a frame's norm is the same number
 // in whichever workgroup it is taken.  Few workgroups wait for memory: a trip has four values of each of the eight
 // frames in flight, next to each other where frames are made of whole aligned 16-byte pieces, else 512 apart (32 frames
 // of 86 401: 201 us with one value a trip, 95 in two launches of a workgroup per pair, 67 now; of 86 400: 33).
 constexpr int kSimTile = 4, kSimThreads = 512, kSimValues = 4;
+
+// in lanes whose bit LANES is 0, a + that of the partner (lane + LANES), in the others b + that of the partner
+template <int LANES> __device__ __forceinline__ double halves_swap(double a, double b) {
+  unsigned al = __double2loint(a), ah = __double2hiint(a), bl = __double2loint(b), bh = __double2hiint(b);
+  if constexpr (LANES == 32) {
+    const auto lo = __builtin_amdgcn_permlane32_swap(al, bl, false, false), hi = __builtin_amdgcn_permlane32_swap(ah, bh, false, false);
+    al = lo[0]; bl = lo[1]; ah = hi[0]; bh = hi[1];
+  } else {
+    const auto lo = __builtin_amdgcn_permlane16_swap(al, bl, false, false), hi = __builtin_amdgcn_permlane16_swap(ah, bh, false, false);
+    al = lo[0]; bl = lo[1]; ah = hi[0]; bh = hi[1];
+  }
+  return __hiloint2double((int)ah, (int)al) + __hiloint2double((int)bh, (int)bl);
+}
+template <int CTRL> __device__ __forceinline__ double dpp64(double v) {
+  const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xF, 0xF, true);
+  const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xF, 0xF, true);
+  return __hiloint2double(hi, lo);
+}
 template <bool VEC>
 __global__ __launch_bounds__(kSimThreads) void k_frame_similarity(const float* __restrict__ frames, int T, long long F,
                                                                   float* __restrict__ sim) {
@@ -183,18 +202,25 @@ __global__ __launch_bounds__(kSimThreads) void k_frame_similarity(const float* _
     add(x, 1);
   }
   // 32 sums over 64 lanes: a lane hands half of its sums to its partner and takes the other half, five
-  // times; what is left of each sum is in two lanes
+  // times (lane bits 5 .. 1 choose sum bits 4 .. 0); what is left of each sum is in two lanes.  All of it register to
+  // register: the 62 trips through LDS that it took were 1.2 us of the 7.7 of 64 frames of 10 240, 5.1 -> 3.7 at 2048.
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
-  for (int half = 16; half > 0; half >>= 1) {
-    const bool up = lane & (2 * half);                    // lane bits 5 .. 1 choose sum bits 4 .. 0
+  for (int k = 0; k < 16; ++k) acc[k] = halves_swap<32>(acc[k], acc[k + 16]);
+#pragma unroll
+  for (int k = 0; k < 8; ++k) acc[k] = halves_swap<16>(acc[k], acc[k + 8]);
+  auto trade = [&](auto pattern, int half, int bit) {
+    const bool up = lane & bit;
 #pragma unroll
     for (int k = 0; k < half; ++k) {
       const double mine = up ? acc[k + half] : acc[k], give = up ? acc[k] : acc[k + half];
-      acc[k] = mine + __shfl_xor(give, 2 * half, 64);
+      acc[k] = mine + dpp64<decltype(pattern)::value>(give);
     }
-  }
-  acc[0] += __shfl_xor(acc[0], 1, 64);
+  };
+  trade(std::integral_constant<int, 0x128>{}, 4, 8);      // lane ^ 8: a row of 16 turned by 8
+  trade(std::integral_constant<int, 0x141>{}, 2, 4);      // 7 - lane in each 8: the other quad
+  trade(std::integral_constant<int, 0x4E>{}, 1, 2);       // lane ^ 2
+  acc[0] += dpp64<0xB1>(acc[0]);                          // lane ^ 1
   __shared__ double part[kSimThreads / 64][32], total[32];
   if (!(lane & 1)) part[wave][lane >> 1] = acc[0];
   __syncthreads();
