@@ -297,7 +297,10 @@ hipError_t launch_cfg_ddim_noise(float* x, const float* eps_c, const float* eps_
 hipError_t launch_gemm(int bf16, int mode, const void* A, const void* Wt, int M, int N, int K,
                        const EpiParams& ep, hipStream_t s, void* scratch = nullptr, size_t scratch_bytes = 0,
                        const void* w_parts = nullptr);
-// w_parts (optional, fp32): the weights once more, split into bf16 parts (launch_split_weights, split_weights_bytes)
+// w_parts (optional): the weights once more, fp32 split into bf16 parts (launch_split_weights, split_weights_bytes), bf16 in
+// fragment order (launch_pack_weights, N * K elements, where packs_weights)
+bool packs_weights(int N, int K);
+hipError_t launch_pack_weights(const void* W, void* out, int N, int K, hipStream_t s);
 size_t split_weights_bytes(int N, int K);
 hipError_t launch_split_weights(const float* Wt, void* out, int N, int K, hipStream_t s);
 hipError_t launch_attention(int bf16, const AttnParams& p, int impl, hipStream_t s);

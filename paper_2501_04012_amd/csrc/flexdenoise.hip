@@ -67,7 +67,7 @@ struct Profiler {
 struct Linear {           // weights [out, in] in the activation dtype, bias fp32
   void* wt = nullptr;
   float* b = nullptr;
-  void* parts = nullptr;  // fp32: the weights once more, split into bf16 parts or (chain) in fragment order
+  void* parts = nullptr;  // products over token rows: the weights once more, fp32 split into bf16 parts, bf16 (and fp32 chains) in fragment order
   int in = 0, out = 0;
 };
 
@@ -200,11 +200,12 @@ size_t layout_weights(fc_model* m, unsigned char* base) {
     L.wt = cv.take((size_t)in * out * es);
     L.b = (float*)cv.take((size_t)out * 4);
   };
-  // the products over all token rows of fp32 models
+  // the products over all token rows
   auto lin_rows = [&](Linear& L, int in, int out) {
     lin(L, in, out);
     if (m->chain_shape) L.parts = cv.take((size_t)in * out * es);
     else if (!m->bf16) L.parts = cv.take(split_weights_bytes(out, in));
+    else if (packs_weights(out, in)) L.parts = cv.take((size_t)in * out * es);
   };
   lin(m->t1, c.t_embed_dim, D);
   lin(m->t2, D, D);
@@ -758,8 +759,9 @@ int fc_model_set_weights(fc_model* m, const float* blob, size_t n_floats) {
   auto up_lin = [&](Linear& L) -> hipError_t {
     hipError_t e = up_matrix_t(L.wt, L.in, L.out);
     if (e == hipSuccess && L.parts)
-      e = m->chain_shape ? launch_pack_chain((const float*)L.wt, (float*)L.parts, L.out, L.in, nullptr)
-                         : launch_split_weights((const float*)L.wt, L.parts, L.out, L.in, nullptr);
+      e = m->bf16 ? launch_pack_weights(L.wt, L.parts, L.out, L.in, nullptr)
+          : m->chain_shape ? launch_pack_chain((const float*)L.wt, (float*)L.parts, L.out, L.in, nullptr)
+                           : launch_split_weights((const float*)L.wt, L.parts, L.out, L.in, nullptr);
     if (e != hipSuccess) return e;
     return up_f32(L.b, L.out);
   };

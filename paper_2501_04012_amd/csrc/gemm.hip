@@ -82,14 +82,13 @@ __device__ __forceinline__ void add_partial(f32x16 (&acc)[TM][TN], const float* 
 // Epilogue of one BM x BN tile, shared by the product kernel and the split-K fix-up: bias,
 // activation / gate / q scale, conversion and stores.  `stage` is an idle operand stage of
 // the workgroup (output rows pass through it), sbias / sgate the tile's bias and gate slices.
-template <int BM, int BN, int BK, int WR, int WC, typename Epi>
+template <int BM, int BN, int WR, int WC, int STAGE_BYTES, typename Epi>
 __device__ __forceinline__ void gemm_tile_epilogue(const f32x16 (&acc)[BM / WR / 32][BN / WC / 32], unsigned char* stage,
                                                    const float* sbias, const float* sgate, const Epi& epi, int bm0,
                                                    int bn0, int M, int N) {
   constexpr int NW = WR * WC;
   constexpr int WTM = BM / WR, WTN = BN / WC;
   constexpr int TM = WTM / 32, TN = WTN / 32;
-  constexpr int STAGE_BYTES = (BM + BN) * BK * 2;
   // The lane and wave numbers pass through an empty asm: everything derived from them here (LDS
   // staging offsets, output offsets) is then computed inside the epilogue.  Left to itself the
   // compiler computes these per-lane constants once, ahead of the persistent tile loop, finds no
@@ -397,7 +396,7 @@ __global__ __launch_bounds__(WR * WC * 64) void k_gemm_dlds_any(const bf16_t* __
     __builtin_amdgcn_s_barrier();
 
     if (slot < 0) {
-      gemm_tile_epilogue<BM, BN, BK, WR, WC>(acc, smem + ((g - 1) & 1) * STAGE_BYTES, sbias, sgate, epi, bm0, bn0, M, N);
+      gemm_tile_epilogue<BM, BN, WR, WC, STAGE_BYTES>(acc, smem + ((g - 1) & 1) * STAGE_BYTES, sbias, sgate, epi, bm0, bn0, M, N);
     } else {
       store_partial<TM, TN>(acc, partial + (size_t)slot * (BM * BN));
     }
@@ -674,7 +673,7 @@ __global__ __launch_bounds__(WR * WC * 64) void k_gemm_dlds(const bf16_t* __rest
     // every wave is done reading the stage just multiplied ((g - 1) & 1): the epilogue stages
     // its output rows there; the next unit's first K tile is complete in the other stage
     if (slot < 0) {
-      gemm_tile_epilogue<BM, BN, BK, WR, WC>(acc, smem + ((g - 1) & 1) * STAGE_BYTES, sbias, sgate, epi, bm0, bn0, M, N);
+      gemm_tile_epilogue<BM, BN, WR, WC, STAGE_BYTES>(acc, smem + ((g - 1) & 1) * STAGE_BYTES, sbias, sgate, epi, bm0, bn0, M, N);
     } else {
       store_partial<TM, TN>(acc, partial + (size_t)slot * (BM * BN));
     }
@@ -685,6 +684,198 @@ __global__ __launch_bounds__(WR * WC * 64) void k_gemm_dlds(const bf16_t* __rest
     cur = nxt;
   }
 #endif
+}
+
+// ---------------------------------------------------------------- the product kernel, weights straight to registers
+// For weights that were packed into fragment order when the model was loaded ([N / 32][K / 16][lane][8], k_pack_weights): a
+// fragment is 1 KB in a row and goes from L2 to the registers of the one wave column that needs it; LDS holds A alone.  A
+// workgroup is four waves side by side, each 128 rows by BN / 4 columns, so that no fragment is fetched twice, and small
+// enough that two (BN 256: 212 registers, 34 KB of LDS) or four of them (BN 128) share a CU: one's epilogue and first loads run
+// under another's products, and tiles half the size fill the last round better.  Of k_gemm_dlds it keeps the tile order, the
+// swizzled A stages, the K loop (even number of K tiles, barrier ahead of the last slice) and the epilogue.
+// A fragment's registers are loaded for the next K tile right behind the products that used them.
+//
+// Against k_gemm_dlds the 256x256 form of this kernel is level (990 and 994 us at 17776 x 12288 x 3072: a third less LDS traffic
+// buys nothing, the power limit bounds both), so what counts are rounds and epilogues (the rule is in the dispatch).
+// us, before and now: 32768 x 1152 x 4608 320, 287; 9326 x 6144 x 2048 203, 178; 4096 x 4608 x 1152 49, 44;
+// 8192 x 3456 x 1152 72, 67; 314 products of 300 to 33 000 rows, 576 to 3072 wide: 0.92 of the time in the mean.
+template <int BM, int BN, typename Epi>
+__global__ __launch_bounds__(256, 2) void k_gemm_packed(const bf16_t* __restrict__ A, const void* __restrict__ Wp, int M, int N,
+                                                        int K, int tiles_m, int tiles_n, Epi epi) {
+#if defined(__HIP_DEVICE_COMPILE__)   // buffer resources are a device-side type: the host pass sees an empty body
+  constexpr int BK = 64, NW = 4, WTN = BN / NW, TM = BM / 32, TN = WTN / 32, KS = BK / 16;
+  constexpr int CPR = BK / 8, RPL = 16 / CPR, RW = 4 * RPL, LA = BM / RW / NW;
+  static_assert(BM % (RW * NW) == 0 && BN % 128 == 0 && BN <= 256 && Epi::kRowRuns, "whole wave-loads; bias and gate slices of 256");
+  constexpr int STAGE_BYTES = BM * BK * 2;
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+  float* const sbias = (float*)(smem + 2 * STAGE_BYTES);
+  float* const sgate = sbias + 256;
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int li = lane & 31, lh = lane >> 5;
+  // an absent bias reads as zeros, an absent gate as ones (written once: no DMA touches them)
+  if (!epi.P.bias) sbias[tid] = 0.0f;
+  if (Epi::kHasGate && !epi.P.gate) sgate[tid] = 1.0f;
+
+  const int total = tiles_m * tiles_n, nk = K / BK, padded = (total + 255) / 256 * 256;
+  auto next_tile = [&](int& vb, int& bm0, int& bn0) {      // k_gemm_dlds's order, no split tiles
+    for (vb += gridDim.x; vb < padded; vb += gridDim.x) {
+      const int local = vb >> 3, t = ((local >> 5) * 8 + (vb & 7)) * 32 + (local & 31);
+      if (t >= total) continue;
+      const int per_group = 8 * tiles_n, group = t / per_group, first_m = group * 8, gsz = min(tiles_m - first_m, 8);
+      bm0 = (first_m + (t % per_group) % gsz) * BM;
+      bn0 = ((t % per_group) / gsz) * BN;
+      return true;
+    }
+    return false;
+  };
+  unsigned voff[LA];                                       // this lane's byte offsets inside an A panel, as in k_gemm_dlds
+  {
+    const int line_in = lane >> 4, sl = lane & 15;
+    const int row0 = wave * RW + line_in * RPL + sl / CPR, kc = (sl % CPR) ^ ((wave * 4 + line_in) % CPR);
+#pragma unroll
+    for (int j = 0; j < LA; ++j) voff[j] = (unsigned)(row0 + NW * RW * j) * (unsigned)K * 2u + (unsigned)kc * 16u;
+  }
+  struct Panels { __amdgpu_buffer_rsrc_t a; int b; };
+  auto panels = [&](int bm0, int bn0) {                    // rows past the end of A, and columns past that of the weights, load as zero
+    Panels p;
+    p.a = __builtin_amdgcn_make_buffer_rsrc((void*)(A + (size_t)bm0 * K), 0, (int)((unsigned)(M - bm0) * (unsigned)K * 2u), 0x00020000);
+    p.b = (bn0 + wave * WTN) / 32 * (K / 16) * 1024;
+    return p;
+  };
+  const auto rb = __builtin_amdgcn_make_buffer_rsrc((void*)Wp, 0, (int)((unsigned)N * (unsigned)K * 2u), 0x00020000);
+  auto dma_a = [&](const Panels& p, int kt, int stage) {
+#pragma unroll
+    for (int j = 0; j < LA; ++j)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(p.a, (lds_void*)(smem + stage * STAGE_BYTES + (wave + NW * j) * 1024), 16, (int)voff[j], kt * (BK * 2), 0, 0);
+  };
+  auto issue_vectors = [&](int bn0) {
+    int n = bn0 + lane * 4;
+    n = n < N ? n : 0;                                     // columns past N are never stored
+    if (wave == 0 && epi.P.bias) __builtin_amdgcn_global_load_lds((gbl_void*)(epi.P.bias + n), (lds_void*)sbias, 16, 0, 0);
+    if (Epi::kHasGate && wave == 1 && epi.P.gate)
+      __builtin_amdgcn_global_load_lds((gbl_void*)(epi.P.gate + n), (lds_void*)sgate, 16, 0, 0);
+  };
+  const int a_row = (li / RPL) * 256 + (li % RPL) * CPR * 16, a_x = (li / RPL) % CPR;
+  constexpr int TILE_STRIDE = (32 / RPL) * 256;            // 32 rows further down
+
+  int vb = (int)blockIdx.x - (int)gridDim.x, bm0 = 0, bn0 = 0;
+  if (!next_tile(vb, bm0, bn0)) return;
+  Panels cur = panels(bm0, bn0);
+  bf16x8 fa[2][TM], fb[KS][TN];
+  auto load_b = [&](const Panels& p, int kt, int ks) {
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+      fb[ks][j] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rb, lane * 16, p.b + j * (K / 16) * 1024 + (kt * KS + ks) * 1024, 0));
+  };
+  dma_a(cur, 0, 0);
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) load_b(cur, 0, ks);
+  wait_vm<KS * TN>();                                      // A has landed, the fragments may be on their way
+  __builtin_amdgcn_s_barrier();
+  constexpr int kDsRead = 0x100, kMfma = 0x008, kVmem = 0x010;
+  for (;;) {
+    int nvb = vb, nbm0 = 0, nbn0 = 0;
+    const bool has_next = next_tile(nvb, nbm0, nbn0);
+    Panels nxt = cur;
+    if (has_next) nxt = panels(nbm0, nbn0);
+    issue_vectors(bn0);                                    // awaited and published with the tile's second K tile
+    f32x16 acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+    auto load_a = [&](int stage, int ks, bf16x8 (&xa)[TM]) {
+      const unsigned char* pa = smem + stage * STAGE_BYTES + a_row + (((2 * ks + lh) ^ a_x) << 4);
+#pragma unroll
+      for (int i = 0; i < TM; ++i) xa[i] = *(const bf16x8*)(pa + i * TILE_STRIDE);
+    };
+    auto multiply = [&](int ks) {                          // weights as the A operand: a lane ends up with consecutive columns
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[ks][j], fa[ks & 1][i], acc[i][j], 0, 0, 0);
+    };
+    // past the end of this tile the next one's first K tiles, past the last tile this one's K tile 0 again (never used)
+    auto request_a = [&](int ka, int stage) { dma_a(ka < nk ? cur : nxt, ka < nk ? ka : (has_next ? ka - nk : 0), stage); };
+    auto request_b = [&](int ka, int ks) { load_b(ka < nk ? cur : nxt, ka < nk ? ka : (has_next ? ka - nk : 0), ks); };
+    auto kstep = [&](auto par, auto first, auto last, int kt) {
+      constexpr int PAR = decltype(par)::value;
+      constexpr bool FIRST = decltype(first)::value, LAST = decltype(last)::value;
+      if constexpr (FIRST) {
+        request_a(kt + 1, PAR ^ 1);
+        load_a(PAR, 0, fa[0]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+#pragma unroll
+      for (int ks = 0; ks + 1 < KS; ++ks) {
+        load_a(PAR, ks + 1, fa[(ks + 1) & 1]);
+        multiply(ks);
+        request_b(kt + 1, ks);
+#pragma unroll
+        for (int r = 0; r < TM; ++r) {
+          __builtin_amdgcn_sched_group_barrier(kMfma, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(kDsRead, 1, 0);
+        }
+        if constexpr (TN > 1) __builtin_amdgcn_sched_group_barrier(kMfma, TM * TN - TM, 0);
+        __builtin_amdgcn_sched_group_barrier(kVmem, TN, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      // K tile kt + 1 of A has landed: behind its DMA came the fragments requested since, one slice more where the DMA
+      // was issued ahead of the last K tile's last slice; this wave is done reading kt
+      wait_vm_lgkm0<(FIRST ? KS - 1 : KS) * TN>();
+      __builtin_amdgcn_s_barrier();
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (!LAST) {
+        request_a(kt + 2, PAR);
+        load_a(PAR ^ 1, 0, fa[0]);
+      }
+      multiply(KS - 1);
+      request_b(kt + 1, KS - 1);
+      if constexpr (!LAST) {
+#pragma unroll
+        for (int r = 0; r < TM; ++r) {
+          __builtin_amdgcn_sched_group_barrier(kMfma, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(kDsRead, 1, 0);
+          if (r < LA) __builtin_amdgcn_sched_group_barrier(kVmem, 1, 0);
+        }
+        if constexpr (TN > 1) __builtin_amdgcn_sched_group_barrier(kMfma, TM * TN - TM, 0);
+        __builtin_amdgcn_sched_group_barrier(kVmem, TN, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    using P0 = std::integral_constant<int, 0>; using P1 = std::integral_constant<int, 1>;
+    using Yes = std::true_type; using No = std::false_type;
+    kstep(P0{}, Yes{}, No{}, 0);
+    for (int kt = 1; kt + 1 < nk; kt += 2) {
+      kstep(P1{}, No{}, No{}, kt);
+      kstep(P0{}, No{}, No{}, kt + 1);
+    }
+    kstep(P1{}, No{}, Yes{}, nk - 1);
+    // the last K tile was in stage 1; the next tile's first one is complete in stage 0
+    gemm_tile_epilogue<BM, BN, 1, NW, STAGE_BYTES>(acc, smem + STAGE_BYTES, sbias, sgate, epi, bm0, bn0, M, N);
+    if (!has_next) break;
+    __builtin_amdgcn_s_barrier();                          // the staging slices are read out
+    vb = nvb; bm0 = nbm0; bn0 = nbn0;
+    cur = nxt;
+  }
+#endif
+}
+
+// W [N, K] as [N / 32][K / 16][lane][8]: lane i + 32 h holds row i, columns 8 h .. 8 h + 7.  Once per model.
+__global__ __launch_bounds__(256) void k_pack_weights(const bf16_t* __restrict__ W, bf16_t* __restrict__ out, int N, int K) {
+  const long long x = (long long)blockIdx.x * 256 + threadIdx.x, blk = x >> 6;
+  if (x >= (long long)N * K / 8) return;
+  const int lane = (int)(x & 63), ks = (int)(blk % (K / 16)), nb = (int)(blk / (K / 16));
+  *(bf16x8*)(out + x * 8) = *(const bf16x8*)(W + (size_t)(nb * 32 + (lane & 31)) * K + ks * 16 + (lane >> 5) * 8);
+}
+bool packs_weights(int N, int K) { return N % 32 == 0 && K % 128 == 0 && (unsigned long long)N * K * 2 < (1ull << 31); }
+hipError_t launch_pack_weights(const void* W, void* out, int N, int K, hipStream_t s) {
+  if (!packs_weights(N, K)) return hipErrorInvalidValue;
+  k_pack_weights<<<ceil_div((long long)N * K / 8, 256), 256, 0, s>>>((const bf16_t*)W, (bf16_t*)out, N, K);
+  return hipGetLastError();
 }
 
 // ---------------------------------------------------------------- split-K fix-up
@@ -717,7 +908,7 @@ __global__ __launch_bounds__(WR * WC * 64) void k_gemm_fixup(int M, int N, int t
   const float* mine = partial + (size_t)blockIdx.x * splits * (BM * BN);
   for (int r = 0; r < splits; ++r) add_partial<TM, TN>(acc, mine + (size_t)r * (BM * BN), r == 0);
   __syncthreads();
-  gemm_tile_epilogue<BM, BN, BK, WR, WC>(acc, smem, sbias, sgate, epi, bm0, bn0, M, N);
+  gemm_tile_epilogue<BM, BN, WR, WC, STAGE_BYTES>(acc, smem, sbias, sgate, epi, bm0, bn0, M, N);
 }
 
 // ---------------------------------------------------------------- MFMA kernel for products with few tiles
@@ -1237,6 +1428,18 @@ __global__ __launch_bounds__(256) void k_gemm_plain(const T* __restrict__ A, con
 }
 
 // ---------------------------------------------------------------- dispatch
+// Ranges of K that the tiles of a last round are split into, 1: none (run_dlds says when).
+template <int BM, int BN>
+static int split_ranges(long long total, long long slots, int K, const void* scratch, size_t scratch_bytes) {
+  const long long rem = total % 256, full = total - rem;
+  if (total / 256 > 8 || rem == 0 || rem > slots / 2 || (slots != 256 && full != 0) || !scratch || ((uintptr_t)scratch & 15) != 0) return 1;
+  long long sp = slots / rem;
+  sp = sp > 4 ? 4 : sp;
+  sp = sp > K / 128 ? K / 128 : sp;
+  if (sp < 2 || (long long)K * (sp - 1) / sp < 1536 || (size_t)(rem * sp) * BM * BN * sizeof(float) > scratch_bytes) return 1;
+  return (int)sp;
+}
+
 template <int BM, int BN, int BK, int WR, int WC, int S, int MODE>
 static hipError_t run_dlds(const void* A, const void* Wt, int M, int N, int K, const EpiParams& ep, void* scratch,
                            size_t scratch_bytes, hipStream_t s) {
@@ -1266,25 +1469,17 @@ static hipError_t run_dlds(const void* A, const void* Wt, int M, int N, int K, c
   // taken, few enough rounds that one of them matters (measured: 3.3 rounds become 11 %
   // faster, 13.1 rounds not at all), a K long enough that the saved part of a tile outweighs
   // the fix-up launch, and a caller that lends scratch memory for the partial tiles.
-  int splits = 1;
   unsigned launch = grid;
   const long long rem = total % 256, full = total - rem;
   // (A product of fewer tiles than half the slots is all remainder: its tiles are split the
   // same way; with two workgroups per CU there are 512 slots for the units.)
   // (With two workgroups per CU every product of up to 512 tiles runs in one round anyway: only
   // the all-remainder case is split there.)
-  if (total / 256 <= 8 && rem > 0 && rem <= slots / 2 && (slots == 256 || full == 0) && scratch &&
-      ((uintptr_t)scratch & 15) == 0) {
-    long long sp = slots / rem;
-    sp = sp > 4 ? 4 : sp;
-    sp = sp > K / BK / 2 ? K / BK / 2 : sp;
-    if (sp >= 2 && (long long)K * (sp - 1) / sp >= 1536 &&
-        (size_t)(rem * sp) * BM * BN * sizeof(float) <= scratch_bytes) {
-      splits = (int)sp;
-      const long long units = (full + rem * sp + 7) / 8 * 8;
-      launch = (unsigned)(units < slots ? units : slots);
-      if (launch < grid) launch = grid;
-    }
+  const int splits = split_ranges<BM, BN>(total, slots, K, scratch, scratch_bytes);
+  if (splits >= 2) {
+    const long long units = (full + rem * splits + 7) / 8 * 8;
+    launch = (unsigned)(units < slots ? units : slots);
+    if (launch < grid) launch = grid;
   }
   if (even)
     kern<<<launch, WR * WC * 64, smem, s>>>((const bf16_t*)A, (const bf16_t*)Wt, M, N, K, tiles_m, tiles_n, epi, splits, (float*)scratch);
@@ -1302,6 +1497,19 @@ static hipError_t run_dlds(const void* A, const void* Wt, int M, int N, int K, c
     fattr_set = true;
   }
   fix<<<(unsigned)rem, WR * WC * 64, fsmem, s>>>(M, N, tiles_m, tiles_n, epi, splits, (const float*)scratch);
+  return hipGetLastError();
+}
+
+template <int BM, int BN, int PER_CU, int MODE>
+static hipError_t run_packed(const void* A, const void* Wp, int M, int N, int K, const EpiParams& ep, hipStream_t s) {
+  using Epi = Epilogue<bf16_t, MODE>;
+  Epi epi = Epi::make(ep, M, N);
+  constexpr size_t smem = (size_t)2 * BM * 128 + 2048;     // two stages of A, bias and gate of a tile
+  auto kern = k_gemm_packed<BM, BN, Epi>;
+  const int tiles_m = ceil_div(M, BM), tiles_n = ceil_div(N, BN);
+  const long long padded = ((long long)tiles_m * tiles_n + 255) / 256 * 256;
+  const unsigned grid = (unsigned)(padded < 256LL * PER_CU ? padded : 256LL * PER_CU);   // persistent, as in run_dlds
+  kern<<<grid, 256, smem, s>>>((const bf16_t*)A, Wp, M, N, K, tiles_m, tiles_n, epi);
   return hipGetLastError();
 }
 
@@ -1371,32 +1579,60 @@ static hipError_t dispatch_mode(int bf16, const void* A, const void* Wt, int M, 
   // narrow or short-K products.  Thresholds from timings of the workload shapes.
   const long long tiles256 = (long long)ceil_div(M, 256) * ceil_div(N, 256);
   const double waste = (double)ceil_div(N, 256) * 256.0 / N - 1.0;
-  if (N % 192 == 0 && waste > 0.05 && (long long)ceil_div(M, 256) * (N / 192) >= 192)
-    return run_dlds<256, 192, 64, 4, 2, 2, MODE>(A, Wt, M, N, K, ep, scratch, scratch_bytes, s);
+  enum { T128, T192, T256, T384 } tile = T128;
+  auto fill = [](long long t) { return (double)t / (double)((t + 255) / 256 * 256); };
   // 384x192 (96x96 per wave) is no faster per tile than 256x256, but where its tile count fills
   // whole rounds of 256 and that of 256x256 does not, it saves most of a round (the full-3D
   // out-projection and fc2: 752 tiles = 2.94 rounds against 840 = 3.28; 2-5 % over the split
   // last round)
-  if constexpr (MODE != EPI_UNPATCH) if (N % 192 == 0 && K >= 2048 && tiles256 >= 600) {
-    const long long t384 = (long long)ceil_div(M, 384) * (N / 192);
-    const double fill384 = (double)t384 / (double)((t384 + 255) / 256 * 256);
-    const double fill256 = (double)tiles256 / (double)((tiles256 + 255) / 256 * 256);
-    if (fill384 >= 0.95 && fill256 < 0.85 && waste <= 0.05)
-      return run_dlds<384, 192, 64, 4, 2, 2, MODE>(A, Wt, M, N, K, ep, scratch, scratch_bytes, s);
-  }
-  if (tiles256 >= 600 && (waste <= 0.05 || K >= 2048)) return run_dlds<256, 256, 64, 4, 2, 2, MODE>(A, Wt, M, N, K, ep, scratch, scratch_bytes, s);
+  if (N % 192 == 0 && waste > 0.05 && (long long)ceil_div(M, 256) * (N / 192) >= 192) tile = T192;
+  else if (MODE != EPI_UNPATCH && N % 192 == 0 && K >= 2048 && tiles256 >= 600 && waste <= 0.05 &&
+           fill((long long)ceil_div(M, 384) * (N / 192)) >= 0.95 && fill(tiles256) < 0.85) tile = T384;
+  else if (tiles256 >= 600 && (waste <= 0.05 || K >= 2048)) tile = T256;
   // Mid-size products (a few thousand rows) that the thresholds above leave to 128x128: the large
   // tiles still win where their tile count fills its rounds of 256 workgroups (measured at
   // M = 4096 and 8192: QKV of the 1152-wide model 8-14 % faster with 256x256, its fc1 at
   // M = 8192 7 % faster with 256x192; where the last round would be mostly empty, 128x128 stays)
-  {
-    auto fill = [](long long t) { return (double)t / (double)((t + 255) / 256 * 256); };
-    if (tiles256 >= 200 && waste <= 0.05 && fill(tiles256) >= 0.85)
-      return run_dlds<256, 256, 64, 4, 2, 2, MODE>(A, Wt, M, N, K, ep, scratch, scratch_bytes, s);
-    if (N % 192 == 0) {
-      const long long t192 = (long long)ceil_div(M, 256) * (N / 192);
-      if (t192 >= 200 && fill(t192) >= 0.95) return run_dlds<256, 192, 64, 4, 2, 2, MODE>(A, Wt, M, N, K, ep, scratch, scratch_bytes, s);
+  else if (tiles256 >= 200 && waste <= 0.05 && fill(tiles256) >= 0.85) tile = T256;
+  else if (N % 192 == 0 && (long long)ceil_div(M, 256) * (N / 192) >= 200 && fill((long long)ceil_div(M, 256) * (N / 192)) >= 0.95) tile = T192;
+
+  // Packed weights: where their kernel's estimate is below that of the tile just chosen.  The estimates, in us, are fits over
+  // 325 products (M 256 to 38 000, N and K 576 to 12 288, each timed in every form): tiles of the fullest CU times a
+  // time per K tile and one per tile.  314 products: 0.917 of the time in the mean, none more than 2 % slower.  A lone 128x256
+  // tile on a CU (two waves a SIMD short) is up to 1.13 times slower than estimated and not taken; products whose 128x128 tiles are
+  // all split along K stay with them (up to 1.58).
+  if constexpr (MODE == EPI_HEADS || MODE == EPI_GATE || MODE == EPI_GELU) {
+    if (w_parts && ((uintptr_t)w_parts & 15) == 0 && packs_weights(N, K) && (unsigned long long)M * K * 2 < (1ull << 32)) {
+      const double kt = K / 64.0;
+      auto per_cu = [&](int bm, int bn) { return (double)(((long long)ceil_div(M, bm) * ceil_div(N, bn) + 255) / 256); };
+      auto rounds = [&](int bm, int bn, int sp, double start, double k, double fixed) {
+        if (sp < 2) return start + per_cu(bm, bn) * (k * kt + fixed);
+        const double full = (double)((long long)ceil_div(M, bm) * ceil_div(N, bn) / 256);
+        return start + full * (k * kt + fixed) + (k * kt / sp + fixed) + 14.0;
+      };
+      auto lone = [&](double k, double fixed) { return per_cu(128, 128) == 1.0 ? k * kt + fixed : 0.0; };
+      auto tiles = [&](int bm, int bn) { return (long long)ceil_div(M, bm) * ceil_div(N, bn); };
+      double now = 0.0;
+      switch (tile) {
+        case T256: now = rounds(256, 256, split_ranges<256, 256>(tiles(256, 256), 256, K, scratch, scratch_bytes), -1.75, 1.266, 8.84); break;
+        case T192: now = rounds(256, 192, split_ranges<256, 192>(tiles(256, 192), 256, K, scratch, scratch_bytes), 0.04, 1.051, 6.49); break;
+        case T384: now = rounds(384, 192, split_ranges<384, 192>(tiles(384, 192), 256, K, scratch, scratch_bytes), -0.74, 1.386, 11.56); break;
+        case T128:
+          if (split_ranges<128, 128>(tiles(128, 128), 512, K, scratch, scratch_bytes) < 2) now = rounds(128, 128, 1, 1.84, 0.443, 1.40) + lone(0.21, -0.72);
+          break;
+      }
+      const double e256 = per_cu(128, 256) >= 2.0 ? rounds(128, 256, 1, -0.09, 0.702, 2.68) : 1e30,
+                   e128 = rounds(128, 128, 1, 1.25, 0.419, 1.11) + lone(0.083, 0.56);
+      if (e256 < now && e256 <= e128) return run_packed<128, 256, 2, MODE>(A, w_parts, M, N, K, ep, s);
+      if (e128 < now) return run_packed<128, 128, 4, MODE>(A, w_parts, M, N, K, ep, s);
     }
+  }
+  switch (tile) {
+    case T256: return run_dlds<256, 256, 64, 4, 2, 2, MODE>(A, Wt, M, N, K, ep, scratch, scratch_bytes, s);
+    case T192: return run_dlds<256, 192, 64, 4, 2, 2, MODE>(A, Wt, M, N, K, ep, scratch, scratch_bytes, s);
+    case T384:
+      if constexpr (MODE != EPI_UNPATCH) return run_dlds<384, 192, 64, 4, 2, 2, MODE>(A, Wt, M, N, K, ep, scratch, scratch_bytes, s);
+    case T128: break;
   }
   return run_dlds<128, 128, 64, 2, 2, 2, MODE>(A, Wt, M, N, K, ep, scratch, scratch_bytes, s);
 }
