@@ -736,11 +736,14 @@ __global__ __launch_bounds__(256, 2) void k_gemm_packed(const bf16_t* __restrict
 #pragma unroll
     for (int j = 0; j < LA; ++j) voff[j] = (unsigned)(row0 + NW * RW * j) * (unsigned)K * 2u + (unsigned)kc * 16u;
   }
-  struct Panels { __amdgpu_buffer_rsrc_t a; int b; };
-  auto panels = [&](int bm0, int bn0) {                    // rows past the end of A, and columns past that of the weights, load as zero
+  struct Panels { __amdgpu_buffer_rsrc_t a; int b[TN]; };
+  // Rows past the end of A load as zero; columns past N, which are never stored, repeat the last 32 columns: the offset that
+  // chooses a fragment is a scalar one, which the buffer's range check does not cover.
+  auto panels = [&](int bm0, int bn0) {
     Panels p;
     p.a = __builtin_amdgcn_make_buffer_rsrc((void*)(A + (size_t)bm0 * K), 0, (int)((unsigned)(M - bm0) * (unsigned)K * 2u), 0x00020000);
-    p.b = (bn0 + wave * WTN) / 32 * (K / 16) * 1024;
+#pragma unroll
+    for (int j = 0; j < TN; ++j) p.b[j] = min((bn0 + wave * WTN) / 32 + j, N / 32 - 1) * (K / 16) * 1024;
     return p;
   };
   const auto rb = __builtin_amdgcn_make_buffer_rsrc((void*)Wp, 0, (int)((unsigned)N * (unsigned)K * 2u), 0x00020000);
@@ -766,7 +769,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_packed(const bf16_t* __restrict
   auto load_b = [&](const Panels& p, int kt, int ks) {
 #pragma unroll
     for (int j = 0; j < TN; ++j)
-      fb[ks][j] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rb, lane * 16, p.b + j * (K / 16) * 1024 + (kt * KS + ks) * 1024, 0));
+      fb[ks][j] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rb, lane * 16, p.b[j] + (kt * KS + ks) * 1024, 0));
   };
   dma_a(cur, 0, 0);
 #pragma unroll
@@ -1228,7 +1231,8 @@ __global__ __launch_bounds__(WR * WC * 64, PER_SIMD) void k_gemm_f32_parts(const
 #pragma unroll
   for (int j = 0; j < LD; ++j)
     w_off[j] = (wave_u + NW * j) / 3 * slices * 3072 + (wave_u + NW * j) % 3 * 1024 + lane * 16;
-  auto request = [&](int ks, int stage) {
+  auto request = [&](int at, int stage) {
+    const int ks = min(at, slices - 1);                  // the scalar offset is not range-checked: past the end the last slice again
 #pragma unroll
     for (int j = 0; j < LD; ++j) {
       if (WL % NW != 0 && wave_u + NW * j >= WL) break;
