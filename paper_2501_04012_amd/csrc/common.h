@@ -274,11 +274,22 @@ hipError_t launch_transpose_convert(const float* in, void* out, int rows, int co
 hipError_t launch_act_to_f32_rows(int bf16, const void* in, float* out, int rows, int D,
                                   int in_rows_per_b, int out_rows_per_b, int out_row_off,
                                   int in_b_split, int in_shared_tail, hipStream_t s);
-hipError_t launch_sinusoid(float t, int dim, float* out, hipStream_t s);
-hipError_t launch_gemv(int bf16, const float* in, int K, const void* Wt, const float* bias, float* out, int N,
-                       int in_silu, int out_silu, int layers, size_t w_layer_stride, size_t b_layer_stride,
-                       size_t out_layer_stride, hipStream_t s, const void* Wt2 = nullptr,
-                       const float* bias2 = nullptr, float* out2 = nullptr, int N2 = 0);
+constexpr int kGemvSteps = 4;              // steps a launch_gemv takes at once
+struct GemvArgs {                          // out[step][layer][n] = f_out(sum_k f_in(in[step][k]) Wt[layer][n][k] + bias[layer][n])
+  const float* in = nullptr;               // [steps, K]; NULL: the sinusoids of `times`
+  float times[kGemvSteps] = {};
+  int steps = 1, K = 0;
+  const void* Wt = nullptr;
+  const float* bias = nullptr;
+  float* out = nullptr;
+  int N = 0, in_silu = 0, out_silu = 0, layers = 1;
+  size_t w_layer_stride = 0, b_layer_stride = 0, out_layer_stride = 0, out_step_stride = 0;
+  const void* Wt2 = nullptr;               // a second product of the same input: out2 [steps, N2]
+  const float* bias2 = nullptr;
+  float* out2 = nullptr;
+  int N2 = 0;
+};
+hipError_t launch_gemv(int bf16, const GemvArgs& g, hipStream_t s);
 constexpr int kPatchF32 = 3;
 hipError_t launch_patch_embed(const float* latent, int R, int B, const float* Wp, const float* bp,
                               const float* pos_sp, const float* pos_t, float* x, int T, int H, int W, int C,

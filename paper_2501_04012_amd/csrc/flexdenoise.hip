@@ -250,7 +250,8 @@ void sincos_1d(double pos, int dim, float* out) {   // [sin(pos w_i) | cos(pos w
 
 // ---------------------------------------------------------------- workspace
 struct Workspace {
-  float *e, *h1, *c, *mod, *fmod;          // timestep path, fp32
+  float *h1, *c;                           // timestep path, fp32, kGemvSteps rows each
+  float *mod, *fmod;                       // this step's modulation vectors, of the kGemvSteps steps prepared together
   void *txt, *y;                           // text in act dtype, projected text
   void *xk, *xv;                           // cross-attention K / V per block (factorized)
   float* x;                                // residual stream fp32 [B, Ns, D]
@@ -270,11 +271,10 @@ Workspace carve(const fc_model* m, int R, int use_cfg, unsigned char* base) {
   w.NT = R + (use_cfg ? 1 : 0);                 // distinct texts: R prompts (+ the shared null)
   const size_t rows = (size_t)w.B * m->Ns;
   Carver cv(base);
-  w.e = (float*)cv.take((size_t)c.t_embed_dim * 4);
-  w.h1 = (float*)cv.take(D * 4);
-  w.c = (float*)cv.take(D * 4);
-  w.mod = (float*)cv.take((size_t)c.depth * m->nmod * D * 4);
-  w.fmod = (float*)cv.take(2 * D * 4);
+  w.h1 = (float*)cv.take(kGemvSteps * D * 4);
+  w.c = (float*)cv.take(kGemvSteps * D * 4);
+  w.mod = (float*)cv.take((size_t)kGemvSteps * c.depth * m->nmod * D * 4);
+  w.fmod = (float*)cv.take(kGemvSteps * 2 * D * 4);
   w.txt = cv.take((size_t)w.NT * c.text_len * c.text_dim * es);
   w.y = cv.take((size_t)w.NT * c.text_len * D * es);
   if (c.attn_mode == FC_ATTN_FACTORIZED_CROSS) {
@@ -611,31 +611,54 @@ int run_layers(const Ctx& c, const float* latent) {
   return FC_OK;
 }
 
-// One forward pass of all B rows + guidance + DDIM update of the R latents.
+// Modulation vectors of `steps` steps from `first` on: sinusoid -> Linear -> SiLU -> Linear -> c; every adaLN layer reads SiLU(c).
+// They depend on the timesteps alone, so the steps of a resume take them kGemvSteps at a time: the adaLN weights, 9 D^2 per
+// block, are read once for all of them.
+int condition_steps(const Ctx& c, const fc_schedule* sched, int first, int steps) {
+  const fc_model* m = c.m;
+  const fc_model_config& cf = m->cfg;
+  const Workspace& w = c.w;
+  const int D = cf.hidden, nm = m->nmod * D;
+  ProfScope ps(c, PC_TIMESTEP_MOD);
+  GemvArgs g;
+  g.steps = steps;
+  for (int i = 0; i < steps; ++i) {
+    float coef[4];
+    int t = 0, rc = step_coefficients(sched, first + i, coef, &t);
+    if (rc != FC_OK) return rc;
+    g.times[i] = (float)t;
+  }
+  g.K = cf.t_embed_dim; g.Wt = m->t1.wt; g.bias = m->t1.b; g.out = w.h1; g.N = D; g.out_silu = 1; g.out_step_stride = D;
+  HIP_TRY(launch_gemv(m->bf16, g, c.s));
+  g.in = w.h1; g.K = D; g.Wt = m->t2.wt; g.bias = m->t2.b; g.out = w.c; g.out_silu = 0;
+  HIP_TRY(launch_gemv(m->bf16, g, c.s));
+  g.in = w.c; g.in_silu = 1;
+  if (cf.depth > 0) {   // the blocks' modulation vectors and the final layer's: one launch
+    g.Wt = m->mod_w; g.bias = m->mod_b; g.out = w.mod; g.N = nm; g.layers = cf.depth;
+    g.w_layer_stride = (size_t)nm * D; g.b_layer_stride = g.out_layer_stride = nm; g.out_step_stride = (size_t)cf.depth * nm;
+    g.Wt2 = m->fmod.wt; g.bias2 = m->fmod.b; g.out2 = w.fmod; g.N2 = 2 * D;
+  } else {
+    g.Wt = m->fmod.wt; g.bias = m->fmod.b; g.out = w.fmod; g.N = 2 * D; g.out_step_stride = 2 * D;
+  }
+  HIP_TRY(launch_gemv(m->bf16, g, c.s));
+  return FC_OK;
+}
+
+// Steps whose vectors are taken together: their inputs share 64 KB of LDS.
+int conditioned_together(const fc_model* m) {
+  const int K = std::max(m->cfg.hidden, m->cfg.t_embed_dim);
+  return K <= 4092 ? kGemvSteps : 1;
+}
+
+// One forward pass of all B rows + guidance + DDIM update of the R latents (condition_steps has run).
 int run_step(const Ctx& c, float* latent, const fc_schedule* sched, int step, float* eps_out) {
   fc_model* m = c.m;
   const fc_model_config& cf = m->cfg;
   const Workspace& w = c.w;
-  const int D = cf.hidden;
   float coef[4], sigma = 0.0f;
   int t = 0;
   int rc = step_coefficients(sched, step, coef, &t, &sigma);
   if (rc != FC_OK) return rc;
-
-  // conditioning: sinusoid -> Linear -> SiLU -> Linear -> c; every adaLN layer reads SiLU(c)
-  const int nm = m->nmod * D;
-  {
-  ProfScope ps(c, PC_TIMESTEP_MOD);
-  HIP_TRY(launch_sinusoid((float)t, cf.t_embed_dim, w.e, c.s));
-  HIP_TRY(launch_gemv(m->bf16, w.e, cf.t_embed_dim, m->t1.wt, m->t1.b, w.h1, D, 0, 1, 1, 0, 0, 0, c.s));
-  HIP_TRY(launch_gemv(m->bf16, w.h1, D, m->t2.wt, m->t2.b, w.c, D, 0, 0, 1, 0, 0, 0, c.s));
-  // the blocks' modulation vectors and the final layer's, both from SiLU(c): one launch
-  if (cf.depth > 0)
-    HIP_TRY(launch_gemv(m->bf16, w.c, D, m->mod_w, m->mod_b, w.mod, nm, 1, 0, cf.depth, (size_t)nm * D, nm, nm, c.s,
-                        m->fmod.wt, m->fmod.b, w.fmod, 2 * D));
-  else
-    HIP_TRY(launch_gemv(m->bf16, w.c, D, m->fmod.wt, m->fmod.b, w.fmod, 2 * D, 1, 0, 1, 0, 0, 0, c.s));
-  }
 
   const bool fact = cf.attn_mode == FC_ATTN_FACTORIZED_CROSS;
   const bool chain = m->chain_shape && chain_fits(chain_base(c), fact ? std::max(m->S, cf.frames) : m->Ns, fact ? cf.text_len : 0);
@@ -835,6 +858,7 @@ int fc_denoise_step(fc_model* m, float* latent, const float* cond, const float* 
   if (rc != FC_OK) return rc;
   if (step < 1 || step > sched->num_steps) return fail(FC_ERR_RANGE, "step must be in 1..num_steps");
   if ((rc = prepare(ctx, cond, null_cond)) != FC_OK) return rc;
+  if ((rc = condition_steps(ctx, sched, step, 1)) != FC_OK) return rc;
   return run_step(ctx, latent, sched, step, eps_out);
 }
 
@@ -859,8 +883,14 @@ int fc_denoise_resume_ex(fc_model* m, float* latent, const float* cond, const fl
   const fc_model_config& cf = m->cfg;
   const size_t lat_elems = (size_t)R * cf.frames * cf.height * cf.width * cf.channels;
   int next = 0;
+  const int together = conditioned_together(m);
   for (int s = k + 1; s <= sched->num_steps; ++s) {
-    if ((rc = run_step(ctx, latent, sched, s, nullptr)) != FC_OK) return rc;
+    const int ahead = (s - k - 1) % together;              // steps since vectors were last taken
+    if (ahead == 0 && (rc = condition_steps(ctx, sched, s, std::min(together, sched->num_steps - s + 1))) != FC_OK) return rc;
+    Ctx at = ctx;
+    at.w.mod += (size_t)ahead * cf.depth * m->nmod * cf.hidden;
+    at.w.fmod += (size_t)ahead * 2 * cf.hidden;
+    if ((rc = run_step(at, latent, sched, s, nullptr)) != FC_OK) return rc;
     if (next < n_export && export_steps[next] == s) {
       // stream-ordered device copy: the next step reads the latent after it, nothing waits on the host
       HIP_TRY(launch_copy_f32(latent, export_dst[next], lat_elems, ctx.s));
