@@ -1282,16 +1282,19 @@ __global__ __launch_bounds__(WR * WC * 64, PER_SIMD) void k_gemm_f32_parts(const
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
   const int a_off = (wr * WTM + li) * 96 + lh * 16, b_off = ((SPLIT_W ? 0 : BM) + wc * WTN + li) * 96 + lh * 16;
   using P0 = std::integral_constant<int, 0>; using P1 = std::integral_constant<int, 1>;
+  request(0, 0);
+  request(1, 1);
 #pragma unroll
   for (int j = 0; j < LA + LB; ++j) fetch(raw[0], j, 0);
 #pragma unroll
   for (int j = 0; j < LA + LB; ++j) fetch(raw[1], j, 1);
+  // Everything has landed, the weights of slice 1 too: behind those come fewer loads than the count at the end of a slice
+  // leaves on their way (one round of fetches and one of weights, against two and one in every later slice).
+  wait_vm<0>();
   unrolled<0, STEPS>([&](auto x) { split_step(x, P0{}, 0); });
   __builtin_amdgcn_sched_barrier(0);
-  request(0, 0);
-  request(1, 1);
   int w_stage = 0;                                       // of three
-  wait_vm_lgkm0<WL / NW>();
+  wait_vm_lgkm0<2 * (LA + LB) + WL / NW>();              // the values just split are in LDS
   __builtin_amdgcn_s_barrier();
   // One slice.  Past the last one zeros are fetched and split, and weights requested that nothing reads: no branch parts
   // the vector instructions from the matrix ones, and the number of loads in flight is the same throughout.
