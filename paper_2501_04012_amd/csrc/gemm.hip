@@ -436,6 +436,16 @@ __global__ __launch_bounds__(WR * WC * 64) void k_gemm_dlds_any(const bf16_t* __
 template <int N> __device__ __forceinline__ void wait_vm_lgkm0() {
   __builtin_amdgcn_s_waitcnt((N & 0xF) | ((N >> 4) << 14) | (0x7 << 4));
 }
+// The same where the operations that may stay in flight are plain loads: nothing that touches memory moves across, neither in the
+// optimiser (the empty asm; it does not hold loads through a __restrict__ pointer, which such a kernel therefore does not take) nor
+// in the scheduler.
+template <int N> __device__ __forceinline__ void counted_wait_lgkm0() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+  wait_vm_lgkm0<N>();
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("" ::: "memory");
+}
 template <int BM, int BN, int BK, int WR, int WC, typename Epi>
 __global__ __launch_bounds__(WR * WC * 64) void k_gemm_dlds(const bf16_t* __restrict__ A, const bf16_t* __restrict__ Wt,
                                                            int M, int N, int K, int tiles_m, int tiles_n, Epi epi,
@@ -700,7 +710,7 @@ __global__ __launch_bounds__(WR * WC * 64) void k_gemm_dlds(const bf16_t* __rest
 // us, before and now: 32768 x 1152 x 4608 320, 287; 9326 x 6144 x 2048 203, 178; 4096 x 4608 x 1152 49, 44;
 // 8192 x 3456 x 1152 72, 67; 314 products of 300 to 33 000 rows, 576 to 3072 wide: 0.92 of the time in the mean.
 template <int BM, int BN, typename Epi>
-__global__ __launch_bounds__(256, 2) void k_gemm_packed(const bf16_t* __restrict__ A, const void* __restrict__ Wp, int M, int N,
+__global__ __launch_bounds__(256, 2) void k_gemm_packed(const bf16_t* A, const void* Wp, int M, int N,
                                                         int K, int tiles_m, int tiles_n, Epi epi) {
 #if defined(__HIP_DEVICE_COMPILE__)   // buffer resources are a device-side type: the host pass sees an empty body
   constexpr int BK = 64, NW = 4, WTN = BN / NW, TM = BM / 32, TN = WTN / 32, KS = BK / 16;
@@ -774,7 +784,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_packed(const bf16_t* __restrict
   dma_a(cur, 0, 0);
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks) load_b(cur, 0, ks);
-  wait_vm<KS * TN>();                                      // A has landed, the fragments may be on their way
+  wait_vm<0>();
   __builtin_amdgcn_s_barrier();
   constexpr int kDsRead = 0x100, kMfma = 0x008, kVmem = 0x010;
   for (;;) {
@@ -782,7 +792,9 @@ __global__ __launch_bounds__(256, 2) void k_gemm_packed(const bf16_t* __restrict
     const bool has_next = next_tile(nvb, nbm0, nbn0);
     Panels nxt = cur;
     if (has_next) nxt = panels(nbm0, nbn0);
-    issue_vectors(bn0);                                    // awaited and published with the tile's second K tile
+    // Published by the barrier ahead of the first K tile's last slice.  The tile's first product waits for all that is on its way, K tile
+    // 1 too: how many stores the epilogue put behind the fragments it needs is not known when this is compiled.
+    issue_vectors(bn0);
     f32x16 acc[TM][TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
@@ -828,7 +840,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_packed(const bf16_t* __restrict
       }
       // K tile kt + 1 of A has landed: behind its DMA came the fragments requested since, one slice more where the DMA
       // was issued ahead of the last K tile's last slice; this wave is done reading kt
-      wait_vm_lgkm0<(FIRST ? KS - 1 : KS) * TN>();
+      counted_wait_lgkm0<(FIRST ? KS - 1 : KS) * TN>();
       __builtin_amdgcn_s_barrier();
       __builtin_amdgcn_sched_barrier(0);
       if constexpr (!LAST) {
@@ -836,7 +848,6 @@ __global__ __launch_bounds__(256, 2) void k_gemm_packed(const bf16_t* __restrict
         load_a(PAR ^ 1, 0, fa[0]);
       }
       multiply(KS - 1);
-      request_b(kt + 1, KS - 1);
       if constexpr (!LAST) {
 #pragma unroll
         for (int r = 0; r < TM; ++r) {
@@ -845,8 +856,9 @@ __global__ __launch_bounds__(256, 2) void k_gemm_packed(const bf16_t* __restrict
           if (r < LA) __builtin_amdgcn_sched_group_barrier(kVmem, 1, 0);
         }
         if constexpr (TN > 1) __builtin_amdgcn_sched_group_barrier(kMfma, TM * TN - TM, 0);
-        __builtin_amdgcn_sched_group_barrier(kVmem, TN, 0);
       }
+      __builtin_amdgcn_sched_barrier(0);                   // the DMA stays ahead of the fragments
+      request_b(kt + 1, KS - 1);
       __builtin_amdgcn_sched_barrier(0);
     };
     using P0 = std::integral_constant<int, 0>; using P1 = std::integral_constant<int, 1>;
@@ -1190,7 +1202,7 @@ __device__ __forceinline__ void unrolled(F f) {
 }
 
 template <int BM, int BN, int WR, int WC, int PER_SIMD, bool SPLIT_W, typename Epi>
-__global__ __launch_bounds__(WR * WC * 64, PER_SIMD) void k_gemm_f32_parts(const float* __restrict__ A, const void* __restrict__ Wt,
+__global__ __launch_bounds__(WR * WC * 64, PER_SIMD) void k_gemm_f32_parts(const float* A, const void* Wt,
                                                                      int M, int N, int K, int tiles_m, int tiles_n, Epi epi) {
 #if defined(__HIP_DEVICE_COMPILE__)   // buffer resources are a device-side type: the host pass sees an empty body
   constexpr int NW = WR * WC, NT = NW * 64;
@@ -1322,8 +1334,7 @@ __global__ __launch_bounds__(WR * WC * 64, PER_SIMD) void k_gemm_f32_parts(const
       acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[PA[x]][i], fb[PB[x]][j], acc[i][j], 0, 0, 0);
       unrolled<R * STEPS / NM, (R + 1) * STEPS / NM>([&](auto y) { split_step(y, std::integral_constant<int, P ^ 1>{}, ks + 1); });
     });
-    __builtin_amdgcn_sched_barrier(0);
-    wait_vm_lgkm0<2 * (LA + LB) + WL / NW>();            // the next slice's weights have landed, those behind them may be on their way
+    counted_wait_lgkm0<2 * (LA + LB) + WL / NW>();       // the next slice's weights have landed, those behind them may be on their way
     __builtin_amdgcn_s_barrier();
   };
   for (int ks = 0; ks < slices; ks += 2) {
