@@ -1157,7 +1157,7 @@ static hipError_t run_f32(const void* A, const void* Wt, int M, int N, int K, co
 }
 
 // ---------------------------------------------------------------- fp32 on the bf16 matrix cores
-// An fp32 value is the sum of three bf16 values of 8 bits each (high, middle, low: exact), so an fp32 product
+// An fp32 value of at least 2^-110 is the sum of three bf16 values of 8 bits each (high, middle, low: exact), so an fp32 product
 // is nine bf16 products that the matrix cores form exactly and add in fp32.  Six of them are taken: what is
 // left out (middle x low twice, low x low) is at most 2^-23 of a product and of either sign, below what the fp32
 // additions round away.  Six bf16 instructions do what eight v_mfma_f32_32x32x2_f32 of twice the length do:
@@ -1177,11 +1177,17 @@ static hipError_t run_f32(const void* A, const void* Wt, int M, int N, int K, co
 // K need only be a whole number of 16-byte chunks: past its end a lane's offset is moved out of the buffer
 // resource's range, which loads zero, as do rows past the end of an operand.
 //
-// The high part is rounded from the value held to bf16's finite range: infinities, NaN and what rounding would
-// push to infinity go into the low part, whose one product is with the other operand's high part, so that they
-// come out as fp32 products would have them and not as inf - inf or inf * 0.
+// Below 2^-110 a value's low bits lie under bf16's smallest step (2^-133, so at most 2^-134 of it is lost), and above bf16's range
+// or next to infinities and NaN the parts make inf - inf and inf * 0.  Where that could show, a wave forms its products
+// again on the fp32 matrix pipe, operands straight from global memory, sums in the order of k_gemm_f32: if a sum is not finite, and
+// if the tile's operands hold a nonzero value below 2^-110 (noted as they are split) and a sum is below 2^-100 of their
+// largest; to a larger sum all that is lost is 2^-34 per product.  (GELU leaves values between 0 and 2^-110 of inputs around -9.6, decay
+// leaves them in weights that training no longer moves: common enough to be in every tile of a large model.)
+// 4096 x 3456 x 1152: 230 us in parts, 498 where every wave adds the second pass, 282 for k_gemm_f32 alone.
 typedef __attribute__((ext_vector_type(2))) unsigned u32x2;
-constexpr float kBf16Max = 3.3895313892515355e38f;       // largest finite bf16
+// a value's bits without the sign, and those shifted one up, less one: a zero comes out above every other value
+__device__ __forceinline__ unsigned magnitude(float x) { return __builtin_bit_cast(unsigned, x) & 0x7fffffffu; }
+__device__ __forceinline__ unsigned magnitude_or_top(float x) { return (__builtin_bit_cast(unsigned, x) << 1) - 1u; }
 __device__ __forceinline__ unsigned pack_bf16(float x, float y) {
   bf16x2 p;
   p[0] = (bf16_t)x; p[1] = (bf16_t)y;
@@ -1202,7 +1208,7 @@ __device__ __forceinline__ void unrolled(F f) {
 }
 
 template <int BM, int BN, int WR, int WC, int PER_SIMD, bool SPLIT_W, typename Epi>
-__global__ __launch_bounds__(WR * WC * 64, PER_SIMD) void k_gemm_f32_parts(const float* A, const void* Wt,
+__global__ __launch_bounds__(WR * WC * 64, PER_SIMD) void k_gemm_f32_parts(const float* A, const float* Wt, const void* parts,
                                                                      int M, int N, int K, int tiles_m, int tiles_n, Epi epi) {
 #if defined(__HIP_DEVICE_COMPILE__)   // buffer resources are a device-side type: the host pass sees an empty body
   constexpr int NW = WR * WC, NT = NW * 64;
@@ -1226,10 +1232,16 @@ __global__ __launch_bounds__(WR * WC * 64, PER_SIMD) void k_gemm_f32_parts(const
   const int slices = (K + 15) / 16;
 
   const auto ra = __builtin_amdgcn_make_buffer_rsrc((void*)(A + (size_t)bm0 * K), 0, (int)((unsigned)min(M - bm0, BM) * (unsigned)K * 4u), 0x00020000);
-  // split weights: [N / 32][slices][32 rows][3 parts][16] bf16, rows past N zero
+  const auto rw = __builtin_amdgcn_make_buffer_rsrc((void*)(Wt + (size_t)bn0 * K), 0, (int)((unsigned)min(N - bn0, BN) * (unsigned)K * 4u), 0x00020000);
+  // split weights: [N / 32][slices][32 rows][3 parts][16] bf16, rows past N zero, then of each 32 rows the least and the largest magnitude
   const int w_blocks = min((N + 31) / 32 - bn0 / 32, BN / 32);
-  const auto rb = SPLIT_W ? __builtin_amdgcn_make_buffer_rsrc((void*)((const unsigned char*)Wt + (size_t)(bn0 / 32) * slices * 3072), 0, (int)((unsigned)w_blocks * (unsigned)slices * 3072u), 0x00020000)
-                          : __builtin_amdgcn_make_buffer_rsrc((void*)((const float*)Wt + (size_t)bn0 * K), 0, (int)((unsigned)min(N - bn0, BN) * (unsigned)K * 4u), 0x00020000);
+  const auto rb = SPLIT_W ? __builtin_amdgcn_make_buffer_rsrc((void*)((const unsigned char*)parts + (size_t)(bn0 / 32) * slices * 3072), 0, (int)((unsigned)w_blocks * (unsigned)slices * 3072u), 0x00020000) : rw;
+  constexpr unsigned kLeast = ((127u - 110u) << 24) - 1u;              // magnitude_or_top(2^-110)
+  unsigned least = ~0u, most = 0;                        // magnitude_or_top and magnitude of the operands' values, this thread's share
+  if constexpr (SPLIT_W) {
+    const unsigned* ranges = (const unsigned*)((const unsigned char*)parts + (size_t)((N + 31) / 32) * slices * 3072) + bn0 / 32 * 2;
+    for (int x = 0; x < w_blocks; ++x) { least = min(least, ranges[2 * x]); most = max(most, ranges[2 * x + 1]); }
+  }
   // chunk tid + NT j of a slice: row (tid >> 2) + NT / 4 j, floats 4c .. 4c+3
   const int row0 = tid >> 2, c = tid & 3;
   f32x4 raw[2][LA + LB];                                 // of the next slice and of the one behind it
@@ -1258,21 +1270,22 @@ __global__ __launch_bounds__(WR * WC * 64, PER_SIMD) void k_gemm_f32_parts(const
     *(u32x2*)(dst + 32) = m;
     *(u32x2*)(dst + 64) = l;
   };
-  // Step X of the splitting of slice ks: chunk X / 6, a pair of its values after the other in steps of 3, 5 and 7 vector
+  // Step X of the splitting of slice ks: chunk X / 6, a pair of its values after the other in steps of 7, 5 and 5 vector
   // instructions; behind the last the chunk is fetched for slice ks + 2.
-  float ra0 = 0.0f, ra1 = 0.0f, a0 = 0.0f, a1 = 0.0f;    // of the pair: what is left of the value held to range, and of the value
+  float a0 = 0.0f, a1 = 0.0f;                            // what is left of the pair
   unsigned h0 = 0, m0 = 0, l0 = 0, h1 = 0, m1 = 0;
   auto split_step = [&](auto step, auto par, int ks) {
     constexpr int P = decltype(par)::value;                // ks & 1
     constexpr int X = decltype(step)::value, j = X / 6, half = X % 6 / 3;
     if constexpr (X % 3 == 0) {
       a0 = raw[P][j][2 * half]; a1 = raw[P][j][2 * half + 1];
-      ra0 = __builtin_amdgcn_fmed3f(a0, -kBf16Max, kBf16Max); ra1 = __builtin_amdgcn_fmed3f(a1, -kBf16Max, kBf16Max);
-      (half ? h1 : h0) = pack_bf16(ra0, ra1);
+      least = min(least, min(magnitude_or_top(a0), magnitude_or_top(a1)));
+      most = max(most, max(magnitude(a0), magnitude(a1)));
+      (half ? h1 : h0) = pack_bf16(a0, a1);
     } else if constexpr (X % 3 == 1) {
       const unsigned h = half ? h1 : h0;
-      (half ? m1 : m0) = pack_bf16(ra0 - bf16_lo(h), ra1 - bf16_hi(h));
       a0 -= bf16_lo(h); a1 -= bf16_hi(h);
+      (half ? m1 : m0) = pack_bf16(a0, a1);
     } else {
       const unsigned m = half ? m1 : m0, l = pack_bf16(a0 - bf16_lo(m), a1 - bf16_hi(m));
       if constexpr (half == 0) {
@@ -1342,6 +1355,77 @@ __global__ __launch_bounds__(WR * WC * 64, PER_SIMD) void k_gemm_f32_parts(const
     if (ks + 1 < slices) slice(P1{}, ks + 1);
   }
   wait_vm<0>();                                          // nothing is on its way to LDS when the workgroup ends
+  // The stages of split values are read out and nothing is written to them any more.
+  unsigned* const of_waves = (unsigned*)smem;
+  if (lane == 0) of_waves[wave] = 0;
+  if (__any(least < kLeast) && lane == 0) of_waves[wave] = 1;
+  __syncthreads();
+  unsigned small = 0;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) small |= of_waves[w];
+  float finite = 0.0f;                                   // NaN behind a sum that is not
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) finite = __builtin_fmaf(acc[i][j][r], 0.0f, finite);
+  bool again = finite != 0.0f;
+  if (small) {                                           // the same in all waves
+#pragma unroll
+    for (int m = 32; m > 0; m >>= 1) most = max(most, (unsigned)__shfl_xor((int)most, m, 64));
+    if (lane == 0) of_waves[NW + wave] = most;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < NW; ++w) most = max(most, of_waves[NW + w]);
+    const float bar = __builtin_fmaxf(__builtin_bit_cast(float, min(most, 0x7f800000u)) * 0x1p-100f, 0x1p-110f);
+    float low = bar;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const bool in = bm0 + wr * WTM + i * 32 + r / 4 * 8 + lh * 4 + r % 4 < M && bn0 + wc * WTN + j * 32 + li < N;
+          low = in ? __builtin_fminf(low, __builtin_fabsf(acc[i][j][r])) : low;
+        }
+    again |= low < bar;
+  }
+  if (__any(again)) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+    // lane (i, h) holds floats 4h .. 4h + 3 of eight of a row; instruction e contracts elements e of both halves (as k_gemm_f32)
+    const unsigned at_a = (unsigned)(wr * WTM + li) * (unsigned)K * 4u + lh * 16, at_w = (unsigned)(wc * WTN + li) * (unsigned)K * 4u + lh * 16;
+    f32x4 fa[2][TM], fw[2][TN];
+    auto load = [&](int p, int k) {                      // past the end zeros
+      const bool in = k + 4 * lh < K;
+#pragma unroll
+      for (int i = 0; i < TM; ++i) fa[p][i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(ra, (int)(in ? at_a + (unsigned)(i * 32) * (unsigned)K * 4u : 0x80000000u), k * 4, 0));
+#pragma unroll
+      for (int j = 0; j < TN; ++j) fw[p][j] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rw, (int)(in ? at_w + (unsigned)(j * 32) * (unsigned)K * 4u : 0x80000000u), k * 4, 0));
+    };
+    auto multiply = [&](int p) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[p][i][e], fw[p][j][e], acc[i][j], 0, 0, 0);
+    };
+    constexpr bool AHEAD = TM * TN < 8;                  // registers for a second set of fragments
+    if constexpr (AHEAD) load(0, 0);
+#pragma unroll 1
+    for (int k = 0; k < K; k += 16) {
+      if constexpr (AHEAD) load(1, k + 8); else load(0, k);
+      multiply(0);
+      load(0, AHEAD ? k + 16 : k + 8);
+      multiply(AHEAD ? 1 : 0);
+    }
+  }
 #pragma unroll
   for (int j = 0; j < TN; ++j) {
     const auto col = epi.col(bn0 + wc * WTN + j * 32 + li);
@@ -1367,9 +1451,8 @@ __global__ __launch_bounds__(256) void k_split_weights(const float* __restrict__
   for (int x = 0; x < 8; ++x) {
     const int k = ks * 16 + 2 * x;
     const float a = row < N && k < K ? Wt[(size_t)row * K + k] : 0.0f, b = row < N && k + 1 < K ? Wt[(size_t)row * K + k + 1] : 0.0f;
-    const float ca = __builtin_amdgcn_fmed3f(a, -kBf16Max, kBf16Max), cb = __builtin_amdgcn_fmed3f(b, -kBf16Max, kBf16Max);
-    h[x] = pack_bf16(ca, cb);
-    m[x] = pack_bf16(ca - bf16_lo(h[x]), cb - bf16_hi(h[x]));
+    h[x] = pack_bf16(a, b);
+    m[x] = pack_bf16(a - bf16_lo(h[x]), b - bf16_hi(h[x]));
     l[x] = pack_bf16((a - bf16_lo(h[x])) - bf16_lo(m[x]), (b - bf16_hi(h[x])) - bf16_hi(m[x]));
   }
   unsigned* dst = (unsigned*)(out + ((size_t)(row / 32) * slices + ks) * 3072 + (row % 32) * 96);
@@ -1377,17 +1460,40 @@ __global__ __launch_bounds__(256) void k_split_weights(const float* __restrict__
   for (int x = 0; x < 8; ++x) { dst[x] = h[x]; dst[8 + x] = m[x]; dst[16 + x] = l[x]; }
 }
 
-size_t split_weights_bytes(int N, int K) { return (size_t)((N + 31) / 32) * ((K + 15) / 16) * 3072; }
+// Least (magnitude_or_top) and largest magnitude of each 32 rows, behind the parts.
+__global__ __launch_bounds__(256) void k_split_ranges(const float* __restrict__ Wt, unsigned* __restrict__ out, int N, int K) {
+  const int row0 = blockIdx.x * 32, rows = min(N - row0, 32);
+  unsigned least = ~0u, most = 0;
+  for (long long i = threadIdx.x; i < (long long)rows * K; i += 256) {
+    const float w = Wt[(size_t)row0 * K + i];
+    least = min(least, magnitude_or_top(w));
+    most = max(most, magnitude(w));
+  }
+#pragma unroll
+  for (int m = 32; m > 0; m >>= 1) {
+    least = min(least, (unsigned)__shfl_xor((int)least, m, 64));
+    most = max(most, (unsigned)__shfl_xor((int)most, m, 64));
+  }
+  __shared__ unsigned waves[4][2];
+  if ((threadIdx.x & 63) == 0) { waves[threadIdx.x >> 6][0] = least; waves[threadIdx.x >> 6][1] = most; }
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  out[2 * blockIdx.x] = min(min(waves[0][0], waves[1][0]), min(waves[2][0], waves[3][0]));
+  out[2 * blockIdx.x + 1] = max(max(waves[0][1], waves[1][1]), max(waves[2][1], waves[3][1]));
+}
+
+size_t split_weights_bytes(int N, int K) { return (size_t)((N + 31) / 32) * (((K + 15) / 16) * (size_t)3072 + 8); }
 hipError_t launch_split_weights(const float* Wt, void* out, int N, int K, hipStream_t s) {
   const int slices = (K + 15) / 16;
   const long long blocks = ((long long)(N + 31) / 32 * 32 * slices + 255) / 256;
   if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
   k_split_weights<<<(unsigned)blocks, 256, 0, s>>>(Wt, (unsigned char*)out, N, K, slices);
+  k_split_ranges<<<(N + 31) / 32, 256, 0, s>>>(Wt, (unsigned*)((unsigned char*)out + (size_t)((N + 31) / 32) * slices * 3072), N, K);
   return hipGetLastError();
 }
 
 template <int BM, int BN, int WR, int WC, int PER_SIMD, bool SPLIT_W, int MODE>
-static hipError_t run_f32_parts(const void* A, const void* Wt, int M, int N, int K, const EpiParams& ep, hipStream_t s) {
+static hipError_t run_f32_parts(const void* A, const void* Wt, const void* parts, int M, int N, int K, const EpiParams& ep, hipStream_t s) {
   using Epi = Epilogue<float, MODE>;
   Epi epi = Epi::make(ep, M, N);
   const int tiles_m = ceil_div(M, BM), tiles_n = ceil_div(N, BN);
@@ -1401,7 +1507,7 @@ static hipError_t run_f32_parts(const void* A, const void* Wt, int M, int N, int
     if (e != hipSuccess) return e;
     attr_set = true;
   }
-  kern<<<(unsigned)grid, WR * WC * 64, smem, s>>>((const float*)A, Wt, M, N, K, tiles_m, tiles_n, epi);
+  kern<<<(unsigned)grid, WR * WC * 64, smem, s>>>((const float*)A, (const float*)Wt, parts, M, N, K, tiles_m, tiles_n, epi);
   return hipGetLastError();
 }
 
@@ -1558,13 +1664,13 @@ static hipError_t dispatch_f32(const void* A, const void* Wt, const void* w_part
   if (w_parts && K < (1 << 18)) {                        // (K: 32-bit offsets into the split weights)
     const double e64 = estimate(64, 64, 2.3, 4.2), e128 = estimate(64, 128, 3.7, 5.0), e192 = estimate(128, 192, 9.9, 12.0),
                  e256 = estimate(256, 256, 22.0, 23.0);
-    if (e256 < e192 && e256 < e128 && e256 < e64) return run_f32_parts<256, 256, 4, 2, 2, true, MODE>(A, w_parts, M, N, K, ep, s);
-    if (e192 < e128 && e192 < e64) return run_f32_parts<128, 192, 2, 2, 2, true, MODE>(A, w_parts, M, N, K, ep, s);
-    if (e64 < e128) return run_f32_parts<64, 64, 2, 2, 4, true, MODE>(A, w_parts, M, N, K, ep, s);
-    return run_f32_parts<64, 128, 2, 2, 4, true, MODE>(A, w_parts, M, N, K, ep, s);
+    if (e256 < e192 && e256 < e128 && e256 < e64) return run_f32_parts<256, 256, 4, 2, 2, true, MODE>(A, Wt, w_parts, M, N, K, ep, s);
+    if (e192 < e128 && e192 < e64) return run_f32_parts<128, 192, 2, 2, 2, true, MODE>(A, Wt, w_parts, M, N, K, ep, s);
+    if (e64 < e128) return run_f32_parts<64, 64, 2, 2, 4, true, MODE>(A, Wt, w_parts, M, N, K, ep, s);
+    return run_f32_parts<64, 128, 2, 2, 4, true, MODE>(A, Wt, w_parts, M, N, K, ep, s);
   }
-  if (estimate(128, 128, 7.0, 9.0) < estimate(64, 64, 2.4, 4.7)) return run_f32_parts<128, 128, 2, 2, 2, false, MODE>(A, Wt, M, N, K, ep, s);
-  return run_f32_parts<64, 64, 2, 2, 4, false, MODE>(A, Wt, M, N, K, ep, s);
+  if (estimate(128, 128, 7.0, 9.0) < estimate(64, 64, 2.4, 4.7)) return run_f32_parts<128, 128, 2, 2, 2, false, MODE>(A, Wt, nullptr, M, N, K, ep, s);
+  return run_f32_parts<64, 64, 2, 2, 4, false, MODE>(A, Wt, nullptr, M, N, K, ep, s);
 }
 
 template <int MODE>

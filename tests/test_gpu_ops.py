@@ -216,6 +216,72 @@ def test_linear_fp32_in_parts_keeps_values_that_are_not_finite(fc, M, N):
         assert np.abs(got[row][ok] / v - 1).max() < 1e-6
 
 
+def _linear_fp32(fc, A, W):
+    torch = _torch()
+    out = torch.empty((A.shape[0], W.shape[1]), dtype=torch.float32, device="cuda:0")
+    fc.fc_op_linear(fc.FC_F32, dev(A), dev(W.T.copy()), dev(np.zeros(W.shape[1], np.float32)), None, out, A.shape[0], W.shape[1], A.shape[1], 0)
+    torch.cuda.synchronize()
+    return host(out)
+
+
+@pytest.mark.parametrize("M,N", [(1100, 1030), (4100, 1024)])
+@pytest.mark.parametrize("K", [36, 512])
+@pytest.mark.parametrize("scale", [1e-31, 1e-33, 1e-35, 1e-37, 1e-41])
+def test_linear_fp32_of_small_operands(fc, M, N, K, scale):
+    """Values down to the subnormals, whose low bits bf16 parts cannot hold (below 2^-110 = 7.7e-34): as with fp32 products, whichever
+    operand is small, and in single rows and columns of an ordinary product.  A bound as for ordinary values, and 2^-149 more a product."""
+    rng = np.random.default_rng(M + K)
+    A, W = rng.standard_normal((M, K), dtype=np.float32), rng.standard_normal((K, N), dtype=np.float32)
+    small = np.float32(scale)
+    one_a, one_w = A.copy(), W.copy()
+    one_a[77], one_w[:, 65] = one_a[77] * small, one_w[:, 65] * small
+    for a, w, rows, cols in ((A * small, W, slice(0, 600), slice(0, N)), (A, W * small, slice(0, 600), slice(0, N)),
+                             (one_a, W, slice(77, 78), slice(0, N)), (A, one_w, slice(0, 600), slice(65, 66))):
+        got = _linear_fp32(fc, a, w)
+        want = a.astype(np.float64) @ w.astype(np.float64)
+        bound = (K + 2) * (2.0 ** -24 * (np.abs(a).astype(np.float64) @ np.abs(w).astype(np.float64)) + 2.0 ** -149)
+        assert (np.abs(got - want) <= bound).all()
+        if scale < 1e-32:                                 # every tile of these rows and columns holds a value below 2^-110
+            few = _linear_fp32(fc, a[:600], w)            # a product of so few tiles runs on the fp32 pipe: the same sums
+            assert np.array_equal(got[rows, cols], few[rows, cols])
+
+
+def test_linear_fp32_of_one_hot_rows_returns_the_weights(fc):
+    """Sums of a single product: bit for bit the weight, ordinary, small, subnormal and large ones side by side."""
+    rng = np.random.default_rng(4)
+    K, N, M = 64, 1100, 1100
+    W = (rng.standard_normal((K, N)) * 10.0 ** rng.uniform(-44, 38, (K, N))).astype(np.float32)
+    A = np.zeros((M, K), np.float32)
+    A[np.arange(M), np.arange(M) % K] = 1.0
+    assert np.array_equal(_linear_fp32(fc, A, W), W[np.arange(M) % K])
+    W = (rng.standard_normal((K, N)) * 10.0 ** rng.uniform(-33, 38, (K, N))).astype(np.float32)
+    W[np.abs(W) < 2.0 ** -110] = 0.0                      # in parts throughout
+    assert np.array_equal(_linear_fp32(fc, A, W), W[np.arange(M) % K])
+
+
+@pytest.mark.parametrize("M,N", [(1100, 1030), (4100, 1024)])
+def test_linear_fp32_next_to_the_largest_values(fc, M, N):
+    """Finite values above bf16's largest keep their bits, infinities meet partners of any size without losing their sign, and products
+    that leave fp32's range do so as with fp32 products."""
+    rng = np.random.default_rng(N)
+    K = 48
+    top = np.float32(np.finfo(np.float32).max)
+    A = np.zeros((M, K), np.float32)
+    A[:, 3] = (rng.uniform(3.38e38, 3.402e38, M) * rng.choice([-1, 1], M)).astype(np.float32)
+    W = rng.uniform(0.1, 0.9, (K, N)).astype(np.float32) * rng.choice([-1, 1], (K, N)).astype(np.float32)
+    want = A.astype(np.float64) @ W.astype(np.float64)
+    assert np.abs(_linear_fp32(fc, A, W) / want - 1).max() <= 2.0 ** -22
+    A = rng.standard_normal((M, K), dtype=np.float32)
+    A[5, 7], A[600, 8], A[1099, 9] = np.inf, -np.inf, np.inf
+    W = (rng.standard_normal((K, N)) * 10.0 ** rng.uniform(-40, 36, (K, N))).astype(np.float32)
+    W[:, 5] = 0.0
+    got = _linear_fp32(fc, A, W)
+    with np.errstate(invalid="ignore", over="ignore"):
+        want = A.astype(np.float64) @ W.astype(np.float64)
+    assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(got[np.isinf(want)], want[np.isinf(want)])
+    assert (np.isinf(got) == (np.abs(want) > top)).mean() > 1 - 1e-6      # (a sum right at the edge may round either way)
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("gated", [True, False])
 def test_linear_gated_branch_then_residual_layernorm(fc, dtype, gated):
