@@ -1249,19 +1249,20 @@ __global__ __launch_bounds__(WR * WC * 64, PER_SIMD) void k_gemm_f32_parts(const
     const unsigned off = (unsigned)(row0 + NT / 4 * (j < LA ? j : j - LA)) * (unsigned)K * 4u + (unsigned)c * 16u;
     raw[j] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(j < LA ? ra : rb, (int)(ks * 16 + c * 4 < K ? off : 0x80000000u), ks * 64, 0));
   };
-  // split weights go to LDS as they lie: 1 KB a wave-load, three to a block of 32 rows; wave-load wave + NW j
+  // split weights go to LDS as they lie: 1 KB a wave-load, three to a block of 32 rows; wave-load wave + NW j.  A wave for which
+  // there is no such one loads its first once more: all have the same number on their way, and no branch parts them.
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-  int w_off[LD > 0 ? LD : 1];
+  int w_load[LD > 0 ? LD : 1], w_off[LD > 0 ? LD : 1];
 #pragma unroll
-  for (int j = 0; j < LD; ++j)
-    w_off[j] = (wave_u + NW * j) / 3 * slices * 3072 + (wave_u + NW * j) % 3 * 1024 + lane * 16;
+  for (int j = 0; j < LD; ++j) {
+    w_load[j] = wave_u + NW * j < WL ? wave_u + NW * j : wave_u;
+    w_off[j] = w_load[j] / 3 * slices * 3072 + w_load[j] % 3 * 1024 + lane * 16;
+  }
   auto request = [&](int at, int stage) {
     const int ks = min(at, slices - 1);                  // the scalar offset is not range-checked: past the end the last slice again
 #pragma unroll
-    for (int j = 0; j < LD; ++j) {
-      if (WL % NW != 0 && wave_u + NW * j >= WL) break;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lds_void*)(smem + 2 * STAGE + stage * W_STAGE + (wave_u + NW * j) * 1024), 16, w_off[j], ks * 3072, 0, 0);
-    }
+    for (int j = 0; j < LD; ++j)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lds_void*)(smem + 2 * STAGE + stage * W_STAGE + w_load[j] * 1024), 16, w_off[j], ks * 3072, 0, 0);
   };
   auto put = [&](int j, int stage, u32x2 h, u32x2 m, u32x2 l) {
     const int row = j < LA ? row0 + NT / 4 * j : BM + row0 + NT / 4 * (j - LA);
@@ -1319,7 +1320,7 @@ __global__ __launch_bounds__(WR * WC * 64, PER_SIMD) void k_gemm_f32_parts(const
   unrolled<0, STEPS>([&](auto x) { split_step(x, P0{}, 0); });
   __builtin_amdgcn_sched_barrier(0);
   int w_stage = 0;                                       // of three
-  wait_vm_lgkm0<2 * (LA + LB) + WL / NW>();              // the values just split are in LDS
+  wait_vm_lgkm0<2 * (LA + LB) + LD>();                   // the values just split are in LDS
   __builtin_amdgcn_s_barrier();
   // One slice.  Past the last one zeros are fetched and split, and weights requested that nothing reads: no branch parts
   // the vector instructions from the matrix ones, and the number of loads in flight is the same throughout.
@@ -1347,13 +1348,15 @@ __global__ __launch_bounds__(WR * WC * 64, PER_SIMD) void k_gemm_f32_parts(const
       acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[PA[x]][i], fb[PB[x]][j], acc[i][j], 0, 0, 0);
       unrolled<R * STEPS / NM, (R + 1) * STEPS / NM>([&](auto y) { split_step(y, std::integral_constant<int, P ^ 1>{}, ks + 1); });
     });
-    counted_wait_lgkm0<2 * (LA + LB) + WL / NW>();       // the next slice's weights have landed, those behind them may be on their way
+    counted_wait_lgkm0<2 * (LA + LB) + LD>();            // the next slice's weights have landed, those behind them may be on their way
     __builtin_amdgcn_s_barrier();
   };
-  for (int ks = 0; ks < slices; ks += 2) {
+  int ks = 0;
+  for (; ks + 1 < slices; ks += 2) {                     // whole pairs: a way round the second slice would have the first one of the next wait for more
     slice(P0{}, ks);
-    if (ks + 1 < slices) slice(P1{}, ks + 1);
+    slice(P1{}, ks + 1);
   }
+  if (ks < slices) slice(P0{}, ks);
   wait_vm<0>();                                          // nothing is on its way to LDS when the workgroup ends
   // The stages of split values are read out and nothing is written to them any more.
   unsigned* const of_waves = (unsigned*)smem;

@@ -122,3 +122,22 @@ def test_tiles_have_landed_before_they_are_read(listings, kernel, ahead):
     for name in names:
         assert sum(op == "s_barrier" for op, _, _ in listings[name]) >= 2, name
         assert not early_barriers(listings[name], ahead), name
+
+
+def test_no_slice_waits_for_more_than_it_reads(listings):
+    """Both halves of the K loop of k_gemm_f32_parts leave two rounds of fetches and one of split weights on their way: a branch between
+    two loads, or a way round the loop's second half, has the compiler wait for more."""
+    seen = 0
+    for name, code in listings.items():
+        form = re.search(r"k_gemm_f32_partsILi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELi\d+ELb1E", name)
+        if not form:
+            continue
+        bm, bn, wr, wc = map(int, form.groups())
+        waves = wr * wc
+        ahead = 2 * (bm * 4 // (waves * 64)) + -(-(bn * 96 // 1024) // waves)
+        loops = [code[to:at] for at, (op, _, to) in enumerate(code) if to is not None and to < at]
+        body = min((b for b in loops if sum(op == "s_barrier" for op, _, _ in b) == 2), key=len)
+        counts = [int(n) for op, text, _ in body if op == "s_waitcnt" for n in re.findall(r"vmcnt\((\d+)\)", text)]
+        assert counts and min(counts) >= ahead, (name, counts)
+        seen += 1
+    assert seen
