@@ -1044,8 +1044,8 @@ static hipError_t run_skinny(const void* A, const void* Wt, int M, int N, int K,
 
 // ---------------------------------------------------------------- fp32 on the fp32 matrix cores
 // v_mfma_f32_32x32x2_f32: exact fp32 products and sums at 256 FLOP per clock and CU.  For products that are at most one
-// 64x64 tile to a CU (the dispatch): a slice of K is over sooner here than in the kernel below, which is built for
-// throughput (216 tiles of 500 x 1728 x 576: 16 us against 19).  Operand
+// 64x64 tile to a CU, and without split weights some of one 64x128 tile (the dispatch): a slice of K is over sooner here than in the
+// kernel below, which is built for throughput (216 tiles of 500 x 1728 x 576: 16 us against 19).  Operand
 // lane (i, h) supplies row i, k = h, so four instructions consume one 16-byte chunk per lane (4
 // floats of K; instruction e contracts elements e of both halves' chunks): tiles, LDS layout,
 // DMA and fragment addressing are those of the bf16 kernels with 32 floats of K in a 128-byte
@@ -1672,6 +1672,10 @@ static hipError_t dispatch_f32(const void* A, const void* Wt, const void* w_part
     if (e64 < e128) return run_f32_parts<64, 64, 2, 2, 4, true, MODE>(A, Wt, w_parts, M, N, K, ep, s);
     return run_f32_parts<64, 128, 2, 2, 4, true, MODE>(A, Wt, w_parts, M, N, K, ep, s);
   }
+  // Both operands split on the way.  Where 64x128 tiles of the fp32 pipe make one round and there are more than 330 of 64x64, those are
+  // over first (1274 x 1536 x 512: 24.1 us against 25.9, 2000 x 1024 x 4096 164 and 169; below that 712 x 1536 x 512 23.3 and 21.7,
+  // 1167 x 1024 x 1024 43.4 and 40.5).
+  if (t64 > 330 && (long long)ceil_div(M, 64) * ceil_div(N, 128) <= 256) return run_f32<64, 128, 2, 4, MODE>(A, Wt, M, N, K, ep, s);
   if (estimate(128, 128, 7.0, 9.0) < estimate(64, 64, 2.4, 4.7)) return run_f32_parts<128, 128, 2, 2, 2, false, MODE>(A, Wt, nullptr, M, N, K, ep, s);
   return run_f32_parts<64, 64, 2, 2, 4, false, MODE>(A, Wt, nullptr, M, N, K, ep, s);
 }

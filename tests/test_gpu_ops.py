@@ -224,6 +224,15 @@ def _linear_fp32(fc, A, W):
     return host(out)
 
 
+@pytest.mark.parametrize("M,N,K", [(1274, 1536, 52), (1409, 900, 100), (1343, 1027, 16), (2048, 1024, 36)])
+def test_linear_fp32_of_one_round_of_wide_tiles(fc, M, N, K):
+    """331 to 512 tiles of 64x64 that make at most 256 of 64x128: ragged edges, one and several K tiles; bound as above."""
+    rng = np.random.default_rng(M + N + K)
+    A, W = rng.standard_normal((M, K), dtype=np.float32), rng.standard_normal((K, N), dtype=np.float32)
+    want = A.astype(np.float64) @ W.astype(np.float64)
+    assert np.abs(_linear_fp32(fc, A, W) - want).max() <= (K + 2) * 2.0 ** -24 * (np.abs(A) @ np.abs(W)).max()
+
+
 @pytest.mark.parametrize("M,N", [(1100, 1030), (4100, 1024)])
 @pytest.mark.parametrize("K", [36, 512])
 @pytest.mark.parametrize("scale", [1e-31, 1e-33, 1e-35, 1e-37, 1e-41])
