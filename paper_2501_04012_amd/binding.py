@@ -9,6 +9,7 @@ raises.
 from __future__ import annotations
 
 import ctypes as C
+import importlib
 import os
 from array import array
 from typing import Optional
@@ -114,14 +115,15 @@ _lib = _load()
 
 
 def _load_fast():
-    """The cache calls as CPython functions (csrc/pycall.cpp): the library they call, and they."""
+    """The cache calls as CPython functions (csrc/pycall.cpp): the library they call, and they; (None, None) where they were not
+    built for this interpreter, and ctypes makes those calls."""
     try:
-        from . import _pycall
-    except ImportError as e:
-        raise ImportError(f"{os.path.join(_HERE, '_pycall.so')} is not built: run `python -m paper_2501_04012_amd.build`") from e
-    _pycall.bind(*(C.cast(getattr(_lib, "fc_cache_" + n), C.c_void_p).value
-                   for n in ("stitch", "decompress", "alpha", "frame_similarity")))
-    return _lib, _pycall
+        fast = importlib.import_module("._pycall", __package__)
+    except ImportError:
+        return None, None
+    fast.bind(*(C.cast(getattr(_lib, "fc_cache_" + n), C.c_void_p).value
+                for n in ("stitch", "decompress", "alpha", "frame_similarity")))
+    return _lib, fast
 
 
 _fast_lib, _fast = _load_fast()

@@ -15,7 +15,8 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ_DIR = os.path.join(HERE, "_build")
 LIB_PATH = os.path.join(HERE, "libflexdenoise.so")
 SOURCES = ["flexdenoise.hip", "elementwise.hip", "gemm.hip", "attention.hip", "chain.hip", "cache.hip", "microbench.hip"]
-PYCALL_PATH = os.path.join(HERE, "_pycall.so")           # the cache calls as CPython functions (host only)
+# the cache calls as CPython functions (host only), for the interpreter that builds them
+PYCALL_PATH = os.path.join(HERE, "_pycall" + sysconfig.get_config_var("EXT_SUFFIX"))
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -52,8 +53,14 @@ def build(force: bool = True, verbose: bool = False) -> str:
     _run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB_PATH, *objs])
     src = os.path.join(CSRC, "pycall.cpp")
     if force or not os.path.exists(PYCALL_PATH) or os.path.getmtime(PYCALL_PATH) < max(os.path.getmtime(src), newest_hdr):
-        _run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
-              "-I" + sysconfig.get_paths()["include"], src, "-o", PYCALL_PATH])
+        for old in (PYCALL_PATH, os.path.join(os.path.dirname(PYCALL_PATH), "_pycall.so")):      # (any interpreter would load the second)
+            if os.path.exists(old):
+                os.remove(old)
+        try:
+            _run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+                  "-I" + sysconfig.get_paths()["include"], src, "-o", PYCALL_PATH])
+        except (OSError, RuntimeError) as e:             # no host compiler, or no headers of this interpreter
+            print(f"{os.path.basename(PYCALL_PATH)} not built, the cache calls go through ctypes: {e}", file=sys.stderr)
     return LIB_PATH
 
 

@@ -233,3 +233,53 @@ def test_native_route_leaves_other_arguments_to_ctypes():
             binding._fast.fc_cache_decompress(*(plain[:at] + [other] + plain[at + 1:]))
     with pytest.raises(TypeError):
         binding._fast.fc_cache_decompress(*plain[:-1])
+
+
+def test_package_imports_without_the_native_route():
+    """Every cache call has its ctypes form: the package works where the extension was not built for this interpreter."""
+    import subprocess
+    import sys
+    code = """
+import sys
+sys.modules["paper_2501_04012_amd._pycall"] = None        # an import of it fails
+import torch
+import paper_2501_04012_amd as fc
+assert fc.binding._fast is None and fc.binding._fast_lib is None
+t = torch.zeros(16)
+fc.fc_cache_decompress(t, None, 0, 1.0, None, 0, [0], 1, 0, t, stream=1)
+fc.fc_cache_stitch(t, t, t, t, t, 0, 4, stream=1)
+for call, args, status in ((fc.fc_cache_alpha, (t, t, t, 1, 4, t, t), -4), (fc.fc_cache_frame_similarity, (t, 1, 4, t, t), -4)):
+    try:
+        call(*args, stream=1)
+    except fc.FlexDenoiseError as e:
+        assert e.status == status
+    else:
+        raise AssertionError(call)
+"""
+    subprocess.run([sys.executable, "-c", code], cwd=ROOT, check=True)
+
+
+def test_native_route_is_built_for_one_interpreter():
+    import sysconfig
+    from paper_2501_04012_amd import binding, build
+    assert build.PYCALL_PATH.endswith(sysconfig.get_config_var("EXT_SUFFIX")) and "cpython" in os.path.basename(build.PYCALL_PATH)
+    assert binding._fast.__file__ == build.PYCALL_PATH
+
+
+def test_build_without_a_host_compiler(monkeypatch, tmp_path, capsys):
+    """The library is built all the same, an extension of an earlier build does not stay."""
+    from paper_2501_04012_amd import build
+    calls = []
+
+    def run(cmd):
+        if cmd[0] == "no-such-compiler":
+            raise FileNotFoundError(cmd[0])
+        calls.append(cmd)
+        return ""
+    monkeypatch.setenv("CXX", "no-such-compiler")
+    monkeypatch.setattr(build, "_run", run)
+    for name in ("OBJ_DIR", "LIB_PATH", "PYCALL_PATH"):
+        monkeypatch.setattr(build, name, str(tmp_path / os.path.basename(getattr(build, name))))
+    (tmp_path / os.path.basename(build.PYCALL_PATH)).write_bytes(b"old")
+    assert build.build(force=True) == build.LIB_PATH and len(calls) == len(build.SOURCES) + 1
+    assert not os.path.exists(build.PYCALL_PATH) and "ctypes" in capsys.readouterr().err
