@@ -311,6 +311,7 @@ hipError_t launch_gemm(int bf16, int mode, const void* A, const void* Wt, int M,
 // w_parts (optional): the weights once more, fp32 split into bf16 parts (launch_split_weights, split_weights_bytes), bf16 in
 // fragment order (launch_pack_weights, N * K elements, where packs_weights)
 bool packs_weights(int N, int K);
+bool packed_weights_serve(int M, int N, int K);          // whether a product of M rows takes them, with scratch or without
 hipError_t launch_pack_weights(const void* W, void* out, int N, int K, hipStream_t s);
 size_t split_weights_bytes(int N, int K);
 hipError_t launch_split_weights(const float* Wt, void* out, int N, int K, hipStream_t s);

@@ -7,6 +7,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <map>
 #include <string>
 #include <vector>
 
@@ -67,7 +68,8 @@ struct Profiler {
 struct Linear {           // weights [out, in] in the activation dtype, bias fp32
   void* wt = nullptr;
   float* b = nullptr;
-  void* parts = nullptr;  // products over token rows: the weights once more, fp32 split into bf16 parts, bf16 (and fp32 chains) in fragment order
+  void* parts = nullptr;  // products over token rows: the weights once more, fp32 split into bf16 parts, bf16 (and fp32 chains) in
+                          // fragment order; NULL: no product of this model's rows takes them, or no memory for them
   int in = 0, out = 0;
 };
 
@@ -89,7 +91,7 @@ struct fc_model {
   size_t esz = 4;                  // bytes per activation / weight element
 
   unsigned char* wbuf = nullptr;   // one device allocation for all parameters and tables
-  size_t wbytes = 0;
+  unsigned char* copies = nullptr; // the block weights in further layouts (Linear::parts), of models that do not run as chains
   Linear t1, t2, y, fmod, fout;
   float* p_w = nullptr;            // patch embedding stays fp32 [pd, D] (K is tiny)
   float* p_b = nullptr;
@@ -190,11 +192,21 @@ struct Carver {          // bump allocator over a byte range, 256-byte aligned p
   }
 };
 
-// Lays out (base != NULL) or sizes (base == NULL) the parameter buffer.
-size_t layout_weights(fc_model* m, unsigned char* base) {
+// Whether a product of the model's rows takes packed weights at any number of samples: past 2^17 rows the rounds that packed
+// tiles save are less than what they cost.
+bool rows_take_packed(const fc_model* m, int in, int out) {
+  for (long long rows = m->Ns; rows == m->Ns || rows <= 1 << 17; rows += m->Ns)
+    if (packed_weights_serve((int)rows, out, in)) return true;
+  return false;
+}
+
+// Lays out (base != NULL) or sizes (base == NULL) the parameter buffer, and the copies of the block weights (copies NULL: without).
+struct WeightBytes { size_t weights, copies; };
+WeightBytes layout_weights(fc_model* m, unsigned char* base, unsigned char* copies) {
   const fc_model_config& c = m->cfg;
   const size_t D = c.hidden, M = c.mlp_dim, es = m->esz;
-  Carver cv(base);
+  Carver cv(base), cc(copies);
+  std::map<std::pair<int, int>, bool> packed;
   auto lin = [&](Linear& L, int in, int out) {
     L.in = in; L.out = out;
     L.wt = cv.take((size_t)in * out * es);
@@ -203,9 +215,14 @@ size_t layout_weights(fc_model* m, unsigned char* base) {
   // the products over all token rows
   auto lin_rows = [&](Linear& L, int in, int out) {
     lin(L, in, out);
+    L.parts = nullptr;
     if (m->chain_shape) L.parts = cv.take((size_t)in * out * es);
-    else if (!m->bf16) L.parts = cv.take(split_weights_bytes(out, in));
-    else if (packs_weights(out, in)) L.parts = cv.take((size_t)in * out * es);
+    else if (!m->bf16) L.parts = cc.take(split_weights_bytes(out, in));
+    else {
+      const auto known = packed.find({in, out});
+      const bool take = known != packed.end() ? known->second : packed.emplace(std::make_pair(in, out), rows_take_packed(m, in, out)).first->second;
+      if (take) L.parts = cc.take((size_t)in * out * es);
+    }
   };
   lin(m->t1, c.t_embed_dim, D);
   lin(m->t2, D, D);
@@ -236,7 +253,7 @@ size_t layout_weights(fc_model* m, unsigned char* base) {
   lin(m->fout, D, m->pd);
   m->pos_sp = (float*)cv.take((size_t)m->S * D * 4);
   m->pos_t = (float*)cv.take((size_t)c.frames * D * 4);
-  return cv.off;
+  return {cv.off, cc.off};
 }
 
 void sincos_1d(double pos, int dim, float* out) {   // [sin(pos w_i) | cos(pos w_i)], w_i = 10000^(-i/(dim/2))
@@ -755,15 +772,23 @@ int fc_model_set_weights(fc_model* m, const float* blob, size_t n_floats) {
   const fc_model_config& c = m->cfg;
   const int D = c.hidden;
   if (m->wbuf) { (void)hipFree(m->wbuf); m->wbuf = nullptr; m->has_weights = false; }
-  m->wbytes = layout_weights(m, nullptr);
-  HIP_TRY(hipMalloc((void**)&m->wbuf, m->wbytes));
-  layout_weights(m, m->wbuf);
-
+  if (m->copies) { (void)hipFree(m->copies); m->copies = nullptr; }
+  const WeightBytes bytes = layout_weights(m, nullptr, nullptr);
+  HIP_TRY(hipMalloc((void**)&m->wbuf, bytes.weights));
   // staging buffer for one tensor at a time (largest matrix of the model)
   size_t big = (size_t)D * std::max(std::max(3 * D, c.mlp_dim), std::max(c.text_dim, m->nmod * D));
   big = std::max(big, (size_t)c.t_embed_dim * D);
   float* stage = nullptr;
   HIP_TRY(hipMalloc((void**)&stage, big * 4));
+  // The copies make a step faster and are not needed for it: a model whose copies would take more than an eighth of the device (36 GB),
+  // or find no room behind everything that is needed, does without.
+  size_t free_bytes = 0, total = 0;
+  if (bytes.copies != 0 && (hipMemGetInfo(&free_bytes, &total) != hipSuccess || bytes.copies > total / 8 ||
+                            hipMalloc((void**)&m->copies, bytes.copies) != hipSuccess)) {
+    (void)hipGetLastError();
+    m->copies = nullptr;
+  }
+  layout_weights(m, m->wbuf, m->copies);
   size_t off = 0;
   int rc = FC_OK;
   auto up_matrix_t = [&](void* dst, int in, int out) -> hipError_t {   // blob [in,out] -> device [out,in] act dtype
@@ -840,6 +865,7 @@ done:
 int fc_model_destroy(fc_model* m) {
   if (!m) return FC_OK;
   if (m->wbuf) (void)hipFree(m->wbuf);
+  if (m->copies) (void)hipFree(m->copies);
   delete m;
   return FC_OK;
 }

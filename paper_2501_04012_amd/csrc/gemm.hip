@@ -1680,6 +1680,72 @@ static hipError_t dispatch_f32(const void* A, const void* Wt, const void* w_part
   return run_f32_parts<64, 64, 2, 2, 4, false, MODE>(A, Wt, nullptr, M, N, K, ep, s);
 }
 
+enum Bf16Tile { T128, T192, T256, T384 };
+static Bf16Tile bf16_tile(bool unpatch, int M, int N, int K) {
+  // Tile choice.  256x256 (8 waves, one workgroup per CU) has the best operand reuse but
+  // needs several rounds of tiles per CU and wastes the ragged part of N; 256x192 takes
+  // over where N is a multiple of 192 that 256 would pad by more than 5 % (N = 1152:
+  // 11 % padding and 2.5 rounds of tiles become none and 3); 128x128 (4 waves, two
+  // workgroups per CU, so one's epilogue overlaps the other's main loop) wins for
+  // narrow or short-K products.  Thresholds from timings of the workload shapes.
+  const long long tiles256 = (long long)ceil_div(M, 256) * ceil_div(N, 256);
+  const double waste = (double)ceil_div(N, 256) * 256.0 / N - 1.0;
+  auto fill = [](long long t) { return (double)t / (double)((t + 255) / 256 * 256); };
+  // 384x192 (96x96 per wave) is no faster per tile than 256x256, but where its tile count fills
+  // whole rounds of 256 and that of 256x256 does not, it saves most of a round (the full-3D
+  // out-projection and fc2: 752 tiles = 2.94 rounds against 840 = 3.28; 2-5 % over the split
+  // last round)
+  if (N % 192 == 0 && waste > 0.05 && (long long)ceil_div(M, 256) * (N / 192) >= 192) return T192;
+  if (!unpatch && N % 192 == 0 && K >= 2048 && tiles256 >= 600 && waste <= 0.05 &&
+           fill((long long)ceil_div(M, 384) * (N / 192)) >= 0.95 && fill(tiles256) < 0.85) return T384;
+  if (tiles256 >= 600 && (waste <= 0.05 || K >= 2048)) return T256;
+  // Mid-size products (a few thousand rows) that the thresholds above leave to 128x128: the large
+  // tiles still win where their tile count fills its rounds of 256 workgroups (measured at
+  // M = 4096 and 8192: QKV of the 1152-wide model 8-14 % faster with 256x256, its fc1 at
+  // M = 8192 7 % faster with 256x192; where the last round would be mostly empty, 128x128 stays)
+  if (tiles256 >= 200 && waste <= 0.05 && fill(tiles256) >= 0.85) return T256;
+  if (N % 192 == 0 && (long long)ceil_div(M, 256) * (N / 192) >= 200 && fill((long long)ceil_div(M, 256) * (N / 192)) >= 0.95) return T192;
+  return T128;
+}
+
+// Packed weights: where their kernel's estimate is below that of the tile just chosen.  The estimates, in us, are fits over
+// 325 products (M 256 to 38 000, N and K 576 to 12 288, each timed in every form): tiles of the fullest CU times a
+// time per K tile and one per tile.  314 products: 0.917 of the time in the mean, none more than 2 % slower.  A lone 128x256
+// tile on a CU (two waves a SIMD short) is up to 1.13 times slower than estimated and not taken; products whose 128x128 tiles are
+// all split along K stay with them (up to 1.58).
+// Columns of their tile, or 0.
+static int packed_columns(Bf16Tile tile, int M, int N, int K, const void* scratch, size_t scratch_bytes) {
+  if (!packs_weights(N, K) || (unsigned long long)M * K * 2 >= (1ull << 32)) return 0;
+  const double kt = K / 64.0;
+  auto per_cu = [&](int bm, int bn) { return (double)(((long long)ceil_div(M, bm) * ceil_div(N, bn) + 255) / 256); };
+  auto rounds = [&](int bm, int bn, int sp, double start, double k, double fixed) {
+    if (sp < 2) return start + per_cu(bm, bn) * (k * kt + fixed);
+    const double full = (double)((long long)ceil_div(M, bm) * ceil_div(N, bn) / 256);
+    return start + full * (k * kt + fixed) + (k * kt / sp + fixed) + 14.0;
+  };
+  auto lone = [&](double k, double fixed) { return per_cu(128, 128) == 1.0 ? k * kt + fixed : 0.0; };
+  auto tiles = [&](int bm, int bn) { return (long long)ceil_div(M, bm) * ceil_div(N, bn); };
+  double now = 0.0;
+  switch (tile) {
+    case T256: now = rounds(256, 256, split_ranges<256, 256>(tiles(256, 256), 256, K, scratch, scratch_bytes), -1.75, 1.266, 8.84); break;
+    case T192: now = rounds(256, 192, split_ranges<256, 192>(tiles(256, 192), 256, K, scratch, scratch_bytes), 0.04, 1.051, 6.49); break;
+    case T384: now = rounds(384, 192, split_ranges<384, 192>(tiles(384, 192), 256, K, scratch, scratch_bytes), -0.74, 1.386, 11.56); break;
+    case T128:
+      if (split_ranges<128, 128>(tiles(128, 128), 512, K, scratch, scratch_bytes) < 2) now = rounds(128, 128, 1, 1.84, 0.443, 1.40) + lone(0.21, -0.72);
+      break;
+  }
+  const double e256 = per_cu(128, 256) >= 2.0 ? rounds(128, 256, 1, -0.09, 0.702, 2.68) : 1e30,
+               e128 = rounds(128, 128, 1, 1.25, 0.419, 1.11) + lone(0.083, 0.56);
+  if (e256 < now && e256 <= e128) return 256;
+  return e128 < now ? 128 : 0;
+}
+
+bool packed_weights_serve(int M, int N, int K) {
+  if ((long long)ceil_div(M, 128) * ceil_div(N, 128) < 32 || N < 32) return false;      // k_gemm_skinny
+  const Bf16Tile tile = bf16_tile(false, M, N, K);
+  return packed_columns(tile, M, N, K, nullptr, 0) || packed_columns(tile, M, N, K, (const void*)16, ~(size_t)0);
+}
+
 template <int MODE>
 static hipError_t dispatch_mode(int bf16, const void* A, const void* Wt, int M, int N, int K, const EpiParams& ep,
                                 void* scratch, size_t scratch_bytes, const void* w_parts, hipStream_t s) {
@@ -1702,60 +1768,12 @@ static hipError_t dispatch_mode(int bf16, const void* A, const void* Wt, int M, 
       aligned = aligned && ep.ldo % 8 == 0 && ((uintptr_t)ep.out & 15) == 0;
   }
   if (K % 64 != 0 || !aligned || N < 32) return run_plain<bf16_t, MODE>(A, Wt, M, N, K, ep, s);
-  // Tile choice.  256x256 (8 waves, one workgroup per CU) has the best operand reuse but
-  // needs several rounds of tiles per CU and wastes the ragged part of N; 256x192 takes
-  // over where N is a multiple of 192 that 256 would pad by more than 5 % (N = 1152:
-  // 11 % padding and 2.5 rounds of tiles become none and 3); 128x128 (4 waves, two
-  // workgroups per CU, so one's epilogue overlaps the other's main loop) wins for
-  // narrow or short-K products.  Thresholds from timings of the workload shapes.
-  const long long tiles256 = (long long)ceil_div(M, 256) * ceil_div(N, 256);
-  const double waste = (double)ceil_div(N, 256) * 256.0 / N - 1.0;
-  enum { T128, T192, T256, T384 } tile = T128;
-  auto fill = [](long long t) { return (double)t / (double)((t + 255) / 256 * 256); };
-  // 384x192 (96x96 per wave) is no faster per tile than 256x256, but where its tile count fills
-  // whole rounds of 256 and that of 256x256 does not, it saves most of a round (the full-3D
-  // out-projection and fc2: 752 tiles = 2.94 rounds against 840 = 3.28; 2-5 % over the split
-  // last round)
-  if (N % 192 == 0 && waste > 0.05 && (long long)ceil_div(M, 256) * (N / 192) >= 192) tile = T192;
-  else if (MODE != EPI_UNPATCH && N % 192 == 0 && K >= 2048 && tiles256 >= 600 && waste <= 0.05 &&
-           fill((long long)ceil_div(M, 384) * (N / 192)) >= 0.95 && fill(tiles256) < 0.85) tile = T384;
-  else if (tiles256 >= 600 && (waste <= 0.05 || K >= 2048)) tile = T256;
-  // Mid-size products (a few thousand rows) that the thresholds above leave to 128x128: the large
-  // tiles still win where their tile count fills its rounds of 256 workgroups (measured at
-  // M = 4096 and 8192: QKV of the 1152-wide model 8-14 % faster with 256x256, its fc1 at
-  // M = 8192 7 % faster with 256x192; where the last round would be mostly empty, 128x128 stays)
-  else if (tiles256 >= 200 && waste <= 0.05 && fill(tiles256) >= 0.85) tile = T256;
-  else if (N % 192 == 0 && (long long)ceil_div(M, 256) * (N / 192) >= 200 && fill((long long)ceil_div(M, 256) * (N / 192)) >= 0.95) tile = T192;
-
-  // Packed weights: where their kernel's estimate is below that of the tile just chosen.  The estimates, in us, are fits over
-  // 325 products (M 256 to 38 000, N and K 576 to 12 288, each timed in every form): tiles of the fullest CU times a
-  // time per K tile and one per tile.  314 products: 0.917 of the time in the mean, none more than 2 % slower.  A lone 128x256
-  // tile on a CU (two waves a SIMD short) is up to 1.13 times slower than estimated and not taken; products whose 128x128 tiles are
-  // all split along K stay with them (up to 1.58).
+  const Bf16Tile tile = bf16_tile(MODE == EPI_UNPATCH, M, N, K);
   if constexpr (MODE == EPI_HEADS || MODE == EPI_GATE || MODE == EPI_GELU) {
-    if (w_parts && ((uintptr_t)w_parts & 15) == 0 && packs_weights(N, K) && (unsigned long long)M * K * 2 < (1ull << 32)) {
-      const double kt = K / 64.0;
-      auto per_cu = [&](int bm, int bn) { return (double)(((long long)ceil_div(M, bm) * ceil_div(N, bn) + 255) / 256); };
-      auto rounds = [&](int bm, int bn, int sp, double start, double k, double fixed) {
-        if (sp < 2) return start + per_cu(bm, bn) * (k * kt + fixed);
-        const double full = (double)((long long)ceil_div(M, bm) * ceil_div(N, bn) / 256);
-        return start + full * (k * kt + fixed) + (k * kt / sp + fixed) + 14.0;
-      };
-      auto lone = [&](double k, double fixed) { return per_cu(128, 128) == 1.0 ? k * kt + fixed : 0.0; };
-      auto tiles = [&](int bm, int bn) { return (long long)ceil_div(M, bm) * ceil_div(N, bn); };
-      double now = 0.0;
-      switch (tile) {
-        case T256: now = rounds(256, 256, split_ranges<256, 256>(tiles(256, 256), 256, K, scratch, scratch_bytes), -1.75, 1.266, 8.84); break;
-        case T192: now = rounds(256, 192, split_ranges<256, 192>(tiles(256, 192), 256, K, scratch, scratch_bytes), 0.04, 1.051, 6.49); break;
-        case T384: now = rounds(384, 192, split_ranges<384, 192>(tiles(384, 192), 256, K, scratch, scratch_bytes), -0.74, 1.386, 11.56); break;
-        case T128:
-          if (split_ranges<128, 128>(tiles(128, 128), 512, K, scratch, scratch_bytes) < 2) now = rounds(128, 128, 1, 1.84, 0.443, 1.40) + lone(0.21, -0.72);
-          break;
-      }
-      const double e256 = per_cu(128, 256) >= 2.0 ? rounds(128, 256, 1, -0.09, 0.702, 2.68) : 1e30,
-                   e128 = rounds(128, 128, 1, 1.25, 0.419, 1.11) + lone(0.083, 0.56);
-      if (e256 < now && e256 <= e128) return run_packed<128, 256, 2, MODE>(A, w_parts, M, N, K, ep, s);
-      if (e128 < now) return run_packed<128, 128, 4, MODE>(A, w_parts, M, N, K, ep, s);
+    if (w_parts && ((uintptr_t)w_parts & 15) == 0) {
+      const int columns = packed_columns(tile, M, N, K, scratch, scratch_bytes);
+      if (columns == 256) return run_packed<128, 256, 2, MODE>(A, w_parts, M, N, K, ep, s);
+      if (columns == 128) return run_packed<128, 128, 4, MODE>(A, w_parts, M, N, K, ep, s);
     }
   }
   switch (tile) {
