@@ -1664,13 +1664,15 @@ static hipError_t dispatch_f32(const void* A, const void* Wt, const void* w_part
     const long long rounds = ((long long)ceil_div(M, bm) * ceil_div(N, bn) + 255) / 256;
     return rounds == 1 ? alone : rounds * shared;
   };
-  if (w_parts && K < (1 << 18)) {                        // (K: 32-bit offsets into the split weights)
-    const double e64 = estimate(64, 64, 2.3, 4.2), e128 = estimate(64, 128, 3.7, 5.0), e192 = estimate(128, 192, 9.9, 12.0),
-                 e256 = estimate(256, 256, 22.0, 23.0);
-    if (e256 < e192 && e256 < e128 && e256 < e64) return run_f32_parts<256, 256, 4, 2, 2, true, MODE>(A, Wt, w_parts, M, N, K, ep, s);
-    if (e192 < e128 && e192 < e64) return run_f32_parts<128, 192, 2, 2, 2, true, MODE>(A, Wt, w_parts, M, N, K, ep, s);
-    if (e64 < e128) return run_f32_parts<64, 64, 2, 2, 4, true, MODE>(A, Wt, w_parts, M, N, K, ep, s);
-    return run_f32_parts<64, 128, 2, 2, 4, true, MODE>(A, Wt, w_parts, M, N, K, ep, s);
+  if constexpr (MODE == EPI_HEADS || MODE == EPI_GATE || MODE == EPI_GELU) {           // a model's products over token rows
+    if (w_parts && K < (1 << 18)) {                      // (K: 32-bit offsets into the split weights)
+      const double e64 = estimate(64, 64, 2.3, 4.2), e128 = estimate(64, 128, 3.7, 5.0), e192 = estimate(128, 192, 9.9, 12.0),
+                   e256 = estimate(256, 256, 22.0, 23.0);
+      if (e256 < e192 && e256 < e128 && e256 < e64) return run_f32_parts<256, 256, 4, 2, 2, true, MODE>(A, Wt, w_parts, M, N, K, ep, s);
+      if (e192 < e128 && e192 < e64) return run_f32_parts<128, 192, 2, 2, 2, true, MODE>(A, Wt, w_parts, M, N, K, ep, s);
+      if (e64 < e128) return run_f32_parts<64, 64, 2, 2, 4, true, MODE>(A, Wt, w_parts, M, N, K, ep, s);
+      return run_f32_parts<64, 128, 2, 2, 4, true, MODE>(A, Wt, w_parts, M, N, K, ep, s);
+    }
   }
   // Both operands split on the way.  Where 64x128 tiles of the fp32 pipe make one round and there are more than 330 of 64x64, those are
   // over first (1274 x 1536 x 512: 24.1 us against 25.9, 2000 x 1024 x 4096 164 and 169; below that 712 x 1536 x 512 23.3 and 21.7,
