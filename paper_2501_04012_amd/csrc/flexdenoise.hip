@@ -357,6 +357,7 @@ int linear(const Ctx& c, int cat, int mode, const void* A, const Linear& L, int 
            void* scratch = nullptr, size_t scratch_bytes = 0) {
   ep.bias = L.b;
   ProfScope ps(c, cat);
+  // (what k_chain reads in fragment order is no layout of the product kernels)
   HIP_TRY(launch_gemm(c.m->bf16, mode, A, L.wt, M, L.out, L.in, ep, c.s, scratch, scratch_bytes, c.m->chain_shape ? nullptr : L.parts));
   return FC_OK;
 }

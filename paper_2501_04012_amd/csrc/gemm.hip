@@ -1,8 +1,8 @@
 // Linear layers: C[M,N] = A[M,K] * Wt[N,K]^T with fused epilogues.
 //   bf16: MFMA (v_mfma_f32_32x32x16_bf16) kernel, operands DMA'd into swizzled LDS tiles,
 //         fp32 accumulation.
-//   fp32: MFMA kernels, on three bf16 parts of a value or (small products) v_mfma_f32_32x32x2_f32; a plain LDS-tiled FMA kernel for operands that
-//         are not made of whole aligned 16-byte chunks.
+//   fp32: MFMA kernels, on three bf16 parts of a value or (small products, and what the parts cannot hold)
+//         v_mfma_f32_32x32x2_f32; a plain LDS-tiled FMA kernel for operands that are not made of whole aligned 16-byte chunks.
 // Both operands are contiguous along K ("TN" form): activations are [tokens, K]
 // and weights are stored [out, in].
 #include <type_traits>
@@ -700,10 +700,11 @@ __global__ __launch_bounds__(WR * WC * 64) void k_gemm_dlds(const bf16_t* __rest
 // For weights that were packed into fragment order when the model was loaded ([N / 32][K / 16][lane][8], k_pack_weights): a
 // fragment is 1 KB in a row and goes from L2 to the registers of the one wave column that needs it; LDS holds A alone.  A
 // workgroup is four waves side by side, each 128 rows by BN / 4 columns, so that no fragment is fetched twice, and small
-// enough that two (BN 256: 212 registers, 34 KB of LDS) or four of them (BN 128) share a CU: one's epilogue and first loads run
+// enough that two (BN 256: 208 registers, 34 KB of LDS) or four of them (BN 128) share a CU: one's epilogue and first loads run
 // under another's products, and tiles half the size fill the last round better.  Of k_gemm_dlds it keeps the tile order, the
 // swizzled A stages, the K loop (even number of K tiles, barrier ahead of the last slice) and the epilogue.
-// A fragment's registers are loaded for the next K tile right behind the products that used them.
+// A fragment's registers are loaded for the next K tile right behind the products that used them.  Sums are those of k_gemm_dlds bit
+// for bit where that does not split a tile along K.
 //
 // Against k_gemm_dlds the 256x256 form of this kernel is level (990 and 994 us at 17776 x 12288 x 3072: a third less LDS traffic
 // buys nothing, the power limit bounds both), so what counts are rounds and epilogues (the rule is in the dispatch).
@@ -1172,8 +1173,8 @@ static hipError_t run_f32(const void* A, const void* Wt, int M, int N, int K, co
 // instructions; written as a block behind them it cost 10 %.
 // LDS bounds the small tiles (64x128: 580 cycles of reads and writes against 384 of matrix instructions per slice),
 // the power limit the large ones (1.2 PFLOP/s of bf16 products, as in the bf16 kernels).
-// us, fp32 matrix pipe, weights split on the way, and before: 4096 x 3456 x 1152 269, 205, 167; 4096 x 4608 x 1152 339, 254,
-// 212; 4096 x 1152 x 4608 372, 348, 291; 4096 x 1152 x 1152 116, 95, 79; 16000 x 256 x 256 24.6, 19, 18.
+// us, fp32 matrix pipe, weights split on the way, and before (forms of the dispatch, one box): 4096 x 3456 x 1152 292, 216, 177;
+// 4096 x 4608 x 1152 370, 271, 226; 4096 x 1152 x 4608 383, 386, 312; 4096 x 1152 x 1152 103, 100, 84.
 // K need only be a whole number of 16-byte chunks: past its end a lane's offset is moved out of the buffer
 // resource's range, which loads zero, as do rows past the end of an operand.
 //
