@@ -195,6 +195,7 @@ struct Carver {          // bump allocator over a byte range, 256-byte aligned p
 // Whether a product of the model's rows takes packed weights at any number of samples: past 2^17 rows the rounds that packed
 // tiles save are less than what they cost.
 bool rows_take_packed(const fc_model* m, int in, int out) {
+  if (!packs_weights(out, in)) return false;
   for (long long rows = m->Ns; rows == m->Ns || rows <= 1 << 17; rows += m->Ns)
     if (packed_weights_serve((int)rows, out, in)) return true;
   return false;

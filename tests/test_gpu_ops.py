@@ -166,8 +166,8 @@ def test_linear_fp32(fc, M, N, K):
 @pytest.mark.parametrize("M,N,K", [
     (33, 31, 4), (31, 33, 12), (65, 200, 300), (500, 512, 512), (7, 2304, 768), (9000, 16, 36),   # one 32x32 tile per workgroup
     (700, 700, 4), (1025, 577, 100), (1500, 576, 576),                  # 64x64 tiles: ragged edges, K past whole K tiles
-    (1100, 1030, 52), (2113, 520, 16),                                  # bf16 parts: 64x64 tiles
-    (4095, 1025, 132), (2048, 2048, 260)])                              # 128x128 tiles
+    (1100, 1030, 52), (2113, 520, 16), (4095, 1025, 132),               # bf16 parts: 64x64 tiles
+    (2048, 2048, 260), (4000, 1000, 132)])                              # 128x128 tiles
 @pytest.mark.parametrize("epilogue", [0, 2])
 def test_linear_fp32_matrix_cores(fc, M, N, K, epilogue):
     """fp32 sums of K products in any order are within K 2^-24 of sum |a| |w| (here bounded by
@@ -190,9 +190,9 @@ def test_linear_fp32_matrix_cores(fc, M, N, K, epilogue):
     assert rel_l2(got[:M], want) < 2e-6
 
 
-@pytest.mark.parametrize("M,N", [(1100, 1030), (4100, 1024)])
+@pytest.mark.parametrize("M,N", [(1100, 1030), (4100, 1024), (4000, 1000)])
 def test_linear_fp32_in_parts_keeps_values_that_are_not_finite(fc, M, N):
-    """Infinities, NaN and the largest finite values leave exactly the marks that fp32 products leave."""
+    """Infinities, NaN and the largest finite values leave exactly the marks that fp32 products leave: 64x64 and, last, 128x128 tiles."""
     torch = _torch()
     K = 40
     rng = np.random.default_rng(M)
@@ -233,7 +233,7 @@ def test_linear_fp32_of_one_round_of_wide_tiles(fc, M, N, K):
     assert np.abs(_linear_fp32(fc, A, W) - want).max() <= (K + 2) * 2.0 ** -24 * (np.abs(A) @ np.abs(W)).max()
 
 
-@pytest.mark.parametrize("M,N", [(1100, 1030), (4100, 1024)])
+@pytest.mark.parametrize("M,N", [(1100, 1030), (4000, 1000)])           # 64x64 and 128x128 tiles
 @pytest.mark.parametrize("K", [36, 512])
 @pytest.mark.parametrize("scale", [1e-31, 1e-33, 1e-35, 1e-37, 1e-41])
 def test_linear_fp32_of_small_operands(fc, M, N, K, scale):
@@ -255,20 +255,21 @@ def test_linear_fp32_of_small_operands(fc, M, N, K, scale):
             assert np.array_equal(got[rows, cols], few[rows, cols])
 
 
-def test_linear_fp32_of_one_hot_rows_returns_the_weights(fc):
+@pytest.mark.parametrize("M,N", [(1100, 1030), (4000, 1000)])
+def test_linear_fp32_of_one_hot_rows_returns_the_weights(fc, M, N):
     """Sums of a single product: bit for bit the weight, ordinary, small, subnormal and large ones side by side."""
     rng = np.random.default_rng(4)
-    K, N, M = 64, 1100, 1100
-    W = (rng.standard_normal((K, N)) * 10.0 ** rng.uniform(-44, 38, (K, N))).astype(np.float32)
+    K = 64
+    W = (rng.standard_normal((K, N)) * 10.0 ** rng.uniform(-44, 37.5, (K, N))).astype(np.float32)
     A = np.zeros((M, K), np.float32)
     A[np.arange(M), np.arange(M) % K] = 1.0
     assert np.array_equal(_linear_fp32(fc, A, W), W[np.arange(M) % K])
-    W = (rng.standard_normal((K, N)) * 10.0 ** rng.uniform(-33, 38, (K, N))).astype(np.float32)
+    W = (rng.standard_normal((K, N)) * 10.0 ** rng.uniform(-33, 37.5, (K, N))).astype(np.float32)
     W[np.abs(W) < 2.0 ** -110] = 0.0                      # in parts throughout
     assert np.array_equal(_linear_fp32(fc, A, W), W[np.arange(M) % K])
 
 
-@pytest.mark.parametrize("M,N", [(1100, 1030), (4100, 1024)])
+@pytest.mark.parametrize("M,N", [(1100, 1030), (4000, 1000)])
 def test_linear_fp32_next_to_the_largest_values(fc, M, N):
     """Finite values above bf16's largest keep their bits, infinities meet partners of any size without losing their sign, and products
     that leave fp32's range do so as with fp32 products."""
