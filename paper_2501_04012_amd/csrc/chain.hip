@@ -17,15 +17,23 @@
 // (launch_pack_chain): a load of 64 lanes is 1 KB in a row, where rows of the plain layout gave it 64 bytes of each of 16
 // (64 wide, six blocks full 3-D 123 -> 112 us; 128 wide, factorized 379 -> 351; 64 wide resume below 7.85 -> 7.61 ms).
 //
-// A workgroup is alone with its 16 rows, two waves to a SIMD, so what it takes is the instructions of
-// one wave after the other, 4 to 8 cycles each, and little of that is multiplication.  Hence: no
-// 64-bit lane addresses (a uniform base, one 32-bit lane offset, immediate offsets), no predicates
-// where a scalar branch will do, the wave number a scalar (a masked-out matrix instruction would be
-// issued all the same), one kernel per kind of launch, and the first weights of a product on their way
-// before the stage in front of it begins (barriers wait for LDS only).
+// A workgroup is alone with its 16 rows, two waves to a SIMD, so what it takes is the latency of its loads (the weights of a
+// deep model do not stay in an XCD's 4 MB of L2: some 2000 cycles a stage where a stage fetches its own) and the
+// instructions of one wave after the other, 4 to 8 cycles each; the multiplications are a quarter.  Hence:
+// - A product's first two batches of weights, its bias and gate, a LayerNorm's vectors and a head's first keys are on their way two
+//   or three stages ahead (one stage, and only the first batch, with heads above 32, whose key tiles take the registers).
+//   Barriers wait for LDS only.  A wait for a load counts the loads behind it, so these have to be known when this is compiled:
+//   no branch of a single wave around them (what a wave does not need lies past the end of a buffer and reads as zero;
+//   where no wave needs a second batch all skip it, as such a load still takes its 16 cycles of the CU's address unit),
+//   and drain() where a rare path ends.
+// - One miss for all of the kernel's arguments (touch_arguments), and little arithmetic on them: sizes in tiles and bytes come from the host.
+// - No 64-bit lane addresses (a buffer, one 32-bit lane offset, immediate offsets), no predicates where a scalar branch will
+//   do, the wave number a scalar (a masked-out matrix instruction would be issued all the same), one kernel per kind of launch.
 //
-// 64 wide, 4 heads, 28 blocks, 4 requests with guidance (512 rows), ten steps: 17.2 -> 7.6 ms, of which a
-// spatial and a temporal launch take about 9 and 17 us.
+// 64 wide, 4 heads, 28 blocks, 4 requests with guidance (512 rows), ten steps: 17.2 ms with a launch per operator, 7.53 with loads one
+// stage ahead, 5.53 now; a spatial and a temporal launch 9 and 17 us before, 6 and 12 now.  Steps of one to three blocks, 160 sizes of 16
+// to 128 columns: 0.92 of the time in the mean (64 and 128 wide factorized 0.80 to 0.86, full 3-D 0.9 to 1.0), none slower.
+#include <type_traits>
 #include "common.h"
 
 namespace fc {
@@ -88,33 +96,73 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+#if defined(__HIP_DEVICE_COMPILE__)   // buffer resources are a device-side type
+// What lies past `bytes` loads as zero, without a request to memory: loads that a wave may not need are issued all the same, so that
+// the number of loads behind one of them is known where it is waited for (under a branch the wait would be for all of them).
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer(const void* base, unsigned bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, (int)bytes, 0x00020000);
+}
+__device__ __forceinline__ f32x4 load4(__amdgpu_buffer_rsrc_t r, unsigned byte) {
+  return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)byte, 0, 0));
+}
+constexpr unsigned kAll = 0x7ffffff0, kNowhere = 0x7ffffff0;
+// All loads have landed.  At the end of a path that few calls take: behind it a wait counts on the loads of either path, so what
+// this one leaves on its way would be waited for, and all older loads with it, by those that did not take it.
+__device__ __forceinline__ void drain() { __builtin_amdgcn_s_waitcnt(0x0F70); }
+
+// Reads a word of every line of the kernel's arguments, all at once: left to their uses, a line at a time, each of them is a miss of
+// the scalar cache that a stage begins with.
+template <size_t BYTES> __device__ __forceinline__ void touch_arguments() {
+  const auto* p = (const __attribute__((address_space(4))) int*)__builtin_amdgcn_kernarg_segment_ptr();
+  int any = 0;
+#pragma unroll
+  for (size_t b = 0; b < BYTES; b += 64) any |= p[b / 4];
+  asm volatile("" ::"s"(any));
+}
+
+// c + a b.  The sum never shares registers with c: left to itself the compiler moves the sum of a chain by two registers now and then,
+// an output that overlaps the input it is added to without being the same registers, and a build with such products gave wrong
+// sums (128 columns, third batch of a product; tests/test_mfma_registers.py).
+__device__ __forceinline__ f32x4 mac(float a, float b, f32x4 c) {
+  f32x4 d = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+  asm volatile("" : "+v"(d) : "v"(c));
+  return d;
+}
+
+using Yes = std::true_type; using No = std::false_type;
+
+// 16 keys and values of a head, as attend() uses them; past the end the last key again
+template <int HDT> struct KeyTile { f32x4 k[HDT]; float v[4][HDT]; };
+template <int HDT>
+__device__ __forceinline__ void fetch_keys(KeyTile<HDT>& t, const float* K, const float* V, bool on, int k0, int nk, int hd, unsigned stride) {
+  const int lane = threadIdx.x & 63, i = lane & 15, h = lane >> 4;
+  const bool half = hd & 8;
+  const auto rk = buffer(K, on ? kAll : 0), rv = buffer(V, on ? kAll : 0);
+  const unsigned ko = __umul24(min(k0 + i, nk - 1), stride);
+#pragma unroll
+  for (int j = 0; j < HDT; ++j) t.k[j] = load4(rk, 4 * (ko + (j + 1 < HDT || !half || h < 2 ? 16 * j + 4 * h : 0)));
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const unsigned vo = __umul24(min(k0 + 4 * h + e, nk - 1), stride);
+#pragma unroll
+    for (int j = 0; j < HDT; ++j)
+      t.v[e][j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rv, (int)(4 * (vo + (j + 1 < HDT || !half || i < 8 ? 16 * j + i : 0))), 0, 0));
+  }
+}
+
 // One head of one sequence, or of several that lie one after the other, for 16 queries (a lane's
 // query is lane & 15; qs: its head slice, scaled by log2(e) / sqrt(hd) already): scores as keys x
 // queries, so that the probabilities are the B operand of V^T P as they stand.  Key j is at
-// K + j * stride; keys lo .. hi - 1 count for this lane.  out(d, v): four consecutive outputs of the
-// lane's query.  Returns whether a value is not finite: a key that does not count then leaves its mark
+// K + j * stride; keys lo .. hi - 1 count for this lane.  cur: the first 16 keys, on their way.  out(d, v): four consecutive
+// outputs of the lane's query.  Returns whether a value is not finite: a key that does not count then leaves its mark
 // all the same.
 template <int HDT, typename Out>
-__device__ __forceinline__ bool attend(const float* qs, int nk, int lo, int hi, int hd, const float* __restrict__ K,
-                                       const float* __restrict__ V, unsigned stride, Out out) {
+__device__ __forceinline__ bool attend(const float* qs, int nk, int lo, int hi, int hd, const float* K, const float* V, unsigned stride,
+                                       KeyTile<HDT>& cur, Out out) {
   const int lane = threadIdx.x & 63, i = lane & 15, h = lane >> 4;
-  struct Tile { f32x4 k[HDT]; float v[4][HDT]; };
   const bool half = hd & 8;                               // uniform: the last 16 columns are 8
-  auto fetch = [&](int k0, Tile& t) {                     // past the end: the last key again
-    const unsigned ko = __umul24(min(k0 + i, nk - 1), stride);
-#pragma unroll
-    for (int j = 0; j < HDT; ++j) t.k[j] = *(const f32x4*)(K + (ko + (j + 1 < HDT || !half || h < 2 ? 16 * j + 4 * h : 0)));
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const unsigned vo = __umul24(min(k0 + 4 * h + e, nk - 1), stride);
-#pragma unroll
-      for (int j = 0; j < HDT; ++j) t.v[e][j] = V[vo + (j + 1 < HDT || !half || i < 8 ? 16 * j + i : 0)];
-    }
-  };
   constexpr bool AHEAD = HDT <= 4;                        // the next tile's loads run under this one, registers permitting
-  Tile cur, nxt;
-  fetch(0, cur);
-  __builtin_amdgcn_sched_barrier(0);
+  KeyTile<HDT> nxt;
   f32x4 q[HDT], acc[HDT];
 #pragma unroll
   for (int j = 0; j < HDT; ++j) {
@@ -125,16 +173,17 @@ __device__ __forceinline__ bool attend(const float* qs, int nk, int lo, int hi, 
   // kNone: below every score, and finite: a lane may meet a tile without a key of its own first
   constexpr float kNone = -__FLT_MAX__;
   float m = kNone, l = 0.0f, probe = 0.0f;                // probe: 0, or NaN once a value is not finite
-  for (int k0 = 0; k0 < nk; k0 += 16) {
-    if (AHEAD) { if (k0 + 16 < nk) fetch(k0 + 16, nxt); }
-    else if (k0 > 0) fetch(k0, cur);
+  auto tile = [&](int k0, auto more) {
+    constexpr bool MORE = decltype(more)::value;
+    if (AHEAD) { if (MORE && k0 + 16 < nk) fetch_keys<HDT>(nxt, K, V, true, k0 + 16, nk, hd, stride); }
+    else if (k0 > 0) fetch_keys<HDT>(cur, K, V, true, k0, nk, hd, stride);
     __builtin_amdgcn_sched_barrier(0);
     if (half && h >= 2) cur.k[HDT - 1] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     f32x4 s = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
     for (int j = 0; j < HDT; ++j)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_16x16x4f32(cur.k[j][e], q[j][e], s, 0, 0, 0);
+      for (int e = 0; e < 4; ++e) s = mac(cur.k[j][e], q[j][e], s);
     const int key = k0 + 4 * h;
     bool in[4];
     float mc = kNone;
@@ -160,11 +209,17 @@ __device__ __forceinline__ bool attend(const float* qs, int nk, int lo, int hi, 
         float v = cur.v[e][j];
         if (k0 + 16 > nk) v = key + e < nk ? v : 0.0f;
         if (j + 1 == HDT && half) v = i < 8 ? v : 0.0f;
-        acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(v, p, acc[j], 0, 0, 0);
+        acc[j] = mac(v, p, acc[j]);
         probe = __builtin_fmaf(v, 0.0f, probe);
       }
     }
-    if (AHEAD) cur = nxt;
+    if (AHEAD && MORE) cur = nxt;
+  };
+  if (HDT <= 2 && nk <= 16) {                             // on its own, for the same reason as drain()
+    tile(0, No{});
+  } else {
+    for (int k0 = 0; k0 < nk; k0 += 16) tile(k0, Yes{});
+    drain();
   }
   const float inv = 1.0f / quad_sum(l);
 #pragma unroll
@@ -172,10 +227,13 @@ __device__ __forceinline__ bool attend(const float* qs, int nk, int lo, int hi, 
     if (j + 1 < HDT || !half || h < 2) out(16 * j + 4 * h, acc[j] * inv);
   return probe != 0.0f;
 }
+#endif
 
-// First weights of a product: what product() starts with.
+// What a product starts with: the first two batches of a wave's weights, bias and gate of its first two tiles.
 constexpr int U = 4;                                      // chunks of 16 of K per batch of loads
-struct Ahead { f32x4 w[U]; };
+struct Ahead { f32x4 w[2][U], bias[2], gate[2]; };
+// What a LayerNorm needs besides the rows
+struct Modulation { f32x4 shift, scale; };
 
 // The launches of a step.  CHAIN_EMBED: patch embedding.  CHAIN_SELF: self-attention.  CHAIN_CROSS,
 // CHAIN_MLP: those branches.  All of them end with a LayerNorm and the next QKV projection or the head.
@@ -183,7 +241,11 @@ enum { CHAIN_EMBED = 1, CHAIN_SELF = 2, CHAIN_CROSS = 4, CHAIN_MLP = 8 };
 
 template <int HDT, int KIND>
 __global__ __launch_bounds__(kThreads) void k_chain(ChainArgs a) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  constexpr bool TEMPORAL = KIND & CHAIN_CROSS;            // rows in (b, s, t) order
+  constexpr bool FULL = (KIND & CHAIN_MLP) && !(KIND & CHAIN_CROSS);            // full 3-D: one sequence per batch row
   extern __shared__ __attribute__((aligned(16))) float smem[];
+  touch_arguments<sizeof(ChainArgs)>();
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), i = lane & 15, h = lane >> 4;
   const int D = a.D, hd = a.hd, ld = lds_row(D), ldm = lds_row(a.mlp);
   float* const xt = smem;                                 // residual rows
@@ -191,11 +253,13 @@ __global__ __launch_bounds__(kThreads) void k_chain(ChainArgs a) {
   float* const o = u + kChainRows * ld;                   // queries
   float* const hid = o + kChainRows * ld;
   f32x4* const red = (f32x4*)(hid + (KIND & CHAIN_MLP ? kChainRows * ldm : 0));
+  int* const again = (int*)(red + 6 * 64);                // the last KB of red: parts take 6 at most
+  if (threadIdx.x == 0) *again = 0;
 
   // Row index -> row of the activations: natural order, or (b, s, t), in which temporal sequences are runs.
   // q, k and v of temporal attention are stored in that order.
   auto natural = [&](int idx) -> int {
-    if (!a.temporal) return idx;
+    if (!TEMPORAL) return idx;
     const int b = a.by_N.div(idx), r = idx - b * a.N, s = a.by_T.div(r), t = r - s * a.T;
     return b * a.N + t * a.S + s;
   };
@@ -207,210 +271,345 @@ __global__ __launch_bounds__(kThreads) void k_chain(ChainArgs a) {
   const bool e_in = ec < D;
   const int e_idx = min(idx0 + er, last), e_row = natural(e_idx);
   const int my = min(idx0 + i, last);
-  const int my_row = a.temporal ? natural(my) : my;
+  const int my_row = natural(my);
   int my_alt = 0, e_alt = 0, e_b = 0, e_pos = 0;          // the text rows' own modulation set
-  if (a.alt_rows || (KIND & CHAIN_EMBED)) {
+  if ((FULL && a.alt_rows) || (KIND & CHAIN_EMBED)) {
     e_b = a.by_Ns.div(e_row);
     e_pos = e_row - e_b * a.Ns;
     e_alt = e_pos < a.alt_rows ? 6 * D : 0;
     my_alt = my_row - (int)a.by_Ns.div(my_row) * a.Ns < a.alt_rows ? 6 * D : 0;
   }
 
-  // ---- the rows
-  if (e_in) {
-    f32x4 x4;
-    if constexpr (!(KIND & CHAIN_EMBED)) {
-      x4 = *(const f32x4*)(a.x + (unsigned)(e_row * D + ec));
-      *(f32x4*)(o + er * ld + ec) = *(const f32x4*)(a.q + (unsigned)(e_idx * D + ec));
-    } else if (e_pos < a.text_rows) {
-      const int tb = a.kv_shared_tail && e_b >= a.kv_split ? a.kv_split : e_b;
-      x4 = *(const f32x4*)(a.y + ((size_t)tb * a.text_rows + e_pos) * D + ec);
-    } else {
-      const int run = a.p * a.C, n = e_pos - a.text_rows, t = a.by_S.div(n), s = n - t * a.S;
-      const int ph = a.by_gw.div(s), pw = s - ph * a.by_gw.d;
-      const float* src = a.latent + ((((size_t)(e_b < a.R ? e_b : e_b - a.R) * a.T + t) * a.H + (size_t)ph * a.p) * a.W + (size_t)pw * a.p) * a.C;
-      const f32x4 pos = *(const f32x4*)(a.pos_sp + (size_t)s * D + ec) + *(const f32x4*)(a.pos_t + (size_t)t * D + ec);
-      x4 = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-      for (int dh = 0; dh < a.p; ++dh)
-#pragma unroll 4
-        for (int f = 0; f < run; ++f)
-          x4 += src[(size_t)dh * a.W * a.C + f] * *(const f32x4*)(a.p_w + (size_t)(dh * run + f) * D + ec);
-      x4 = (x4 + *(const f32x4*)(a.p_b + ec)) + pos;
+  // ---- loads ahead of their use
+  auto issued = [] { __builtin_amdgcn_sched_barrier(0); };   // behind them: the scheduler would move the loads to their use
+  // Products: tiles of 16 outputs, one per wave at a time; K in batches of U chunks.  K % 16 == 0; N % 16 == 0 but in the
+  // head, whose rows past the end repeat the last.  With few tiles and a long K, several waves share a tile's K; their
+  // parts are added in order through `red`.
+  struct Share { int part, c0, c1, t; };
+  auto share = [&](const ChainStep& p, bool split) {
+    Share s{0, 0, p.chunks, wave};
+    if (split && p.split) {
+      s.part = (wave * p.split_mul) >> 8;                 // wave / tiles
+      s.t = wave - s.part * p.tiles;
+      s.c0 = (s.part * p.chunks) >> p.split;
+      s.c1 = s.part >> p.split ? s.c0 : ((s.part + 1) * p.chunks) >> p.split;
     }
-    *(f32x4*)(xt + er * ld + ec) = x4;
-  }
+    return s;
+  };
+  auto fetch = [&](const ChainStep& p, int t, int c, f32x4 (&r)[U]) {
+    const auto w = buffer(p.packed, p.w_bytes);
+    const unsigned at = 1024u * (t * p.chunks + c) + 16u * lane;
+#pragma unroll
+    for (int x = 0; x < U; ++x) r[x] = load4(w, at + 1024 * x);
+  };
+  auto fetch_columns = [&](const ChainStep& p, int t, bool gated, f32x4& bias, f32x4& gate) {
+    const unsigned at = 64u * t + 16u * h;
+    bias = load4(buffer(p.bias, p.bias_bytes), at);
+    if (gated) gate = load4(buffer(p.gate, p.vec_bytes), at + 4 * my_alt);
+  };
+  auto start_first = [&](const ChainStep& p, bool split, Ahead& f) {
+    const Share s = share(p, split);
+    fetch(p, s.t, s.c0, f.w[0]);
+  };
+  auto start_rest = [&](const ChainStep& p, bool split, bool gated, Ahead& f) {
+    const Share s = share(p, split);
+    fetch_columns(p, s.t, gated, f.bias[0], f.gate[0]);
+    if (p.tiles > kChainWaves || p.chunks > U) {          // some wave has a second batch
+      const bool same = s.c0 + U < s.c1;
+      fetch(p, same ? s.t : s.t + kChainWaves, same ? s.c0 + U : s.c0, f.w[1]);
+      if (p.tiles > kChainWaves) fetch_columns(p, s.t + kChainWaves, gated, f.bias[1], f.gate[1]);
+    }
+  };
+  auto start = [&](const ChainStep& p, bool split, bool gated, Ahead& f) {
+    start_first(p, split, f);
+    start_rest(p, split, gated, f);
+  };
+  auto start_norm = [&](const ChainStep& p, int alt, Modulation& m) {
+    const unsigned at = 4u * (alt + ec);                  // (columns past D are not used)
+    m.shift = load4(buffer(p.shift, p.vec_bytes), at);
+    m.scale = load4(buffer(p.scale, p.vec_bytes), at);
+  };
+  // A unit of attention is a head of one of the sequences (len rows each) these rows are in or, where those are shorter than
+  // a key tile and lie one after the other, a head of all of them.
+  struct Sequences { int first, n, mine; bool together; };
+  auto sequences = [&](int len, const FastDiv& by_len, bool cross) {
+    Sequences q;
+    q.first = by_len.div(idx0);
+    q.n = (int)by_len.div(last) - q.first + 1;
+    q.mine = q.n > 1 ? (int)by_len.div(my) - q.first : 0;
+    q.together = !cross && q.n > 1 && len < kChainRows;
+    return q;
+  };
+  struct Unit { int sq, head, nk; size_t base; };
+  auto unit = [&](int un, const Sequences& q, int len, int nk, bool cross, bool together) {
+    Unit w;
+    w.sq = un < a.heads ? 0 : (int)a.by_heads.div(un);
+    w.head = un - w.sq * a.heads;
+    const int seq = q.first + w.sq;
+    w.nk = together ? q.n * len : nk;
+    if (!cross) {
+      w.base = (size_t)(seq * len) * D + w.head * hd;
+    } else {
+      const int kb = a.kv_shared_tail && seq >= a.kv_split ? a.kv_split : seq;
+      w.base = ((size_t)kb * a.heads + w.head) * nk * hd;
+    }
+    return w;
+  };
+  auto start_keys = [&](const float* k, const float* v, int len, const FastDiv& by_len, int nk, bool cross, KeyTile<HDT>& t) {
+    const Sequences q = sequences(len, by_len, cross);
+    const Unit w = unit(wave, q, len, nk, cross, q.together);
+    const bool on = wave < a.heads * (q.together ? 1 : q.n);
+    fetch_keys<HDT>(t, k + (on ? w.base : 0), v + (on ? w.base : 0), on, 0, w.nk, hd, cross ? hd : D);
+  };
 
   // ---- stages
-  auto layer_norm = [&](const float* shift, const float* scale, int alt) {
-    f32x4 v = {0.0f, 0.0f, 0.0f, 0.0f}, sh = v, sc = v;
-    if (e_in) {
-      if (shift) { sh = *(const f32x4*)(shift + (unsigned)(alt + ec)); sc = *(const f32x4*)(scale + (unsigned)(alt + ec)); }
-      v = *(const f32x4*)(xt + er * ld + ec);
-    }
+  auto layer_norm = [&](const Modulation* m) {
+    f32x4 v = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (e_in) v = *(const f32x4*)(xt + er * ld + ec);
     const float mean = row_sum((v[0] + v[1]) + (v[2] + v[3])) * a.inv_d;
     f32x4 d = v - mean;
     if (!e_in) d = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     const float var = row_sum((d[0] * d[0] + d[1] * d[1]) + (d[2] * d[2] + d[3] * d[3])) * a.inv_d;
     d = d * __builtin_amdgcn_rsqf(var + a.ln_eps);
-    if (shift) d = d * (1.0f + sc) + sh;
+    if (m) d = d * (1.0f + m->scale) + m->shift;
     if (e_in) *(f32x4*)(u + er * ld + ec) = d;
     return v;
   };
-  // Tiles of 16 outputs, one per wave at a time; K in batches of U chunks whose loads run one batch ahead and
-  // on into the wave's next tile.  K % 16 == 0; N % 16 == 0 but in the head, whose rows past the end
-  // repeat the last.  With few tiles and a long K, several waves share a tile's K; their parts are added in
-  // order through `red`.
-  struct Share { int nt, ch, part, parts, c0, c1, t; };
-  auto share = [&](int N, int K, bool split) {
-    Share s;
-    s.nt = (N + 15) >> 4; s.ch = K >> 4; s.part = 0; s.parts = 1; s.c0 = 0; s.c1 = s.ch; s.t = wave;
-    if (split && s.nt * 2 <= kChainWaves && s.ch >= 8) {
-      s.parts = s.nt * 4 <= kChainWaves ? 4 : 2;
-      for (; s.t >= s.nt; s.t -= s.nt) ++s.part;
-      s.c0 = s.part * s.ch / s.parts;
-      s.c1 = s.part < s.parts ? (s.part + 1) * s.ch / s.parts : s.c0;
-    }
-    return s;
-  };
-  auto fetch = [&](const ChainStep& p, int t, int c, int c1, f32x4 (&r)[U]) {
-    const float* base = p.packed + (size_t)(t * (p.K >> 4) + c) * 256;     // uniform
-#pragma unroll
-    for (int x = 0; x < U; ++x)
-      if (c + x < c1) r[x] = *(const f32x4*)(base + 256 * x + 4 * lane);
-  };
-  auto ahead = [&](const ChainStep& p, bool split) {
-    Ahead f;
-    const Share s = share(p.N, p.K, split);
-    if (s.t < s.nt) fetch(p, s.t, s.c0, s.c1, f.w);
-    __builtin_amdgcn_sched_barrier(0);
-    return f;
-  };
-  auto product = [&](const ChainStep& p, bool split, Ahead& f, const float* in, auto gate_at, auto store) {
-    const Share s = share(p.N, p.K, split);
+  auto product = [&](const ChainStep& p, auto split_k, auto gated_by, Ahead& f, const float* in, auto store) {
+    constexpr bool SPLIT = decltype(split_k)::value, GATED = decltype(gated_by)::value;
+    const Share s = share(p, SPLIT);
+    const int nt = p.tiles;
+    const bool split = SPLIT && p.split;
     const float* ap = in + 4 * h;
-    for (int t = s.t; t < s.nt; t += kChainWaves) {
-      const int n = t * 16 + 4 * h;
-      f32x4 v = {0.0f, 0.0f, 0.0f, 0.0f}, bias = v;
-      if (n < p.N) bias = *(const f32x4*)(p.bias + (unsigned)n);      // the buffer is a multiple of 256 bytes
-      const f32x4 gate = gate_at(n);
-      for (int c = s.c0; c < s.c1; c += U) {
-        f32x4 nx[U];
-        if (c + U < s.c1) fetch(p, t, c + U, s.c1, nx);
-        else if (s.parts == 1 && t + kChainWaves < s.nt) fetch(p, t + kChainWaves, s.c0, s.c1, nx);
-        __builtin_amdgcn_sched_barrier(0);                // the scheduler would move the loads to their use
+    int t = s.t, c = s.c0, ft = s.t, fc = s.c0;           // being multiplied; to be fetched next
+    auto advance = [&](int& t, int& c) {
+      c += U;
+      if (c >= s.c1) { c = s.c0; t += kChainWaves; }
+    };
+    advance(ft, fc);
+    advance(ft, fc);
+    f32x4 v = {0.0f, 0.0f, 0.0f, 0.0f};
+    // one batch; its registers take the one after the next; true while there is another
+    auto batch = [&](f32x4 (&w)[U]) {
+      f32x4 r[U];
 #pragma unroll
-        for (int x = 0; x < U; ++x)
-          if (c + x < s.c1) {
-            const f32x4 r = *(const f32x4*)(ap + 16 * (c + x));
+      for (int x = 0; x < U; ++x) r[x] = *(const f32x4*)(ap + 16 * (c + x));
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v = __builtin_amdgcn_mfma_f32_16x16x4f32(f.w[x][e], r[e], v, 0, 0, 0);
-          }
+      for (int x = 0; x < U; ++x)
+        if (x == 0 || c + x < s.c1)                       // past the end of K: other rows and weights
 #pragma unroll
-        for (int x = 0; x < U; ++x) f.w[x] = nx[x];
+          for (int e = 0; e < 4; ++e) v = mac(w[x][e], r[x][e], v);
+      if (ft < nt) {
+        fetch(p, ft, fc, w);
+        advance(ft, fc);
       }
-      if (s.parts > 1) {
-        if (s.part > 0 && s.part < s.parts) red[((s.part - 1) * s.nt + t) * 64 + lane] = v;
-        lds_barrier();                                    // once, and by every wave: t < nt
-        if (s.part > 0) break;
-        for (int q = 1; q < s.parts; ++q) v += red[((q - 1) * s.nt + t) * 64 + lane];
+      c += U;
+      if (c < s.c1) return true;
+      if (split) return false;
+      store(t * 16 + 4 * h, v + f.bias[0], f.gate[0]);
+      t += kChainWaves;
+      if (t >= nt) return false;
+      v = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+      c = s.c0;
+      f.bias[0] = f.bias[1];
+      if (GATED) f.gate[0] = f.gate[1];
+      if (t + kChainWaves < nt) fetch_columns(p, t + kChainWaves, GATED, f.bias[1], f.gate[1]);
+      return true;
+    };
+    if (t < nt && c < s.c1) {
+      // the first two outside the loop: inside, a wait would have to hold for a fetch just made as well
+      if (batch(f.w[0]) && batch(f.w[1])) {
+        while (batch(f.w[0]) && batch(f.w[1])) {}
+        drain();
       }
-      store(n, v + bias, gate);
+    }
+    if (split) {
+      const int parts = 1 << p.split;
+      if (s.part > 0 && s.part < parts) red[((s.part - 1) * nt + s.t) * 64 + lane] = v;
+      lds_barrier();
+      if (s.part == 0) {
+        for (int q = 1; q < parts; ++q) v += red[((q - 1) * nt + s.t) * 64 + lane];
+        store(s.t * 16 + 4 * h, v + f.bias[0], f.gate[0]);
+      }
     }
   };
-  auto no_gate = [](int) { return f32x4{1.0f, 1.0f, 1.0f, 1.0f}; };
-  auto add = [&](int n, f32x4 v, f32x4 gate) { *(f32x4*)(xt + i * ld + n) += gate * v; };   // the residual; only this lane touches it
+  auto add = [&](int n, f32x4 v, f32x4) { *(f32x4*)(xt + i * ld + n) += v; };              // the residual; only this lane touches it
+  auto add_gated = [&](int n, f32x4 v, f32x4 gate) { *(f32x4*)(xt + i * ld + n) += gate * v; };
 
-  // Attention of the queries in o into u.  A unit is a head of one of the sequences (len rows each) these rows
-  // are in or, where those are shorter than a key tile and lie one after the other, a head of all of them:
-  // repeated by sequence should a value of one not be finite, which zero weights do not keep from the others.
-  auto attention = [&](const float* k, const float* v, int len, const FastDiv& by_len, int nk, bool cross) {
-    const int seq0 = by_len.div(idx0), nseq = (int)by_len.div(last) - seq0 + 1;
-    const int my_seq = nseq > 1 ? (int)by_len.div(my) - seq0 : 0;
-    bool together = !cross && nseq > 1 && len < kChainRows;
+  // Attention of the queries in o into u, and a barrier.  first: keys and values of this wave's first unit.  Units of several
+  // sequences are repeated by sequence should a value of one not be finite, which zero weights do not keep from the others.
+  auto attention = [&](const float* k, const float* v, int len, const FastDiv& by_len, int nk, bool cross, KeyTile<HDT>& first) {
+    const Sequences q = sequences(len, by_len, cross);
+    const unsigned stride = cross ? hd : D;
+    bool together = q.together;
+    auto one = [&](int un, KeyTile<HDT>& t) {
+      const Unit w = unit(un, q, len, nk, cross, together);
+      const bool mine = together || q.mine == w.sq;       // a lane of another sequence computes and drops
+      const int lo = together ? q.mine * len : 0;
+      return attend<HDT>(o + i * ld + w.head * hd, w.nk, lo, lo + nk, hd, k + w.base, v + w.base, stride, t,
+                         [&](int d, f32x4 r) { if (mine) *(f32x4*)(u + i * ld + w.head * hd + d) = r; });
+    };
+    int un = wave, units = a.heads * (together ? 1 : q.n);
+    bool bad = false;
+    if (un < units) bad = one(un, first);
+    un += kChainWaves;
     for (;;) {
-      bool bad = false;
-      const int units = a.heads * (together ? 1 : nseq);
-      for (int un = wave; un < units; un += kChainWaves) {
-        const int sq = un < a.heads ? 0 : (int)a.by_heads.div(un), head = un - sq * a.heads, seq = seq0 + sq;
-        size_t base;
-        if (!cross) {
-          base = (size_t)(seq * len) * D + head * hd;
-        } else {
-          const int kb = a.kv_shared_tail && seq >= a.kv_split ? a.kv_split : seq;
-          base = ((size_t)kb * a.heads + head) * nk * hd;
+      if (un < units) {
+        for (; un < units; un += kChainWaves) {
+          const Unit w = unit(un, q, len, nk, cross, together);
+          KeyTile<HDT> t;
+          fetch_keys<HDT>(t, k + w.base, v + w.base, true, 0, w.nk, hd, stride);
+          bad |= one(un, t);
         }
-        const bool mine = together || my_seq == sq;       // a lane of another sequence computes and drops
-        const int lo = together ? my_seq * len : 0;
-        bad |= attend<HDT>(o + i * ld + head * hd, together ? nseq * len : nk, lo, lo + nk, hd, k + base, v + base, cross ? hd : D,
-                           [&](int d, f32x4 r) { if (mine) *(f32x4*)(u + i * ld + head * hd + d) = r; });
+        drain();
       }
-      if (!together) break;
+      if (together && bad) *again = 1;
+      lds_barrier();
+      if (!together || !__builtin_amdgcn_readfirstlane(*again)) break;
       together = false;
-      if (!__syncthreads_or(bad)) break;
+      un = wave;
+      units = a.heads * q.n;
     }
   };
+
+  // ---- the rows, and what the first stages need
+  constexpr bool EARLY = HDT <= 2;                        // registers permitting; else right before the stage
+  const ChainStep& proj = a.step[CHAIN_PROJ];
+  const ChainStep& next = a.step[CHAIN_NEXT];
+  Ahead f_proj, f_xq, f_xproj, f_fc1, f_fc2, f_next;
+  Modulation m_fc1, m_next;
+  KeyTile<HDT> keys, xkeys;
+  auto start_next = [&] {
+    start(next, false, false, f_next);
+    start_norm(next, a.eps ? 0 : e_alt, m_next);
+  };
+  if constexpr (!(KIND & CHAIN_EMBED)) {
+    const f32x4 x4 = load4(buffer(a.x, kAll), e_in ? 4u * (unsigned)(e_row * D + ec) : kNowhere);
+    const f32x4 q4 = load4(buffer(a.q, kAll), e_in ? 4u * (unsigned)(e_idx * D + ec) : kNowhere);
+    if constexpr (EARLY) {
+      start_keys(a.k, a.v, a.seq_len, a.by_len, a.seq_len, false, keys);
+      start(proj, false, true, f_proj);
+      if constexpr (KIND & CHAIN_CROSS) start(a.step[CHAIN_XQ], false, false, f_xq);
+      else if constexpr (KIND & CHAIN_MLP) { start(a.step[CHAIN_FC1], false, false, f_fc1); start_norm(a.step[CHAIN_FC1], e_alt, m_fc1); }
+      else start_next();
+    }
+    issued();
+    if (e_in) {
+      *(f32x4*)(xt + er * ld + ec) = x4;
+      *(f32x4*)(o + er * ld + ec) = q4;
+    }
+  } else {
+    start_next();
+    issued();
+    if (e_in) {
+      f32x4 x4;
+      if (e_pos < a.text_rows) {
+        const int tb = a.kv_shared_tail && e_b >= a.kv_split ? a.kv_split : e_b;
+        x4 = *(const f32x4*)(a.y + ((size_t)tb * a.text_rows + e_pos) * D + ec);
+      } else {
+        const int run = a.p * a.C, n = e_pos - a.text_rows, t = a.by_S.div(n), s = n - t * a.S;
+        const int ph = a.by_gw.div(s), pw = s - ph * a.by_gw.d;
+        const float* src = a.latent + ((((size_t)(e_b < a.R ? e_b : e_b - a.R) * a.T + t) * a.H + (size_t)ph * a.p) * a.W + (size_t)pw * a.p) * a.C;
+        const f32x4 pos = *(const f32x4*)(a.pos_sp + (size_t)s * D + ec) + *(const f32x4*)(a.pos_t + (size_t)t * D + ec);
+        x4 = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        for (int dh = 0; dh < a.p; ++dh)
+#pragma unroll 8
+          for (int f = 0; f < run; ++f)
+            x4 += src[(size_t)dh * a.W * a.C + f] * *(const f32x4*)(a.p_w + (size_t)(dh * run + f) * D + ec);
+        x4 = (x4 + *(const f32x4*)(a.p_b + ec)) + pos;
+      }
+      *(f32x4*)(xt + er * ld + ec) = x4;
+    }
+  }
 
   if constexpr (KIND & CHAIN_SELF) {
-    const ChainStep& p = a.step[CHAIN_PROJ];
-    Ahead f = ahead(p, false);
+    if constexpr (!EARLY) {
+      start_keys(a.k, a.v, a.seq_len, a.by_len, a.seq_len, false, keys);
+      start_first(proj, false, f_proj);
+      issued();
+    }
     lds_barrier();
-    attention(a.k, a.v, a.seq_len, a.by_len, a.seq_len, false);
-    lds_barrier();
-    product(p, false, f, u + i * ld, [&](int n) { return *(const f32x4*)(p.gate + (unsigned)(my_alt + n)); }, add);
+    attention(a.k, a.v, a.seq_len, a.by_len, a.seq_len, false, keys);
+    if constexpr (!EARLY) start_rest(proj, false, true, f_proj);
+    if constexpr (EARLY && (KIND & CHAIN_CROSS)) {
+      start_keys(a.xk, a.xv, a.Ns, a.by_Ns, a.L, true, xkeys);
+      start(a.step[CHAIN_XPROJ], false, false, f_xproj);
+    } else if constexpr (EARLY && (KIND & CHAIN_MLP)) {
+      start(a.step[CHAIN_FC2], true, true, f_fc2);
+    }
+    issued();
+    product(proj, No{}, Yes{}, f_proj, u + i * ld, add_gated);
   }
   if constexpr (KIND & CHAIN_CROSS) {
-    const ChainStep& pq = a.step[CHAIN_XQ];
-    Ahead f = ahead(pq, false);
+    const ChainStep& p = a.step[CHAIN_XQ];
+    if constexpr (EARLY) {
+      start(a.step[CHAIN_FC1], false, false, f_fc1);
+      start_norm(a.step[CHAIN_FC1], e_alt, m_fc1);
+    } else {
+      start(p, false, false, f_xq);
+    }
+    issued();
     lds_barrier();
-    layer_norm(nullptr, nullptr, 0);
+    layer_norm(nullptr);
     lds_barrier();
-    product(pq, false, f, u + i * ld, no_gate, [&](int n, f32x4 v, f32x4) { *(f32x4*)(o + i * ld + n) = v * a.qscale; });
-    const ChainStep& p = a.step[CHAIN_XPROJ];
-    f = ahead(p, false);
+    product(p, No{}, No{}, f_xq, u + i * ld, [&](int n, f32x4 v, f32x4) { *(f32x4*)(o + i * ld + n) = v * a.qscale; });
+    if constexpr (EARLY) {
+      start(a.step[CHAIN_FC2], true, true, f_fc2);
+    } else {
+      start_keys(a.xk, a.xv, a.Ns, a.by_Ns, a.L, true, xkeys);
+      start_first(a.step[CHAIN_XPROJ], false, f_xproj);
+    }
+    issued();
     lds_barrier();
-    attention(a.xk, a.xv, a.Ns, a.by_Ns, a.L, true);
-    lds_barrier();
-    product(p, false, f, u + i * ld, no_gate, add);
+    attention(a.xk, a.xv, a.Ns, a.by_Ns, a.L, true, xkeys);
+    if constexpr (!EARLY) start_rest(a.step[CHAIN_XPROJ], false, false, f_xproj);
+    issued();
+    product(a.step[CHAIN_XPROJ], No{}, No{}, f_xproj, u + i * ld, add);
   }
   if constexpr (KIND & CHAIN_MLP) {
-    const ChainStep& p1 = a.step[CHAIN_FC1];
-    Ahead f = ahead(p1, false);
+    const ChainStep& p = a.step[CHAIN_FC1];
+    if constexpr (EARLY) {
+      start_next();
+    } else {
+      start(p, false, false, f_fc1);
+      start_norm(p, e_alt, m_fc1);
+    }
+    issued();
     lds_barrier();
-    layer_norm(p1.shift, p1.scale, e_alt);
+    layer_norm(&m_fc1);
     lds_barrier();
-    product(p1, false, f, u + i * ld, no_gate, [&](int n, f32x4 v, f32x4) {
+    product(p, No{}, No{}, f_fc1, u + i * ld, [&](int n, f32x4 v, f32x4) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[e] = gelu_tanh_f(v[e]);
       *(f32x4*)(hid + i * ldm + n) = v;
     });
-    const ChainStep& p2 = a.step[CHAIN_FC2];
-    f = ahead(p2, true);
+    if constexpr (!EARLY) start(a.step[CHAIN_FC2], true, true, f_fc2);
+    issued();
     lds_barrier();
-    product(p2, true, f, hid + i * ldm, [&](int n) { return *(const f32x4*)(p2.gate + (unsigned)(my_alt + n)); }, add);
+    product(a.step[CHAIN_FC2], Yes{}, Yes{}, f_fc2, hid + i * ldm, add_gated);
   }
   // ---- the next self-attention's queries, keys and values, or the output head
-  const ChainStep& p = a.step[CHAIN_NEXT];
+  if constexpr (!EARLY && !(KIND & CHAIN_EMBED)) start_next();
+  issued();
+  lds_barrier();
+  const f32x4 x4 = layer_norm(&m_next);
   if (!a.eps) {
-    Ahead f = ahead(p, false);
-    lds_barrier();
-    const f32x4 x4 = layer_norm(p.shift, p.scale, e_alt);
     if (e_in && idx0 + er <= last) *(f32x4*)(a.x_out + (unsigned)(e_row * D + ec)) = x4;
     lds_barrier();
     int out_row = my_row;                                 // in the next attention's order
-    if (a.next_temporal) {
+    if constexpr (KIND == CHAIN_SELF) {
       const int b = a.by_N.div(my_row), r = my_row - b * a.N, t = a.by_S.div(r), s = r - t * a.S;
       out_row = b * a.N + s * a.T + t;
     }
     const bool mine = idx0 + i <= last;
-    product(p, false, f, u + i * ld, no_gate, [&](int n, f32x4 v, f32x4) {
+    product(next, No{}, No{}, f_next, u + i * ld, [&](int n, f32x4 v, f32x4) {
       const int which = n >= 2 * D ? 2 : n >= D ? 1 : 0, c = n - which * D;     // D % 16 == 0: uniform but for c
       float* dst = which == 0 ? a.q_out : which == 1 ? a.k_out : a.v_out;
       if (which == 0) v *= a.qscale;
       if (mine) *(f32x4*)(dst + (unsigned)(out_row * D + c)) = v;
     });
   } else {
-    lds_barrier();
-    layer_norm(p.shift, p.scale, 0);
+    const ChainStep& p = next;
     lds_barrier();
     const int b = a.by_Ns.div(my_row), n0 = my_row - b * a.Ns - a.text_rows;
     const bool mine = idx0 + i <= last && n0 >= 0;        // text rows have no head
@@ -424,7 +623,7 @@ __global__ __launch_bounds__(kThreads) void k_chain(ChainArgs a) {
       for (int c = 0; c < D; c += 16) {
         const f32x4 w = *(const f32x4*)(wp + c), r = *(const f32x4*)(u + i * ld + 4 * h + c);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v = __builtin_amdgcn_mfma_f32_16x16x4f32(w[e], r[e], v, 0, 0, 0);
+        for (int e = 0; e < 4; ++e) v = mac(w[e], r[e], v);
       }
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
@@ -436,6 +635,7 @@ __global__ __launch_bounds__(kThreads) void k_chain(ChainArgs a) {
       }
     }
   }
+#endif
 }
 
 __global__ __launch_bounds__(256) void k_pack_chain(const float* __restrict__ w, float* __restrict__ packed, int N, int K) {
@@ -446,6 +646,7 @@ __global__ __launch_bounds__(256) void k_pack_chain(const float* __restrict__ w,
 
 template <int HDT, int KIND>
 hipError_t run_chain(const ChainArgs& a, hipStream_t s) {
+  static_assert(kThreads == 512, "eight waves");
   const size_t smem = (size_t)kChainRows * (3 * lds_row(a.D) + (KIND & CHAIN_MLP ? lds_row(a.mlp) : 0)) * 4 + (kChainWaves - 1) * 1024;
   k_chain<HDT, KIND><<<ceil_div(a.rows, kChainRows), kThreads, smem, s>>>(a);
   return hipGetLastError();
@@ -498,6 +699,15 @@ hipError_t launch_chain(const ChainArgs& args, hipStream_t s) {
   a.inv_d = 1.0f / (float)a.D;
   a.by_N = FastDiv(a.N); a.by_Ns = FastDiv(a.Ns); a.by_T = FastDiv(a.T); a.by_S = FastDiv(a.S);
   a.by_heads = FastDiv(a.heads); a.by_len = FastDiv(a.seq_len > 0 ? a.seq_len : 1);
+  for (ChainStep& p : a.step) {
+    if (!p.w) continue;
+    p.tiles = ceil_div(p.N, 16); p.chunks = p.K / 16;
+    p.split = 2 * p.tiles <= kChainWaves && p.chunks >= 8 ? 4 * p.tiles <= kChainWaves ? 2 : 1 : 0;
+    p.split_mul = 256 / p.tiles + 1;                      // wave * mul >> 8 = wave / tiles: 8 waves, up to 4 tiles
+    p.w_bytes = p.packed ? (unsigned)p.N * p.K * 4 : 0;   // (nothing is loaded for the head, which reads w)
+    p.bias_bytes = p.N * 4;
+    p.vec_bytes = (a.alt_rows ? 7 : 1) * a.D * 4;         // gate, shift, scale; a text row's are 6 D on
+  }
   a.by_run = FastDiv(a.p * a.C); a.by_gw = FastDiv(a.W / a.p);
   if (a.latent) return run_chain<1, CHAIN_EMBED>(a, s);
   switch ((a.hd + 15) / 16) {

@@ -328,9 +328,12 @@ enum ChainStage : int { CHAIN_PROJ, CHAIN_XQ, CHAIN_XPROJ, CHAIN_FC1, CHAIN_FC2,
 struct ChainStep {
   const float *w, *bias;                   // [N, K], [N]
   const float* packed;                     // w in fragment order (launch_pack_chain); NULL: the output head, which reads w
+  const float* gate;                       // PROJ, FC2: on what is added to the rows
+  const float *shift, *scale;              // FC1, NEXT: of the LayerNorm in front
   int N, K;
-  const float* gate;                       // PROJ, XPROJ, FC2: on what is added to the rows (NULL: 1)
-  const float *shift, *scale;              // XQ, FC1, NEXT: of the LayerNorm in front (NULL: none)
+  // filled by launch_chain: tiles of 16 outputs and chunks of 16 of K, log2 of the waves that share a tile's K, bytes of the arrays
+  int tiles, chunks, split, split_mul;
+  unsigned w_bytes, bias_bytes, vec_bytes;
 };
 struct ChainArgs {
   int rows, D, heads, hd, mlp;             // rows: all batch rows' tokens (B * Ns)
@@ -338,8 +341,6 @@ struct ChainArgs {
   int text_rows, alt_rows;                 // leading text tokens of a batch row; those with their own modulation set
   int kv_split, kv_shared_tail;            // text of batch row b: b, or kv_split from there on
   float ln_eps, qscale;
-  int temporal;                            // rows are taken in (b, s, t) order
-  int next_temporal;                       // the next q, k, v are stored in that order
   FastDiv by_N, by_Ns, by_T, by_S, by_heads, by_len, by_run, by_gw;   // these and inv_d: filled by launch_chain
   float inv_d;
   // the rows: patch embedding of the latent and text rows (latent != NULL), else x

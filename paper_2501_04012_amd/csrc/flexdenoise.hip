@@ -527,14 +527,13 @@ int run_chains(const Ctx& c, const float* latent) {
   float* const sets[2][3] = {{(float*)w.q, (float*)w.k, (float*)w.v}, {(float*)w.u, (float*)w.p[0], (float*)w.p[1]}};
   int cur = 0;
   auto step = [](const Linear& L, const float* gate, const float* shift, const float* scale) {
-    return ChainStep{(const float*)L.wt, L.b, (const float*)L.parts, L.out, L.in, gate, shift, scale};
+    return ChainStep{(const float*)L.wt, L.b, (const float*)L.parts, gate, shift, scale, L.out, L.in};
   };
   auto next_qkv = [&](ChainArgs& a, int l, int br) {
     const float* mv = w.mod + ((size_t)l * m->nmod + (size_t)br * 3) * D;
     a.step[CHAIN_NEXT] = step(m->blocks[l].qkv[br], nullptr, mv, mv + D);
     a.q_out = sets[cur][0]; a.k_out = sets[cur][1]; a.v_out = sets[cur][2];
     a.x_out = w.x;
-    a.next_temporal = br;
   };
   auto head = [&](ChainArgs& a) {
     a.step[CHAIN_NEXT] = step(m->fout, nullptr, w.fmod, w.fmod + D);
@@ -553,7 +552,6 @@ int run_chains(const Ctx& c, const float* latent) {
     for (int br = 0; br < (fact ? 2 : 1); ++br) {
       ChainArgs a = chain_base(c);
       a.x = w.x;
-      a.temporal = br;
       a.seq_len = !fact ? m->Ns : br == 0 ? m->S : cf.frames;
       a.q = sets[cur][0]; a.k = sets[cur][1]; a.v = sets[cur][2];
       a.step[CHAIN_PROJ] = step(b.proj[br], mod + ((size_t)br * 3 + 2) * D, nullptr, nullptr);
