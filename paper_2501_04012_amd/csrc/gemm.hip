@@ -894,6 +894,196 @@ hipError_t launch_pack_weights(const void* W, void* out, int N, int K, hipStream
   return hipGetLastError();
 }
 
+// ---------------------------------------------------------------- the product kernel, tiles of 128 x 288
+// For widths that are whole multiples of 288 (models of 576 and 1152 columns) where such tiles fill the chip and those above do not: 8192 x 1152
+// is 192 tiles of 256x192 but 256 of 128x288.  One tile to a workgroup, one workgroup to a CU.  A wave owns 64 rows by 144 columns, the
+// shape that keeps LDS reads under the matrix instructions (13 fragments per 36 v_mfma_f32_16x16x32_bf16; 16 wide, as 144 is no
+// multiple of 32).  The tile is only four such waves, so the eight waves of a workgroup are two groups that each take one half of every
+// K tile and add their sums through LDS at the end (in a fixed order; the K loop's stages are free by then).  LDS layout, DMA and swizzle are
+// those of k_gemm_dlds, as is the barrier ahead of a stage's last products, behind which the next stage's first fragments are read and
+// its buffer requested again.  Three stages: with two, one round of tiles is level where operands come from the L2, four are slower
+// (32768 x 1152 x 4608: 353 us against 314).
+// Bound by the operand stream (53 KB per K tile in 0.9 us and CU) and, where K is small, by what is not the K loop (10 us: first tile, sums,
+// epilogue).  us, best form before and this one, operands by turns from four to six products: 8192 x 1152 x 4608 105, 80;
+// 15742 x 576 x 2304 59, 46; the same product again and again: 94, 74 and 53, 42.
+// The same kernel with 128x144 tiles (four groups, 128 of K a stage, two stages) was faster over operands from the L2 (4096 x 1152 x 4608
+// 58 -> 47 us), but not in a model, where they come from further off (62 us and 60).
+struct Tile288 {
+  static constexpr int BM = 128, BN = 288, kStages = 3, kStage = (BM + BN) * 128;
+  static constexpr int kSlice = 2 * 9 * 1024;              // half a wave's sums
+  static constexpr int kBytes = kStages * kStage + 2 * BN * 4;        // and bias and gate of the tile's columns
+};
+template <typename Epi>
+__global__ __launch_bounds__(512, 2) void k_gemm_288(const bf16_t* __restrict__ A, const bf16_t* __restrict__ Wt, int M, int N, int K,
+                                                     int tiles_m, int tiles_n, Epi epi) {
+#if defined(__HIP_DEVICE_COMPILE__)   // buffer resources are a device-side type: the host pass sees an empty body
+  using L = Tile288;
+  constexpr int BM = L::BM, BN = L::BN, S = L::kStages, TM = 4, TN = 9;
+  static_assert(Epi::kRowRuns, "stores of 16-byte runs");
+  static_assert(S * L::kStage >= 8 * L::kSlice, "the sums fit the stages");
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+  float* const sbias = (float*)(smem + S * L::kStage);
+  float* const sgate = sbias + BN;
+
+  const int total = tiles_m * tiles_n, local = (int)blockIdx.x >> 3, t = ((local >> 5) * 8 + ((int)blockIdx.x & 7)) * 32 + (local & 31);
+  if (t >= total) return;                                  // k_gemm_dlds's tile order
+  const int per_group = 8 * tiles_n, group = t / per_group, first_m = group * 8, gsz = min(tiles_m - first_m, 8);
+  const int bm0 = (first_m + (t % per_group) % gsz) * BM, bn0 = ((t % per_group) / gsz) * BN;
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int li = lane & 15, lh = lane >> 4;
+  const int kg = wave >> 2, wm = wave & 1, wn = (wave >> 1) & 1;
+  if (tid < BN) {
+    sbias[tid] = epi.P.bias ? epi.P.bias[bn0 + tid] : 0.0f;
+    if constexpr (Epi::kHasGate) sgate[tid] = epi.P.gate ? epi.P.gate[bn0 + tid] : 1.0f;
+  }
+
+  // ---- operand tiles: 8 rows of 128 bytes a wave-load, swizzled as in k_gemm_dlds
+  const int row0 = wave * 8 + (lane >> 4) * 2 + ((lane & 15) >> 3), kc = (lane & 7) ^ ((wave * 4 + (lane >> 4)) & 7);
+  const unsigned v0 = (unsigned)row0 * (unsigned)K * 2u + (unsigned)kc * 16u, rows64 = 64u * (unsigned)K * 2u;
+  const auto ra = __builtin_amdgcn_make_buffer_rsrc((void*)(A + (size_t)bm0 * K), 0, (int)((unsigned)(M - bm0) * (unsigned)K * 2u), 0x00020000);
+  const auto rb = __builtin_amdgcn_make_buffer_rsrc((void*)(Wt + (size_t)bn0 * K), 0, (int)((unsigned)BN * (unsigned)K * 2u), 0x00020000);
+  auto request = [&](int st, int stage) {
+    unsigned char* const dst = smem + stage + wave * 1024;
+#pragma unroll
+    for (int j = 0; j < BM / 64; ++j)                      // rows past the end of A load as zero
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_void*)(dst + j * 8192), 16, (int)(v0 + j * rows64), st * 128, 0, 0);
+#pragma unroll
+    for (int j = 0; j < BN / 64; ++j)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lds_void*)(dst + BM * 128 + j * 8192), 16, (int)(v0 + j * rows64), st * 128, 0, 0);
+  };
+  auto request_rest = [&](int st, int stage) {             // the last 32 rows of the weights, by half the waves
+    if (wave < BN % 64 / 8)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lds_void*)(smem + stage + wave * 1024 + BM * 128 + BN / 64 * 8192), 16,
+                                               (int)(v0 + BN / 64 * rows64), st * 128, 0, 0);
+  };
+  // ---- fragments.  The second group's accumulators hold row tiles 2, 3, 0, 1: the first two are the ones that a wave finishes.
+  const int fo = (li >> 1) * 256 + ((li & 1) * 8 + ((4 * kg + lh) ^ (li >> 1))) * 16;
+  int oa[TM];
+#pragma unroll
+  for (int i = 0; i < TM; ++i) oa[i] = fo + wm * 8192 + (i ^ (2 * kg)) * 2048;
+  const int ob = fo + BM * 128 + wn * (144 * 128);
+
+  f32x4 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  bf16x8 fa[2][TM], fb[TN];
+  auto load_a = [&](int set, int stage, int i) { fa[set][i] = *(const bf16x8*)(smem + stage + oa[i]); };
+  auto load_b = [&](int stage, int j) { fb[j] = *(const bf16x8*)(smem + stage + ob + j * 2048); };
+  auto multiply = [&](int set, int j) {                    // weights as the A operand: a lane ends up with consecutive columns
+#pragma unroll
+    for (int i = 0; i < TM; ++i) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j], fa[set][i], acc[i][j], 0, 0, 0);
+  };
+
+  // Stages are numbered by K; stage st lies at offset st % S of LDS.  Past the end the last one is requested again (never read).
+  const int nst = K / 64;
+  constexpr int kDsRead = 0x100, kMfma = 0x008, kVmem = 0x010, AHEAD = 3, LOADS = BM / 64 + BN / 64;
+  // All but the last `stages` stages requested; this wave's LDS reads too.  (A wave that requests the rest of the weights waits for those
+  // of a younger stage as well.)
+  auto landed = [&](auto stages) {
+    wait_vm_lgkm0<decltype(stages)::value * LOADS>();
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+  };
+#pragma unroll
+  for (int st = 0; st < S; ++st) {
+    if (st == S - 1) landed(std::integral_constant<int, 0>{});
+    request_rest(min(st, nst - 1), st * L::kStage);
+    request(min(st, nst - 1), st * L::kStage);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+#pragma unroll
+  for (int i = 0; i < TM; ++i) load_a(0, 0, i);
+#pragma unroll
+  for (int j = 0; j < AHEAD; ++j) load_b(0, j);
+  __builtin_amdgcn_sched_barrier(0);
+  int at = 0;                                              // offset of the stage being multiplied
+  auto step = [&](auto par, int st) {
+    constexpr int PAR = decltype(par)::value;
+    const int after = at == (S - 1) * L::kStage ? 0 : at + L::kStage;
+#pragma unroll
+    for (int j = 0; j + AHEAD < TN; ++j) {
+      load_b(at, j + AHEAD);
+      multiply(PAR, j);
+    }
+#pragma unroll
+    for (int j = 0; j + AHEAD < TN; ++j) {
+      __builtin_amdgcn_sched_group_barrier(kMfma, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(kDsRead, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(kMfma, TM - 1, 0);
+    }
+    landed(std::integral_constant<int, S - 2>{});          // stage st + 1 has, and every wave is done reading st
+    request_rest(min(st + S, nst - 1), at);
+    __builtin_amdgcn_sched_barrier(0);
+    request(min(st + S, nst - 1), at);
+#pragma unroll
+    for (int i = 0; i < TM; ++i) load_a(PAR ^ 1, after, i);
+#pragma unroll
+    for (int j = 0; j < AHEAD; ++j) load_b(after, j);
+#pragma unroll
+    for (int j = TN - AHEAD; j < TN; ++j) multiply(PAR, j);
+#pragma unroll
+    for (int r = 0; r < AHEAD * TM; ++r) {
+      __builtin_amdgcn_sched_group_barrier(kMfma, 1, 0);
+      if (r < TM + AHEAD) __builtin_amdgcn_sched_group_barrier(kDsRead, 1, 0);
+      if (r < LOADS) __builtin_amdgcn_sched_group_barrier(kVmem, 1, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    at = after;
+  };
+  using P0 = std::integral_constant<int, 0>; using P1 = std::integral_constant<int, 1>;
+  int st = 0;
+  for (; st + 1 < nst; st += 2) {
+    step(P0{}, st);
+    step(P1{}, st + 1);
+  }
+  if (st < nst) step(P0{}, st);
+
+  // ---- the groups' sums: a wave and its partner in the other group exchange halves through LDS, no longer read as stages
+  wait_vm_lgkm0<0>();
+  __builtin_amdgcn_s_barrier();
+  unsigned char* const cst = smem + (wave ^ 4) * L::kSlice;           // the partner's slice, which this wave alone reads, and then reuses
+  f32x4* const mine = (f32x4*)(smem + wave * L::kSlice) + lane;
+  const f32x4* const theirs = (const f32x4*)cst + lane;
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) mine[(i * TN + j) * 64] = acc[2 + i][j];
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      const f32x4 o = theirs[(i * TN + j) * 64];
+      acc[i][j] = kg ? o + acc[i][j] : acc[i][j] + o;
+    }
+
+  // ---- epilogue: 32 rows of 144 columns through the slice, out in runs of 16 bytes
+  constexpr int ROWB = 304;                                // bytes of a staged row, 16 of them padding
+  const int nw = wn * 144, m0 = bm0 + wm * 64 + kg * 32;
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      const int c = 16 * j + 4 * lh;
+      float v[4] = {acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]};
+      epi.apply4(bn0 + nw + c, v, sbias + nw + c, sgate + nw + c);
+      bf16x4 o;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[e] = (bf16_t)v[e];
+      *(bf16x4*)(cst + (i * 16 + li) * ROWB + c * 2) = o;
+    }
+#pragma unroll
+  for (int it = 0; it < 32 * 18 / 64; ++it) {
+    const int idx = it * 64 + lane, row = idx / 18, chunk = idx - row * 18;
+    const bf16x8 o = *(const bf16x8*)(cst + row * ROWB + chunk * 16);
+    if (m0 + row < M) __builtin_nontemporal_store(o, (bf16x8*)epi.run8(m0 + row, bn0 + nw + chunk * 8));
+  }
+#endif
+}
+
 // ---------------------------------------------------------------- split-K fix-up
 // One workgroup per tile of the split round: adds the tile's `splits` partial accumulators in
 // range order (bitwise repeatable) and runs the product kernel's epilogue on the sum.
@@ -1641,6 +1831,23 @@ static hipError_t run_packed(const void* A, const void* Wp, int M, int N, int K,
   return hipGetLastError();
 }
 
+template <int MODE>
+static hipError_t run_288(const void* A, const void* Wt, int M, int N, int K, const EpiParams& ep, hipStream_t s) {
+  using Epi = Epilogue<bf16_t, MODE>;
+  using L = Tile288;
+  Epi epi = Epi::make(ep, M, N);
+  auto kern = k_gemm_288<Epi>;
+  static bool attr_set = false;
+  if (!attr_set) {
+    const hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, L::kBytes);
+    if (e != hipSuccess) return e;
+    attr_set = true;
+  }
+  const int tiles_m = ceil_div(M, L::BM), tiles_n = N / L::BN;
+  kern<<<round_up((size_t)tiles_m * tiles_n, 256), 512, L::kBytes, s>>>((const bf16_t*)A, (const bf16_t*)Wt, M, N, K, tiles_m, tiles_n, epi);
+  return hipGetLastError();
+}
+
 template <typename T, int MODE>
 static hipError_t run_plain(const void* A, const void* Wt, int M, int N, int K, const EpiParams& ep, hipStream_t s) {
   using Epi = Epilogue<T, MODE>;
@@ -1711,42 +1918,66 @@ static Bf16Tile bf16_tile(bool unpatch, int M, int N, int K) {
   return T128;
 }
 
-// Packed weights: where their kernel's estimate is below that of the tile just chosen.  The estimates, in us, are fits over
-// 325 products (M 256 to 38 000, N and K 576 to 12 288, each timed in every form): tiles of the fullest CU times a
-// time per K tile and one per tile.  314 products: 0.917 of the time in the mean, none more than 2 % slower.  A lone 128x256
-// tile on a CU (two waves a SIMD short) is up to 1.13 times slower than estimated and not taken; products whose 128x128 tiles are
-// all split along K stay with them (up to 1.58).
-// Columns of their tile, or 0.
-static int packed_columns(Bf16Tile tile, int M, int N, int K, const void* scratch, size_t scratch_bytes) {
-  if (!packs_weights(N, K) || (unsigned long long)M * K * 2 >= (1ull << 32)) return 0;
+// The form of a model's product: the tile just chosen, or one whose estimated time is below that tile's.  The estimates, in us: tiles
+// of the fullest CU times a time per K tile and one per tile, fitted over 325 products (M 256 to 38 000, N and K 576 to 12 288, each timed in
+// every form); for the tiles of 288 columns also the tiles per CU of the whole chip (the power limit), over 400 products.
+//   Packed weights (`packed`: there are some): 314 products, 0.917 of the time in the mean, none more than 2 % slower.  A lone 128x256
+//   tile on a CU (two waves a SIMD short) is up to 1.13 times slower than estimated and not taken; products whose 128x128 tiles are
+//   all split along K stay with them (up to 1.58).
+//   128x288, 384x192: where the estimate is 6 % (384x192: 9 %) lower, so much being what the estimates are worth.  Their tiles fill
+//   rounds that the others leave half empty: of 680 products 29 take one of them, 0.88 of the time in the mean, none slower (without
+//   the margin 0.85 to 1.13).  128x288 adds its sums in two parts: only from the K on at which a last round may be split along K
+//   too.  Below it a row's result does not depend on how many rows there are, bit for bit.
+enum Bf16Form { F128, F192, F256, F384, P128, P256, W288 };
+static Bf16Form bf16_form(int M, int N, int K, bool packed, const void* scratch, size_t scratch_bytes) {
+  const Bf16Tile tile = bf16_tile(false, M, N, K);
   const double kt = K / 64.0;
-  auto per_cu = [&](int bm, int bn) { return (double)(((long long)ceil_div(M, bm) * ceil_div(N, bn) + 255) / 256); };
+  auto tiles = [&](int bm, int bn) { return (long long)ceil_div(M, bm) * ceil_div(N, bn); };
+  auto per_cu = [&](int bm, int bn) { return (double)((tiles(bm, bn) + 255) / 256); };
   auto rounds = [&](int bm, int bn, int sp, double start, double k, double fixed) {
     if (sp < 2) return start + per_cu(bm, bn) * (k * kt + fixed);
-    const double full = (double)((long long)ceil_div(M, bm) * ceil_div(N, bn) / 256);
+    const double full = (double)(tiles(bm, bn) / 256);
     return start + full * (k * kt + fixed) + (k * kt / sp + fixed) + 14.0;
   };
   auto lone = [&](double k, double fixed) { return per_cu(128, 128) == 1.0 ? k * kt + fixed : 0.0; };
-  auto tiles = [&](int bm, int bn) { return (long long)ceil_div(M, bm) * ceil_div(N, bn); };
+  const double e384 = rounds(384, 192, split_ranges<384, 192>(tiles(384, 192), 256, K, scratch, scratch_bytes), -0.74, 1.386, 11.56);
+  Bf16Form form = F128;
   double now = 0.0;
   switch (tile) {
-    case T256: now = rounds(256, 256, split_ranges<256, 256>(tiles(256, 256), 256, K, scratch, scratch_bytes), -1.75, 1.266, 8.84); break;
-    case T192: now = rounds(256, 192, split_ranges<256, 192>(tiles(256, 192), 256, K, scratch, scratch_bytes), 0.04, 1.051, 6.49); break;
-    case T384: now = rounds(384, 192, split_ranges<384, 192>(tiles(384, 192), 256, K, scratch, scratch_bytes), -0.74, 1.386, 11.56); break;
+    case T256: form = F256; now = rounds(256, 256, split_ranges<256, 256>(tiles(256, 256), 256, K, scratch, scratch_bytes), -1.75, 1.266, 8.84); break;
+    case T192: form = F192; now = rounds(256, 192, split_ranges<256, 192>(tiles(256, 192), 256, K, scratch, scratch_bytes), 0.04, 1.051, 6.49); break;
+    case T384: form = F384; now = e384; break;
     case T128:
-      if (split_ranges<128, 128>(tiles(128, 128), 512, K, scratch, scratch_bytes) < 2) now = rounds(128, 128, 1, 1.84, 0.443, 1.40) + lone(0.21, -0.72);
+      if (split_ranges<128, 128>(tiles(128, 128), 512, K, scratch, scratch_bytes) >= 2) return F128;
+      now = rounds(128, 128, 1, 1.84, 0.443, 1.40) + lone(0.21, -0.72);
       break;
   }
-  const double e256 = per_cu(128, 256) >= 2.0 ? rounds(128, 256, 1, -0.09, 0.702, 2.68) : 1e30,
-               e128 = rounds(128, 128, 1, 1.25, 0.419, 1.11) + lone(0.083, 0.56);
-  if (e256 < now && e256 <= e128) return 256;
-  return e128 < now ? 128 : 0;
+  if ((unsigned long long)M * K * 2 >= (1ull << 32) || (unsigned long long)N * K * 2 >= (1ull << 32)) return form;     // 32-bit offsets
+  if (packed && packs_weights(N, K)) {
+    const double e256 = per_cu(128, 256) >= 2.0 ? rounds(128, 256, 1, -0.09, 0.702, 2.68) : 1e30,
+                 e128 = rounds(128, 128, 1, 1.25, 0.419, 1.11) + lone(0.083, 0.56);
+    if (e256 < now && e256 <= e128) { form = P256; now = e256; }
+    else if (e128 < now) {
+      form = P128;                                         // four tiles share a CU: the few tiles of a last round take half of one
+      now = e128 - 0.5 * (per_cu(128, 128) - tiles(128, 128) / 256.0) * (0.419 * kt + 1.11);
+    }
+  }
+  double least = 0.94 * now;
+  if (N % 288 == 0 && K >= 2048) {
+    const double e = 2.53 + per_cu(128, 288) * (0.629 * kt + 5.71) + tiles(128, 288) / 256.0 * 0.234 * kt;
+    if (e < least) { form = W288; least = e; }
+  }
+  if (N % 192 == 0 && e384 < 0.97 * least) form = F384;
+  return form;
 }
 
 bool packed_weights_serve(int M, int N, int K) {
   if ((long long)ceil_div(M, 128) * ceil_div(N, 128) < 32 || N < 32) return false;      // k_gemm_skinny
-  const Bf16Tile tile = bf16_tile(false, M, N, K);
-  return packed_columns(tile, M, N, K, nullptr, 0) || packed_columns(tile, M, N, K, (const void*)16, ~(size_t)0);
+  auto taken = [&](const void* scratch, size_t bytes) {
+    const Bf16Form form = bf16_form(M, N, K, true, scratch, bytes);
+    return form == P128 || form == P256;
+  };
+  return taken(nullptr, 0) || taken((const void*)16, ~(size_t)0);
 }
 
 template <int MODE>
@@ -1771,12 +2002,14 @@ static hipError_t dispatch_mode(int bf16, const void* A, const void* Wt, int M, 
       aligned = aligned && ep.ldo % 8 == 0 && ((uintptr_t)ep.out & 15) == 0;
   }
   if (K % 64 != 0 || !aligned || N < 32) return run_plain<bf16_t, MODE>(A, Wt, M, N, K, ep, s);
-  const Bf16Tile tile = bf16_tile(MODE == EPI_UNPATCH, M, N, K);
+  Bf16Tile tile = bf16_tile(MODE == EPI_UNPATCH, M, N, K);
   if constexpr (MODE == EPI_HEADS || MODE == EPI_GATE || MODE == EPI_GELU) {
-    if (w_parts && ((uintptr_t)w_parts & 15) == 0) {
-      const int columns = packed_columns(tile, M, N, K, scratch, scratch_bytes);
-      if (columns == 256) return run_packed<128, 256, 2, MODE>(A, w_parts, M, N, K, ep, s);
-      if (columns == 128) return run_packed<128, 128, 4, MODE>(A, w_parts, M, N, K, ep, s);
+    switch (bf16_form(M, N, K, w_parts && ((uintptr_t)w_parts & 15) == 0, scratch, scratch_bytes)) {
+      case P256: return run_packed<128, 256, 2, MODE>(A, w_parts, M, N, K, ep, s);
+      case P128: return run_packed<128, 128, 4, MODE>(A, w_parts, M, N, K, ep, s);
+      case W288: return run_288<MODE>(A, Wt, M, N, K, ep, s);
+      case F384: tile = T384; break;
+      default: break;
     }
   }
   switch (tile) {
