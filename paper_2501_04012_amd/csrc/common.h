@@ -269,7 +269,8 @@ struct AttnParams {
 constexpr int kKeyNormChunks = 32;
 
 // ---------------------------------------------------------------- launchers (defined in the .hip files)
-hipError_t launch_convert_f32(const float* in, void* out, size_t n, int to_bf16, hipStream_t s);
+// out [n + n2] (act) = in [n], then in2 [n2]
+hipError_t launch_convert_f32(const float* in, size_t n, const float* in2, size_t n2, void* out, int to_bf16, hipStream_t s);
 hipError_t launch_transpose_convert(const float* in, void* out, int rows, int cols, int to_bf16, hipStream_t s);
 hipError_t launch_act_to_f32_rows(int bf16, const void* in, float* out, int rows, int D,
                                   int in_rows_per_b, int out_rows_per_b, int out_row_off,

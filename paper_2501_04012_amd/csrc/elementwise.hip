@@ -7,20 +7,34 @@
 namespace fc {
 
 // ---------------------------------------------------------------- conversions
-template <typename T>
-__global__ void k_convert(const float* __restrict__ in, T* __restrict__ out, size_t n) {
-  size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  size_t stride = (size_t)gridDim.x * blockDim.x;
-  for (; i < n; i += stride) out[i] = from_f32<T>(in[i]);
+// The texts of a call in the activation type: the requests' and the one that all guidance rows share, in one launch (4.5 us each when
+// they were two).  VEC: pieces of four.
+template <typename T, int VEC>
+__global__ __launch_bounds__(256) void k_convert(const float* __restrict__ in, size_t n, const float* __restrict__ in2, size_t n2, T* __restrict__ out) {
+  typedef __attribute__((ext_vector_type(VEC))) float F;
+  typedef __attribute__((ext_vector_type(VEC))) T O;
+  const size_t i = ((size_t)blockIdx.x * 256 + threadIdx.x) * VEC;
+  if (i >= n + n2) return;
+  const F v = *(const F*)(i < n ? in + i : in2 + (i - n));
+  O o;
+#pragma unroll
+  for (int e = 0; e < VEC; ++e) o[e] = from_f32<T>(v[e]);
+  *(O*)(out + i) = o;
 }
 
-hipError_t launch_convert_f32(const float* in, void* out, size_t n, int to_bf16, hipStream_t s) {
-  if (n == 0) return hipSuccess;
-  int blocks = (int)((n + 255) / 256);
-  if (blocks > 65536) blocks = 65536;
-  if (to_bf16) k_convert<bf16_t><<<blocks, 256, 0, s>>>(in, (bf16_t*)out, n);
-  else k_convert<float><<<blocks, 256, 0, s>>>(in, (float*)out, n);
+template <typename T>
+static hipError_t run_convert(const float* in, size_t n, const float* in2, size_t n2, T* out, hipStream_t s) {
+  const bool vec = n % 4 == 0 && n2 % 4 == 0 && (((uintptr_t)in | (uintptr_t)in2 | (uintptr_t)out) & 15) == 0;
+  const size_t pieces = vec ? (n + n2) / 4 : n + n2;
+  const unsigned blocks = (unsigned)((pieces + 255) / 256);
+  if (vec) k_convert<T, 4><<<blocks, 256, 0, s>>>(in, n, in2, n2, out);
+  else k_convert<T, 1><<<blocks, 256, 0, s>>>(in, n, in2, n2, out);
   return hipGetLastError();
+}
+
+hipError_t launch_convert_f32(const float* in, size_t n, const float* in2, size_t n2, void* out, int to_bf16, hipStream_t s) {
+  if (n + n2 == 0) return hipSuccess;
+  return to_bf16 ? run_convert(in, n, in2, n2, (bf16_t*)out, s) : run_convert(in, n, in2, n2, (float*)out, s);
 }
 
 // in [rows, cols] fp32 row-major -> out [cols, rows] (T): linear weights are kept

@@ -380,16 +380,16 @@ int prepare(const Ctx& c, const float* cond, const float* null_cond) {
   const fc_model_config& cf = m->cfg;
   const Workspace& w = c.w;
   const size_t per_text = (size_t)cf.text_len * cf.text_dim;
-  {
-  ProfScope ps(c, PC_OTHER);
-  HIP_TRY(launch_convert_f32(cond, w.txt, per_text * c.R, m->bf16, c.s));
-  if (c.use_cfg)
-    HIP_TRY(launch_convert_f32(null_cond, (unsigned char*)w.txt + per_text * c.R * m->esz, per_text, m->bf16, c.s));
+  // one fp32 text is the operand as it stands; unaligned it would take the plain kernel, so that goes through the copy
+  const bool direct = !m->bf16 && !c.use_cfg && ((uintptr_t)cond & 15) == 0;
+  if (!direct) {
+    ProfScope ps(c, PC_OTHER);
+    HIP_TRY(launch_convert_f32(cond, per_text * c.R, c.use_cfg ? null_cond : nullptr, c.use_cfg ? per_text : 0, w.txt, m->bf16, c.s));
   }
   EpiParams ep;
   ep.out = w.y; ep.ldo = cf.hidden;
   // few rows, long K: split along K through hid, which nothing uses before the first block's MLP
-  int rc = linear(c, PC_GEMM_OTHER, EPI_STORE, w.txt, m->y, w.NT * cf.text_len, ep, w.hid,
+  int rc = linear(c, PC_GEMM_OTHER, EPI_STORE, direct ? (const void*)cond : w.txt, m->y, w.NT * cf.text_len, ep, w.hid,
                   (size_t)w.B * m->Ns * cf.mlp_dim * m->esz);
   if (rc != FC_OK) return rc;
   if (cf.attn_mode == FC_ATTN_FACTORIZED_CROSS && cf.depth > 0) {
