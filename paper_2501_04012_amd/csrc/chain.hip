@@ -31,7 +31,7 @@
 //   do, the wave number a scalar (a masked-out matrix instruction would be issued all the same), one kernel per kind of launch.
 //
 // 64 wide, 4 heads, 28 blocks, 4 requests with guidance (512 rows), ten steps: 17.2 ms with a launch per operator, 7.53 with loads one
-// stage ahead, 5.53 now; a spatial and a temporal launch 9 and 17 us before, 6 and 12 now.  Steps of one to three blocks, 160 sizes of 16
+// stage ahead, 5.53 now; a spatial and a temporal launch 9 and 17 us before, 6 and 13 now.  Steps of one to three blocks, 160 sizes of 16
 // to 128 columns: 0.92 of the time in the mean (64 and 128 wide factorized 0.80 to 0.86, full 3-D 0.9 to 1.0), none slower.
 #include <type_traits>
 #include "common.h"
