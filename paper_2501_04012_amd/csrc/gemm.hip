@@ -898,29 +898,30 @@ hipError_t launch_pack_weights(const void* W, void* out, int N, int K, hipStream
 // For widths that are whole multiples of 288 (models of 576 and 1152 columns) where such tiles fill the chip and those above do not: 8192 x 1152
 // is 192 tiles of 256x192 but 256 of 128x288.  One tile to a workgroup, one workgroup to a CU.  A wave owns 64 rows by 144 columns, the
 // shape that keeps LDS reads under the matrix instructions (13 fragments per 36 v_mfma_f32_16x16x32_bf16; 16 wide, as 144 is no
-// multiple of 32).  The tile is only four such waves, so the eight waves of a workgroup are two groups that each take one half of every
-// K tile and add their sums through LDS at the end (in a fixed order; the K loop's stages are free by then).  LDS layout, DMA and swizzle are
-// those of k_gemm_dlds, as is the barrier ahead of a stage's last products, behind which the next stage's first fragments are read and
-// its buffer requested again.  Three stages: with two, one round of tiles is level where operands come from the L2, four are slower
-// (32768 x 1152 x 4608: 353 us against 314).
-// Bound by the operand stream (53 KB per K tile in 0.9 us and CU) and, where K is small, by what is not the K loop (10 us: first tile, sums,
-// epilogue).  us, best form before and this one, operands by turns from four to six products: 8192 x 1152 x 4608 105, 80;
-// 15742 x 576 x 2304 59, 46; the same product again and again: 94, 74 and 53, 42.
-// The same kernel with 128x144 tiles (four groups, 128 of K a stage, two stages) was faster over operands from the L2 (4096 x 1152 x 4608
-// 58 -> 47 us), but not in a model, where they come from further off (62 us and 60).
+// multiple of 32), so the tile is four waves, one to a SIMD, and what would stop the wave stops the SIMD: fragments are read four
+// columns of products ahead, and requests for operand tiles are spread over the matrix instructions (all thirteen of a wave in
+// the tail of a step: 96 us where it is 76).  Sums go along K in order, and one v_mfma_f32_16x16x32_bf16 rounds like two
+// v_mfma_f32_32x32x16_bf16: results are those of k_gemm_dlds bit for bit where that does not split a tile along K.  LDS layout, DMA and
+// swizzle are those of k_gemm_dlds, as is the barrier ahead of a stage's last products, behind which the next stage's first fragments
+// are read.  Three stages of LDS.
+// Bound by the operand stream (53 KB per K tile in 0.9 us and CU) and, where K is small, by what is not the K loop (10 us: first tile,
+// epilogue).  us, best form before and this one, operands by turns from four to six products: 8192 x 1152 x 4608 106, 76;
+// 7300 x 1152 x 4608 95, 70; 15742 x 576 x 2304 57, 43; 900 x 9216 x 2304 51, 37.  (Eight waves in two groups, each on one half of every
+// K tile, added at the end, took 80, 74, 44 and 38 and gave a row other sums than the other tiles do.)
 struct Tile288 {
   static constexpr int BM = 128, BN = 288, kStages = 3, kStage = (BM + BN) * 128;
-  static constexpr int kSlice = 2 * 9 * 1024;              // half a wave's sums
+  static constexpr int kRow = 304;                         // bytes of a staged row of 144 results, 16 of them padding
   static constexpr int kBytes = kStages * kStage + 2 * BN * 4;        // and bias and gate of the tile's columns
 };
 template <typename Epi>
-__global__ __launch_bounds__(512, 2) void k_gemm_288(const bf16_t* __restrict__ A, const bf16_t* __restrict__ Wt, int M, int N, int K,
+__global__ __launch_bounds__(256, 2) void k_gemm_288(const bf16_t* __restrict__ A, const bf16_t* __restrict__ Wt, int M, int N, int K,
                                                      int tiles_m, int tiles_n, Epi epi) {
 #if defined(__HIP_DEVICE_COMPILE__)   // buffer resources are a device-side type: the host pass sees an empty body
   using L = Tile288;
-  constexpr int BM = L::BM, BN = L::BN, S = L::kStages, TM = 4, TN = 9;
+  constexpr int BM = L::BM, BN = L::BN, S = L::kStages, TM = 4, TN = 9, RW = 32;        // RW: rows of a load by all waves
   static_assert(Epi::kRowRuns, "stores of 16-byte runs");
-  static_assert(S * L::kStage >= 8 * L::kSlice, "the sums fit the stages");
+  static_assert(BM % RW == 0 && BN % RW == 0, "whole loads");
+  static_assert(S * L::kStage >= 4 * 64 * L::kRow, "the results fit the stages");
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   float* const sbias = (float*)(smem + S * L::kStage);
   float* const sgate = sbias + BN;
@@ -932,56 +933,45 @@ __global__ __launch_bounds__(512, 2) void k_gemm_288(const bf16_t* __restrict__ 
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int li = lane & 15, lh = lane >> 4;
-  const int kg = wave >> 2, wm = wave & 1, wn = (wave >> 1) & 1;
-  if (tid < BN) {
-    sbias[tid] = epi.P.bias ? epi.P.bias[bn0 + tid] : 0.0f;
-    if constexpr (Epi::kHasGate) sgate[tid] = epi.P.gate ? epi.P.gate[bn0 + tid] : 1.0f;
+  const int wm = wave & 1, wn = wave >> 1;
+  for (int c = tid; c < BN; c += 256) {
+    sbias[c] = epi.P.bias ? epi.P.bias[bn0 + c] : 0.0f;
+    if constexpr (Epi::kHasGate) sgate[c] = epi.P.gate ? epi.P.gate[bn0 + c] : 1.0f;
   }
 
   // ---- operand tiles: 8 rows of 128 bytes a wave-load, swizzled as in k_gemm_dlds
   const int row0 = wave * 8 + (lane >> 4) * 2 + ((lane & 15) >> 3), kc = (lane & 7) ^ ((wave * 4 + (lane >> 4)) & 7);
-  const unsigned v0 = (unsigned)row0 * (unsigned)K * 2u + (unsigned)kc * 16u, rows64 = 64u * (unsigned)K * 2u;
+  const unsigned v0 = (unsigned)row0 * (unsigned)K * 2u + (unsigned)kc * 16u, rows = (unsigned)RW * (unsigned)K * 2u;
   const auto ra = __builtin_amdgcn_make_buffer_rsrc((void*)(A + (size_t)bm0 * K), 0, (int)((unsigned)(M - bm0) * (unsigned)K * 2u), 0x00020000);
   const auto rb = __builtin_amdgcn_make_buffer_rsrc((void*)(Wt + (size_t)bn0 * K), 0, (int)((unsigned)BN * (unsigned)K * 2u), 0x00020000);
-  auto request = [&](int st, int stage) {
-    unsigned char* const dst = smem + stage + wave * 1024;
-#pragma unroll
-    for (int j = 0; j < BM / 64; ++j)                      // rows past the end of A load as zero
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_void*)(dst + j * 8192), 16, (int)(v0 + j * rows64), st * 128, 0, 0);
-#pragma unroll
-    for (int j = 0; j < BN / 64; ++j)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lds_void*)(dst + BM * 128 + j * 8192), 16, (int)(v0 + j * rows64), st * 128, 0, 0);
+  auto request_a = [&](int st, int stage, int j) {         // rows past the end of A load as zero
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_void*)(smem + stage + wave * 1024 + j * RW * 128), 16, (int)(v0 + j * rows), st * 128, 0, 0);
   };
-  auto request_rest = [&](int st, int stage) {             // the last 32 rows of the weights, by half the waves
-    if (wave < BN % 64 / 8)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lds_void*)(smem + stage + wave * 1024 + BM * 128 + BN / 64 * 8192), 16,
-                                               (int)(v0 + BN / 64 * rows64), st * 128, 0, 0);
+  auto request_b = [&](int st, int stage, int j) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lds_void*)(smem + stage + wave * 1024 + (BM + j * RW) * 128), 16, (int)(v0 + j * rows), st * 128, 0, 0);
   };
-  // ---- fragments.  The second group's accumulators hold row tiles 2, 3, 0, 1: the first two are the ones that a wave finishes.
-  const int fo = (li >> 1) * 256 + ((li & 1) * 8 + ((4 * kg + lh) ^ (li >> 1))) * 16;
-  int oa[TM];
-#pragma unroll
-  for (int i = 0; i < TM; ++i) oa[i] = fo + wm * 8192 + (i ^ (2 * kg)) * 2048;
-  const int ob = fo + BM * 128 + wn * (144 * 128);
+  // ---- fragments: two halves of a stage's K, one after the other
+  const int fo = (li >> 1) * 256 + ((li & 1) * 8 + (lh ^ (li >> 1))) * 16;
+  const int oa = fo + wm * 64 * 128, ob = fo + BM * 128 + wn * (144 * 128);
 
   f32x4 acc[TM][TN];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-  bf16x8 fa[2][TM], fb[TN];
-  auto load_a = [&](int set, int stage, int i) { fa[set][i] = *(const bf16x8*)(smem + stage + oa[i]); };
-  auto load_b = [&](int stage, int j) { fb[j] = *(const bf16x8*)(smem + stage + ob + j * 2048); };
-  auto multiply = [&](int set, int j) {                    // weights as the A operand: a lane ends up with consecutive columns
+  bf16x8 fa[2][TM], fb[2][TN];
+  auto load_a = [&](int stage, int half, int i) { fa[half][i] = *(const bf16x8*)(smem + stage + (oa ^ (half * 64)) + i * 2048); };
+  auto load_b = [&](int stage, int half, int j) { fb[half][j] = *(const bf16x8*)(smem + stage + (ob ^ (half * 64)) + j * 2048); };
+  auto multiply = [&](int half, int j) {                   // weights as the A operand: a lane ends up with consecutive columns
 #pragma unroll
-    for (int i = 0; i < TM; ++i) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j], fa[set][i], acc[i][j], 0, 0, 0);
+    for (int i = 0; i < TM; ++i) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[half][j], fa[half][i], acc[i][j], 0, 0, 0);
   };
 
-  // Stages are numbered by K; stage st lies at offset st % S of LDS.  Past the end the last one is requested again (never read).
+  // Stages are numbered by K; stage st lies at offset st % S of LDS.  Past the end the last one is requested again (never used).
   const int nst = K / 64;
-  constexpr int kDsRead = 0x100, kMfma = 0x008, kVmem = 0x010, AHEAD = 3, LOADS = BM / 64 + BN / 64;
-  // All but the last `stages` stages requested; this wave's LDS reads too.  (A wave that requests the rest of the weights waits for those
-  // of a younger stage as well.)
+  // A stage's rows of A are requested in the tail of the step that frees its buffer, its weights along the step after.
+  constexpr int kDsRead = 0x100, kMfma = 0x008, kVmem = 0x010, AHEAD = 4, LA = BM / RW, LB = BN / RW, LOADS = LA + LB;
+  // All but the last `stages` stages requested; this wave's LDS reads too.
   auto landed = [&](auto stages) {
     wait_vm_lgkm0<decltype(stages)::value * LOADS>();
     __builtin_amdgcn_s_barrier();
@@ -990,81 +980,73 @@ __global__ __launch_bounds__(512, 2) void k_gemm_288(const bf16_t* __restrict__ 
 #pragma unroll
   for (int st = 0; st < S; ++st) {
     if (st == S - 1) landed(std::integral_constant<int, 0>{});
-    request_rest(min(st, nst - 1), st * L::kStage);
-    request(min(st, nst - 1), st * L::kStage);
+#pragma unroll
+    for (int j = 0; j < LA; ++j) request_a(min(st, nst - 1), st * L::kStage, j);
+    if (st < S - 1) {
+#pragma unroll
+      for (int j = 0; j < LB; ++j) request_b(min(st, nst - 1), st * L::kStage, j);
+    }
     __builtin_amdgcn_sched_barrier(0);
   }
 #pragma unroll
   for (int i = 0; i < TM; ++i) load_a(0, 0, i);
 #pragma unroll
-  for (int j = 0; j < AHEAD; ++j) load_b(0, j);
+  for (int j = 0; j < AHEAD; ++j) load_b(0, 0, j);
   __builtin_amdgcn_sched_barrier(0);
   int at = 0;                                              // offset of the stage being multiplied
-  auto step = [&](auto par, int st) {
-    constexpr int PAR = decltype(par)::value;
-    const int after = at == (S - 1) * L::kStage ? 0 : at + L::kStage;
+  auto step = [&](int st) {
+    const int after = at == (S - 1) * L::kStage ? 0 : at + L::kStage, before = at == 0 ? (S - 1) * L::kStage : at - L::kStage;
+    // every fragment of the stage is read ahead of its last AHEAD columns of products
 #pragma unroll
-    for (int j = 0; j + AHEAD < TN; ++j) {
-      load_b(at, j + AHEAD);
-      multiply(PAR, j);
+    for (int j = 0; j < 2 * TN - AHEAD; ++j) {
+      const int n = j + AHEAD;
+      load_b(at, n / TN, n % TN);
+      if (j < TM) load_a(at, 1, j);
+      if (j < LB) request_b(min(st + S - 1, nst - 1), before, j);
+      multiply(j / TN, j % TN);
     }
 #pragma unroll
-    for (int j = 0; j + AHEAD < TN; ++j) {
+    for (int j = 0; j < 2 * TN - AHEAD; ++j) {
       __builtin_amdgcn_sched_group_barrier(kMfma, 1, 0);
       __builtin_amdgcn_sched_group_barrier(kDsRead, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(kMfma, TM - 1, 0);
+      __builtin_amdgcn_sched_group_barrier(kMfma, 1, 0);
+      if (j < TM) __builtin_amdgcn_sched_group_barrier(kDsRead, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(kMfma, 1, 0);
+      if (j < LB) __builtin_amdgcn_sched_group_barrier(kVmem, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(kMfma, TM - 3, 0);
     }
     landed(std::integral_constant<int, S - 2>{});          // stage st + 1 has, and every wave is done reading st
-    request_rest(min(st + S, nst - 1), at);
-    __builtin_amdgcn_sched_barrier(0);
-    request(min(st + S, nst - 1), at);
 #pragma unroll
-    for (int i = 0; i < TM; ++i) load_a(PAR ^ 1, after, i);
+    for (int j = 0; j < LA; ++j) request_a(min(st + S, nst - 1), at, j);
 #pragma unroll
-    for (int j = 0; j < AHEAD; ++j) load_b(after, j);
+    for (int i = 0; i < TM; ++i) load_a(after, 0, i);
 #pragma unroll
-    for (int j = TN - AHEAD; j < TN; ++j) multiply(PAR, j);
+    for (int j = 0; j < AHEAD; ++j) load_b(after, 0, j);
+#pragma unroll
+    for (int j = TN - AHEAD; j < TN; ++j) multiply(1, j);
 #pragma unroll
     for (int r = 0; r < AHEAD * TM; ++r) {
       __builtin_amdgcn_sched_group_barrier(kMfma, 1, 0);
-      if (r < TM + AHEAD) __builtin_amdgcn_sched_group_barrier(kDsRead, 1, 0);
-      if (r < LOADS) __builtin_amdgcn_sched_group_barrier(kVmem, 1, 0);
+      if (r < LA) __builtin_amdgcn_sched_group_barrier(kVmem, 1, 0);
+      else if (r < LA + TM + AHEAD) __builtin_amdgcn_sched_group_barrier(kDsRead, 1, 0);
     }
     __builtin_amdgcn_sched_barrier(0);
     at = after;
   };
-  using P0 = std::integral_constant<int, 0>; using P1 = std::integral_constant<int, 1>;
   int st = 0;
   for (; st + 1 < nst; st += 2) {
-    step(P0{}, st);
-    step(P1{}, st + 1);
+    step(st);
+    step(st + 1);
   }
-  if (st < nst) step(P0{}, st);
+  if (st < nst) step(st);
 
-  // ---- the groups' sums: a wave and its partner in the other group exchange halves through LDS, no longer read as stages
+  // ---- epilogue: a wave's 64 rows of 144 columns through LDS that it alone uses, no longer read as stages; out in runs of 16 bytes
   wait_vm_lgkm0<0>();
-  __builtin_amdgcn_s_barrier();
-  unsigned char* const cst = smem + (wave ^ 4) * L::kSlice;           // the partner's slice, which this wave alone reads, and then reuses
-  f32x4* const mine = (f32x4*)(smem + wave * L::kSlice) + lane;
-  const f32x4* const theirs = (const f32x4*)cst + lane;
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j) mine[(i * TN + j) * 64] = acc[2 + i][j];
   __syncthreads();
+  unsigned char* const cst = smem + wave * (64 * L::kRow);
+  const int nw = wn * 144, m0 = bm0 + wm * 64;
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-      const f32x4 o = theirs[(i * TN + j) * 64];
-      acc[i][j] = kg ? o + acc[i][j] : acc[i][j] + o;
-    }
-
-  // ---- epilogue: 32 rows of 144 columns through the slice, out in runs of 16 bytes
-  constexpr int ROWB = 304;                                // bytes of a staged row, 16 of them padding
-  const int nw = wn * 144, m0 = bm0 + wm * 64 + kg * 32;
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
       const int c = 16 * j + 4 * lh;
@@ -1073,12 +1055,12 @@ __global__ __launch_bounds__(512, 2) void k_gemm_288(const bf16_t* __restrict__ 
       bf16x4 o;
 #pragma unroll
       for (int e = 0; e < 4; ++e) o[e] = (bf16_t)v[e];
-      *(bf16x4*)(cst + (i * 16 + li) * ROWB + c * 2) = o;
+      *(bf16x4*)(cst + (i * 16 + li) * L::kRow + c * 2) = o;
     }
 #pragma unroll
-  for (int it = 0; it < 32 * 18 / 64; ++it) {
+  for (int it = 0; it < 64 * 18 / 64; ++it) {
     const int idx = it * 64 + lane, row = idx / 18, chunk = idx - row * 18;
-    const bf16x8 o = *(const bf16x8*)(cst + row * ROWB + chunk * 16);
+    const bf16x8 o = *(const bf16x8*)(cst + row * L::kRow + chunk * 16);
     if (m0 + row < M) __builtin_nontemporal_store(o, (bf16x8*)epi.run8(m0 + row, bn0 + nw + chunk * 8));
   }
 #endif
@@ -1844,7 +1826,7 @@ static hipError_t run_288(const void* A, const void* Wt, int M, int N, int K, co
     attr_set = true;
   }
   const int tiles_m = ceil_div(M, L::BM), tiles_n = N / L::BN;
-  kern<<<round_up((size_t)tiles_m * tiles_n, 256), 512, L::kBytes, s>>>((const bf16_t*)A, (const bf16_t*)Wt, M, N, K, tiles_m, tiles_n, epi);
+  kern<<<round_up((size_t)tiles_m * tiles_n, 256), 256, L::kBytes, s>>>((const bf16_t*)A, (const bf16_t*)Wt, M, N, K, tiles_m, tiles_n, epi);
   return hipGetLastError();
 }
 
@@ -1926,8 +1908,7 @@ static Bf16Tile bf16_tile(bool unpatch, int M, int N, int K) {
 //   all split along K stay with them (up to 1.58).
 //   128x288, 384x192: where the estimate is 6 % (384x192: 9 %) lower, so much being what the estimates are worth.  Their tiles fill
 //   rounds that the others leave half empty: of 680 products 29 take one of them, 0.88 of the time in the mean, none slower (without
-//   the margin 0.85 to 1.13).  128x288 adds its sums in two parts: only from the K on at which a last round may be split along K
-//   too.  Below it a row's result does not depend on how many rows there are, bit for bit.
+//   the margin 0.85 to 1.13).  128x288 from K = 2048 on: below it is mostly first tile and epilogue, which the estimate was not held against.
 enum Bf16Form { F128, F192, F256, F384, P128, P256, W288 };
 static Bf16Form bf16_form(int M, int N, int K, bool packed, const void* scratch, size_t scratch_bytes) {
   const Bf16Tile tile = bf16_tile(false, M, N, K);

@@ -38,3 +38,25 @@ def test_linear_in_tiles_that_fill_the_chip(fc, M, N, K, epilogue):
     err = (out.double() - want).norm(dim=1) / want.norm(dim=1)
     assert float(err.max()) < 4e-3, (float(err.max()), int(err.argmax()))
     assert np.isfinite(float(err.sum()))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,N,K,fewer", [
+    (8192, 1152, 4608, 2000), (7681, 1152, 4608, 1000), (15742, 576, 2304, 6001), (900, 9216, 2112, 257), (2900, 2880, 2880, 1300),
+    (14592, 1152, 4608, 4096)])                               # 384x192 tiles, and of 128x288
+@pytest.mark.parametrize("epilogue", [1, 2])
+def test_rows_do_not_depend_on_their_number(fc, M, N, K, fewer, epilogue):
+    """Without scratch no product of more than a few tiles adds its sums in parts: its first rows alone, in other tiles, get the same bits."""
+    import torch
+    g = torch.Generator(device="cuda:0").manual_seed(M + N + K)
+    A = torch.randn(M, K, device="cuda:0", generator=g).bfloat16()
+    W = (torch.randn(N, K, device="cuda:0", generator=g) / math.sqrt(K)).bfloat16()
+    b, gate = torch.randn(N, device="cuda:0", generator=g), torch.randn(N, device="cuda:0", generator=g)
+    got = []
+    for rows in (M, fewer):
+        out = torch.full((rows, N), float("nan"), dtype=torch.bfloat16, device="cuda:0")
+        fc.fc_op_linear(fc.FC_BF16, A, W, b, gate if epilogue == 2 else None, out, rows, N, K, epilogue)
+        got.append(out)
+    torch.cuda.synchronize()
+    assert bool(torch.isfinite(got[0].float()).all())
+    assert torch.equal(got[0][:fewer], got[1])
