@@ -1902,15 +1902,20 @@ static Bf16Tile bf16_tile(bool unpatch, int M, int N, int K) {
 
 // The form of a model's product: the tile just chosen, or one whose estimated time is below that tile's.  The estimates, in us: tiles
 // of the fullest CU times a time per K tile and one per tile, fitted over 325 products (M 256 to 38 000, N and K 576 to 12 288, each timed in
-// every form); for the tiles of 288 columns also the tiles per CU of the whole chip (the power limit), over 400 products.
+// every form, the same product again and again); for the tiles of 288 columns also the tiles per CU of the whole chip (the power limit), over
+// 400 products.  They rank forms that differ by whole rounds.  As times they are up to a quarter too short where a product has many rounds
+// of long K, whose operands come from further off (256x192 at 32768 x 1152 x 4608: 246 estimated, 325 with operands by turns, where packed
+// 128x256 takes 290 and is estimated at 266).
 //   Packed weights (`packed`: there are some): 314 products, 0.917 of the time in the mean, none more than 2 % slower.  A lone 128x256
 //   tile on a CU (two waves a SIMD short) is up to 1.13 times slower than estimated and not taken; products whose 128x128 tiles are
 //   all split along K stay with them (up to 1.58).
-//   128x288, 384x192: where the estimate is 6 % (384x192: 9 %) lower, so much being what the estimates are worth.  Their tiles fill
-//   rounds that the others leave half empty: of 680 products 29 take one of them, 0.88 of the time in the mean, none slower (without
-//   the margin 0.85 to 1.13).  128x288 from K = 2048 on: below it is mostly first tile and epilogue, which the estimate was not held against.
-enum Bf16Form { F128, F192, F256, F384, P128, P256, W288 };
-static Bf16Form bf16_form(int M, int N, int K, bool packed, const void* scratch, size_t scratch_bytes) {
+//   128x288, 384x192: where the estimate is 6 % (384x192: 9 %) lower, a nearly empty last round counted as what it takes.  Their tiles
+//   fill rounds that the others leave half empty.  821 products at the lower ends and inside of the windows of M that these rules give 14
+//   widths of 576 to 4608, with operands by turns: 0.84 of the time in the mean, four slower by more than 1 %, by 2.8 % at most (all rounds
+//   counted as full: up to 1.29, 6545 x 576 x 2304 28 us, and 36).  384x192 takes nothing from packed 128x256 (66 products that the
+//   estimates would give it: 0.89 to 1.10 of the time, 1.02 in the mean; 4753 x 6912 x 2304 126 us, and 139).  128x288 from K = 2048 on:
+//   below it is mostly first tile and epilogue, which the estimate was not held against.
+Bf16Form bf16_form(int M, int N, int K, bool packed, const void* scratch, size_t scratch_bytes) {
   const Bf16Tile tile = bf16_tile(false, M, N, K);
   const double kt = K / 64.0;
   auto tiles = [&](int bm, int bn) { return (long long)ceil_div(M, bm) * ceil_div(N, bn); };
@@ -1922,10 +1927,11 @@ static Bf16Form bf16_form(int M, int N, int K, bool packed, const void* scratch,
   };
   auto lone = [&](double k, double fixed) { return per_cu(128, 128) == 1.0 ? k * kt + fixed : 0.0; };
   const double e384 = rounds(384, 192, split_ranges<384, 192>(tiles(384, 192), 256, K, scratch, scratch_bytes), -0.74, 1.386, 11.56);
+  const int splits256 = split_ranges<256, 256>(tiles(256, 256), 256, K, scratch, scratch_bytes);
   Bf16Form form = F128;
   double now = 0.0;
   switch (tile) {
-    case T256: form = F256; now = rounds(256, 256, split_ranges<256, 256>(tiles(256, 256), 256, K, scratch, scratch_bytes), -1.75, 1.266, 8.84); break;
+    case T256: form = F256; now = rounds(256, 256, splits256, -1.75, 1.266, 8.84); break;
     case T192: form = F192; now = rounds(256, 192, split_ranges<256, 192>(tiles(256, 192), 256, K, scratch, scratch_bytes), 0.04, 1.051, 6.49); break;
     case T384: form = F384; now = e384; break;
     case T128:
@@ -1938,17 +1944,21 @@ static Bf16Form bf16_form(int M, int N, int K, bool packed, const void* scratch,
     const double e256 = per_cu(128, 256) >= 2.0 ? rounds(128, 256, 1, -0.09, 0.702, 2.68) : 1e30,
                  e128 = rounds(128, 128, 1, 1.25, 0.419, 1.11) + lone(0.083, 0.56);
     if (e256 < now && e256 <= e128) { form = P256; now = e256; }
-    else if (e128 < now) {
-      form = P128;                                         // four tiles share a CU: the few tiles of a last round take half of one
-      now = e128 - 0.5 * (per_cu(128, 128) - tiles(128, 128) / 256.0) * (0.419 * kt + 1.11);
-    }
+    else if (e128 < now) { form = P128; now = e128; }
   }
+  // What a last round takes less than the others: 128x128 tiles of packed weights, four to a CU, as it is less full; staged ones, two to a CU, and
+  // 256x256 tiles where it is less than a quarter full (for the former: and the second that CUs share).
+  auto empty = [&](int bm, int bn) { return per_cu(bm, bn) - tiles(bm, bn) / 256.0; };
+  const bool packed256 = form == P256;
+  if (form == P128) now -= 0.5 * empty(128, 128) * (0.419 * kt + 1.11);
+  else if (form == F128 && empty(128, 128) > 0.75 && (long long)per_cu(128, 128) % 2 == 0) now -= 0.5 * empty(128, 128) * (0.443 * kt + 1.40);
+  else if (form == F256 && empty(256, 256) > 0.75 && splits256 < 2) now -= 0.15 * empty(256, 256) * (1.266 * kt + 8.84);
   double least = 0.94 * now;
   if (N % 288 == 0 && K >= 2048) {
     const double e = 2.53 + per_cu(128, 288) * (0.629 * kt + 5.71) + tiles(128, 288) / 256.0 * 0.234 * kt;
     if (e < least) { form = W288; least = e; }
   }
-  if (N % 192 == 0 && e384 < 0.97 * least) form = F384;
+  if (N % 192 == 0 && !packed256 && e384 < 0.97 * least) form = F384;
   return form;
 }
 
