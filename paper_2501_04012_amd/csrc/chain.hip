@@ -120,9 +120,11 @@ template <size_t BYTES> __device__ __forceinline__ void touch_arguments() {
   asm volatile("" ::"s"(any));
 }
 
-// c + a b.  The sum never shares registers with c: left to itself the compiler moves the sum of a chain by two registers now and then,
-// an output that overlaps the input it is added to without being the same registers, and a build with such products gave wrong
-// sums (128 columns, third batch of a product; tests/test_mfma_registers.py).
+// c + a b.  The sum never shares registers with c.  Left to itself the compiler moves the sum of a chain by two registers now and then, an
+// output that overlaps the input it is added to without being the same registers.  What is known: a build with such products gave wrong
+// sums (128 columns, third batch of a product, which is also the first whose weights take registers used before), and with this
+// line, which changes schedule and waits besides, the sums are right.  That the overlap was the reason is inferred: waits for weights
+// are the compiler's in either build.  tests/test_mfma_registers.py holds the rule.
 __device__ __forceinline__ f32x4 mac(float a, float b, f32x4 c) {
   f32x4 d = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
   asm volatile("" : "+v"(d) : "v"(c));

@@ -708,8 +708,8 @@ __global__ __launch_bounds__(WR * WC * 64) void k_gemm_dlds(const bf16_t* __rest
 //
 // Against k_gemm_dlds the 256x256 form of this kernel is level (990 and 994 us at 17776 x 12288 x 3072: a third less LDS traffic
 // buys nothing, the power limit bounds both), so what counts are rounds and epilogues (the rule is in the dispatch).
-// us, before and now: 32768 x 1152 x 4608 320, 287; 9326 x 6144 x 2048 203, 178; 4096 x 4608 x 1152 49, 44;
-// 8192 x 3456 x 1152 72, 67; 314 products of 300 to 33 000 rows, 576 to 3072 wide: 0.92 of the time in the mean.
+// us, before and now: 9326 x 6144 x 2048 203, 178; 4096 x 4608 x 1152 49, 44; 8192 x 3456 x 1152 72, 67 (and where the rule stays with
+// 256x192 all the same: 32768 x 1152 x 4608 320, 287); 314 products of 300 to 33 000 rows, 576 to 3072 wide: 0.92 of the time in the mean.
 template <int BM, int BN, typename Epi>
 __global__ __launch_bounds__(256, 2) void k_gemm_packed(const bf16_t* A, const void* Wp, int M, int N,
                                                         int K, int tiles_m, int tiles_n, Epi epi) {

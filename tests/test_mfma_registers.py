@@ -1,6 +1,6 @@
 """Registers of the matrix instructions in the built library: a sum lies in the registers of the sum it is added to, or in none of them.
-The compiler gives four-register sums outputs that overlap their input by two registers, and a build with such instructions in its
-loops gave wrong sums."""
+Left to itself the compiler gives four-register sums outputs that overlap their input by two registers.  A build with such instructions
+in its loops gave wrong sums; that they were the reason is inferred (the build without them differs in schedule and waits too)."""
 import os
 import re
 import subprocess
