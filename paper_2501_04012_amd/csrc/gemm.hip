@@ -11,27 +11,23 @@
 namespace fc {
 
 // ---------------------------------------------------------------- bf16 MFMA kernel, direct-to-LDS
-// (k_gemm_dlds_any: the general form, any K that is a multiple of 64 and operands of any size.
-// k_gemm_dlds further down is the one the workloads run; what is said here about tiles, layout,
-// tile order and units of work holds for both.)
-// Block tile BM x BN x BK, NW = WR x WC waves, each wave owns a (BM/WR) x (BN/WC) tile built
-// from 32x32 MFMA accumulators.  MFMA operand layout (32x32x16, wave64), lane = i + 32*h:
-//   A: row i of the 32-row tile, k = 8h .. 8h+7        (8 bf16 = one 16-byte LDS read)
-//   B: column i of the 32-col tile, k = 8h .. 8h+7
-//   D: column i, rows 8g + 4h + e for register 4g + e   (g, e in 0..3)
-// The operand tiles go from global memory straight into LDS (global_load_lds_dwordx4: lane l's 16 bytes land at
-// base + 16 l), S stages deep, with no register staging and no ds_write.
+// Block tile BM x BN x 64, NW = WR x WC waves, each wave owns a (BM/WR) x (BN/WC) tile built
+// from 16x16 MFMA accumulators.  MFMA operand layout (16x16x32, wave64), lane = i + 16*h:
+//   A: row i of the 16-row tile, k = 8h .. 8h+7        (8 bf16 = one 16-byte LDS read)
+//   B: column i of the 16-col tile, k = 8h .. 8h+7
+//   D: column i, rows 4h + e in register e
+// 16x16x32 and not 32x32x16: the matrix pipe runs at the power limit, and 16x16x32, which reads and writes half as many
+// sums per product, holds a higher clock there (random operands out of registers 2040 TFLOP/s against 1835, with the
+// fragments read from LDS 1845 against 1665), and its sums are those of two 32x32x16 bit for bit.
+// The operand tiles go from global memory straight into LDS (buffer_load ... lds: lane l's 16 bytes land at
+// base + 16 l), two stages, with no register staging and no ds_write.
 //
-// LDS layout of a stage: BM rows of A then BN rows of B, BK*2 bytes each, unpadded.
-// A 256-byte LDS line holds RPL = 128/BK rows; chunk kc (16 bytes) of row r sits at
-//   line r/RPL, slot (r % RPL) * CPR + (kc ^ ((r/RPL) % CPR)),   CPR = BK/8,
+// LDS layout of a stage: BM rows of A then BN rows of B, 128 bytes each, unpadded.
+// A 256-byte LDS line holds 2 rows; chunk kc (16 bytes) of row r sits at
+//   line r/2, slot (r % 2) * 8 + (kc ^ ((r/2) % 8)),
 // so that the 16 rows a ds_read_b128 touches at one kc fall into 16 distinct slots
 // (no bank conflicts).  Because the DMA fixes the LDS position per lane, the swizzle
 // is applied on the global side: each lane fetches the chunk that belongs in its slot.
-//
-// Pipeline per K tile: wait until this tile's loads have landed (vmcnt), barrier
-// (publishes every wave's part and frees the stage read in the previous iteration),
-// issue the loads of tile kt+S-1 into that stage, then run the MFMAs of tile kt.
 //
 // Tile order.  Workgroup ids are dealt round-robin to the 8 XCDs, each with its own L2.
 // Id -> tile index is chosen so that 32 workgroups running together on one XCD hold 32
@@ -46,49 +42,78 @@ template <int N> __device__ __forceinline__ void wait_vm() {
   __builtin_amdgcn_s_waitcnt((N & 0xF) | ((N >> 4) << 14) | (0x7 << 4) | (0xF << 8));
 }
 
-// Split-K partial tiles: a wave's accumulators in the order (i, j, register quad, lane), 16
+// acc += x * y, 16x16x32.  An instruction of its own in asm for one reason: its sum has to stay in its registers.  The compiler ties the
+// sums of 32x32 instructions to their inputs but not those of four registers, moves them about between the two halves of a K
+// tile and then spills (50 registers of the 256x256 tile).  What the compiler would see to otherwise: nothing but other
+// such instructions touches a sum before settled().
+__device__ __forceinline__ void mfma_into(f32x4& acc, const bf16x8& x, const bf16x8& y) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(__builtin_bit_cast(f32x4, x)), "v"(__builtin_bit_cast(f32x4, y)));
+#endif
+}
+// The last of them are over (a result is there 11 cycles of issue behind its instruction): other instructions may use the sums.
+template <int TM, int TN>
+__device__ __forceinline__ void settled(f32x4 (&acc)[TM][TN]) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("s_nop 15" ::: "memory");
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) asm volatile("" : "+v"(acc[i][j]));
+#endif
+}
+
+__device__ __forceinline__ void wait_lgkm0() { __builtin_amdgcn_s_waitcnt(0xC07F); }
+
+// Split-K partial tiles: a wave's accumulators in the order (i, j, lane), 16
 // bytes per lane, so that every wave-store covers 1 KB of consecutive addresses.  The
 // fix-up kernel reads them back in the same order: no layout knowledge beyond this pair.
 template <int TM, int TN>
-__device__ __forceinline__ void store_partial(const f32x16 (&acc)[TM][TN], float* tile) {
+__device__ __forceinline__ void store_partial(const f32x4 (&acc)[TM][TN], float* tile) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  f32x4* dst = (f32x4*)tile + (size_t)wave * (TM * TN * 4 * 64) + lane;
+  f32x4* dst = (f32x4*)tile + (size_t)wave * (TM * TN * 64) + lane;
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        f32x4 v = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
-        dst[((i * TN + j) * 4 + q) * 64] = v;
-      }
+    for (int j = 0; j < TN; ++j) dst[(i * TN + j) * 64] = acc[i][j];
 }
 template <int TM, int TN>
-__device__ __forceinline__ void add_partial(f32x16 (&acc)[TM][TN], const float* tile, bool first) {
+__device__ __forceinline__ void add_partial(f32x4 (&acc)[TM][TN], const float* tile, bool first) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const f32x4* src = (const f32x4*)tile + (size_t)wave * (TM * TN * 4 * 64) + lane;
+  const f32x4* src = (const f32x4*)tile + (size_t)wave * (TM * TN * 64) + lane;
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
+    for (int j = 0; j < TN; ++j) {
+      const f32x4 v = src[(i * TN + j) * 64];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const f32x4 v = src[((i * TN + j) * 4 + q) * 64];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) acc[i][j][4 * q + e] = first ? v[e] : acc[i][j][4 * q + e] + v[e];
-      }
+      for (int e = 0; e < 4; ++e) acc[i][j][e] = first ? v[e] : acc[i][j][e] + v[e];
+    }
+}
+
+// Bias and gate of 256 columns of the output, from column bn0, to LDS (1 KB each); columns past N, never stored, read as zero.  By buffer
+// loads: behind a global_load_lds, which it takes for a flat access, the compiler waits for all LDS reads wherever it waits for one.
+template <typename Epi>
+__device__ __forceinline__ void dma_vectors(const Epi& epi, unsigned char* sbias, int wave, int lane, int bn0, int N) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  auto load = [&](const float* v, unsigned char* to) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void*)(v + bn0), 0, (N - bn0) * 4, 0x00020000), (lds_void*)to, 16, lane * 16, 0, 0, 0);
+  };
+  if (wave == 0 && epi.P.bias) load(epi.P.bias, sbias);
+  if (Epi::kHasGate && wave == 1 && epi.P.gate) load(epi.P.gate, sbias + 1024);
+#endif
 }
 
 // Epilogue of one BM x BN tile, shared by the product kernel and the split-K fix-up: bias,
 // activation / gate / q scale, conversion and stores.  `stage` is an idle operand stage of
 // the workgroup (output rows pass through it), sbias / sgate the tile's bias and gate slices.
 template <int BM, int BN, int WR, int WC, int STAGE_BYTES, typename Epi>
-__device__ __forceinline__ void gemm_tile_epilogue(const f32x16 (&acc)[BM / WR / 32][BN / WC / 32], unsigned char* stage,
+__device__ __forceinline__ void gemm_tile_epilogue(const f32x4 (&acc)[BM / WR / 16][BN / WC / 16], unsigned char* stage,
                                                    const float* sbias, const float* sgate, const Epi& epi, int bm0,
                                                    int bn0, int M, int N) {
   constexpr int NW = WR * WC;
   constexpr int WTM = BM / WR, WTN = BN / WC;
-  constexpr int TM = WTM / 32, TN = WTN / 32;
+  constexpr int TM = WTM / 16, TN = WTN / 16;
   // The lane and wave numbers pass through an empty asm: everything derived from them here (LDS
   // staging offsets, output offsets) is then computed inside the epilogue.  Left to itself the
   // compiler computes these per-lane constants once, ahead of the persistent tile loop, finds no
@@ -97,9 +122,9 @@ __device__ __forceinline__ void gemm_tile_epilogue(const f32x16 (&acc)[BM / WR /
   int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   asm volatile("" : "+v"(lane), "+v"(wave));
   const int wr = wave / WC, wc = wave % WC;
-  const int li = lane & 31, lh = lane >> 5;
+  const int li = lane & 15, lh = lane >> 4;
   if constexpr (Epi::kRowRuns) {
-    // Accumulator lane (li, lh) holds row m = 32 i + li, columns 32 j + 8 g + 4 lh + e.
+    // Accumulator lane (li, lh) holds row m = 16 i + li, columns 16 j + 4 lh + e.
     // The finished bf16 values go, 32 rows at a time, through this wave's slice of the
     // idle operand stage, swizzled by 16-byte chunk, and leave as 16-byte stores: a
     // wave-store covers whole 2 WTN-byte row segments instead of 2 bytes per lane.
@@ -116,18 +141,19 @@ __device__ __forceinline__ void gemm_tile_epilogue(const f32x16 (&acc)[BM / WR /
     unsigned char* cst = stage + wave * (32 * ROWB);
     const int wave_u = __builtin_amdgcn_readfirstlane(wave), wr_u = wave_u / WC, wc_u = wave_u % WC;   // known to be uniform
 #pragma unroll
-    for (int i = 0; i < TM; ++i) {
+    for (int i = 0; i < TM / 2; ++i) {
 #pragma unroll
       for (int j = 0; j < TN; ++j)
 #pragma unroll
-        for (int gq = 0; gq < 4; ++gq) {
-          const int n0 = bn0 + wc * WTN + j * 32 + gq * 8 + lh * 4;
-          float v[4] = {acc[i][j][4 * gq], acc[i][j][4 * gq + 1], acc[i][j][4 * gq + 2], acc[i][j][4 * gq + 3]};
-          epi.apply4(n0, v, sbias + (n0 - bn0), sgate + (n0 - bn0));
+        for (int h = 0; h < 2; ++h) {
+          const f32x4& a = acc[2 * i + h][j];
+          const int c0 = j * 16 + lh * 4, row = h * 16 + li;      // of the wave's columns, of the pass's rows
+          float v[4] = {a[0], a[1], a[2], a[3]};
+          epi.apply4(bn0 + wc * WTN + c0, v, sbias + wc * WTN + c0, sgate + wc * WTN + c0);
           bf16x4 o;
 #pragma unroll
           for (int e = 0; e < 4; ++e) o[e] = (bf16_t)v[e];
-          *(bf16x4*)(cst + li * ROWB + (swz(li, 4 * j + gq) << 4) + lh * 8) = o;
+          *(bf16x4*)(cst + row * ROWB + (swz(row, 2 * j + (lh >> 1)) << 4) + (lh & 1) * 8) = o;
         }
       constexpr int NIT = 32 * CPRW / 64;
       if (bm0 + BM <= M && bn0 + BN <= N) {
@@ -173,50 +199,76 @@ __device__ __forceinline__ void gemm_tile_epilogue(const f32x16 (&acc)[BM / WR /
     }
   } else {
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+    for (int j = 0; j < TN; ++j) {
+      const auto col = epi.col(bn0 + wc * WTN + j * 16 + li);
 #pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const auto col = epi.col(bn0 + wc * WTN + j * 32 + li);
-#pragma unroll
-        for (int gq = 0; gq < 4; ++gq) {
-          const int m0 = bm0 + wr * WTM + i * 32 + gq * 8 + lh * 4;
-          float v[4] = {acc[i][j][4 * gq], acc[i][j][4 * gq + 1], acc[i][j][4 * gq + 2], acc[i][j][4 * gq + 3]};
-          epi.store4(col, m0, v);
-        }
+      for (int i = 0; i < TM; ++i) {
+        const float v[4] = {acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]};
+        epi.store4(col, bm0 + wr * WTM + i * 16 + lh * 4, v);
       }
+    }
   }
 }
 
-template <int BM, int BN, int BK, int WR, int WC, int S, typename Epi>
-__global__ __launch_bounds__(WR * WC * 64) void k_gemm_dlds_any(const bf16_t* __restrict__ A,
-                                                            const bf16_t* __restrict__ Wt, int M, int N, int K,
-                                                            int tiles_m, int tiles_n, Epi epi, int splits,
-                                                            float* __restrict__ partial) {
-  static_assert(S == 2, "two stages: one being multiplied, one in flight");
+// s_waitcnt vmcnt(N) lgkmcnt(0)
+template <int N> __device__ __forceinline__ void wait_vm_lgkm0() {
+  __builtin_amdgcn_s_waitcnt((N & 0xF) | ((N >> 4) << 14) | (0x7 << 4));
+}
+// The same where the operations that may stay in flight are plain loads: nothing that touches memory moves across, neither in the
+// optimiser (the empty asm; it does not hold loads through a __restrict__ pointer, which such a kernel therefore does not take) nor
+// in the scheduler.
+template <int N> __device__ __forceinline__ void counted_wait_lgkm0() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+  wait_vm_lgkm0<N>();
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("" ::: "memory");
+}
+// ---------------------------------------------------------------- the product kernel
+// Addresses are buffer offsets.  A lane's byte offset inside an operand panel is the
+// same for every tile and every K tile: the tile enters through the base of a buffer resource
+// rebuilt per tile in scalar registers, the K tile through the scalar offset of the load.  Rows
+// past the end of an operand are out of the resource's range and load as zero.
+//
+// A K tile is 2 TN columns of products (two halves of K, 32 each), TM matrix instructions a column.  The fragment of
+// a column is read AHEAD columns before it is multiplied; the row fragments of the second half are read
+// during the first.  The barrier that publishes K tile g + 1 sits TAIL columns before the end of g, whose
+// fragments are all in registers by then.  After it a wave requests K tile g + 2 into the stage it
+// has just stopped reading, reads the first fragments of g + 1, and only then multiplies g's
+// last columns: neither the requests nor the LDS latency of the first fragments find the matrix
+// pipe empty, and a DMA still has a whole K tile of matrix work to land.
+// us, with 32x32x16 instructions and this form, same products by turns: 256x256 tiles 17776 x 12288 x 3072 1108, 1046, 9326 x 8192 x 2048
+// 284, 263; 384x192 17776 x 3072 x 12288 1047, 981; 256x192 32768 x 1152 x 1152 98, 92; 128x128 9326 x 2048 x 2048 85, 80.
+template <int BM, int BN, int BK, int WR, int WC, typename Epi>
+__global__ __launch_bounds__(WR * WC * 64) void k_gemm_dlds(const bf16_t* __restrict__ A, const bf16_t* __restrict__ Wt,
+                                                           int M, int N, int K, int tiles_m, int tiles_n, Epi epi,
+                                                           int splits, float* __restrict__ partial) {
+#if defined(__HIP_DEVICE_COMPILE__)   // buffer resources are a device-side type: the host pass sees an empty body
   constexpr int NW = WR * WC;
   constexpr int WTM = BM / WR, WTN = BN / WC;
-  constexpr int TM = WTM / 32, TN = WTN / 32;
-  constexpr int CPR = BK / 8;              // 16-byte chunks per row
-  constexpr int RPL = 16 / CPR;            // rows per 256-byte LDS line
-  constexpr int RW = 4 * RPL;              // rows per wave-load (1 KB)
-  constexpr int ROWS = BM + BN;
-  constexpr int WL = ROWS / RW;            // wave-loads per stage
-  constexpr int LPW = WL / NW;             // per wave
-  constexpr int STAGE_BYTES = ROWS * BK * 2;
-  static_assert(WL % NW == 0, "loads must divide among waves");
-  static_assert(BM % RW == 0, "A/B boundary must fall between wave-loads");
+  constexpr int TM = WTM / 16, TN = WTN / 16;
+  constexpr int AHEAD = TN < 5 ? TN : 5, TAIL = AHEAD - 1, COLS = 2 * TN;
+  static_assert(BK == 64, "128-byte rows, two halves of 32");
+  static_assert(TN >= 4 && TM <= 2 * TN, "fragments of the second half are read during the first");
+  constexpr int CPR = BK / 8, RPL = 16 / CPR, RW = 4 * RPL;
+  constexpr int LA = BM / RW / NW, LB = BN / RW / NW;      // wave-loads per wave and K tile: rows of A, rows of Wt
+  static_assert(BM % (RW * NW) == 0 && BN % (RW * NW) == 0, "loads must divide among waves");
+  static_assert(LB <= LA, "B shares A's lane offsets");
+  static_assert((NW * 4) % CPR == 0 && (BM / RW * 4) % CPR == 0, "the swizzle must not depend on the load index");
+  constexpr int STAGE_BYTES = (BM + BN) * BK * 2;
+  constexpr int B_REGION = BM * BK * 2;
 
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   // bias and gate of the current tile's BN columns, 1 KB each behind the two operand stages:
   // fetched by DMA with the tile's first operand loads, read by the epilogue from LDS.  With
   // loads from global memory in the epilogue every one of them was waited for in turn, behind
   // the stores issued before it (the counter is shared): 10 000 cycles per 256x192 tile.
-  float* const sbias = (float*)(smem + S * STAGE_BYTES);
+  float* const sbias = (float*)(smem + 2 * STAGE_BYTES);
   float* const sgate = sbias + 256;
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wr = wave / WC, wc = wave % WC;
-  const int li = lane & 31, lh = lane >> 5;
+  const int li = lane & 15, lh = lane >> 4;
   // an absent bias reads as zeros, an absent gate as ones (written once: no DMA touches them)
   if constexpr (Epi::kRowRuns) {
     if (tid < 256) {
@@ -268,251 +320,6 @@ __global__ __launch_bounds__(WR * WC * 64) void k_gemm_dlds_any(const bf16_t* __
     return false;
   };
 
-  // ---- global source pointers of this lane for its LPW wave-loads of a tile
-  auto sources = [&](int bm0, int bn0, int kt_first, const bf16_t* (&gp)[LPW]) {
-#pragma unroll
-    for (int j = 0; j < LPW; ++j) {
-      const int wl = wave + NW * j;
-      const int line_in = lane >> 4, slot = lane & 15;
-      const int row = wl * RW + line_in * RPL + slot / CPR;
-      const int kc = (slot % CPR) ^ ((wl * 4 + line_in) % CPR);
-      if (row < BM) {
-        int gm = bm0 + row; gm = gm < M ? gm : M - 1;
-        gp[j] = A + (size_t)gm * K + kc * 8 + kt_first * BK;
-      } else {
-        int gn = bn0 + row - BM; gn = gn < N ? gn : N - 1;
-        gp[j] = Wt + (size_t)gn * K + kc * 8 + kt_first * BK;
-      }
-    }
-  };
-  auto issue = [&](const bf16_t* const (&gp)[LPW], int kt, int stage) {
-#pragma unroll
-    for (int j = 0; j < LPW; ++j) {
-      const int wl = wave + NW * j;
-      __builtin_amdgcn_global_load_lds((gbl_void*)(gp[j] + (size_t)kt * BK),
-                                       (lds_void*)(smem + stage * STAGE_BYTES + wl * 1024), 16, 0, 0);
-    }
-  };
-
-  auto issue_vectors = [&](int bn0) {
-    if constexpr (Epi::kRowRuns) {
-      int n = bn0 + lane * 4;
-      n = n < N ? n : 0;                           // columns past N are never stored
-      if (wave == 0 && epi.P.bias)
-        __builtin_amdgcn_global_load_lds((gbl_void*)(epi.P.bias + n), (lds_void*)sbias, 16, 0, 0);
-      if (Epi::kHasGate && wave == 1 && epi.P.gate)
-        __builtin_amdgcn_global_load_lds((gbl_void*)(epi.P.gate + n), (lds_void*)sgate, 16, 0, 0);
-    }
-  };
-
-  // ---- fragment read offsets (bytes within a stage)
-  const int ra = wr * WTM + li, rb = BM + wc * WTN + li;
-  const int a_row = (ra / RPL) * 256 + (ra % RPL) * CPR * 16, a_x = (ra / RPL) % CPR;
-  const int b_row = (rb / RPL) * 256 + (rb % RPL) * CPR * 16, b_x = (rb / RPL) % CPR;
-  constexpr int TILE_STRIDE = (32 / RPL) * 256;   // 32 rows further down
-
-  int vb = (int)blockIdx.x - (int)gridDim.x, bm0 = 0, bn0 = 0, kt0 = 0, kt1 = 0, slot = -1;
-  if (!next_tile(vb, bm0, bn0, kt0, kt1, slot)) return;
-  const bf16_t* gp[LPW];
-  sources(bm0, bn0, kt0, gp);
-  int nk = kt1 - kt0;                              // K tiles of the current unit; gp points at its first one
-  issue(gp, 0, 0);
-  wait_vm<0>();
-  __builtin_amdgcn_s_barrier();
-  int g = 0;                                       // K tiles consumed so far; the current one sits in stage g & 1
-
-  // One pass per output tile.  The operand pipeline runs across tiles: the first K tile of
-  // the workgroup's next output tile is requested while the last K tile of this one is
-  // being multiplied, and lands during the epilogue.
-  for (;;) {
-    int nvb = vb, nbm0 = 0, nbn0 = 0, nkt0 = 0, nkt1 = 0, nslot = -1;
-    const bool has_next = next_tile(nvb, nbm0, nbn0, nkt0, nkt1, nslot);
-    const bf16_t* gpn[LPW];
-    if (has_next) sources(nbm0, nbn0, nkt0, gpn);
-
-    f32x16 acc[TM][TN];
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
-
-    for (int kt = 0; kt < nk; ++kt, ++g) {
-      if (kt > 0) {                                // the unit's first K tile was awaited and published before the previous epilogue
-        wait_vm<0>();
-        __builtin_amdgcn_s_barrier();
-      }
-      if (kt == 0) issue_vectors(bn0);
-      if (kt + 1 < nk) issue(gp, kt + 1, (g + 1) & 1);
-      else if (has_next) issue(gpn, 0, (g + 1) & 1);
-      const unsigned char* st = smem + (g & 1) * STAGE_BYTES;
-      // Fragment reads run one 16-wide k-slice ahead of the MFMAs that consume them, in
-      // two register sets.  The scheduling groups below pin the instruction order the
-      // compiler would otherwise collapse into read-all / wait / multiply: after the first
-      // slice's reads, every read of slice ks+1 is paired with one MFMA of slice ks, so the
-      // LDS latency is spent under matrix work of the same wave.
-      constexpr int KS = BK / 16;
-      bf16x8 fa[2][TM], fb[2][TN];
-      auto load = [&](int ks, bf16x8 (&xa)[TM], bf16x8 (&xb)[TN]) {
-        const unsigned char* pa = st + a_row + (((2 * ks + lh) ^ a_x) << 4);
-        const unsigned char* pb = st + b_row + (((2 * ks + lh) ^ b_x) << 4);
-#pragma unroll
-        for (int i = 0; i < TM; ++i) xa[i] = *(const bf16x8*)(pa + i * TILE_STRIDE);
-#pragma unroll
-        for (int j = 0; j < TN; ++j) xb[j] = *(const bf16x8*)(pb + j * TILE_STRIDE);
-      };
-      load(0, fa[0], fb[0]);
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        if (ks + 1 < KS) load(ks + 1, fa[(ks + 1) & 1], fb[(ks + 1) & 1]);
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-          for (int j = 0; j < TN; ++j)
-            // row-run epilogues want a lane to hold consecutive n: D rows come from the A
-            // operand, so the weight fragment goes there (the operand layouts are alike)
-            acc[i][j] = Epi::kRowRuns
-                            ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[ks & 1][j], fa[ks & 1][i], acc[i][j], 0, 0, 0)
-                            : __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[ks & 1][i], fb[ks & 1][j], acc[i][j], 0, 0, 0);
-      }
-      constexpr int kDsRead = 0x100, kMfma = 0x008;
-      __builtin_amdgcn_sched_group_barrier(kDsRead, TM + TN, 0);
-#pragma unroll
-      for (int ks = 0; ks + 1 < KS; ++ks) {
-#pragma unroll
-        for (int r = 0; r < TM + TN; ++r) {
-          __builtin_amdgcn_sched_group_barrier(kMfma, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(kDsRead, 1, 0);
-        }
-        if (TM * TN > TM + TN) __builtin_amdgcn_sched_group_barrier(kMfma, TM * TN - (TM + TN), 0);
-      }
-      __builtin_amdgcn_sched_group_barrier(kMfma, TM * TN, 0);
-    }
-
-    // the next output tile's first K tile has landed (stage g & 1); every wave is done
-    // reading the stage just multiplied ((g - 1) & 1), which the epilogue may now reuse
-    wait_vm<0>();
-    __builtin_amdgcn_s_barrier();
-
-    if (slot < 0) {
-      gemm_tile_epilogue<BM, BN, WR, WC, STAGE_BYTES>(acc, smem + ((g - 1) & 1) * STAGE_BYTES, sbias, sgate, epi, bm0, bn0, M, N);
-    } else {
-      store_partial<TM, TN>(acc, partial + (size_t)slot * (BM * BN));
-    }
-    if (!has_next) break;
-    // the staging slices are read out: the next tile's second K tile may overwrite that stage
-    __builtin_amdgcn_s_barrier();
-    vb = nvb; bm0 = nbm0; bn0 = nbn0; nk = nkt1 - nkt0; slot = nslot;
-#pragma unroll
-    for (int j = 0; j < LPW; ++j) gp[j] = gpn[j];
-  }
-}
-
-// ---------------------------------------------------------------- the product kernel
-// Same tiles, LDS layout, tile order and epilogue as k_gemm_dlds_any above (which stays for the
-// shapes this one does not take), with two changes to the K loop.
-//
-// Addresses are buffer offsets.  A lane's byte offset inside a 256-row operand panel is the
-// same for every tile and every K tile: the tile enters through the base of a buffer resource
-// rebuilt per tile in scalar registers, the K tile through the scalar offset of the load.  The
-// per-lane pointer arrays of k_gemm_dlds_any (32 registers, recomputed per tile, advanced per
-// K tile with 64-bit vector adds) are gone, and so are the clamps at the ragged edges: rows
-// past the end of an operand are out of the resource's range and load as zero.
-//
-// The barrier that publishes K tile g + 1 sits before the MFMAs of g's last k-slice, whose
-// fragments are in registers by then.  After it a wave requests K tile g + 2 into the stage it
-// has just stopped reading, reads the first fragments of g + 1, and only then multiplies g's
-// last slice: neither the requests nor the LDS latency of the first fragments find the matrix
-// pipe empty, and a DMA still has a whole K tile of matrix work to land.
-//
-// Measured against k_gemm_dlds_any in one process, bit-identical results: 5-11 % faster on the
-// products of the two large configurations (K = 1152 .. 3072), 5 % at K = 12288, level at
-// 256x192 with K = 4608, 5-10 % on the 128x128 products of a single block.
-//
-// Needs an even number of K tiles (the stage of a K tile is a compile-time constant: units
-// start at stage 0) and operands below 4 GB (32-bit buffer ranges).
-// s_waitcnt vmcnt(N) lgkmcnt(0)
-template <int N> __device__ __forceinline__ void wait_vm_lgkm0() {
-  __builtin_amdgcn_s_waitcnt((N & 0xF) | ((N >> 4) << 14) | (0x7 << 4));
-}
-// The same where the operations that may stay in flight are plain loads: nothing that touches memory moves across, neither in the
-// optimiser (the empty asm; it does not hold loads through a __restrict__ pointer, which such a kernel therefore does not take) nor
-// in the scheduler.
-template <int N> __device__ __forceinline__ void counted_wait_lgkm0() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_sched_barrier(0);
-  wait_vm_lgkm0<N>();
-  __builtin_amdgcn_sched_barrier(0);
-  asm volatile("" ::: "memory");
-}
-template <int BM, int BN, int BK, int WR, int WC, typename Epi>
-__global__ __launch_bounds__(WR * WC * 64) void k_gemm_dlds(const bf16_t* __restrict__ A, const bf16_t* __restrict__ Wt,
-                                                           int M, int N, int K, int tiles_m, int tiles_n, Epi epi,
-                                                           int splits, float* __restrict__ partial) {
-#if defined(__HIP_DEVICE_COMPILE__)   // buffer resources are a device-side type: the host pass sees an empty body
-  constexpr int NW = WR * WC;
-  constexpr int WTM = BM / WR, WTN = BN / WC;
-  constexpr int TM = WTM / 32, TN = WTN / 32;
-  static_assert(BK == 64, "128-byte rows");
-  constexpr int CPR = BK / 8, RPL = 16 / CPR, RW = 4 * RPL;
-  constexpr int LA = BM / RW / NW, LB = BN / RW / NW;      // wave-loads per wave and K tile: rows of A, rows of Wt
-  static_assert(BM % (RW * NW) == 0 && BN % (RW * NW) == 0, "loads must divide among waves");
-  static_assert(LB <= LA, "B shares A's lane offsets");
-  static_assert((NW * 4) % CPR == 0 && (BM / RW * 4) % CPR == 0, "the swizzle must not depend on the load index");
-  constexpr int STAGE_BYTES = (BM + BN) * BK * 2;
-  constexpr int B_REGION = BM * BK * 2;
-  constexpr int KS = BK / 16;
-
-  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-  float* const sbias = (float*)(smem + 2 * STAGE_BYTES);
-  float* const sgate = sbias + 256;
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wr = wave / WC, wc = wave % WC;
-  const int li = lane & 31, lh = lane >> 5;
-  // an absent bias reads as zeros, an absent gate as ones (written once: no DMA touches them)
-  if constexpr (Epi::kRowRuns) {
-    if (tid < 256) {
-      if (!epi.P.bias) sbias[tid] = 0.0f;
-      if (Epi::kHasGate && !epi.P.gate) sgate[tid] = 1.0f;
-    }
-  }
-
-  // ---- units of work (as in k_gemm_dlds_any; split ranges start at even K tiles)
-  const int total = tiles_m * tiles_n;
-  const int nkt = K / BK;
-  const int full = total / 256 * 256, rem = total - full;
-  // virtual ids run over the whole rounds and, behind them, the units of the last one
-  const int padded = splits >= 2 ? ((full + rem * splits + 7) & ~7) : (total + 255) / 256 * 256;
-  auto tile_of = [&](int vb, int& bm0, int& bn0, int& kt0, int& kt1, int& slot) {
-    const int xcd = vb & 7, local = vb >> 3;
-    int t = ((local >> 5) * 8 + xcd) * 32 + (local & 31);
-    kt0 = 0; kt1 = nkt; slot = -1;
-    if (splits >= 2 && vb >= full) {
-      const int w = vb - full;
-      if (w >= rem * splits) return false;
-      const int r = w / rem;
-      t = full + w % rem;
-      kt0 = (r * nkt / splits) & ~1; kt1 = r + 1 == splits ? nkt : ((r + 1) * nkt / splits) & ~1;   // even: see the K loop
-      slot = (w % rem) * splits + r;
-    }
-    if (t >= total) return false;
-    constexpr int GM = 8;
-    const int per_group = GM * tiles_n;
-    const int group = t / per_group;
-    const int first_m = group * GM;
-    const int gsz = min(tiles_m - first_m, GM);
-    bm0 = (first_m + (t % per_group) % gsz) * BM;
-    bn0 = ((t % per_group) / gsz) * BN;
-    return true;
-  };
-  auto next_tile = [&](int& vb, int& bm0, int& bn0, int& kt0, int& kt1, int& slot) {
-    for (vb += gridDim.x; vb < padded; vb += gridDim.x)
-      if (tile_of(vb, bm0, bn0, kt0, kt1, slot)) return true;
-    return false;
-  };
-
   // ---- this lane's byte offsets inside an operand panel, one per wave-load (the swizzled
   // 16-byte chunk of row (wave + NW j) RW + ... that lands in its LDS slot)
   unsigned voff[LA];
@@ -524,166 +331,112 @@ __global__ __launch_bounds__(WR * WC * 64) void k_gemm_dlds(const bf16_t* __rest
     for (int j = 0; j < LA; ++j) voff[j] = (unsigned)(row0 + NW * RW * j) * (unsigned)K * 2u + (unsigned)kc * 16u;
   }
   struct Panels { __amdgpu_buffer_rsrc_t a, b; int kbase; };
-  auto panels = [&](int bm0, int bn0, int kt_first) {
+  auto panels = [&](int bm0, int bn0, int kt_first) {      // (the rows of a tile alone: below 4 GB, however large the operand)
     Panels p;
-    p.a = __builtin_amdgcn_make_buffer_rsrc((void*)(A + (size_t)bm0 * K), 0, (int)((unsigned)(M - bm0) * (unsigned)K * 2u), 0x00020000);
-    p.b = __builtin_amdgcn_make_buffer_rsrc((void*)(Wt + (size_t)bn0 * K), 0, (int)((unsigned)(N - bn0) * (unsigned)K * 2u), 0x00020000);
+    p.a = __builtin_amdgcn_make_buffer_rsrc((void*)(A + (size_t)bm0 * K), 0, (int)((unsigned)min(M - bm0, BM) * (unsigned)K * 2u), 0x00020000);
+    p.b = __builtin_amdgcn_make_buffer_rsrc((void*)(Wt + (size_t)bn0 * K), 0, (int)((unsigned)min(N - bn0, BN) * (unsigned)K * 2u), 0x00020000);
     p.kbase = kt_first * BK * 2;
     return p;
   };
-  auto dma_a = [&](const Panels& p, int kt, int stage) {
-#pragma unroll
-    for (int j = 0; j < LA; ++j)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(p.a, (lds_void*)(smem + stage * STAGE_BYTES + (wave + NW * j) * 1024), 16, (int)voff[j],
+  auto dma = [&](const Panels& p, int kt, int stage, int j) {         // wave-load j of LA + LB
+    if (j < LA)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(p.a, (lds_void*)(smem + stage + (wave + NW * j) * 1024), 16, (int)voff[j], p.kbase + kt * (BK * 2), 0, 0);
+    else
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(p.b, (lds_void*)(smem + stage + B_REGION + (wave + NW * (j - LA)) * 1024), 16, (int)voff[j - LA],
                                                p.kbase + kt * (BK * 2), 0, 0);
   };
-  auto dma_b = [&](const Panels& p, int kt, int stage) {
-#pragma unroll
-    for (int j = 0; j < LB; ++j)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(p.b, (lds_void*)(smem + stage * STAGE_BYTES + B_REGION + (wave + NW * j) * 1024), 16,
-                                               (int)voff[j], p.kbase + kt * (BK * 2), 0, 0);
-  };
-  auto issue_vectors = [&](int bn0) {
-    if constexpr (Epi::kRowRuns) {
-      int n = bn0 + lane * 4;
-      n = n < N ? n : 0;                           // columns past N are never stored
-      if (wave == 0 && epi.P.bias)
-        __builtin_amdgcn_global_load_lds((gbl_void*)(epi.P.bias + n), (lds_void*)sbias, 16, 0, 0);
-      if (Epi::kHasGate && wave == 1 && epi.P.gate)
-        __builtin_amdgcn_global_load_lds((gbl_void*)(epi.P.gate + n), (lds_void*)sgate, 16, 0, 0);
-    }
-  };
-
-  // ---- fragment read offsets (bytes within a stage)
-  const int ra = wr * WTM + li, rb = BM + wc * WTN + li;
-  const int a_row = (ra / RPL) * 256 + (ra % RPL) * CPR * 16, a_x = (ra / RPL) % CPR;
-  const int b_row = (rb / RPL) * 256 + (rb % RPL) * CPR * 16, b_x = (rb / RPL) % CPR;
-  constexpr int TILE_STRIDE = (32 / RPL) * 256;   // 32 rows further down
+  // ---- fragment read offsets (bytes within a stage): the chunk of half 0, half 1's is 64 bytes across
+  const int ra = wr * WTM + li, rb = wc * WTN + li;
+  const int oa = (ra / RPL) * 256 + (ra % RPL) * 128 + ((lh ^ ((ra / RPL) % CPR)) << 4);
+  const int ob = B_REGION + (rb / RPL) * 256 + (rb % RPL) * 128 + ((lh ^ ((rb / RPL) % CPR)) << 4);
 
   int vb = (int)blockIdx.x - (int)gridDim.x, bm0 = 0, bn0 = 0, kt0 = 0, kt1 = 0, slot = -1;
   if (!next_tile(vb, bm0, bn0, kt0, kt1, slot)) return;
   Panels cur = panels(bm0, bn0, kt0);
-  int nk = kt1 - kt0;                              // K tiles of the current unit, at least 2
-
-  // K tiles are numbered g = 0, 1, ... across this workgroup's units; K tile g is multiplied
-  // out of stage g & 1.
-  dma_a(cur, 0, 0);
-  dma_b(cur, 0, 0);
+  int nk = kt1 - kt0;                              // K tiles of the current unit, at least 1
+  int at = 0;                                      // offset of the stage that holds the K tile being multiplied
+#pragma unroll
+  for (int j = 0; j < LA + LB; ++j) dma(cur, 0, at, j);
   wait_vm<0>();
   __builtin_amdgcn_s_barrier();
-  int g = 0;
 
-  constexpr int kDsRead = 0x100, kMfma = 0x008, kVmem = 0x010;
   for (;;) {
     int nvb = vb, nbm0 = 0, nbn0 = 0, nkt0 = 0, nkt1 = 0, nslot = -1;
     const bool has_next = next_tile(nvb, nbm0, nbn0, nkt0, nkt1, nslot);
     Panels nxt = cur;
     if (has_next) nxt = panels(nbm0, nbn0, nkt0);
-    issue_vectors(bn0);                            // awaited and published with the unit's first K tile
+    if constexpr (Epi::kRowRuns) dma_vectors(epi, smem + 2 * STAGE_BYTES, wave, lane, bn0, N);      // awaited and published with the unit's first K tile
 
-    f32x16 acc[TM][TN];
+    f32x4 acc[TM][TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
-
+      for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     bf16x8 fa[2][TM], fb[2][TN];
-    auto load = [&](int stage, int ks, bf16x8 (&xa)[TM], bf16x8 (&xb)[TN]) {
-      const unsigned char* st = smem + stage * STAGE_BYTES;
-      const unsigned char* pa = st + a_row + (((2 * ks + lh) ^ a_x) << 4);
-      const unsigned char* pb = st + b_row + (((2 * ks + lh) ^ b_x) << 4);
-#pragma unroll
-      for (int i = 0; i < TM; ++i) xa[i] = *(const bf16x8*)(pa + i * TILE_STRIDE);
-#pragma unroll
-      for (int j = 0; j < TN; ++j) xb[j] = *(const bf16x8*)(pb + j * TILE_STRIDE);
-    };
-    auto multiply = [&](int set) {
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-          // row-run epilogues want a lane to hold consecutive n: D rows come from the A
-          // operand, so the weight fragment goes there (the operand layouts are alike)
-          acc[i][j] = Epi::kRowRuns ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[set][j], fa[set][i], acc[i][j], 0, 0, 0)
-                                    : __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[set][i], fb[set][j], acc[i][j], 0, 0, 0);
-    };
-    // requests K tile ka of this unit into `stage`, continuing into the next unit past the end;
-    // past the last K tile of the last unit K tile 0 of the current panels is requested again
-    // (in range, never read) rather than branching around the loads
-    auto request = [&](int ka, int stage) {
-      const bool ina = ka < nk;
-      const Panels& pa = ina ? cur : nxt;
-      const int k = ina ? ka : (has_next ? ka - nk : 0);
-      dma_a(pa, k, stage);
-      dma_b(pa, k, stage);
+    // fragment r of a stage's first ones: the rows' half 0, AHEAD columns
+    auto load_a = [&](int stage, int half, int i) { fa[half][i] = *(const bf16x8*)(smem + stage + (oa ^ (half * 64)) + i * 2048); };
+    auto load_b = [&](int stage, int n) { fb[n / TN][n % TN] = *(const bf16x8*)(smem + stage + (ob ^ (n / TN * 64)) + n % TN * 2048); };
+    auto load_first = [&](int stage, int r) { if (r < TM) load_a(stage, 0, r); else load_b(stage, r - TM); };
+    auto multiply = [&](int n, int i) {
+      // row-run epilogues want a lane to hold consecutive n: D rows come from the A
+      // operand, so the weight fragment goes there (the operand layouts are alike)
+      if constexpr (Epi::kRowRuns) mfma_into(acc[i][n % TN], fb[n / TN][n % TN], fa[n / TN][i]);
+      else mfma_into(acc[i][n % TN], fa[n / TN][i], fb[n / TN][n % TN]);
     };
 
-    // One K tile.  PAR = g & 1 selects the stage at compile time: every unit has an even number
-    // of K tiles (the dispatcher sends other K to k_gemm_dlds_any), so a unit always starts at
-    // PAR 0.  FIRST: the unit's first K tile (its successor not requested yet, no fragments in
-    // registers: the only reads of a unit with no matrix work in front of them); LAST: its last
-    // one (no requests: the stage it frees is where the epilogue stages its output rows).
-    auto kstep = [&](auto par, auto first, auto last, int kt) {
-      constexpr int PAR = decltype(par)::value;
-      constexpr bool FIRST = decltype(first)::value, LAST = decltype(last)::value;
-      if constexpr (FIRST) {
-        request(kt + 1, PAR ^ 1);
-        load(PAR, 0, fa[0], fb[0]);
-        __builtin_amdgcn_sched_group_barrier(kVmem, LA + LB, 0);
-        __builtin_amdgcn_sched_group_barrier(kDsRead, TM + TN, 0);
-      }
-      // k-slices 0 .. KS-2; the fragments of slice ks + 1 are read under the MFMAs of slice ks,
-      // the order pinned (left alone the compiler emits read-all / wait / multiply per slice)
+    // One K tile, in this order of instructions.  LAST: the unit's last one (no requests: the stage it frees is where the
+    // epilogue stages its output rows).
+    auto kstep = [&](auto last, int kt) {
+      constexpr bool LAST = decltype(last)::value;
 #pragma unroll
-      for (int ks = 0; ks + 1 < KS; ++ks) {
-        load(PAR, ks + 1, fa[(ks + 1) & 1], fb[(ks + 1) & 1]);
-        multiply(ks & 1);
-      }
+      for (int n = 0; n < COLS - TAIL; ++n) {
+        if (n + AHEAD < COLS) load_b(at, n + AHEAD);
 #pragma unroll
-      for (int ks = 0; ks + 1 < KS; ++ks) {
+        for (int i = 2 * n; i < 2 * n + 2; ++i)
+          if (i < TM) load_a(at, 1, i);
 #pragma unroll
-        for (int r = 0; r < TM + TN; ++r) {
-          __builtin_amdgcn_sched_group_barrier(kMfma, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(kDsRead, 1, 0);
-        }
-        if (TM * TN > TM + TN) __builtin_amdgcn_sched_group_barrier(kMfma, TM * TN - (TM + TN), 0);
+        for (int i = 0; i < TM; ++i) multiply(n, i);
+        __builtin_amdgcn_sched_barrier(0);
       }
-      wait_vm_lgkm0<0>();                          // K tile g + 1 has landed; this wave is done reading g
+      wait_vm_lgkm0<0>();                          // K tile kt + 1 has landed; this wave is done reading kt
       __builtin_amdgcn_s_barrier();
       __builtin_amdgcn_sched_barrier(0);
-      if constexpr (!LAST) {
-        request(kt + 2, PAR);
-        load(PAR ^ 1, 0, fa[0], fb[0]);
-      }
-      multiply((KS - 1) & 1);
-      if constexpr (!LAST) {
-        constexpr int PER = (LA + LB + TM * TN - 1) / (TM * TN);
+      // Requests K tile kt + 2 of this unit, continuing into the next unit past the end; past the last K tile of the
+      // last unit K tile 0 of the current panels again (in range, never read) rather than branching around the loads.
+      const bool ina = kt + 2 < nk;
+      const Panels& p = ina ? cur : nxt;
+      const int k = ina ? kt + 2 : (has_next ? kt + 2 - nk : 0);
 #pragma unroll
-        for (int r = 0; r < TM * TN; ++r) {
-          __builtin_amdgcn_sched_group_barrier(kMfma, 1, 0);
-          if (r < TM + TN) __builtin_amdgcn_sched_group_barrier(kDsRead, 1, 0);
-          if (r * PER < LA + LB) __builtin_amdgcn_sched_group_barrier(kVmem, PER, 0);
+      for (int r = 0; r < TAIL * TM; ++r) {
+        multiply(COLS - TAIL + r / TM, r % TM);
+        if constexpr (!LAST) {
+          if (r < TM + AHEAD) load_first(STAGE_BYTES - at, r);
+          if (r < LA + LB) dma(p, k, at, r);
+          __builtin_amdgcn_sched_barrier(0);
         }
       }
       __builtin_amdgcn_sched_barrier(0);
+      at = STAGE_BYTES - at;
     };
 
-    using P0 = std::integral_constant<int, 0>; using P1 = std::integral_constant<int, 1>;
-    using Yes = std::true_type; using No = std::false_type;
-    kstep(P0{}, Yes{}, No{}, 0);
-    for (int kt = 1; kt + 1 < nk; kt += 2) {
-      kstep(P1{}, No{}, No{}, kt);
-      kstep(P0{}, No{}, No{}, kt + 1);
+    {                                              // K tile 1, or the next unit's first one
+      const bool ina = nk > 1;
+      const Panels& p = ina ? cur : nxt;
+#pragma unroll
+      for (int j = 0; j < LA + LB; ++j) dma(p, ina ? 1 : 0, STAGE_BYTES - at, j);
     }
-    kstep(P1{}, No{}, Yes{}, nk - 1);
-    g += nk;
+#pragma unroll
+    for (int r = 0; r < TM + AHEAD; ++r) load_first(at, r);      // the only reads of a unit with no matrix work in front of them
+    wait_lgkm0();                                  // (and nothing else is on its way, so that the loop's waits can count)
+    __builtin_amdgcn_sched_barrier(0);
+    for (int kt = 0; kt + 1 < nk; ++kt) kstep(std::false_type{}, kt);
+    kstep(std::true_type{}, nk - 1);
+    settled(acc);
 
-    // every wave is done reading the stage just multiplied ((g - 1) & 1): the epilogue stages
+    // every wave is done reading the stage just multiplied: the epilogue stages
     // its output rows there; the next unit's first K tile is complete in the other stage
     if (slot < 0) {
-      gemm_tile_epilogue<BM, BN, WR, WC, STAGE_BYTES>(acc, smem + ((g - 1) & 1) * STAGE_BYTES, sbias, sgate, epi, bm0, bn0, M, N);
+      gemm_tile_epilogue<BM, BN, WR, WC, STAGE_BYTES>(acc, smem + (STAGE_BYTES - at), sbias, sgate, epi, bm0, bn0, M, N);
     } else {
       store_partial<TM, TN>(acc, partial + (size_t)slot * (BM * BN));
     }
@@ -697,24 +450,25 @@ __global__ __launch_bounds__(WR * WC * 64) void k_gemm_dlds(const bf16_t* __rest
 }
 
 // ---------------------------------------------------------------- the product kernel, weights straight to registers
-// For weights that were packed into fragment order when the model was loaded ([N / 32][K / 16][lane][8], k_pack_weights): a
+// For weights that were packed into fragment order when the model was loaded ([N / 16][K / 32][lane][8], k_pack_weights): a
 // fragment is 1 KB in a row and goes from L2 to the registers of the one wave column that needs it; LDS holds A alone.  A
 // workgroup is four waves side by side, each 128 rows by BN / 4 columns, so that no fragment is fetched twice, and small
-// enough that two (BN 256: 208 registers, 34 KB of LDS) or four of them (BN 128) share a CU: one's epilogue and first loads run
+// enough that two (BN 256: 204 registers, 34 KB of LDS) or four of them (BN 128: 125) share a CU: one's epilogue and first loads run
 // under another's products, and tiles half the size fill the last round better.  Of k_gemm_dlds it keeps the tile order, the
-// swizzled A stages, the K loop (even number of K tiles, barrier ahead of the last slice) and the epilogue.
-// A fragment's registers are loaded for the next K tile right behind the products that used them.  Sums are those of k_gemm_dlds bit
-// for bit where that does not split a tile along K.
+// swizzled A stages and the epilogue.  Sums are those of k_gemm_dlds bit for bit where that does not split a tile along K.
 //
-// Against k_gemm_dlds the 256x256 form of this kernel is level (990 and 994 us at 17776 x 12288 x 3072: a third less LDS traffic
-// buys nothing, the power limit bounds both), so what counts are rounds and epilogues (the rule is in the dispatch).
-// us, before and now: 9326 x 6144 x 2048 203, 178; 4096 x 4608 x 1152 49, 44; 8192 x 3456 x 1152 72, 67 (and where the rule stays with
-// 256x192 all the same: 32768 x 1152 x 4608 320, 287); 314 products of 300 to 33 000 rows, 576 to 3072 wide: 0.92 of the time in the mean.
+// Products go column by column of 16 weights, all 128 rows of a column in a row: a column's registers are loaded for the next K
+// tile right behind it and have nearly a whole K tile to arrive (row by row, with every column's registers in
+// use to the end of a half, that was half a K tile: 0 to 18 % slower, most where a CU has one or two workgroups).  The price is that all
+// row fragments of a half are needed from its first column on: they are replaced in place, one by one, under the last column before.
+// Bound by the power limit with large products (17776 x 12288 x 3072: 1361 TFLOP/s), by rounds of tiles with small ones.
+// us, 32x32x16 instructions row by row, and this form, operands by turns: 8192 x 1152 x 1152 (BN 128) 30.6, 25.5; 8192 x 3456 x 1152
+// (BN 256) 73.8, 63.1; 32768 x 4608 x 1152 314, 304; 32768 x 1152 x 4608 304, 283; 17776 x 9216 x 3072 783, 731.
 template <int BM, int BN, typename Epi>
-__global__ __launch_bounds__(256, 2) void k_gemm_packed(const bf16_t* A, const void* Wp, int M, int N,
+__global__ __launch_bounds__(256, BN == 128 ? 4 : 2) void k_gemm_packed(const bf16_t* A, const void* Wp, int M, int N,
                                                         int K, int tiles_m, int tiles_n, Epi epi) {
 #if defined(__HIP_DEVICE_COMPILE__)   // buffer resources are a device-side type: the host pass sees an empty body
-  constexpr int BK = 64, NW = 4, WTN = BN / NW, TM = BM / 32, TN = WTN / 32, KS = BK / 16;
+  constexpr int BK = 64, NW = 4, WTN = BN / NW, TM = BM / 16, TN = WTN / 16;
   constexpr int CPR = BK / 8, RPL = 16 / CPR, RW = 4 * RPL, LA = BM / RW / NW;
   static_assert(BM % (RW * NW) == 0 && BN % 128 == 0 && BN <= 256 && Epi::kRowRuns, "whole wave-loads; bias and gate slices of 256");
   constexpr int STAGE_BYTES = BM * BK * 2;
@@ -723,7 +477,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_packed(const bf16_t* A, const v
   float* const sgate = sbias + 256;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int li = lane & 31, lh = lane >> 5;
+  const int li = lane & 15, lh = lane >> 4;
   // an absent bias reads as zeros, an absent gate as ones (written once: no DMA touches them)
   if (!epi.P.bias) sbias[tid] = 0.0f;
   if (Epi::kHasGate && !epi.P.gate) sgate[tid] = 1.0f;
@@ -748,130 +502,95 @@ __global__ __launch_bounds__(256, 2) void k_gemm_packed(const bf16_t* A, const v
     for (int j = 0; j < LA; ++j) voff[j] = (unsigned)(row0 + NW * RW * j) * (unsigned)K * 2u + (unsigned)kc * 16u;
   }
   struct Panels { __amdgpu_buffer_rsrc_t a; int b[TN]; };
-  // Rows past the end of A load as zero; columns past N, which are never stored, repeat the last 32 columns: the offset that
+  // Rows past the end of A load as zero; columns past N, which are never stored, repeat the last 16 columns: the offset that
   // chooses a fragment is a scalar one, which the buffer's range check does not cover.
   auto panels = [&](int bm0, int bn0) {
     Panels p;
     p.a = __builtin_amdgcn_make_buffer_rsrc((void*)(A + (size_t)bm0 * K), 0, (int)((unsigned)(M - bm0) * (unsigned)K * 2u), 0x00020000);
 #pragma unroll
-    for (int j = 0; j < TN; ++j) p.b[j] = min((bn0 + wave * WTN) / 32 + j, N / 32 - 1) * (K / 16) * 1024;
+    for (int j = 0; j < TN; ++j) p.b[j] = min((bn0 + wave * WTN) / 16 + j, N / 16 - 1) * (K / 32) * 1024;
     return p;
   };
   const auto rb = __builtin_amdgcn_make_buffer_rsrc((void*)Wp, 0, (int)((unsigned)N * (unsigned)K * 2u), 0x00020000);
-  auto dma_a = [&](const Panels& p, int kt, int stage) {
-#pragma unroll
-    for (int j = 0; j < LA; ++j)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(p.a, (lds_void*)(smem + stage * STAGE_BYTES + (wave + NW * j) * 1024), 16, (int)voff[j], kt * (BK * 2), 0, 0);
+  auto dma_a = [&](const Panels& p, int kt, int stage, int j) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(p.a, (lds_void*)(smem + stage + (wave + NW * j) * 1024), 16, (int)voff[j], kt * (BK * 2), 0, 0);
   };
-  auto issue_vectors = [&](int bn0) {
-    int n = bn0 + lane * 4;
-    n = n < N ? n : 0;                                     // columns past N are never stored
-    if (wave == 0 && epi.P.bias) __builtin_amdgcn_global_load_lds((gbl_void*)(epi.P.bias + n), (lds_void*)sbias, 16, 0, 0);
-    if (Epi::kHasGate && wave == 1 && epi.P.gate)
-      __builtin_amdgcn_global_load_lds((gbl_void*)(epi.P.gate + n), (lds_void*)sgate, 16, 0, 0);
-  };
-  const int a_row = (li / RPL) * 256 + (li % RPL) * CPR * 16, a_x = (li / RPL) % CPR;
-  constexpr int TILE_STRIDE = (32 / RPL) * 256;            // 32 rows further down
+  const int oa = (li / RPL) * 256 + (li % RPL) * 128 + ((lh ^ ((li / RPL) % CPR)) << 4);      // half 0's chunk, half 1's is 64 bytes across
 
   int vb = (int)blockIdx.x - (int)gridDim.x, bm0 = 0, bn0 = 0;
   if (!next_tile(vb, bm0, bn0)) return;
   Panels cur = panels(bm0, bn0);
-  bf16x8 fa[2][TM], fb[KS][TN];
-  auto load_b = [&](const Panels& p, int kt, int ks) {
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-      fb[ks][j] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rb, lane * 16, p.b[j] + (kt * KS + ks) * 1024, 0));
+  bf16x8 fa[TM], fb[2][TN];
+  auto load_b = [&](const Panels& p, int kt, int half, int j) {
+    fb[half][j] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rb, lane * 16, p.b[j] + (kt * 2 + half) * 1024, 0));
   };
-  dma_a(cur, 0, 0);
+  int at = 0;                                              // offset of the stage that holds the K tile being multiplied
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks) load_b(cur, 0, ks);
+  for (int j = 0; j < LA; ++j) dma_a(cur, 0, at, j);
+#pragma unroll
+  for (int n = 0; n < 2 * TN; ++n) load_b(cur, 0, n / TN, n % TN);
   wait_vm<0>();
   __builtin_amdgcn_s_barrier();
-  constexpr int kDsRead = 0x100, kMfma = 0x008, kVmem = 0x010;
   for (;;) {
     int nvb = vb, nbm0 = 0, nbn0 = 0;
     const bool has_next = next_tile(nvb, nbm0, nbn0);
     Panels nxt = cur;
     if (has_next) nxt = panels(nbm0, nbn0);
-    // Published by the barrier ahead of the first K tile's last slice.  The tile's first product waits for all that is on its way, K tile
+    // Published by the barrier ahead of the first K tile's last products.  The tile's first product waits for all that is on its way, K tile
     // 1 too: how many stores the epilogue put behind the fragments it needs is not known when this is compiled.
-    issue_vectors(bn0);
-    f32x16 acc[TM][TN];
+    dma_vectors(epi, smem + 2 * STAGE_BYTES, wave, lane, bn0, N);
+    f32x4 acc[TM][TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int j = 0; j < TN; ++j)
+      for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    auto load_a = [&](int stage, int half, int i) { fa[i] = *(const bf16x8*)(smem + stage + (oa ^ (half * 64)) + i * 2048); };
+    // weights as the A operand: a lane ends up with consecutive columns
+    auto multiply = [&](int half, int j, int i) { mfma_into(acc[i][j], fb[half][j], fa[i]); };
+    // One K tile, in this order of instructions: 2 TN columns of products (two halves of K), TM instructions each.  A column's
+    // weights are requested for the next K tile right behind it; the row fragments are replaced one by one
+    // under the last column of a half.  LAST: the tile's last one (no requests of A: the stage it frees is where the epilogue stages its rows).
+    auto kstep = [&](auto last, int kt) {
+      constexpr bool LAST = decltype(last)::value;
+      // past the end of this tile the next one's first K tiles, past the last tile this one's K tile 0 again (never used)
+      const int kb = kt + 1 < nk ? kt + 1 : 0, ka = kt + 2 < nk ? kt + 2 : (has_next ? kt + 2 - nk : 0);
+      const Panels& pb = kt + 1 < nk ? cur : nxt;
+      const Panels& pa = kt + 2 < nk ? cur : nxt;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
-    auto load_a = [&](int stage, int ks, bf16x8 (&xa)[TM]) {
-      const unsigned char* pa = smem + stage * STAGE_BYTES + a_row + (((2 * ks + lh) ^ a_x) << 4);
+      for (int n = 0; n < 2 * TN; ++n) {
+        const int half = n / TN, j = n % TN;
+        if (n == 2 * TN - 1) {
+          // K tile kt + 1 of A has landed: behind its DMA came 2 TN - 1 columns of weights requested since (and in front of them, but
+          // for a tile's first K tile, those of this column, which it needs anyway); this wave is done reading kt
+          counted_wait_lgkm0<2 * TN - 1>();
+          __builtin_amdgcn_s_barrier();
+          __builtin_amdgcn_sched_barrier(0);
+        }
 #pragma unroll
-      for (int i = 0; i < TM; ++i) xa[i] = *(const bf16x8*)(pa + i * TILE_STRIDE);
-    };
-    auto multiply = [&](int ks) {                          // weights as the A operand: a lane ends up with consecutive columns
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[ks][j], fa[ks & 1][i], acc[i][j], 0, 0, 0);
-    };
-    // past the end of this tile the next one's first K tiles, past the last tile this one's K tile 0 again (never used)
-    auto request_a = [&](int ka, int stage) { dma_a(ka < nk ? cur : nxt, ka < nk ? ka : (has_next ? ka - nk : 0), stage); };
-    auto request_b = [&](int ka, int ks) { load_b(ka < nk ? cur : nxt, ka < nk ? ka : (has_next ? ka - nk : 0), ks); };
-    auto kstep = [&](auto par, auto first, auto last, int kt) {
-      constexpr int PAR = decltype(par)::value;
-      constexpr bool FIRST = decltype(first)::value, LAST = decltype(last)::value;
-      if constexpr (FIRST) {
-        request_a(kt + 1, PAR ^ 1);
-        load_a(PAR, 0, fa[0]);
+        for (int i = 0; i < TM; ++i) {
+          multiply(half, j, i);
+          if (j == TN - 1 && !(LAST && half == 1)) {
+            load_a(half == 0 ? at : STAGE_BYTES - at, half ^ 1, i);
+            if (half == 1 && i < LA) dma_a(pa, ka, at, i);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);                 // the DMA stays ahead of the weights
+        load_b(pb, kb, half, j);
         __builtin_amdgcn_sched_barrier(0);
       }
-#pragma unroll
-      for (int ks = 0; ks + 1 < KS; ++ks) {
-        load_a(PAR, ks + 1, fa[(ks + 1) & 1]);
-        multiply(ks);
-        request_b(kt + 1, ks);
-#pragma unroll
-        for (int r = 0; r < TM; ++r) {
-          __builtin_amdgcn_sched_group_barrier(kMfma, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(kDsRead, 1, 0);
-        }
-        if constexpr (TN > 1) __builtin_amdgcn_sched_group_barrier(kMfma, TM * TN - TM, 0);
-        __builtin_amdgcn_sched_group_barrier(kVmem, TN, 0);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      // K tile kt + 1 of A has landed: behind its DMA came the fragments requested since, one slice more where the DMA
-      // was issued ahead of the last K tile's last slice; this wave is done reading kt
-      counted_wait_lgkm0<(FIRST ? KS - 1 : KS) * TN>();
-      __builtin_amdgcn_s_barrier();
-      __builtin_amdgcn_sched_barrier(0);
-      if constexpr (!LAST) {
-        request_a(kt + 2, PAR);
-        load_a(PAR ^ 1, 0, fa[0]);
-      }
-      multiply(KS - 1);
-      if constexpr (!LAST) {
-#pragma unroll
-        for (int r = 0; r < TM; ++r) {
-          __builtin_amdgcn_sched_group_barrier(kMfma, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(kDsRead, 1, 0);
-          if (r < LA) __builtin_amdgcn_sched_group_barrier(kVmem, 1, 0);
-        }
-        if constexpr (TN > 1) __builtin_amdgcn_sched_group_barrier(kMfma, TM * TN - TM, 0);
-      }
-      __builtin_amdgcn_sched_barrier(0);                   // the DMA stays ahead of the fragments
-      request_b(kt + 1, KS - 1);
-      __builtin_amdgcn_sched_barrier(0);
+      at = STAGE_BYTES - at;
     };
-    using P0 = std::integral_constant<int, 0>; using P1 = std::integral_constant<int, 1>;
-    using Yes = std::true_type; using No = std::false_type;
-    kstep(P0{}, Yes{}, No{}, 0);
-    for (int kt = 1; kt + 1 < nk; kt += 2) {
-      kstep(P1{}, No{}, No{}, kt);
-      kstep(P0{}, No{}, No{}, kt + 1);
-    }
-    kstep(P1{}, No{}, Yes{}, nk - 1);
-    // the last K tile was in stage 1; the next tile's first one is complete in stage 0
-    gemm_tile_epilogue<BM, BN, 1, NW, STAGE_BYTES>(acc, smem + STAGE_BYTES, sbias, sgate, epi, bm0, bn0, M, N);
+#pragma unroll
+    for (int j = 0; j < LA; ++j) dma_a(cur, 1, STAGE_BYTES - at, j);      // (at least two K tiles)
+#pragma unroll
+    for (int i = 0; i < TM; ++i) load_a(at, 0, i);
+    __builtin_amdgcn_sched_barrier(0);
+    for (int kt = 0; kt + 1 < nk; ++kt) kstep(std::false_type{}, kt);
+    kstep(std::true_type{}, nk - 1);
+    settled(acc);
+    // the next tile's first K tile is complete in the other stage
+    gemm_tile_epilogue<BM, BN, 1, NW, STAGE_BYTES>(acc, smem + (STAGE_BYTES - at), sbias, sgate, epi, bm0, bn0, M, N);
     if (!has_next) break;
     __builtin_amdgcn_s_barrier();                          // the staging slices are read out
     vb = nvb; bm0 = nbm0; bn0 = nbn0;
@@ -880,12 +599,12 @@ __global__ __launch_bounds__(256, 2) void k_gemm_packed(const bf16_t* A, const v
 #endif
 }
 
-// W [N, K] as [N / 32][K / 16][lane][8]: lane i + 32 h holds row i, columns 8 h .. 8 h + 7.  Once per model.
+// W [N, K] as [N / 16][K / 32][lane][8]: lane i + 16 h holds row i, columns 8 h .. 8 h + 7.  Once per model.
 __global__ __launch_bounds__(256) void k_pack_weights(const bf16_t* __restrict__ W, bf16_t* __restrict__ out, int N, int K) {
   const long long x = (long long)blockIdx.x * 256 + threadIdx.x, blk = x >> 6;
   if (x >= (long long)N * K / 8) return;
-  const int lane = (int)(x & 63), ks = (int)(blk % (K / 16)), nb = (int)(blk / (K / 16));
-  *(bf16x8*)(out + x * 8) = *(const bf16x8*)(W + (size_t)(nb * 32 + (lane & 31)) * K + ks * 16 + (lane >> 5) * 8);
+  const int lane = (int)(x & 63), ks = (int)(blk % (K / 32)), nb = (int)(blk / (K / 32));
+  *(bf16x8*)(out + x * 8) = *(const bf16x8*)(W + (size_t)(nb * 16 + (lane & 15)) * K + ks * 32 + (lane >> 4) * 8);
 }
 bool packs_weights(int N, int K) { return N % 32 == 0 && K % 128 == 0 && (unsigned long long)N * K * 2 < (1ull << 31); }
 hipError_t launch_pack_weights(const void* W, void* out, int N, int K, hipStream_t s) {
@@ -1072,7 +791,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_288(const bf16_t* __restrict__ 
 template <int BM, int BN, int BK, int WR, int WC, typename Epi>
 __global__ __launch_bounds__(WR * WC * 64) void k_gemm_fixup(int M, int N, int tiles_m, int tiles_n, Epi epi, int splits,
                                                              const float* __restrict__ partial) {
-  constexpr int TM = BM / WR / 32, TN = BN / WC / 32;
+  constexpr int TM = BM / WR / 16, TN = BN / WC / 16;
   constexpr int STAGE_BYTES = (BM + BN) * BK * 2;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   float* const sbias = (float*)(smem + STAGE_BYTES);
@@ -1092,7 +811,7 @@ __global__ __launch_bounds__(WR * WC * 64) void k_gemm_fixup(int M, int N, int t
     sbias[threadIdx.x] = (epi.P.bias && n < N) ? epi.P.bias[n] : 0.0f;
     if constexpr (Epi::kHasGate) sgate[threadIdx.x] = (epi.P.gate && n < N) ? epi.P.gate[n] : 1.0f;
   }
-  f32x16 acc[TM][TN];
+  f32x4 acc[TM][TN];
   const float* mine = partial + (size_t)blockIdx.x * splits * (BM * BN);
   for (int r = 0; r < splits; ++r) add_partial<TM, TN>(acc, mine + (size_t)r * (BM * BN), r == 0);
   __syncthreads();
@@ -1170,7 +889,7 @@ __global__ __launch_bounds__(NW * 64) void k_gemm_skinny(const T* __restrict__ A
         for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[ks][e], fb[ks][e], acc, 0, 0, 0);
       }
     }
-    __builtin_amdgcn_s_waitcnt(0xC07F);                  // lgkmcnt(0): the stage is read out before a DMA may overwrite it
+    wait_lgkm0();                                        // the stage is read out before a DMA may overwrite it
     __builtin_amdgcn_sched_barrier(0);
   }
   // partial tiles, each in its wave's own LDS: [16][64]
@@ -1207,7 +926,7 @@ static hipError_t run_skinny_waves(const T* A, const T* Wt, int M, int N, int K,
 }
 
 // Eight waves fill a CU's LDS: for as many tiles as there are CUs.  Above that four, two workgroups to a CU.
-constexpr int kSkinnyMaxK = 1 << 22;                     // 32 rows within a buffer resource's 31-bit range
+constexpr int kSkinnyMaxK = 1 << 22;                     // 32 rows within a buffer resource's 31-bit range, a tile's within 32 bits
 template <typename T, int MODE>
 static hipError_t run_skinny(const void* A, const void* Wt, int M, int N, int K, const EpiParams& ep, hipStream_t s) {
   if ((long long)ceil_div(N, 32) * ceil_div(M, 32) <= 256)
@@ -1740,21 +1459,16 @@ static int split_ranges(long long total, long long slots, int K, const void* scr
   return (int)sp;
 }
 
-template <int BM, int BN, int BK, int WR, int WC, int S, int MODE>
+template <int BM, int BN, int BK, int WR, int WC, int MODE>
 static hipError_t run_dlds(const void* A, const void* Wt, int M, int N, int K, const EpiParams& ep, void* scratch,
                            size_t scratch_bytes, hipStream_t s) {
   using Epi = Epilogue<bf16_t, MODE>;
   Epi epi = Epi::make(ep, M, N);
-  constexpr size_t smem = (size_t)S * (BM + BN) * BK * sizeof(bf16_t) + 2048;   // + bias and gate of a tile
-  // k_gemm_dlds needs an even number of K tiles and addresses its operands as 32-bit buffer
-  // ranges; anything else goes to k_gemm_dlds_any
-  const bool even = K % (2 * BK) == 0 && (unsigned long long)M * K * 2 < (1ull << 32) && (unsigned long long)N * K * 2 < (1ull << 32);
+  constexpr size_t smem = (size_t)2 * (BM + BN) * BK * sizeof(bf16_t) + 2048;   // + bias and gate of a tile
   auto kern = k_gemm_dlds<BM, BN, BK, WR, WC, Epi>;
-  auto kern_any = k_gemm_dlds_any<BM, BN, BK, WR, WC, S, Epi>;
   static bool attr_set = false;
   if (!attr_set) {
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-    if (e == hipSuccess) e = hipFuncSetAttribute((const void*)kern_any, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     if (e != hipSuccess) return e;
     attr_set = true;
   }
@@ -1781,11 +1495,7 @@ static hipError_t run_dlds(const void* A, const void* Wt, int M, int N, int K, c
     launch = (unsigned)(units < slots ? units : slots);
     if (launch < grid) launch = grid;
   }
-  if (even)
-    kern<<<launch, WR * WC * 64, smem, s>>>((const bf16_t*)A, (const bf16_t*)Wt, M, N, K, tiles_m, tiles_n, epi, splits, (float*)scratch);
-  else
-    kern_any<<<launch, WR * WC * 64, smem, s>>>((const bf16_t*)A, (const bf16_t*)Wt, M, N, K, tiles_m, tiles_n, epi, splits,
-                                              (float*)scratch);
+  kern<<<launch, WR * WC * 64, smem, s>>>((const bf16_t*)A, (const bf16_t*)Wt, M, N, K, tiles_m, tiles_n, epi, splits, (float*)scratch);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || splits < 2) return e;
   auto fix = k_gemm_fixup<BM, BN, BK, WR, WC, Epi>;
@@ -1992,7 +1702,7 @@ static hipError_t dispatch_mode(int bf16, const void* A, const void* Wt, int M, 
     else
       aligned = aligned && ep.ldo % 8 == 0 && ((uintptr_t)ep.out & 15) == 0;
   }
-  if (K % 64 != 0 || !aligned || N < 32) return run_plain<bf16_t, MODE>(A, Wt, M, N, K, ep, s);
+  if (K % 64 != 0 || !aligned || N < 32 || K >= kSkinnyMaxK) return run_plain<bf16_t, MODE>(A, Wt, M, N, K, ep, s);
   Bf16Tile tile = bf16_tile(MODE == EPI_UNPATCH, M, N, K);
   if constexpr (MODE == EPI_HEADS || MODE == EPI_GATE || MODE == EPI_GELU) {
     switch (bf16_form(M, N, K, w_parts && ((uintptr_t)w_parts & 15) == 0, scratch, scratch_bytes)) {
@@ -2004,13 +1714,13 @@ static hipError_t dispatch_mode(int bf16, const void* A, const void* Wt, int M, 
     }
   }
   switch (tile) {
-    case T256: return run_dlds<256, 256, 64, 4, 2, 2, MODE>(A, Wt, M, N, K, ep, scratch, scratch_bytes, s);
-    case T192: return run_dlds<256, 192, 64, 4, 2, 2, MODE>(A, Wt, M, N, K, ep, scratch, scratch_bytes, s);
+    case T256: return run_dlds<256, 256, 64, 4, 2, MODE>(A, Wt, M, N, K, ep, scratch, scratch_bytes, s);
+    case T192: return run_dlds<256, 192, 64, 4, 2, MODE>(A, Wt, M, N, K, ep, scratch, scratch_bytes, s);
     case T384:
-      if constexpr (MODE != EPI_UNPATCH) return run_dlds<384, 192, 64, 4, 2, 2, MODE>(A, Wt, M, N, K, ep, scratch, scratch_bytes, s);
+      if constexpr (MODE != EPI_UNPATCH) return run_dlds<384, 192, 64, 4, 2, MODE>(A, Wt, M, N, K, ep, scratch, scratch_bytes, s);
     case T128: break;
   }
-  return run_dlds<128, 128, 64, 2, 2, 2, MODE>(A, Wt, M, N, K, ep, scratch, scratch_bytes, s);
+  return run_dlds<128, 128, 64, 2, 2, MODE>(A, Wt, M, N, K, ep, scratch, scratch_bytes, s);
 }
 
 hipError_t launch_gemm(int bf16, int mode, const void* A, const void* Wt, int M, int N, int K, const EpiParams& ep,
