@@ -77,94 +77,134 @@ __device__ __forceinline__ void store_partial(const f32x4 (&acc)[TM][TN], float*
 #pragma unroll
     for (int j = 0; j < TN; ++j) dst[(i * TN + j) * 64] = acc[i][j];
 }
+// acc = the sum of `splits` of them, `stride` floats apart, in order.  Loads run a group ahead of the additions: left to itself the compiler
+// keeps one to three on their way (22 us of a launch instead of 12).
 template <int TM, int TN>
-__device__ __forceinline__ void add_partial(f32x4 (&acc)[TM][TN], const float* tile, bool first) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const f32x4* src = (const f32x4*)tile + (size_t)wave * (TM * TN * 64) + lane;
+__device__ __forceinline__ void add_partials(f32x4 (&acc)[TM][TN], const float* tile, int wave, int splits, size_t stride) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  constexpr int G = TM * TN % 8 == 0 ? 8 : 6, NG = TM * TN / G;
+  static_assert(TM * TN % G == 0, "whole groups");
+  const f32x4* src = (const f32x4*)(tile + (size_t)wave * (TM * TN * 256)) + (threadIdx.x & 63);
+  f32x4 v[2][G];
+  auto load = [&](int r, int g, f32x4 (&to)[G]) {
+#pragma unroll
+    for (int x = 0; x < G; ++x) to[x] = src[(size_t)r * (stride / 4) + (g * G + x) * 64];
+    __builtin_amdgcn_sched_barrier(0);
+  };
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < TN; ++j) {
-      const f32x4 v = src[(i * TN + j) * 64];
+    for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{-0.0f, -0.0f, -0.0f, -0.0f};      // (x + -0 is x)
+  load(0, 0, v[0]);
+  for (int r = 0; r < splits; ++r) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) acc[i][j][e] = first ? v[e] : acc[i][j][e] + v[e];
+    for (int g = 0; g < NG; ++g) {
+      // past the end the last group again (never used)
+      load(g + 1 < NG ? r : min(r + 1, splits - 1), (g + 1) % NG, v[(g + 1) & 1]);
+#pragma unroll
+      for (int x = 0; x < G; ++x) acc[(g * G + x) / TN][(g * G + x) % TN] += v[g & 1][x];
+      __builtin_amdgcn_sched_barrier(0);
     }
-}
-
-// Bias and gate of 256 columns of the output, from column bn0, to LDS (1 KB each); columns past N, never stored, read as zero.  By buffer
-// loads: behind a global_load_lds, which it takes for a flat access, the compiler waits for all LDS reads wherever it waits for one.
-template <typename Epi>
-__device__ __forceinline__ void dma_vectors(const Epi& epi, unsigned char* sbias, int wave, int lane, int bn0, int N) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  auto load = [&](const float* v, unsigned char* to) {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void*)(v + bn0), 0, (N - bn0) * 4, 0x00020000), (lds_void*)to, 16, lane * 16, 0, 0, 0);
-  };
-  if (wave == 0 && epi.P.bias) load(epi.P.bias, sbias);
-  if (Epi::kHasGate && wave == 1 && epi.P.gate) load(epi.P.gate, sbias + 1024);
+    if constexpr (NG % 2 == 1) {
+#pragma unroll
+      for (int x = 0; x < G; ++x) v[0][x] = v[1][x];
+    }
+  }
 #endif
 }
 
-// Epilogue of one BM x BN tile, shared by the product kernel and the split-K fix-up: bias,
-// activation / gate / q scale, conversion and stores.  `stage` is an idle operand stage of
-// the workgroup (output rows pass through it), sbias / sgate the tile's bias and gate slices.
-template <int BM, int BN, int WR, int WC, int STAGE_BYTES, typename Epi>
-__device__ __forceinline__ void gemm_tile_epilogue(const f32x4 (&acc)[BM / WR / 16][BN / WC / 16], unsigned char* stage,
-                                                   const float* sbias, const float* sgate, const Epi& epi, int bm0,
-                                                   int bn0, int M, int N) {
-  constexpr int NW = WR * WC;
-  constexpr int WTM = BM / WR, WTN = BN / WC;
+// Bias and gate of a wave's WTN columns, one value a lane and register, and as the epilogue reads them: in LDS that the wave alone uses.
+// Fetched when the tile is begun (loads in the epilogue are waited for in turn behind the stores issued before them: the counter is
+// shared); LDS holds them only there, in a stage that is then idle, so that the operands have all of it until then.
+// Columns past N, never stored, read as zero.
+template <int WTN, typename Epi>
+struct TileVectors {
+  static constexpr int NV = ((Epi::kHasGate ? 2 : 1) * WTN + 63) / 64, BYTES = 2 * WTN * 4;
+  float v[NV];
+#if defined(__HIP_DEVICE_COMPILE__)   // buffer resources are a device-side type
+  __device__ __forceinline__ void fetch(const Epi& epi, int lane, int n0, int N) {       // n0: the wave's first column
+    const auto rb = __builtin_amdgcn_make_buffer_rsrc((void*)epi.P.bias, 0, epi.P.bias ? N * 4 : 0, 0x00020000);
+    const auto rg = __builtin_amdgcn_make_buffer_rsrc((void*)epi.P.gate, 0, Epi::kHasGate && epi.P.gate ? N * 4 : 0, 0x00020000);
+#pragma unroll
+    for (int x = 0; x < NV; ++x) {
+      const int c = x * 64 + lane;
+      // (WTN is a multiple of 32: lanes of one load may belong to bias and to gate)
+      if (x * 64 + 63 < WTN || !Epi::kHasGate)
+        v[x] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rb, (n0 + c) * 4, 0, 0));
+      else if (x * 64 >= WTN)
+        v[x] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rg, (n0 + c - WTN) * 4, 0, 0));
+      else
+        v[x] = c < WTN ? __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rb, (n0 + c) * 4, 0, 0))
+                       : __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rg, (n0 + c - WTN) * 4, 0, 0));
+    }
+  }
+#endif
+  __device__ __forceinline__ void to_lds(const Epi& epi, int lane, float* lds) const {   // bias, then gate (absent: ones)
+    const bool ones = Epi::kHasGate && !epi.P.gate;
+#pragma unroll
+    for (int x = 0; x < NV; ++x) {
+      const int c = x * 64 + lane;
+      if (c < (Epi::kHasGate ? 2 : 1) * WTN) lds[c] = ones && c >= WTN ? 1.0f : v[x];
+    }
+  }
+};
+
+// Epilogue of a wave's WTM x WTN part of a tile, shared by the product kernels and the split-K fix-up: bias,
+// activation / gate / q scale, conversion and stores.  (wm0, wn0): its place in the output, the same for all lanes; `cst`: SLICE bytes of
+// LDS that the wave alone uses (output rows pass through them), `vectors` those that TileVectors wrote.
+template <int WTM, int WTN, int SLICE, typename Epi>
+__device__ __forceinline__ void wave_epilogue(const f32x4 (&acc)[WTM / 16][WTN / 16], unsigned char* cst, const float* vectors,
+                                              const Epi& epi, int wm0, int wn0, int M, int N) {
   constexpr int TM = WTM / 16, TN = WTN / 16;
-  // The lane and wave numbers pass through an empty asm: everything derived from them here (LDS
+  // The lane number passes through an empty asm: everything derived from it here (LDS
   // staging offsets, output offsets) is then computed inside the epilogue.  Left to itself the
   // compiler computes these per-lane constants once, ahead of the persistent tile loop, finds no
   // registers for them across the K loop and reloads them from scratch in the epilogue, each
   // reload waiting for the stores issued before it.
-  int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  asm volatile("" : "+v"(lane), "+v"(wave));
-  const int wr = wave / WC, wc = wave % WC;
+  int lane = threadIdx.x & 63;
+  asm volatile("" : "+v"(lane));
   const int li = lane & 15, lh = lane >> 4;
   if constexpr (Epi::kRowRuns) {
     // Accumulator lane (li, lh) holds row m = 16 i + li, columns 16 j + 4 lh + e.
-    // The finished bf16 values go, 32 rows at a time, through this wave's slice of the
+    // The finished bf16 values go, PR rows at a time, through this wave's slice of the
     // idle operand stage, swizzled by 16-byte chunk, and leave as 16-byte stores: a
     // wave-store covers whole 2 WTN-byte row segments instead of 2 bytes per lane.
     constexpr int ROWB = WTN * 2;                     // bytes per staged row
     constexpr int CPRW = WTN / 8;                     // 16-byte chunks per row
     constexpr int RPLC = 256 / ROWB > 0 ? 256 / ROWB : 1;   // rows per 256-byte LDS line
     constexpr bool POW2 = (CPRW & (CPRW - 1)) == 0;
-    static_assert(NW * 32 * ROWB <= STAGE_BYTES, "staging area");
-    static_assert((32 * CPRW) % 64 == 0, "whole wave-stores");
+    constexpr int PR = 32 * ROWB <= SLICE ? 32 : 16;
+    static_assert(PR * ROWB <= SLICE && WTM % PR == 0, "staging area");
+    static_assert((PR * CPRW) % 64 == 0, "whole wave-stores");
     // chunk position inside a row: XOR with the line index (power-of-two rows), else a rotation
     auto swz = [](int row, int chunk) {
       return POW2 ? (chunk ^ ((row / RPLC) & (CPRW - 1))) : (chunk + row) % CPRW;
     };
-    unsigned char* cst = stage + wave * (32 * ROWB);
-    const int wave_u = __builtin_amdgcn_readfirstlane(wave), wr_u = wave_u / WC, wc_u = wave_u % WC;   // known to be uniform
 #pragma unroll
-    for (int i = 0; i < TM / 2; ++i) {
+    for (int i = 0; i < WTM / PR; ++i) {
 #pragma unroll
       for (int j = 0; j < TN; ++j)
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const f32x4& a = acc[2 * i + h][j];
+        for (int h = 0; h < PR / 16; ++h) {
+          const f32x4& a = acc[i * (PR / 16) + h][j];
           const int c0 = j * 16 + lh * 4, row = h * 16 + li;      // of the wave's columns, of the pass's rows
           float v[4] = {a[0], a[1], a[2], a[3]};
-          epi.apply4(bn0 + wc * WTN + c0, v, sbias + wc * WTN + c0, sgate + wc * WTN + c0);
+          epi.apply4(wn0 + c0, v, vectors + c0, vectors + WTN + c0);
           bf16x4 o;
 #pragma unroll
           for (int e = 0; e < 4; ++e) o[e] = (bf16_t)v[e];
           *(bf16x4*)(cst + row * ROWB + (swz(row, 2 * j + (lh >> 1)) << 4) + (lh & 1) * 8) = o;
         }
-      constexpr int NIT = 32 * CPRW / 64;
-      if (bm0 + BM <= M && bn0 + BN <= N) {
-        // a whole tile (wave-uniform): all reads of the pass in flight together, no predicates,
+      constexpr int NIT = PR * CPRW / 64;
+      const int m0 = wm0 + i * PR;
+      if (m0 + PR <= M && wn0 + WTN <= N) {
+        // whole rows (wave-uniform): all reads of the pass in flight together, no predicates,
         // and for the row-major outputs a wave-uniform row pointer plus a 32-bit lane offset
         constexpr int RB = NIT % 4 == 0 ? 4 : NIT % 3 == 0 ? 3 : NIT % 2 == 0 ? 2 : 1;   // reads in flight together
-        const int m0 = bm0 + wr_u * WTM + i * 32, nb = bn0 + wc_u * WTN;
         // per-head outputs: with 64 % CPRW == 0 a lane keeps its column over all passes
         constexpr bool kFixedCol = !Epi::kLinearOut && 64 % CPRW == 0;
         bf16_t* colp = nullptr;
-        if constexpr (kFixedCol) colp = epi.head_col_ptr(nb + (lane % CPRW) * 8);
+        if constexpr (kFixedCol) colp = epi.head_col_ptr(wn0 + (lane % CPRW) * 8);
 #pragma unroll
         for (int it0 = 0; it0 < NIT; it0 += RB) {
           bf16x8 o[RB];
@@ -179,11 +219,11 @@ __device__ __forceinline__ void gemm_tile_epilogue(const f32x4 (&acc)[BM / WR / 
             const int idx = (it0 + r) * 64 + lane;
             const int row = idx / CPRW, chunk = idx % CPRW;
             if constexpr (Epi::kLinearOut)
-              __builtin_nontemporal_store(o[r], (bf16x8*)(epi.row_ptr(m0, nb) + ((unsigned)row * (unsigned)epi.P.ldo + (unsigned)chunk * 8u)));
+              __builtin_nontemporal_store(o[r], (bf16x8*)(epi.row_ptr(m0, wn0) + ((unsigned)row * (unsigned)epi.P.ldo + (unsigned)chunk * 8u)));
             else if constexpr (kFixedCol)
               __builtin_nontemporal_store(o[r], (bf16x8*)(colp + epi.head_row_off(m0 + row)));
             else
-              __builtin_nontemporal_store(o[r], (bf16x8*)epi.run8(m0 + row, nb + chunk * 8));
+              __builtin_nontemporal_store(o[r], (bf16x8*)epi.run8(m0 + row, wn0 + chunk * 8));
           }
         }
       } else {
@@ -192,7 +232,7 @@ __device__ __forceinline__ void gemm_tile_epilogue(const f32x4 (&acc)[BM / WR / 
           const int idx = it * 64 + lane;
           const int row = idx / CPRW, chunk = idx % CPRW;
           const bf16x8 o = *(const bf16x8*)(cst + row * ROWB + (swz(row, chunk) << 4));
-          const int m = bm0 + wr * WTM + i * 32 + row, n0 = bn0 + wc * WTN + chunk * 8;
+          const int m = m0 + row, n0 = wn0 + chunk * 8;
           if (m < M && n0 < N) __builtin_nontemporal_store(o, (bf16x8*)epi.run8(m, n0));
         }
       }
@@ -200,11 +240,11 @@ __device__ __forceinline__ void gemm_tile_epilogue(const f32x4 (&acc)[BM / WR / 
   } else {
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
-      const auto col = epi.col(bn0 + wc * WTN + j * 16 + li);
+      const auto col = epi.col(wn0 + j * 16 + li);
 #pragma unroll
       for (int i = 0; i < TM; ++i) {
         const float v[4] = {acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]};
-        epi.store4(col, bm0 + wr * WTM + i * 16 + lh * 4, v);
+        epi.store4(col, wm0 + i * 16 + lh * 4, v);
       }
     }
   }
@@ -239,10 +279,14 @@ template <int N> __device__ __forceinline__ void counted_wait_lgkm0() {
 // pipe empty, and a DMA still has a whole K tile of matrix work to land.
 // us, with 32x32x16 instructions and this form, same products by turns: 256x256 tiles 17776 x 12288 x 3072 1108, 1046, 9326 x 8192 x 2048
 // 284, 263; 384x192 17776 x 3072 x 12288 1047, 981; 256x192 32768 x 1152 x 1152 98, 92; 128x128 9326 x 2048 x 2048 85, 80.
+// LDS of k_gemm_dlds: a row of either operand is 128 bytes of a K tile; SA stages of A rows, two of B rows.
+template <int BM, int BN, int NW> struct DldsStages {
+  static constexpr int A = BM * 128, B = BN * 128, SA = NW == 8 && 3 * A + 2 * B <= 160 * 1024 ? 3 : 2, BYTES = SA * A + 2 * B;
+};
 template <int BM, int BN, int BK, int WR, int WC, typename Epi>
-__global__ __launch_bounds__(WR * WC * 64) void k_gemm_dlds(const bf16_t* __restrict__ A, const bf16_t* __restrict__ Wt,
+__global__ __launch_bounds__(WR * WC * 64) void k_gemm_dlds(const bf16_t* A, const bf16_t* Wt,
                                                            int M, int N, int K, int tiles_m, int tiles_n, Epi epi,
-                                                           int splits, float* __restrict__ partial) {
+                                                           int splits, float* partial) {
 #if defined(__HIP_DEVICE_COMPILE__)   // buffer resources are a device-side type: the host pass sees an empty body
   constexpr int NW = WR * WC;
   constexpr int WTM = BM / WR, WTN = BN / WC;
@@ -255,28 +299,13 @@ __global__ __launch_bounds__(WR * WC * 64) void k_gemm_dlds(const bf16_t* __rest
   static_assert(BM % (RW * NW) == 0 && BN % (RW * NW) == 0, "loads must divide among waves");
   static_assert(LB <= LA, "B shares A's lane offsets");
   static_assert((NW * 4) % CPR == 0 && (BM / RW * 4) % CPR == 0, "the swizzle must not depend on the load index");
-  constexpr int STAGE_BYTES = (BM + BN) * BK * 2;
-  constexpr int B_REGION = BM * BK * 2;
-
+  using L = DldsStages<BM, BN, NW>;
+  constexpr int SA = L::SA, B_REGION = SA * L::A;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-  // bias and gate of the current tile's BN columns, 1 KB each behind the two operand stages:
-  // fetched by DMA with the tile's first operand loads, read by the epilogue from LDS.  With
-  // loads from global memory in the epilogue every one of them was waited for in turn, behind
-  // the stores issued before it (the counter is shared): 10 000 cycles per 256x192 tile.
-  float* const sbias = (float*)(smem + 2 * STAGE_BYTES);
-  float* const sgate = sbias + 256;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wr = wave / WC, wc = wave % WC;
   const int li = lane & 15, lh = lane >> 4;
-  // an absent bias reads as zeros, an absent gate as ones (written once: no DMA touches them)
-  if constexpr (Epi::kRowRuns) {
-    if (tid < 256) {
-      if (!epi.P.bias) sbias[tid] = 0.0f;
-      if (Epi::kHasGate && !epi.P.gate) sgate[tid] = 1.0f;
-    }
-  }
-
   // ---- tiles of this workgroup: virtual ids blockIdx.x, + gridDim.x, ... below `padded`
   // (the grid may be one workgroup per slot of the chip: persistent).  gridDim.x is a
   // multiple of 8, so every id of a workgroup lands on its XCD.
@@ -338,26 +367,30 @@ __global__ __launch_bounds__(WR * WC * 64) void k_gemm_dlds(const bf16_t* __rest
     p.kbase = kt_first * BK * 2;
     return p;
   };
-  auto dma = [&](const Panels& p, int kt, int stage, int j) {         // wave-load j of LA + LB
-    if (j < LA)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(p.a, (lds_void*)(smem + stage + (wave + NW * j) * 1024), 16, (int)voff[j], p.kbase + kt * (BK * 2), 0, 0);
-    else
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(p.b, (lds_void*)(smem + stage + B_REGION + (wave + NW * (j - LA)) * 1024), 16, (int)voff[j - LA],
-                                               p.kbase + kt * (BK * 2), 0, 0);
+  auto dma_a = [&](const Panels& p, int kt, int stage, int j) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(p.a, (lds_void*)(smem + stage + (wave + NW * j) * 1024), 16, (int)voff[j], p.kbase + kt * (BK * 2), 0, 0);
+  };
+  auto dma_b = [&](const Panels& p, int kt, int stage, int j) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(p.b, (lds_void*)(smem + B_REGION + stage + (wave + NW * j) * 1024), 16, (int)voff[j], p.kbase + kt * (BK * 2), 0, 0);
   };
   // ---- fragment read offsets (bytes within a stage): the chunk of half 0, half 1's is 64 bytes across
   const int ra = wr * WTM + li, rb = wc * WTN + li;
   const int oa = (ra / RPL) * 256 + (ra % RPL) * 128 + ((lh ^ ((ra / RPL) % CPR)) << 4);
-  const int ob = B_REGION + (rb / RPL) * 256 + (rb % RPL) * 128 + ((lh ^ ((rb / RPL) % CPR)) << 4);
+  const int ob = (rb / RPL) * 256 + (rb % RPL) * 128 + ((lh ^ ((rb / RPL) % CPR)) << 4);
 
   int vb = (int)blockIdx.x - (int)gridDim.x, bm0 = 0, bn0 = 0, kt0 = 0, kt1 = 0, slot = -1;
   if (!next_tile(vb, bm0, bn0, kt0, kt1, slot)) return;
   Panels cur = panels(bm0, bn0, kt0);
-  int nk = kt1 - kt0;                              // K tiles of the current unit, at least 1
-  int at = 0;                                      // offset of the stage that holds the K tile being multiplied
+  int nk = kt1 - kt0;                              // K tiles of the current unit, at least SA - 1
+  int ata = 0, atb = 0;                            // offsets of the stages that hold the K tile being multiplied
+  auto next_a = [&](int stage) { return stage == (SA - 1) * L::A ? 0 : stage + L::A; };
 #pragma unroll
-  for (int j = 0; j < LA + LB; ++j) dma(cur, 0, at, j);
-  wait_vm<0>();
+  for (int j = 0; j < LB; ++j) dma_b(cur, 0, 0, j);
+#pragma unroll
+  for (int kt = 0; kt < SA - 1; ++kt)
+#pragma unroll
+    for (int j = 0; j < LA; ++j) dma_a(cur, kt, kt * L::A, j);
+  counted_wait_lgkm0<(SA - 2) * LA>();
   __builtin_amdgcn_s_barrier();
 
   for (;;) {
@@ -365,7 +398,8 @@ __global__ __launch_bounds__(WR * WC * 64) void k_gemm_dlds(const bf16_t* __rest
     const bool has_next = next_tile(nvb, nbm0, nbn0, nkt0, nkt1, nslot);
     Panels nxt = cur;
     if (has_next) nxt = panels(nbm0, nbn0, nkt0);
-    if constexpr (Epi::kRowRuns) dma_vectors(epi, smem + 2 * STAGE_BYTES, wave, lane, bn0, N);      // awaited and published with the unit's first K tile
+    TileVectors<WTN, Epi> vectors;
+    if constexpr (Epi::kRowRuns) vectors.fetch(epi, lane, bn0 + wc * WTN, N);
 
     f32x4 acc[TM][TN];
 #pragma unroll
@@ -373,10 +407,16 @@ __global__ __launch_bounds__(WR * WC * 64) void k_gemm_dlds(const bf16_t* __rest
 #pragma unroll
       for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     bf16x8 fa[2][TM], fb[2][TN];
-    // fragment r of a stage's first ones: the rows' half 0, AHEAD columns
     auto load_a = [&](int stage, int half, int i) { fa[half][i] = *(const bf16x8*)(smem + stage + (oa ^ (half * 64)) + i * 2048); };
-    auto load_b = [&](int stage, int n) { fb[n / TN][n % TN] = *(const bf16x8*)(smem + stage + (ob ^ (n / TN * 64)) + n % TN * 2048); };
-    auto load_first = [&](int stage, int r) { if (r < TM) load_a(stage, 0, r); else load_b(stage, r - TM); };
+    auto load_b = [&](int stage, int n) { fb[n / TN][n % TN] = *(const bf16x8*)(smem + B_REGION + stage + (ob ^ (n / TN * 64)) + n % TN * 2048); };
+    // fragment r of a K tile's first ones: the rows' half 0, AHEAD columns
+    auto load_first = [&](int sa, int sb, int r) { if (r < TM) load_a(sa, 0, r); else load_b(sb, r - TM); };
+    // A wave's requests r = 0 .. LB + LA - 1: K tile kb of B, then K tile ka of A, into stages just read.  K tiles count on into the next unit; past
+    // the last unit K tile 0 of the current panels again (in range, never read) rather than branching around the loads.
+    auto request = [&](int kb, int sb, int ka, int sa, int r) {
+      if (r < LB) dma_b(kb < nk ? cur : nxt, kb < nk ? kb : (has_next ? kb - nk : 0), sb, r);
+      else if (r < LB + LA) dma_a(ka < nk ? cur : nxt, ka < nk ? ka : (has_next ? ka - nk : 0), sa, r - LB);
+    };
     auto multiply = [&](int n, int i) {
       // row-run epilogues want a lane to hold consecutive n: D rows come from the A
       // operand, so the weight fragment goes there (the operand layouts are alike)
@@ -390,53 +430,53 @@ __global__ __launch_bounds__(WR * WC * 64) void k_gemm_dlds(const bf16_t* __rest
       constexpr bool LAST = decltype(last)::value;
 #pragma unroll
       for (int n = 0; n < COLS - TAIL; ++n) {
-        if (n + AHEAD < COLS) load_b(at, n + AHEAD);
+        if (n + AHEAD < COLS) load_b(atb, n + AHEAD);
 #pragma unroll
         for (int i = 2 * n; i < 2 * n + 2; ++i)
-          if (i < TM) load_a(at, 1, i);
+          if (i < TM) load_a(ata, 1, i);
 #pragma unroll
         for (int i = 0; i < TM; ++i) multiply(n, i);
         __builtin_amdgcn_sched_barrier(0);
       }
-      wait_vm_lgkm0<0>();                          // K tile kt + 1 has landed; this wave is done reading kt
+      // K tile kt + 1 has landed (behind it came A's K tile kt + 2, if it has three stages); this wave is done reading kt
+      counted_wait_lgkm0<(SA - 2) * LA>();
       __builtin_amdgcn_s_barrier();
       __builtin_amdgcn_sched_barrier(0);
-      // Requests K tile kt + 2 of this unit, continuing into the next unit past the end; past the last K tile of the
-      // last unit K tile 0 of the current panels again (in range, never read) rather than branching around the loads.
-      const bool ina = kt + 2 < nk;
-      const Panels& p = ina ? cur : nxt;
-      const int k = ina ? kt + 2 : (has_next ? kt + 2 - nk : 0);
 #pragma unroll
       for (int r = 0; r < TAIL * TM; ++r) {
         multiply(COLS - TAIL + r / TM, r % TM);
         if constexpr (!LAST) {
-          if (r < TM + AHEAD) load_first(STAGE_BYTES - at, r);
-          if (r < LA + LB) dma(p, k, at, r);
+          if (r < TM + AHEAD) load_first(next_a(ata), L::B - atb, r);
+          request(kt + 2, atb, kt + SA, ata, r);
           __builtin_amdgcn_sched_barrier(0);
         }
       }
       __builtin_amdgcn_sched_barrier(0);
-      at = STAGE_BYTES - at;
+      ata = next_a(ata);
+      atb = L::B - atb;
     };
 
-    {                                              // K tile 1, or the next unit's first one
-      const bool ina = nk > 1;
-      const Panels& p = ina ? cur : nxt;
+    // B's K tile 1 and A's K tile SA - 1, into the stages that the last unit's rows went through
 #pragma unroll
-      for (int j = 0; j < LA + LB; ++j) dma(p, ina ? 1 : 0, STAGE_BYTES - at, j);
+    for (int r = 0; r < LB + LA; ++r) {
+      request(1, L::B - atb, SA - 1, SA == 3 ? next_a(next_a(ata)) : next_a(ata), r);
+      __builtin_amdgcn_sched_barrier(0);
     }
 #pragma unroll
-    for (int r = 0; r < TM + AHEAD; ++r) load_first(at, r);      // the only reads of a unit with no matrix work in front of them
+    for (int r = 0; r < TM + AHEAD; ++r) load_first(ata, atb, r);      // the only reads of a unit with no matrix work in front of them
     wait_lgkm0();                                  // (and nothing else is on its way, so that the loop's waits can count)
     __builtin_amdgcn_sched_barrier(0);
     for (int kt = 0; kt + 1 < nk; ++kt) kstep(std::false_type{}, kt);
     kstep(std::true_type{}, nk - 1);
     settled(acc);
 
-    // every wave is done reading the stage just multiplied: the epilogue stages
-    // its output rows there; the next unit's first K tile is complete in the other stage
+    // Every wave is done reading the stages just multiplied: the epilogue stages its output rows in A's, its vectors in B's; the
+    // next unit's first K tile is complete in others.
     if (slot < 0) {
-      gemm_tile_epilogue<BM, BN, WR, WC, STAGE_BYTES>(acc, smem + (STAGE_BYTES - at), sbias, sgate, epi, bm0, bn0, M, N);
+      const int last_a = ata == 0 ? (SA - 1) * L::A : ata - L::A, last_b = B_REGION + L::B - atb;
+      float* const mine = (float*)(smem + last_b + wave * TileVectors<WTN, Epi>::BYTES);
+      if constexpr (Epi::kRowRuns) vectors.to_lds(epi, lane, mine);
+      wave_epilogue<WTM, WTN, L::A / NW>(acc, smem + last_a + wave * (L::A / NW), mine, epi, bm0 + wr * WTM, bn0 + wc * WTN, M, N);
     } else {
       store_partial<TM, TN>(acc, partial + (size_t)slot * (BM * BN));
     }
@@ -446,6 +486,7 @@ __global__ __launch_bounds__(WR * WC * 64) void k_gemm_dlds(const bf16_t* __rest
     vb = nvb; bm0 = nbm0; bn0 = nbn0; nk = nkt1 - nkt0; slot = nslot;
     cur = nxt;
   }
+  wait_vm<0>();                                    // nothing is on its way to LDS when the workgroup ends
 #endif
 }
 
@@ -473,14 +514,9 @@ __global__ __launch_bounds__(256, BN == 128 ? 4 : 2) void k_gemm_packed(const bf
   static_assert(BM % (RW * NW) == 0 && BN % 128 == 0 && BN <= 256 && Epi::kRowRuns, "whole wave-loads; bias and gate slices of 256");
   constexpr int STAGE_BYTES = BM * BK * 2;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-  float* const sbias = (float*)(smem + 2 * STAGE_BYTES);
-  float* const sgate = sbias + 256;
-
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int li = lane & 15, lh = lane >> 4;
-  // an absent bias reads as zeros, an absent gate as ones (written once: no DMA touches them)
-  if (!epi.P.bias) sbias[tid] = 0.0f;
-  if (Epi::kHasGate && !epi.P.gate) sgate[tid] = 1.0f;
+  float* const mine = (float*)(smem + 2 * STAGE_BYTES + wave * TileVectors<WTN, Epi>::BYTES);
 
   const int total = tiles_m * tiles_n, nk = K / BK, padded = (total + 255) / 256 * 256;
   auto next_tile = [&](int& vb, int& bm0, int& bn0) {      // k_gemm_dlds's order, no split tiles
@@ -536,9 +572,10 @@ __global__ __launch_bounds__(256, BN == 128 ? 4 : 2) void k_gemm_packed(const bf
     const bool has_next = next_tile(nvb, nbm0, nbn0);
     Panels nxt = cur;
     if (has_next) nxt = panels(nbm0, nbn0);
-    // Published by the barrier ahead of the first K tile's last products.  The tile's first product waits for all that is on its way, K tile
-    // 1 too: how many stores the epilogue put behind the fragments it needs is not known when this is compiled.
-    dma_vectors(epi, smem + 2 * STAGE_BYTES, wave, lane, bn0, N);
+    // The tile's first product waits for all that is on its way, K tile 1 too: how many stores the epilogue put behind the fragments it
+    // needs is not known when this is compiled.
+    TileVectors<WTN, Epi> vectors;
+    vectors.fetch(epi, lane, bn0 + wave * WTN, N);
     f32x4 acc[TM][TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
@@ -590,7 +627,8 @@ __global__ __launch_bounds__(256, BN == 128 ? 4 : 2) void k_gemm_packed(const bf
     kstep(std::true_type{}, nk - 1);
     settled(acc);
     // the next tile's first K tile is complete in the other stage
-    gemm_tile_epilogue<BM, BN, 1, NW, STAGE_BYTES>(acc, smem + (STAGE_BYTES - at), sbias, sgate, epi, bm0, bn0, M, N);
+    vectors.to_lds(epi, lane, mine);
+    wave_epilogue<BM, WTN, STAGE_BYTES / NW>(acc, smem + (STAGE_BYTES - at) + wave * (STAGE_BYTES / NW), mine, epi, bm0, bn0 + wave * WTN, M, N);
     if (!has_next) break;
     __builtin_amdgcn_s_barrier();                          // the staging slices are read out
     vb = nvb; bm0 = nbm0; bn0 = nbn0;
@@ -606,7 +644,7 @@ __global__ __launch_bounds__(256) void k_pack_weights(const bf16_t* __restrict__
   const int lane = (int)(x & 63), ks = (int)(blk % (K / 32)), nb = (int)(blk / (K / 32));
   *(bf16x8*)(out + x * 8) = *(const bf16x8*)(W + (size_t)(nb * 16 + (lane & 15)) * K + ks * 32 + (lane >> 4) * 8);
 }
-bool packs_weights(int N, int K) { return N % 32 == 0 && K % 128 == 0 && (unsigned long long)N * K * 2 < (1ull << 31); }
+bool packs_weights(int N, int K) { return N % 32 == 0 && K % 64 == 0 && K >= 128 && (unsigned long long)N * K * 2 < (1ull << 31); }
 hipError_t launch_pack_weights(const void* W, void* out, int N, int K, hipStream_t s) {
   if (!packs_weights(N, K)) return hipErrorInvalidValue;
   k_pack_weights<<<ceil_div((long long)N * K / 8, 256), 256, 0, s>>>((const bf16_t*)W, (bf16_t*)out, N, K);
@@ -786,36 +824,33 @@ __global__ __launch_bounds__(256, 2) void k_gemm_288(const bf16_t* __restrict__ 
 }
 
 // ---------------------------------------------------------------- split-K fix-up
-// One workgroup per tile of the split round: adds the tile's `splits` partial accumulators in
+// One wave's part of a tile of the split round to a workgroup (of one wave: nothing is shared, and eight times the workgroups reach
+// CUs that a tile to a workgroup leaves idle): adds the part's `splits` partial accumulators in
 // range order (bitwise repeatable) and runs the product kernel's epilogue on the sum.
-template <int BM, int BN, int BK, int WR, int WC, typename Epi>
-__global__ __launch_bounds__(WR * WC * 64) void k_gemm_fixup(int M, int N, int tiles_m, int tiles_n, Epi epi, int splits,
-                                                             const float* __restrict__ partial) {
-  constexpr int TM = BM / WR / 16, TN = BN / WC / 16;
-  constexpr int STAGE_BYTES = (BM + BN) * BK * 2;
-  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-  float* const sbias = (float*)(smem + STAGE_BYTES);
-  float* const sgate = sbias + 256;
-  const int total = tiles_m * tiles_n;
-  const int t = total / 256 * 256 + (int)blockIdx.x;
+template <int BM, int BN, int WR, int WC, typename Epi>
+__global__ __launch_bounds__(64) void k_gemm_fixup(int M, int N, int tiles_m, int tiles_n, Epi epi, int splits, const float* __restrict__ partial) {
+#if defined(__HIP_DEVICE_COMPILE__)   // buffer resources are a device-side type: the host pass sees an empty body
+  constexpr int NW = WR * WC, WTM = BM / WR, WTN = BN / WC, SLICE = 32 * WTN * 2;
+  __shared__ __attribute__((aligned(256))) unsigned char smem[SLICE + TileVectors<WTN, Epi>::BYTES];
+  const int total = tiles_m * tiles_n, in_round = (int)blockIdx.x / NW, wave = (int)blockIdx.x % NW;
+  const int t = total / 256 * 256 + in_round;
   if (t >= total) return;
   constexpr int GM = 8;                              // the product kernel's tile order
   const int per_group = GM * tiles_n;
   const int group = t / per_group;
   const int first_m = group * GM;
   const int gsz = min(tiles_m - first_m, GM);
-  const int bm0 = (first_m + (t % per_group) % gsz) * BM;
-  const int bn0 = ((t % per_group) / gsz) * BN;
-  if (threadIdx.x < 256) {
-    const int n = bn0 + (int)threadIdx.x;
-    sbias[threadIdx.x] = (epi.P.bias && n < N) ? epi.P.bias[n] : 0.0f;
-    if constexpr (Epi::kHasGate) sgate[threadIdx.x] = (epi.P.gate && n < N) ? epi.P.gate[n] : 1.0f;
-  }
-  f32x4 acc[TM][TN];
-  const float* mine = partial + (size_t)blockIdx.x * splits * (BM * BN);
-  for (int r = 0; r < splits; ++r) add_partial<TM, TN>(acc, mine + (size_t)r * (BM * BN), r == 0);
-  __syncthreads();
-  gemm_tile_epilogue<BM, BN, WR, WC, STAGE_BYTES>(acc, smem, sbias, sgate, epi, bm0, bn0, M, N);
+  const int wm0 = (first_m + (t % per_group) % gsz) * BM + wave / WC * WTM;
+  const int wn0 = ((t % per_group) / gsz) * BN + wave % WC * WTN;
+  if (wm0 >= M || wn0 >= N) return;
+  float* const vectors = (float*)(smem + SLICE);
+  TileVectors<WTN, Epi> v;
+  if constexpr (Epi::kRowRuns) v.fetch(epi, threadIdx.x, wn0, N);
+  f32x4 acc[WTM / 16][WTN / 16];
+  add_partials<WTM / 16, WTN / 16>(acc, partial + (size_t)in_round * splits * (BM * BN), wave, splits, BM * BN);
+  if constexpr (Epi::kRowRuns) v.to_lds(epi, threadIdx.x, vectors);
+  wave_epilogue<WTM, WTN, SLICE>(acc, smem, vectors, epi, wm0, wn0, M, N);
+#endif
 }
 
 // ---------------------------------------------------------------- MFMA kernel for products with few tiles
@@ -1464,7 +1499,7 @@ static hipError_t run_dlds(const void* A, const void* Wt, int M, int N, int K, c
                            size_t scratch_bytes, hipStream_t s) {
   using Epi = Epilogue<bf16_t, MODE>;
   Epi epi = Epi::make(ep, M, N);
-  constexpr size_t smem = (size_t)2 * (BM + BN) * BK * sizeof(bf16_t) + 2048;   // + bias and gate of a tile
+  constexpr size_t smem = DldsStages<BM, BN, WR * WC>::BYTES;
   auto kern = k_gemm_dlds<BM, BN, BK, WR, WC, Epi>;
   static bool attr_set = false;
   if (!attr_set) {
@@ -1498,15 +1533,7 @@ static hipError_t run_dlds(const void* A, const void* Wt, int M, int N, int K, c
   kern<<<launch, WR * WC * 64, smem, s>>>((const bf16_t*)A, (const bf16_t*)Wt, M, N, K, tiles_m, tiles_n, epi, splits, (float*)scratch);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || splits < 2) return e;
-  auto fix = k_gemm_fixup<BM, BN, BK, WR, WC, Epi>;
-  constexpr size_t fsmem = (size_t)(BM + BN) * BK * sizeof(bf16_t) + 2048;
-  static bool fattr_set = false;
-  if (!fattr_set) {
-    e = hipFuncSetAttribute((const void*)fix, hipFuncAttributeMaxDynamicSharedMemorySize, (int)fsmem);
-    if (e != hipSuccess) return e;
-    fattr_set = true;
-  }
-  fix<<<(unsigned)rem, WR * WC * 64, fsmem, s>>>(M, N, tiles_m, tiles_n, epi, splits, (const float*)scratch);
+  k_gemm_fixup<BM, BN, WR, WC, Epi><<<(unsigned)rem * WR * WC, 64, 0, s>>>(M, N, tiles_m, tiles_n, epi, splits, (const float*)scratch);
   return hipGetLastError();
 }
 
@@ -1514,7 +1541,7 @@ template <int BM, int BN, int PER_CU, int MODE>
 static hipError_t run_packed(const void* A, const void* Wp, int M, int N, int K, const EpiParams& ep, hipStream_t s) {
   using Epi = Epilogue<bf16_t, MODE>;
   Epi epi = Epi::make(ep, M, N);
-  constexpr size_t smem = (size_t)2 * BM * 128 + 2048;     // two stages of A, bias and gate of a tile
+  constexpr size_t smem = (size_t)2 * BM * 128 + BN * 8;   // two stages of A, bias and gate of a tile
   auto kern = k_gemm_packed<BM, BN, Epi>;
   const int tiles_m = ceil_div(M, BM), tiles_n = ceil_div(N, BN);
   const long long padded = ((long long)tiles_m * tiles_n + 255) / 256 * 256;
@@ -1704,6 +1731,7 @@ static hipError_t dispatch_mode(int bf16, const void* A, const void* Wt, int M, 
   }
   if (K % 64 != 0 || !aligned || N < 32 || K >= kSkinnyMaxK) return run_plain<bf16_t, MODE>(A, Wt, M, N, K, ep, s);
   Bf16Tile tile = bf16_tile(MODE == EPI_UNPATCH, M, N, K);
+  if (K < 128) tile = T128;                              // three stages of A: at least two K tiles
   if constexpr (MODE == EPI_HEADS || MODE == EPI_GATE || MODE == EPI_GELU) {
     switch (bf16_form(M, N, K, w_parts && ((uintptr_t)w_parts & 15) == 0, scratch, scratch_bytes)) {
       case P256: return run_packed<128, 256, 2, MODE>(A, w_parts, M, N, K, ep, s);
