@@ -312,10 +312,11 @@ hipError_t launch_gemm(int bf16, int mode, const void* A, const void* Wt, int M,
 // w_parts (optional): the weights once more, fp32 split into bf16 parts (launch_split_weights, split_weights_bytes), bf16 in
 // fragment order (launch_pack_weights, N * K elements, where packs_weights)
 bool packs_weights(int N, int K);
-// what a model's bf16 product runs on: k_gemm_dlds (128x128, 256x192, 256x256, 384x192), k_gemm_packed (128x128, 128x256), k_gemm_288
+// what a model's bf16 product runs on: k_gemm_dlds (128x128, 256x192, 256x256, 384x192), k_gemm_packed (narrow: 128x128 or 128x192; 128x256),
+// k_gemm_288
 enum Bf16Form : int { F128, F192, F256, F384, P128, P256, W288 };
 Bf16Form bf16_form(int M, int N, int K, bool packed, const void* scratch, size_t scratch_bytes);
-bool packed_weights_serve(int M, int N, int K);          // whether a product of M rows takes them, with scratch or without
+bool packed_weights_serve(int M, int N, int K, bool lent);          // whether a product of M rows takes them, with scratch lent or without
 hipError_t launch_pack_weights(const void* W, void* out, int N, int K, hipStream_t s);
 size_t split_weights_bytes(int N, int K);
 hipError_t launch_split_weights(const float* Wt, void* out, int N, int K, hipStream_t s);

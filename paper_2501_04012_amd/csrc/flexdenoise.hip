@@ -193,11 +193,12 @@ struct Carver {          // bump allocator over a byte range, 256-byte aligned p
 };
 
 // Whether a product of the model's rows takes packed weights at any number of samples: past 2^17 rows the rounds that packed
-// tiles save are less than what they cost.
+// tiles save are less than what they cost.  All products over token rows are lent scratch memory but the queries of the cross attention.
 bool rows_take_packed(const fc_model* m, int in, int out) {
   if (!packs_weights(out, in)) return false;
+  const bool queries = m->cfg.attn_mode == FC_ATTN_FACTORIZED_CROSS && in == m->cfg.hidden && out == m->cfg.hidden;
   for (long long rows = m->Ns; rows == m->Ns || rows <= 1 << 17; rows += m->Ns)
-    if (packed_weights_serve((int)rows, out, in)) return true;
+    if (packed_weights_serve((int)rows, out, in, true) || (queries && packed_weights_serve((int)rows, out, in, false))) return true;
   return false;
 }
 

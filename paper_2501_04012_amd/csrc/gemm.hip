@@ -31,9 +31,17 @@ namespace fc {
 //
 // Tile order.  Workgroup ids are dealt round-robin to the 8 XCDs, each with its own L2.
 // Id -> tile index is chosen so that 32 workgroups running together on one XCD hold 32
-// consecutive tile indices, and consecutive indices walk GM = 8 tile rows before moving to
+// consecutive tile indices, and consecutive indices walk 8 tile rows before moving to
 // the next tile column: an XCD works on an 8 x 4 patch of C and streams 8 + 4 operand
-// panels through its L2 instead of 1 + 32.
+// panels through its L2 instead of 1 + 32.  (Products of few tile columns row by row, so that no rows are read by two XCDs: 2 to 9 % faster
+// where operands come by turns from four products, 1 to 2 % slower inside a step.)
+[[maybe_unused]] constexpr int kPatchRows = 8;
+// Tile of workgroup id `vb` (total or more: none).  A last round of fewer than 256 tiles is spread over all XCDs, an eighth of it each:
+// their L2s and their ways to memory serve it too.
+__device__ __forceinline__ int tile_index(int vb, int total) {
+  const int round = vb & ~255, xcd = vb & 7, slot = (vb >> 3) & 31, per = min((total - round + 7) >> 3, 32);
+  return slot < per ? round + xcd * per + slot : total;
+}
 typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((address_space(1))) const void gbl_void;
 
@@ -321,8 +329,7 @@ __global__ __launch_bounds__(WR * WC * 64) void k_gemm_dlds(const bf16_t* A, con
   // virtual ids run over the whole rounds and, behind them, the units of the last one
   const int padded = splits >= 2 ? ((full + rem * splits + 7) & ~7) : (total + 255) / 256 * 256;
   auto tile_of = [&](int vb, int& bm0, int& bn0, int& kt0, int& kt1, int& slot) {
-    const int xcd = vb & 7, local = vb >> 3;
-    int t = ((local >> 5) * 8 + xcd) * 32 + (local & 31);
+    int t = tile_index(vb, total);
     kt0 = 0; kt1 = nkt; slot = -1;
     if (splits >= 2 && vb >= full) {
       const int w = vb - full;
@@ -333,7 +340,7 @@ __global__ __launch_bounds__(WR * WC * 64) void k_gemm_dlds(const bf16_t* A, con
       slot = (w % rem) * splits + r;
     }
     if (t >= total) return false;
-    constexpr int GM = 8;
+    constexpr int GM = kPatchRows;
     const int per_group = GM * tiles_n;
     const int group = t / per_group;
     const int first_m = group * GM;
@@ -494,7 +501,7 @@ __global__ __launch_bounds__(WR * WC * 64) void k_gemm_dlds(const bf16_t* A, con
 // For weights that were packed into fragment order when the model was loaded ([N / 16][K / 32][lane][8], k_pack_weights): a
 // fragment is 1 KB in a row and goes from L2 to the registers of the one wave column that needs it; LDS holds A alone.  A
 // workgroup is four waves side by side, each 128 rows by BN / 4 columns, so that no fragment is fetched twice, and small
-// enough that two (BN 256: 204 registers, 34 KB of LDS) or four of them (BN 128: 125) share a CU: one's epilogue and first loads run
+// enough that two (BN 256: 206 registers, 34 KB of LDS), three (BN 192: 168) or four of them (BN 128: 126) share a CU: one's epilogue and first loads run
 // under another's products, and tiles half the size fill the last round better.  Of k_gemm_dlds it keeps the tile order, the
 // swizzled A stages and the epilogue.  Sums are those of k_gemm_dlds bit for bit where that does not split a tile along K.
 //
@@ -506,12 +513,12 @@ __global__ __launch_bounds__(WR * WC * 64) void k_gemm_dlds(const bf16_t* A, con
 // us, 32x32x16 instructions row by row, and this form, operands by turns: 8192 x 1152 x 1152 (BN 128) 30.6, 25.5; 8192 x 3456 x 1152
 // (BN 256) 73.8, 63.1; 32768 x 4608 x 1152 314, 304; 32768 x 1152 x 4608 304, 283; 17776 x 9216 x 3072 783, 731.
 template <int BM, int BN, typename Epi>
-__global__ __launch_bounds__(256, BN == 128 ? 4 : 2) void k_gemm_packed(const bf16_t* A, const void* Wp, int M, int N,
+__global__ __launch_bounds__(256, BN == 128 ? 4 : BN == 192 ? 3 : 2) void k_gemm_packed(const bf16_t* A, const void* Wp, int M, int N,
                                                         int K, int tiles_m, int tiles_n, Epi epi) {
 #if defined(__HIP_DEVICE_COMPILE__)   // buffer resources are a device-side type: the host pass sees an empty body
   constexpr int BK = 64, NW = 4, WTN = BN / NW, TM = BM / 16, TN = WTN / 16;
   constexpr int CPR = BK / 8, RPL = 16 / CPR, RW = 4 * RPL, LA = BM / RW / NW;
-  static_assert(BM % (RW * NW) == 0 && BN % 128 == 0 && BN <= 256 && Epi::kRowRuns, "whole wave-loads; bias and gate slices of 256");
+  static_assert(BM % (RW * NW) == 0 && BN % 64 == 0 && BN <= 256 && Epi::kRowRuns, "whole wave-loads");
   constexpr int STAGE_BYTES = BM * BK * 2;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -521,9 +528,10 @@ __global__ __launch_bounds__(256, BN == 128 ? 4 : 2) void k_gemm_packed(const bf
   const int total = tiles_m * tiles_n, nk = K / BK, padded = (total + 255) / 256 * 256;
   auto next_tile = [&](int& vb, int& bm0, int& bn0) {      // k_gemm_dlds's order, no split tiles
     for (vb += gridDim.x; vb < padded; vb += gridDim.x) {
-      const int local = vb >> 3, t = ((local >> 5) * 8 + (vb & 7)) * 32 + (local & 31);
+      const int t = tile_index(vb, total);
       if (t >= total) continue;
-      const int per_group = 8 * tiles_n, group = t / per_group, first_m = group * 8, gsz = min(tiles_m - first_m, 8);
+      constexpr int gm = kPatchRows;
+  const int per_group = gm * tiles_n, group = t / per_group, first_m = group * gm, gsz = min(tiles_m - first_m, gm);
       bm0 = (first_m + (t % per_group) % gsz) * BM;
       bn0 = ((t % per_group) / gsz) * BN;
       return true;
@@ -683,9 +691,10 @@ __global__ __launch_bounds__(256, 2) void k_gemm_288(const bf16_t* __restrict__ 
   float* const sbias = (float*)(smem + S * L::kStage);
   float* const sgate = sbias + BN;
 
-  const int total = tiles_m * tiles_n, local = (int)blockIdx.x >> 3, t = ((local >> 5) * 8 + ((int)blockIdx.x & 7)) * 32 + (local & 31);
+  const int total = tiles_m * tiles_n, t = tile_index(blockIdx.x, total);
   if (t >= total) return;                                  // k_gemm_dlds's tile order
-  const int per_group = 8 * tiles_n, group = t / per_group, first_m = group * 8, gsz = min(tiles_m - first_m, 8);
+  constexpr int gm = kPatchRows;
+  const int per_group = gm * tiles_n, group = t / per_group, first_m = group * gm, gsz = min(tiles_m - first_m, gm);
   const int bm0 = (first_m + (t % per_group) % gsz) * BM, bn0 = ((t % per_group) / gsz) * BN;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -835,7 +844,7 @@ __global__ __launch_bounds__(64) void k_gemm_fixup(int M, int N, int tiles_m, in
   const int total = tiles_m * tiles_n, in_round = (int)blockIdx.x / NW, wave = (int)blockIdx.x % NW;
   const int t = total / 256 * 256 + in_round;
   if (t >= total) return;
-  constexpr int GM = 8;                              // the product kernel's tile order
+  constexpr int GM = kPatchRows;                     // the product kernel's tile order
   const int per_group = GM * tiles_n;
   const int group = t / per_group;
   const int first_m = group * GM;
@@ -994,11 +1003,11 @@ __global__ __launch_bounds__(WR * WC * 64) void k_gemm_f32(const float* __restri
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wr = wave / WC, wc = wave % WC;
   const int li = lane & 31, lh = lane >> 5;
-  // workgroup -> tile: runs of 32 consecutive tiles per XCD, 8 tile rows before the next tile column
-  const int vb = blockIdx.x, local = vb >> 3;
-  const int t = ((local >> 5) * 8 + (vb & 7)) * 32 + (local & 31);
+  // workgroup -> tile as in k_gemm_dlds
+  const int t = tile_index(blockIdx.x, tiles_m * tiles_n);
   if (t >= tiles_m * tiles_n) return;
-  const int per_group = 8 * tiles_n, group = t / per_group, first_m = group * 8, gsz = min(tiles_m - first_m, 8);
+  constexpr int gm = kPatchRows;
+  const int per_group = gm * tiles_n, group = t / per_group, first_m = group * gm, gsz = min(tiles_m - first_m, gm);
   const int bm0 = (first_m + (t % per_group) % gsz) * BM, bn0 = ((t % per_group) / gsz) * BN;
 
   const auto ra = __builtin_amdgcn_make_buffer_rsrc((void*)(A + (size_t)bm0 * K), 0, (int)((unsigned)min(M - bm0, BM) * (unsigned)K * 4u), 0x00020000);
@@ -1150,11 +1159,11 @@ __global__ __launch_bounds__(WR * WC * 64, PER_SIMD) void k_gemm_f32_parts(const
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wr = wave / WC, wc = wave % WC;
   const int li = lane & 31, lh = lane >> 5;
-  // workgroup -> tile: runs of 32 consecutive tiles per XCD, 8 tile rows before the next tile column
-  const int vb = blockIdx.x, local = vb >> 3;
-  const int t = ((local >> 5) * 8 + (vb & 7)) * 32 + (local & 31);
+  // workgroup -> tile as in k_gemm_dlds
+  const int t = tile_index(blockIdx.x, tiles_m * tiles_n);
   if (t >= tiles_m * tiles_n) return;
-  const int per_group = 8 * tiles_n, group = t / per_group, first_m = group * 8, gsz = min(tiles_m - first_m, 8);
+  constexpr int gm = kPatchRows;
+  const int per_group = gm * tiles_n, group = t / per_group, first_m = group * gm, gsz = min(tiles_m - first_m, gm);
   const int bm0 = (first_m + (t % per_group) % gsz) * BM, bn0 = ((t % per_group) / gsz) * BN;
   const int slices = (K + 15) / 16;
 
@@ -1637,22 +1646,16 @@ static Bf16Tile bf16_tile(bool unpatch, int M, int N, int K) {
   return T128;
 }
 
-// The form of a model's product: the tile just chosen, or one whose estimated time is below that tile's.  The estimates, in us: tiles
-// of the fullest CU times a time per K tile and one per tile, fitted over 325 products (M 256 to 38 000, N and K 576 to 12 288, each timed in
-// every form, the same product again and again); for the tiles of 288 columns also the tiles per CU of the whole chip (the power limit), over
-// 400 products.  They rank forms that differ by whole rounds.  As times they are up to a quarter too short where a product has many rounds
-// of long K, whose operands come from further off (256x192 at 32768 x 1152 x 4608: 246 estimated, 325 with operands by turns, where packed
-// 128x256 takes 290 and is estimated at 266).
-//   Packed weights (`packed`: there are some): 314 products, 0.917 of the time in the mean, none more than 2 % slower.  A lone 128x256
-//   tile on a CU (two waves a SIMD short) is up to 1.13 times slower than estimated and not taken; products whose 128x128 tiles are
-//   all split along K stay with them (up to 1.58).
+// The form of a model's product without packed weights: the tile just chosen, or one whose estimated time is below that tile's.  The
+// estimates, in us: tiles of the fullest CU times a time per K tile and one per tile, fitted over 325 products (M 256 to 38 000, N and K 576 to
+// 12 288, the same product again and again) with 32x32x16 instructions; for the tiles of 288 columns also the tiles per CU of the whole
+// chip (the power limit), over 400 products.  They rank forms that differ by whole rounds: 978 products of ten widths from 576 to 3072 and 25
+// numbers of rows take 1.04 of their best staged form's time in the mean, 1.026 in the sum (1.57 where a product of 128x128 tiles would be best in
+// 256x192: 13113 x 768 x 3072 99 us, 61).
 //   128x288, 384x192: where the estimate is 6 % (384x192: 9 %) lower, a nearly empty last round counted as what it takes.  Their tiles
-//   fill rounds that the others leave half empty.  821 products at the lower ends and inside of the windows of M that these rules give 14
-//   widths of 576 to 4608, with operands by turns: 0.84 of the time in the mean, four slower by more than 1 %, by 2.8 % at most (all rounds
-//   counted as full: up to 1.29, 6545 x 576 x 2304 28 us, and 36).  384x192 takes nothing from packed 128x256 (66 products that the
-//   estimates would give it: 0.89 to 1.10 of the time, 1.02 in the mean; 4753 x 6912 x 2304 126 us, and 139).  128x288 from K = 2048 on:
-//   below it is mostly first tile and epilogue, which the estimate was not held against.
-Bf16Form bf16_form(int M, int N, int K, bool packed, const void* scratch, size_t scratch_bytes) {
+//   fill rounds that the others leave half empty (all rounds counted as full: up to 1.29 times as long, 6545 x 576 x 2304 28 us, and 36).  128x288
+//   from K = 2048 on: below it is mostly first tile and epilogue, which the estimate was not held against.
+static Bf16Form staged_form(int M, int N, int K, const void* scratch, size_t scratch_bytes) {
   const Bf16Tile tile = bf16_tile(false, M, N, K);
   const double kt = K / 64.0;
   auto tiles = [&](int bm, int bn) { return (long long)ceil_div(M, bm) * ceil_div(N, bn); };
@@ -1676,36 +1679,87 @@ Bf16Form bf16_form(int M, int N, int K, bool packed, const void* scratch, size_t
       now = rounds(128, 128, 1, 1.84, 0.443, 1.40) + lone(0.21, -0.72);
       break;
   }
-  if ((unsigned long long)M * K * 2 >= (1ull << 32) || (unsigned long long)N * K * 2 >= (1ull << 32)) return form;     // 32-bit offsets
-  if (packed && packs_weights(N, K)) {
-    const double e256 = per_cu(128, 256) >= 2.0 ? rounds(128, 256, 1, -0.09, 0.702, 2.68) : 1e30,
-                 e128 = rounds(128, 128, 1, 1.25, 0.419, 1.11) + lone(0.083, 0.56);
-    if (e256 < now && e256 <= e128) { form = P256; now = e256; }
-    else if (e128 < now) { form = P128; now = e128; }
-  }
-  // What a last round takes less than the others: 128x128 tiles of packed weights, four to a CU, as it is less full; staged ones, two to a CU, and
-  // 256x256 tiles where it is less than a quarter full (for the former: and the second that CUs share).
+  if ((unsigned long long)M * K * 2 >= (1ull << 32) || (unsigned long long)N * K * 2 >= (1ull << 32)) return form;     // 128x288: 32-bit offsets
+  // What a nearly empty last round takes less than the others: 128x128 tiles, two to a CU, and 256x256 tiles where it is less than a
+  // quarter full (for the former: and the second that CUs share).
   auto empty = [&](int bm, int bn) { return per_cu(bm, bn) - tiles(bm, bn) / 256.0; };
-  const bool packed256 = form == P256;
-  if (form == P128) now -= 0.5 * empty(128, 128) * (0.419 * kt + 1.11);
-  else if (form == F128 && empty(128, 128) > 0.75 && (long long)per_cu(128, 128) % 2 == 0) now -= 0.5 * empty(128, 128) * (0.443 * kt + 1.40);
+  if (form == F128 && empty(128, 128) > 0.75 && (long long)per_cu(128, 128) % 2 == 0) now -= 0.5 * empty(128, 128) * (0.443 * kt + 1.40);
   else if (form == F256 && empty(256, 256) > 0.75 && splits256 < 2) now -= 0.15 * empty(256, 256) * (1.266 * kt + 8.84);
   double least = 0.94 * now;
   if (N % 288 == 0 && K >= 2048) {
     const double e = 2.53 + per_cu(128, 288) * (0.629 * kt + 5.71) + tiles(128, 288) / 256.0 * 0.234 * kt;
     if (e < least) { form = W288; least = e; }
   }
-  if (N % 192 == 0 && !packed256 && e384 < 0.97 * least) form = F384;
+  if (N % 192 == 0 && e384 < 0.97 * least) form = F384;
   return form;
 }
 
-bool packed_weights_serve(int M, int N, int K) {
-  if ((long long)ceil_div(M, 128) * ceil_div(N, 128) < 32 || N < 32) return false;      // k_gemm_skinny
-  auto taken = [&](const void* scratch, size_t bytes) {
-    const Bf16Form form = bf16_form(M, N, K, true, scratch, bytes);
-    return form == P128 || form == P256;
+// What the forms take, in us: start + c (k kt + fixed) + tiles / 256 chip kt, kt K tiles, c tiles on the fullest CU (chip: what all CUs share, the
+// power limit and the memory); a CU's only tile takes lone + lone_k kt more (fewer waves hide its latencies), a last round in ranges of K
+// only its part and the fix-up.  Fitted over 978 products of ten widths from 576 to 3072 and 25 numbers of rows from 300 to 40 960, each in every form,
+// operands by turns from four products; those where the form is within 15 % of the best count five times (rms of these 3 to 6 %).
+struct FormTime { int bm, bn; double start, k, fixed, chip, lone, lone_k, fixup; };
+static constexpr FormTime kF128{128, 128, 0.756, 0.318, 1.629, 0.157, 2.003, 0.219, 5.000}, kF192{256, 192, 0.000, 0.732, 5.514, 0.434, 0.847, 0.018, 10.757},
+    kF256{256, 256, 0.000, 0.889, 6.654, 0.571, 0.279, 0.022, 10.808}, kF384{384, 192, 0.000, 1.051, 7.722, 0.610, 0.109, 0.044, 12.090},
+    kP128{128, 128, 1.825, 0.322, 1.058, 0.111, 1.387, 0.104, 0.000}, kP192{128, 192, 1.506, 0.408, 2.042, 0.189, 2.027, 0.008, 0.000},
+    kP256{128, 256, 1.302, 0.405, 2.376, 0.342, 1.481, 0.027, 0.000}, kW288{128, 288, 1.483, 0.515, 6.489, 0.365, 0.644, -0.038, 0.000};
+static double form_time(const FormTime& f, int M, int N, int K, int splits = 1) {
+  const long long tiles = (long long)ceil_div(M, f.bm) * ceil_div(N, f.bn);
+  const double kt = K / 64.0, chip = f.start + tiles / 256.0 * f.chip * kt;
+  if (splits >= 2) {
+    const double full = (double)(tiles / 256);
+    return chip + full * (f.k * kt + f.fixed) + f.k * kt / splits + f.fixed + f.fixup;
+  }
+  const double c = (double)((tiles + 255) / 256);
+  return chip + c * (f.k * kt + f.fixed) + (c == 1.0 ? f.lone + f.lone_k * kt : 0.0);
+}
+// Packed tiles of 128x128 or 128x192 (P128): 192 columns where their estimate is the lower one, three of them for four rounds of the
+// others.  us, 128x128 and 128x192: 4096 x 1152 x 1152 17.0, 14.6; 4096 x 4608 x 1152 44.3, 40.6; 8192 x 3456 x 1152 71.6, 63.4.
+static bool narrow_is_192(int M, int N, int K) { return form_time(kP192, M, N, K) < form_time(kP128, M, N, K); }
+
+// The form of a model's product.  With packed weights: the tile that bf16_tile gives, or packed ones.  Wide ones (128x256) where they are 2 %
+// lower than 256x192 tiles, 3.2 % than larger ones or 2.5 % than a lone 256x256 tile to a CU (less does not pay for weights held twice: one or
+// two percent here are none inside a step), narrow ones 6 % (all packed estimates are somewhat short where a product has many rounds), both wherever the
+// tile would be 128x128; narrow ones only where wide ones take 3 % more (a narrow tile writes per-head outputs in pieces of 64 bytes, which the
+// estimates, all epilogues alike, leave out: 4096 x 1728 x 576 13.3 us wide, 16.6 narrow).  256x192 tiles where they are 6 %
+// lower still (7300 x 1536 x 6144 118 us, 133 in narrow ones), 128x288 (K from 2048) and 384x192 likewise; 384x192 is taken over
+// narrow tiles at any lower estimate (in the mean that is level or better), and takes nothing from wide ones (66 products that the estimates would give it: 0.89
+// to 1.10 of the time, 1.02 in the mean).
+// The products above take 1.012 of their best form's time in the mean, 1.014 in the sum, 1.12 at most (by the rule before, whose estimates were
+// fitted with 32x32x16 instructions: 1.034, 1.021, 1.40).
+Bf16Form bf16_form(int M, int N, int K, bool packed, const void* scratch, size_t scratch_bytes) {
+  if (!packed || !packs_weights(N, K) || (unsigned long long)M * K * 2 >= (1ull << 32))                  // 32-bit offsets
+    return staged_form(M, N, K, scratch, scratch_bytes);
+  auto staged = [&](Bf16Form f) {
+    auto tiles = [&](int bm, int bn) { return (long long)ceil_div(M, bm) * ceil_div(N, bn); };
+    switch (f) {
+      case F192: return form_time(kF192, M, N, K, split_ranges<256, 192>(tiles(256, 192), 256, K, scratch, scratch_bytes));
+      case F256: return form_time(kF256, M, N, K, split_ranges<256, 256>(tiles(256, 256), 256, K, scratch, scratch_bytes));
+      case F384: return form_time(kF384, M, N, K, split_ranges<384, 192>(tiles(384, 192), 256, K, scratch, scratch_bytes));
+      default: return form_time(kF128, M, N, K, split_ranges<128, 128>(tiles(128, 128), 512, K, scratch, scratch_bytes));
+    }
   };
-  return taken(nullptr, 0) || taken((const void*)16, ~(size_t)0);
+  constexpr Bf16Form kOfTile[] = {F128, F192, F256, F384};            // T128, T192, T256, T384
+  Bf16Form form = kOfTile[bf16_tile(false, M, N, K)];
+  double now = staged(form);
+  const double wide = form_time(kP256, M, N, K), narrow = form_time(narrow_is_192(M, N, K) ? kP192 : kP128, M, N, K);
+  if (wide <= 1.03 * narrow) {
+    const bool lone = form == F256 && (long long)ceil_div(M, 256) * ceil_div(N, 256) <= 256;
+    if (wide < (form == F128 ? 1.0 : form == F192 ? 0.98 : lone ? 0.975 : 0.968) * now) { form = P256; now = wide; }
+  } else if (narrow < (form == F128 ? 1.0 : 0.94) * now) {
+    form = P128;
+    now = narrow;
+  }
+  if (N % 192 == 0 && form != F192 && form != F256 && form != F384 && staged(F192) < 0.94 * now) { form = F192; now = staged(F192); }
+  if (N % 288 == 0 && K >= 2048 && form_time(kW288, M, N, K) < 0.94 * now) { form = W288; now = form_time(kW288, M, N, K); }
+  if (N % 192 == 0 && form != P256 && form != F384 && staged(F384) < (form == P128 ? 1.0 : 0.94) * now) form = F384;
+  return form;
+}
+
+bool packed_weights_serve(int M, int N, int K, bool lent) {
+  if ((long long)ceil_div(M, 128) * ceil_div(N, 128) < 32 || N < 32) return false;      // k_gemm_skinny
+  const Bf16Form form = lent ? bf16_form(M, N, K, true, (const void*)16, ~(size_t)0) : bf16_form(M, N, K, true, nullptr, 0);
+  return form == P128 || form == P256;
 }
 
 template <int MODE>
@@ -1735,7 +1789,9 @@ static hipError_t dispatch_mode(int bf16, const void* A, const void* Wt, int M, 
   if constexpr (MODE == EPI_HEADS || MODE == EPI_GATE || MODE == EPI_GELU) {
     switch (bf16_form(M, N, K, w_parts && ((uintptr_t)w_parts & 15) == 0, scratch, scratch_bytes)) {
       case P256: return run_packed<128, 256, 2, MODE>(A, w_parts, M, N, K, ep, s);
-      case P128: return run_packed<128, 128, 4, MODE>(A, w_parts, M, N, K, ep, s);
+      case P128:
+        if (narrow_is_192(M, N, K)) return run_packed<128, 192, 3, MODE>(A, w_parts, M, N, K, ep, s);
+        return run_packed<128, 128, 4, MODE>(A, w_parts, M, N, K, ep, s);
       case W288: return run_288<MODE>(A, Wt, M, N, K, ep, s);
       case F384: tile = T384; break;
       default: break;
