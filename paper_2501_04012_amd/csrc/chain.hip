@@ -478,12 +478,13 @@ __global__ __launch_bounds__(kThreads) void k_chain(ChainArgs a) {
   constexpr bool EARLY = HDT <= 2;                        // registers permitting; else right before the stage
   const ChainStep& proj = a.step[CHAIN_PROJ];
   const ChainStep& next = a.step[CHAIN_NEXT];
+  const bool head = !a.q_out;
   Ahead f_proj, f_xq, f_xproj, f_fc1, f_fc2, f_next;
   Modulation m_fc1, m_next;
   KeyTile<HDT> keys, xkeys;
   auto start_next = [&] {
     start(next, false, false, f_next);
-    start_norm(next, a.eps ? 0 : e_alt, m_next);
+    start_norm(next, head ? 0 : e_alt, m_next);
   };
   if constexpr (!(KIND & CHAIN_EMBED)) {
     const f32x4 x4 = load4(buffer(a.x, kAll), e_in ? 4u * (unsigned)(e_row * D + ec) : kNowhere);
@@ -595,7 +596,7 @@ __global__ __launch_bounds__(kThreads) void k_chain(ChainArgs a) {
   issued();
   lds_barrier();
   const f32x4 x4 = layer_norm(&m_next);
-  if (!a.eps) {
+  if (!head) {
     if (e_in && idx0 + er <= last) *(f32x4*)(a.x_out + (unsigned)(e_row * D + ec)) = x4;
     lds_barrier();
     int out_row = my_row;                                 // in the next attention's order
@@ -616,7 +617,7 @@ __global__ __launch_bounds__(kThreads) void k_chain(ChainArgs a) {
     const int b = a.by_Ns.div(my_row), n0 = my_row - b * a.Ns - a.text_rows;
     const bool mine = idx0 + i <= last && n0 >= 0;        // text rows have no head
     const int f0 = a.by_S.div(mine ? n0 : 0), s = (mine ? n0 : 0) - f0 * a.S, ph = a.by_gw.div(s), pw = s - ph * a.by_gw.d;
-    float* dst = a.eps + ((((size_t)b * a.T + f0) * a.H + (size_t)ph * a.p) * a.W + (size_t)pw * a.p) * a.C;
+    const size_t at = ((((size_t)b * a.T + f0) * a.H + (size_t)ph * a.p) * a.W + (size_t)pw * a.p) * a.C;
     for (int t = wave; t * 16 < p.N; t += kChainWaves) {
       const int row = t * 16 + i;
       const float* wp = p.w + (size_t)(row < p.N ? row : p.N - 1) * D + 4 * h;
@@ -632,7 +633,13 @@ __global__ __launch_bounds__(kThreads) void k_chain(ChainArgs a) {
         const int n = t * 16 + 4 * h + e;
         if (mine && n < p.N) {
           const int dh = a.by_run.div(n), c = n - dh * a.by_run.d;
-          dst[(size_t)dh * a.W * a.C + c] = v[e] + p.bias[n];
+          const size_t o = at + (size_t)dh * a.W * a.C + c;
+          const float est = v[e] + p.bias[n];
+          if (a.latent_out) {                             // no other row reads or writes these elements
+            const float x0 = (a.latent_out[o] - a.c1 * est) / a.c0;
+            a.latent_out[o] = a.c2 * x0 + a.c3 * est;
+          }
+          if (a.eps) a.eps[o] = est;
         }
       }
     }

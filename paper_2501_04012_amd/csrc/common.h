@@ -357,8 +357,11 @@ struct ChainArgs {
   int L;
   ChainStep step[CHAIN_STEPS];
   float* x_out;                            // the rows' new residual stream
-  float *q_out, *k_out, *v_out;            // NEXT, eps NULL
-  float* eps;                              // NEXT as the output head: [B, T, H, W, C]
+  float *q_out, *k_out, *v_out;            // NEXT; NULL where it is the output head
+  float* eps;                              // of the head: [B, T, H, W, C]
+  // ... and with it the update of the latent (k_cfg_ddim's, for batch rows without guidance; NULL: none): eps is then optional
+  float* latent_out;
+  float c0, c1, c2, c3;
 };
 // w [N, K], both multiples of 16, as [N / 16][K / 16][lane][4]: lane i + 16 h holds row i, columns 4 h .. 4 h + 3
 hipError_t launch_pack_chain(const float* w, float* packed, int N, int K, hipStream_t s);

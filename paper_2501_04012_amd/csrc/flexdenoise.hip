@@ -519,7 +519,11 @@ ChainArgs chain_base(const Ctx& c) {
   return a;
 }
 
-int run_chains(const Ctx& c, const float* latent) {
+// update (optional): the last launch also takes the latents a step further, by these coefficients, and leaves the noise estimate in eps_out
+// (optional) instead of the workspace: one launch less.  us, one request without guidance, before and now: a step of one block 64 wide
+// 43.5 and 42.2, 32 wide 41.5 and 39.5, full 3-D 64 wide 33.3 and 31.9, a resume of ten steps of four blocks 889 and 872.
+struct ChainUpdate { float* latent; float* eps_out; const float* coef; };
+int run_chains(const Ctx& c, const float* latent, const ChainUpdate* update) {
   const fc_model* m = c.m;
   const fc_model_config& cf = m->cfg;
   const Workspace& w = c.w;
@@ -538,7 +542,11 @@ int run_chains(const Ctx& c, const float* latent) {
   };
   auto head = [&](ChainArgs& a) {
     a.step[CHAIN_NEXT] = step(m->fout, nullptr, w.fmod, w.fmod + D);
-    a.eps = w.eps;
+    a.eps = update ? update->eps_out : w.eps;
+    if (update) {
+      a.latent_out = update->latent;
+      a.c0 = update->coef[0]; a.c1 = update->coef[1]; a.c2 = update->coef[2]; a.c3 = update->coef[3];
+    }
   };
   ProfScope ps(c, PC_OTHER);
   {
@@ -680,8 +688,11 @@ int run_step(const Ctx& c, float* latent, const fc_schedule* sched, int step, fl
 
   const bool fact = cf.attn_mode == FC_ATTN_FACTORIZED_CROSS;
   const bool chain = m->chain_shape && chain_fits(chain_base(c), fact ? std::max(m->S, cf.frames) : m->Ns, fact ? cf.text_len : 0);
-  rc = chain ? run_chains(c, latent) : run_layers(c, latent);
-  if (rc != FC_OK) return rc;
+  // Without guidance a row's noise estimate is all that its latent waits for.  (No blocks: the same launch reads the latents.)
+  const bool updates = chain && !c.use_cfg && sigma == 0.0f && cf.depth > 0;
+  const ChainUpdate update{latent, eps_out, coef};
+  rc = chain ? run_chains(c, latent, updates ? &update : nullptr) : run_layers(c, latent);
+  if (rc != FC_OK || updates) return rc;
 
   const size_t n = (size_t)c.R * cf.frames * cf.height * cf.width * cf.channels;
   ProfScope ps(c, PC_CFG_DDIM);
