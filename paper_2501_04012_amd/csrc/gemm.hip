@@ -1,5 +1,5 @@
 // Linear layers: C[M,N] = A[M,K] * Wt[N,K]^T with fused epilogues.
-//   bf16: MFMA (v_mfma_f32_32x32x16_bf16) kernel, operands DMA'd into swizzled LDS tiles,
+//   bf16: MFMA (v_mfma_f32_16x16x32_bf16) kernels, operands DMA'd into swizzled LDS tiles,
 //         fp32 accumulation.
 //   fp32: MFMA kernels, on three bf16 parts of a value or (small products, and what the parts cannot hold)
 //         v_mfma_f32_32x32x2_f32; a plain LDS-tiled FMA kernel for operands that are not made of whole aligned 16-byte chunks.
@@ -37,7 +37,8 @@ namespace fc {
 // where operands come by turns from four products, 1 to 2 % slower inside a step.)
 [[maybe_unused]] constexpr int kPatchRows = 8;
 // Tile of workgroup id `vb` (total or more: none).  A last round of fewer than 256 tiles is spread over all XCDs, an eighth of it each:
-// their L2s and their ways to memory serve it too.
+// their L2s and their ways to memory serve it too (32 to an XCD until there are none left, before: us, 8192 x 1152 x 1152 in 192 tiles of 256x192
+// 26.4, 23.1; 8192 x 1152 x 4608 90, 85; 9326 x 2048 x 2048 in packed 128x256 72, 67; fp32 step of a 1152-wide block 1489, 1418).
 __device__ __forceinline__ int tile_index(int vb, int total) {
   const int round = vb & ~255, xcd = vb & 7, slot = (vb >> 3) & 31, per = min((total - round + 7) >> 3, 32);
   return slot < per ? round + xcd * per + slot : total;
@@ -86,7 +87,7 @@ __device__ __forceinline__ void store_partial(const f32x4 (&acc)[TM][TN], float*
     for (int j = 0; j < TN; ++j) dst[(i * TN + j) * 64] = acc[i][j];
 }
 // acc = the sum of `splits` of them, `stride` floats apart, in order.  Loads run a group ahead of the additions: left to itself the compiler
-// keeps one to three on their way (22 us of a launch instead of 12).
+// keeps one to three on their way (300 x 2304 x 2048 in 256x192 tiles, four ranges of K: 48.7 us with one, 30.2 with three, 23.2 here).
 template <int TM, int TN>
 __device__ __forceinline__ void add_partials(f32x4 (&acc)[TM][TN], const float* tile, int wave, int splits, size_t stride) {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -287,7 +288,10 @@ template <int N> __device__ __forceinline__ void counted_wait_lgkm0() {
 // pipe empty, and a DMA still has a whole K tile of matrix work to land.
 // us, with 32x32x16 instructions and this form, same products by turns: 256x256 tiles 17776 x 12288 x 3072 1108, 1046, 9326 x 8192 x 2048
 // 284, 263; 384x192 17776 x 3072 x 12288 1047, 981; 256x192 32768 x 1152 x 1152 98, 92; 128x128 9326 x 2048 x 2048 85, 80.
-// LDS of k_gemm_dlds: a row of either operand is 128 bytes of a K tile; SA stages of A rows, two of B rows.
+// LDS of k_gemm_dlds: a row of either operand is 128 bytes of a K tile; SA stages of A rows, two of B rows.  A's rows come from HBM and have two K
+// tiles of time to arrive with three stages, the weights, which all workgroups read, from the caches.  us with two stages and three,
+// operands by turns: 32768 x 1152 x 4608 in 256x192 tiles 319, 284, 32768 x 1152 x 1152 93, 82, 8192 x 1152 x 4608 104, 90; 32768 x 4608 x 1152
+// in 256x256 327, 308.  384x192 tiles have no room for a third; 128x128 tiles, two to a CU, gain at some sizes (0.89) and lose at others (1.12).
 template <int BM, int BN, int NW> struct DldsStages {
   static constexpr int A = BM * 128, B = BN * 128, SA = NW == 8 && 3 * A + 2 * B <= 160 * 1024 ? 3 : 2, BYTES = SA * A + 2 * B;
 };
@@ -666,7 +670,7 @@ hipError_t launch_pack_weights(const void* W, void* out, int N, int K, hipStream
 // multiple of 32), so the tile is four waves, one to a SIMD, and what would stop the wave stops the SIMD: fragments are read four
 // columns of products ahead, and requests for operand tiles are spread over the matrix instructions (all thirteen of a wave in
 // the tail of a step: 96 us where it is 76).  Sums go along K in order, and one v_mfma_f32_16x16x32_bf16 rounds like two
-// v_mfma_f32_32x32x16_bf16: results are those of k_gemm_dlds bit for bit where that does not split a tile along K.  LDS layout, DMA and
+// v_mfma_f32_32x32x16_bf16 would: results are those of k_gemm_dlds bit for bit where that does not split a tile along K.  LDS layout, DMA and
 // swizzle are those of k_gemm_dlds, as is the barrier ahead of a stage's last products, behind which the next stage's first fragments
 // are read.  Three stages of LDS.
 // Bound by the operand stream (53 KB per K tile in 0.9 us and CU) and, where K is small, by what is not the K loop (10 us: first tile,
