@@ -1622,8 +1622,9 @@ static hipError_t dispatch_f32(const void* A, const void* Wt, const void* w_part
   return run_f32_parts<64, 64, 2, 2, 4, false, MODE>(A, Wt, nullptr, M, N, K, ep, s);
 }
 
-enum Bf16Tile { T128, T192, T256, T384 };
-static Bf16Tile bf16_tile(bool unpatch, int M, int N, int K) {
+// The tile of a product of k_gemm_dlds.
+static Bf16Form bf16_tile(bool unpatch, int M, int N, int K) {
+  if (K < 128) return F128;                              // three stages of A: at least two K tiles
   // Tile choice.  256x256 (8 waves, one workgroup per CU) has the best operand reuse but
   // needs several rounds of tiles per CU and wastes the ragged part of N; 256x192 takes
   // over where N is a multiple of 192 that 256 would pad by more than 5 % (N = 1152:
@@ -1637,17 +1638,17 @@ static Bf16Tile bf16_tile(bool unpatch, int M, int N, int K) {
   // whole rounds of 256 and that of 256x256 does not, it saves most of a round (the full-3D
   // out-projection and fc2: 752 tiles = 2.94 rounds against 840 = 3.28; 2-5 % over the split
   // last round)
-  if (N % 192 == 0 && waste > 0.05 && (long long)ceil_div(M, 256) * (N / 192) >= 192) return T192;
+  if (N % 192 == 0 && waste > 0.05 && (long long)ceil_div(M, 256) * (N / 192) >= 192) return F192;
   if (!unpatch && N % 192 == 0 && K >= 2048 && tiles256 >= 600 && waste <= 0.05 &&
-           fill((long long)ceil_div(M, 384) * (N / 192)) >= 0.95 && fill(tiles256) < 0.85) return T384;
-  if (tiles256 >= 600 && (waste <= 0.05 || K >= 2048)) return T256;
+           fill((long long)ceil_div(M, 384) * (N / 192)) >= 0.95 && fill(tiles256) < 0.85) return F384;
+  if (tiles256 >= 600 && (waste <= 0.05 || K >= 2048)) return F256;
   // Mid-size products (a few thousand rows) that the thresholds above leave to 128x128: the large
   // tiles still win where their tile count fills its rounds of 256 workgroups (measured at
   // M = 4096 and 8192: QKV of the 1152-wide model 8-14 % faster with 256x256, its fc1 at
   // M = 8192 7 % faster with 256x192; where the last round would be mostly empty, 128x128 stays)
-  if (tiles256 >= 200 && waste <= 0.05 && fill(tiles256) >= 0.85) return T256;
-  if (N % 192 == 0 && (long long)ceil_div(M, 256) * (N / 192) >= 200 && fill((long long)ceil_div(M, 256) * (N / 192)) >= 0.95) return T192;
-  return T128;
+  if (tiles256 >= 200 && waste <= 0.05 && fill(tiles256) >= 0.85) return F256;
+  if (N % 192 == 0 && (long long)ceil_div(M, 256) * (N / 192) >= 200 && fill((long long)ceil_div(M, 256) * (N / 192)) >= 0.95) return F192;
+  return F128;
 }
 
 // The form of a model's product without packed weights: the tile just chosen, or one whose estimated time is below that tile's.  The
@@ -1660,7 +1661,7 @@ static Bf16Tile bf16_tile(bool unpatch, int M, int N, int K) {
 //   fill rounds that the others leave half empty (all rounds counted as full: up to 1.29 times as long, 6545 x 576 x 2304 28 us, and 36).  128x288
 //   from K = 2048 on: below it is mostly first tile and epilogue, which the estimate was not held against.
 static Bf16Form staged_form(int M, int N, int K, const void* scratch, size_t scratch_bytes) {
-  const Bf16Tile tile = bf16_tile(false, M, N, K);
+  const Bf16Form tile = bf16_tile(false, M, N, K);
   const double kt = K / 64.0;
   auto tiles = [&](int bm, int bn) { return (long long)ceil_div(M, bm) * ceil_div(N, bn); };
   auto per_cu = [&](int bm, int bn) { return (double)((tiles(bm, bn) + 255) / 256); };
@@ -1672,13 +1673,13 @@ static Bf16Form staged_form(int M, int N, int K, const void* scratch, size_t scr
   auto lone = [&](double k, double fixed) { return per_cu(128, 128) == 1.0 ? k * kt + fixed : 0.0; };
   const double e384 = rounds(384, 192, split_ranges<384, 192>(tiles(384, 192), 256, K, scratch, scratch_bytes), -0.74, 1.386, 11.56);
   const int splits256 = split_ranges<256, 256>(tiles(256, 256), 256, K, scratch, scratch_bytes);
-  Bf16Form form = F128;
+  Bf16Form form = tile;
   double now = 0.0;
   switch (tile) {
-    case T256: form = F256; now = rounds(256, 256, splits256, -1.75, 1.266, 8.84); break;
-    case T192: form = F192; now = rounds(256, 192, split_ranges<256, 192>(tiles(256, 192), 256, K, scratch, scratch_bytes), 0.04, 1.051, 6.49); break;
-    case T384: form = F384; now = e384; break;
-    case T128:
+    case F256: now = rounds(256, 256, splits256, -1.75, 1.266, 8.84); break;
+    case F192: now = rounds(256, 192, split_ranges<256, 192>(tiles(256, 192), 256, K, scratch, scratch_bytes), 0.04, 1.051, 6.49); break;
+    case F384: now = e384; break;
+    default:
       if (split_ranges<128, 128>(tiles(128, 128), 512, K, scratch, scratch_bytes) >= 2) return F128;
       now = rounds(128, 128, 1, 1.84, 0.443, 1.40) + lone(0.21, -0.72);
       break;
@@ -1721,14 +1722,17 @@ static double form_time(const FormTime& f, int M, int N, int K, int splits = 1) 
 // others.  us, 128x128 and 128x192: 4096 x 1152 x 1152 17.0, 14.6; 4096 x 4608 x 1152 44.3, 40.6; 8192 x 3456 x 1152 71.6, 63.4.
 static bool narrow_is_192(int M, int N, int K) { return form_time(kP192, M, N, K) < form_time(kP128, M, N, K); }
 
-// The form of a model's product.  With packed weights: the tile that bf16_tile gives, or packed ones.  Wide ones (128x256) where they are 2 %
-// lower than 256x192 tiles, 3.2 % than larger ones or 2.5 % than a lone 256x256 tile to a CU (less does not pay for weights held twice: one or
-// two percent here are none inside a step), narrow ones 6 % (all packed estimates are somewhat short where a product has many rounds), both wherever the
-// tile would be 128x128; narrow ones only where wide ones take 3 % more (a narrow tile writes per-head outputs in pieces of 64 bytes, which the
-// estimates, all epilogues alike, leave out: 4096 x 1728 x 576 13.3 us wide, 16.6 narrow).  256x192 tiles where they are 6 %
-// lower still (7300 x 1536 x 6144 118 us, 133 in narrow ones), 128x288 (K from 2048) and 384x192 likewise; 384x192 is taken over
-// narrow tiles at any lower estimate (in the mean that is level or better), and takes nothing from wide ones (66 products that the estimates would give it: 0.89
-// to 1.10 of the time, 1.02 in the mean).
+// The form of a model's product; dispatch_mode launches the one named here.  With packed weights: the tile that bf16_tile gives, or packed
+// ones.  Wide ones (128x256) where they are 2 % lower than 256x192 tiles, 3.2 % than larger ones or 2.5 % than a lone 256x256 tile to a CU
+// (the weights are held twice for them; the three lines are drawn by one call, a full-3D step 2048 wide, that took 1.013 of its time with wide
+// tiles wherever their estimate was the lower one, though three of its four products are 3 to 5 % faster in them alone; why is not known), narrow ones
+// 6 % (all packed estimates are somewhat short where a product has many rounds), both wherever the tile would be 128x128; narrow ones only where wide ones
+// take 3 % more (a 128x128 tile writes per-head outputs in pieces of 64 bytes, which the estimates, all epilogues alike, leave out: 4096 x 1728 x 576
+// 13.3 us wide, 16.6 narrow; 128x192 tiles write pieces of 96 bytes and are kept back by the same line, also where they are faster: 8192 x 3456 x
+// 1152 62 us, 66 in the form taken).  128x288 (K from 2048) where it is 6 % lower than the choice so far, 384x192 likewise;
+// that is taken over narrow tiles at any lower estimate (in the mean that is level or better), and takes nothing from wide ones (66 products that the
+// estimates would give it: 0.89 to 1.10 of the time, 1.02 in the mean).  Nothing goes back from narrow tiles to 256x192, though the estimate of 128x192
+// is some 10 % short at long K: 5393 and 7300 x 1536 x 6144 113 and 128 us, 104 and 120 in 256x192.
 // The products above take 1.012 of their best form's time in the mean, 1.014 in the sum, 1.12 at most (by the rule before, whose estimates were
 // fitted with 32x32x16 instructions: 1.034, 1.021, 1.40).
 Bf16Form bf16_form(int M, int N, int K, bool packed, const void* scratch, size_t scratch_bytes) {
@@ -1743,8 +1747,7 @@ Bf16Form bf16_form(int M, int N, int K, bool packed, const void* scratch, size_t
       default: return form_time(kF128, M, N, K, split_ranges<128, 128>(tiles(128, 128), 512, K, scratch, scratch_bytes));
     }
   };
-  constexpr Bf16Form kOfTile[] = {F128, F192, F256, F384};            // T128, T192, T256, T384
-  Bf16Form form = kOfTile[bf16_tile(false, M, N, K)];
+  Bf16Form form = bf16_tile(false, M, N, K);
   double now = staged(form);
   const double wide = form_time(kP256, M, N, K), narrow = form_time(narrow_is_192(M, N, K) ? kP192 : kP128, M, N, K);
   if (wide <= 1.03 * narrow) {
@@ -1754,7 +1757,6 @@ Bf16Form bf16_form(int M, int N, int K, bool packed, const void* scratch, size_t
     form = P128;
     now = narrow;
   }
-  if (N % 192 == 0 && form != F192 && form != F256 && form != F384 && staged(F192) < 0.94 * now) { form = F192; now = staged(F192); }
   if (N % 288 == 0 && K >= 2048 && form_time(kW288, M, N, K) < 0.94 * now) { form = W288; now = form_time(kW288, M, N, K); }
   if (N % 192 == 0 && form != P256 && form != F384 && staged(F384) < (form == P128 ? 1.0 : 0.94) * now) form = F384;
   return form;
@@ -1788,27 +1790,24 @@ static hipError_t dispatch_mode(int bf16, const void* A, const void* Wt, int M, 
       aligned = aligned && ep.ldo % 8 == 0 && ((uintptr_t)ep.out & 15) == 0;
   }
   if (K % 64 != 0 || !aligned || N < 32 || K >= kSkinnyMaxK) return run_plain<bf16_t, MODE>(A, Wt, M, N, K, ep, s);
-  Bf16Tile tile = bf16_tile(MODE == EPI_UNPATCH, M, N, K);
-  if (K < 128) tile = T128;                              // three stages of A: at least two K tiles
+  Bf16Form form = bf16_tile(MODE == EPI_UNPATCH, M, N, K);
+  if constexpr (MODE == EPI_HEADS || MODE == EPI_GATE || MODE == EPI_GELU)           // a model's products over token rows
+    form = bf16_form(M, N, K, w_parts && ((uintptr_t)w_parts & 15) == 0, scratch, scratch_bytes);
+  switch (form) {
+    case F256: return run_dlds<256, 256, 64, 4, 2, MODE>(A, Wt, M, N, K, ep, scratch, scratch_bytes, s);
+    case F192: return run_dlds<256, 192, 64, 4, 2, MODE>(A, Wt, M, N, K, ep, scratch, scratch_bytes, s);
+    case F128: return run_dlds<128, 128, 64, 2, 2, MODE>(A, Wt, M, N, K, ep, scratch, scratch_bytes, s);
+    default: break;
+  }
+  if constexpr (MODE != EPI_UNPATCH)
+    if (form == F384) return run_dlds<384, 192, 64, 4, 2, MODE>(A, Wt, M, N, K, ep, scratch, scratch_bytes, s);
   if constexpr (MODE == EPI_HEADS || MODE == EPI_GATE || MODE == EPI_GELU) {
-    switch (bf16_form(M, N, K, w_parts && ((uintptr_t)w_parts & 15) == 0, scratch, scratch_bytes)) {
-      case P256: return run_packed<128, 256, 2, MODE>(A, w_parts, M, N, K, ep, s);
-      case P128:
-        if (narrow_is_192(M, N, K)) return run_packed<128, 192, 3, MODE>(A, w_parts, M, N, K, ep, s);
-        return run_packed<128, 128, 4, MODE>(A, w_parts, M, N, K, ep, s);
-      case W288: return run_288<MODE>(A, Wt, M, N, K, ep, s);
-      case F384: tile = T384; break;
-      default: break;
-    }
+    if (form == P256) return run_packed<128, 256, 2, MODE>(A, w_parts, M, N, K, ep, s);
+    if (form == P128 && narrow_is_192(M, N, K)) return run_packed<128, 192, 3, MODE>(A, w_parts, M, N, K, ep, s);
+    if (form == P128) return run_packed<128, 128, 4, MODE>(A, w_parts, M, N, K, ep, s);
+    if (form == W288) return run_288<MODE>(A, Wt, M, N, K, ep, s);
   }
-  switch (tile) {
-    case T256: return run_dlds<256, 256, 64, 4, 2, MODE>(A, Wt, M, N, K, ep, scratch, scratch_bytes, s);
-    case T192: return run_dlds<256, 192, 64, 4, 2, MODE>(A, Wt, M, N, K, ep, scratch, scratch_bytes, s);
-    case T384:
-      if constexpr (MODE != EPI_UNPATCH) return run_dlds<384, 192, 64, 4, 2, MODE>(A, Wt, M, N, K, ep, scratch, scratch_bytes, s);
-    case T128: break;
-  }
-  return run_dlds<128, 128, 64, 2, 2, MODE>(A, Wt, M, N, K, ep, scratch, scratch_bytes, s);
+  return hipErrorInvalidValue;                           // (none is left)
 }
 
 hipError_t launch_gemm(int bf16, int mode, const void* A, const void* Wt, int M, int N, int K, const EpiParams& ep,

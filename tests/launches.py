@@ -1,0 +1,59 @@
+"""What a product launches, without a GPU: a program that links the library with launch calls of its own, which note the kernel and do nothing."""
+import os
+import re
+import subprocess
+
+from paper_2501_04012_amd import build
+
+SOURCE = r"""
+#include <dlfcn.h>
+#include <cstdio>
+#include <string>
+#include "common.h"
+static std::string seen;
+extern "C" __attribute__((visibility("default"))) hipError_t hipLaunchKernel(const void* f, dim3, dim3, void**, size_t, hipStream_t) {
+  Dl_info info;
+  seen += std::string(" ") + (dladdr(f, &info) && info.dli_sname ? info.dli_sname : "unknown");
+  return hipSuccess;
+}
+extern "C" __attribute__((visibility("default"))) hipError_t __hipPushCallConfiguration(dim3, dim3, size_t, hipStream_t) { return hipSuccess; }
+extern "C" __attribute__((visibility("default"))) hipError_t __hipPopCallConfiguration(dim3*, dim3*, size_t*, hipStream_t*) { return hipSuccess; }
+extern "C" __attribute__((visibility("default"))) hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) { return hipSuccess; }
+extern "C" __attribute__((visibility("default"))) hipError_t hipGetLastError() { return hipSuccess; }
+int main() {
+  using namespace fc;
+  int mode, M, N, K, packed;
+  size_t lent;
+  while (scanf("%d %d %d %d %d %zu", &mode, &M, &N, &K, &packed, &lent) == 6) {
+    EpiParams ep;                                        // addresses that are never used
+    ep.out = ep.q = ep.k = ep.v = (void*)4096;
+    ep.ldo = N; ep.D = mode == EPI_HEADS ? N / 3 : N; ep.hd = 32; ep.heads = ep.D / 32; ep.tokens = M; ep.layer_stride = (size_t)M * N;
+    ep.T = 1; ep.H = M; ep.W = 1; ep.p = 1; ep.C = N; ep.eps = (float*)4096;
+    void* const scratch = lent ? (void*)4096 : nullptr;
+    seen.clear();
+    const hipError_t e = launch_gemm(1, mode, (void*)4096, (void*)4096, M, N, K, ep, nullptr, scratch, lent, packed ? (void*)4096 : nullptr);
+    printf("%d %d%s\n", (int)e, (int)bf16_form(M, N, K, packed, scratch, lent), seen.c_str());
+  }
+}
+"""
+
+
+class Launches:
+    def __init__(self, folder):
+        src, self.exe = str(folder / "launches.hip"), str(folder / "launches")
+        with open(src, "w") as f:
+            f.write(SOURCE)
+        subprocess.run([build.HIPCC, "-std=c++17", "-O1", "-w", "--offload-host-only", "-I" + build.CSRC, "-c", src, "-o", self.exe + ".o"], check=True)
+        subprocess.run([build.HIPCC, "-rdynamic", self.exe + ".o", build.LIB_PATH, "-Wl,-rpath," + os.path.dirname(build.LIB_PATH), "-ldl", "-o", self.exe], check=True)
+
+    def __call__(self, products):
+        """products: (mode, M, N, K, packed weights, bytes of scratch memory).  For each: status, bf16_form, [(kernel, tile rows, columns)]."""
+        text = "".join("%d %d %d %d %d %d\n" % tuple(map(int, p)) for p in products)
+        out = subprocess.run([self.exe], input=text, check=True, capture_output=True, text=True).stdout.splitlines()
+        assert len(out) == len(products)
+        found = []
+        for line in out:
+            status, form, *names = line.split()
+            kernels = [re.match(r"_ZN2fc\d+(k_[a-z0-9_]+?)(?:ILi(\d+)ELi(\d+)E|I|E)", n).groups() for n in names]
+            found.append((int(status), int(form), [(k, int(a or 0), int(b or 0)) for k, a, b in kernels]))
+        return found
