@@ -974,7 +974,7 @@ static hipError_t run_skinny_waves(const T* A, const T* Wt, int M, int N, int K,
 }
 
 // Eight waves fill a CU's LDS: for as many tiles as there are CUs.  Above that four, two workgroups to a CU.
-constexpr int kSkinnyMaxK = 1 << 22;                     // 32 rows within a buffer resource's 31-bit range, a tile's within 32 bits
+constexpr int kSkinnyMaxK = 1 << 22;                     // 32 rows within a buffer resource's 31-bit range
 template <typename T, int MODE>
 static hipError_t run_skinny(const void* A, const void* Wt, int M, int N, int K, const EpiParams& ep, hipStream_t s) {
   if ((long long)ceil_div(N, 32) * ceil_div(M, 32) <= 256)
@@ -1622,9 +1622,12 @@ static hipError_t dispatch_f32(const void* A, const void* Wt, const void* w_part
   return run_f32_parts<64, 64, 2, 2, 4, false, MODE>(A, Wt, nullptr, M, N, K, ep, s);
 }
 
+// K that the tiles take: the rows of one lie within 32-bit offsets, up to kTileMaxK those of all tiles (384 of them), up to kNarrowMaxK those of 128x128
+// ones.  320 x 320 x 4 194 368: 67 ms, in the plain kernel 565.
+constexpr int kTileMaxK = 1 << 22, kNarrowMaxK = 1 << 24;
 // The tile of a product of k_gemm_dlds.
 static Bf16Form bf16_tile(bool unpatch, int M, int N, int K) {
-  if (K < 128) return F128;                              // three stages of A: at least two K tiles
+  if (K < 128 || K >= kTileMaxK) return F128;            // (K < 128: three stages of A take at least two K tiles)
   // Tile choice.  256x256 (8 waves, one workgroup per CU) has the best operand reuse but
   // needs several rounds of tiles per CU and wastes the ragged part of N; 256x192 takes
   // over where N is a multiple of 192 that 256 would pad by more than 5 % (N = 1152:
@@ -1736,6 +1739,7 @@ static bool narrow_is_192(int M, int N, int K) { return form_time(kP192, M, N, K
 // The products above take 1.012 of their best form's time in the mean, 1.014 in the sum, 1.12 at most (by the rule before, whose estimates were
 // fitted with 32x32x16 instructions: 1.034, 1.021, 1.40).
 Bf16Form bf16_form(int M, int N, int K, bool packed, const void* scratch, size_t scratch_bytes) {
+  if (K >= kTileMaxK) return F128;
   if (!packed || !packs_weights(N, K) || (unsigned long long)M * K * 2 >= (1ull << 32))                  // 32-bit offsets
     return staged_form(M, N, K, scratch, scratch_bytes);
   auto staged = [&](Bf16Form f) {
@@ -1789,7 +1793,7 @@ static hipError_t dispatch_mode(int bf16, const void* A, const void* Wt, int M, 
     else
       aligned = aligned && ep.ldo % 8 == 0 && ((uintptr_t)ep.out & 15) == 0;
   }
-  if (K % 64 != 0 || !aligned || N < 32 || K >= kSkinnyMaxK) return run_plain<bf16_t, MODE>(A, Wt, M, N, K, ep, s);
+  if (K % 64 != 0 || !aligned || N < 32 || K >= kNarrowMaxK) return run_plain<bf16_t, MODE>(A, Wt, M, N, K, ep, s);
   Bf16Form form = bf16_tile(MODE == EPI_UNPATCH, M, N, K);
   if constexpr (MODE == EPI_HEADS || MODE == EPI_GATE || MODE == EPI_GELU)           // a model's products over token rows
     form = bf16_form(M, N, K, w_parts && ((uintptr_t)w_parts & 15) == 0, scratch, scratch_bytes);
