@@ -36,13 +36,7 @@ namespace fc {
 // panels through its L2 instead of 1 + 32.  (Products of few tile columns row by row, so that no rows are read by two XCDs: 2 to 9 % faster
 // where operands come by turns from four products, 1 to 2 % slower inside a step.)
 [[maybe_unused]] constexpr int kPatchRows = 8;
-// Tile of workgroup id `vb` (total or more: none).  A last round of fewer than 256 tiles is spread over all XCDs, an eighth of it each:
-// their L2s and their ways to memory serve it too (32 to an XCD until there are none left, before: us, 8192 x 1152 x 1152 in 192 tiles of 256x192
-// 26.4, 23.1; 8192 x 1152 x 4608 90, 85; 9326 x 2048 x 2048 in packed 128x256 72, 67; fp32 step of a 1152-wide block 1489, 1418).
-__device__ __forceinline__ int tile_index(int vb, int total) {
-  const int round = vb & ~255, xcd = vb & 7, slot = (vb >> 3) & 31, per = min((total - round + 7) >> 3, 32);
-  return slot < per ? round + xcd * per + slot : total;
-}
+// (tile_index: the tile of a workgroup id, and how a last round of fewer than 256 is dealt out.)
 typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((address_space(1))) const void gbl_void;
 
@@ -333,7 +327,7 @@ __global__ __launch_bounds__(WR * WC * 64) void k_gemm_dlds(const bf16_t* A, con
   // virtual ids run over the whole rounds and, behind them, the units of the last one
   const int padded = splits >= 2 ? ((full + rem * splits + 7) & ~7) : (total + 255) / 256 * 256;
   auto tile_of = [&](int vb, int& bm0, int& bn0, int& kt0, int& kt1, int& slot) {
-    int t = tile_index(vb, total);
+    int t = tile_index(vb, total, spread_round(BM, BN));
     kt0 = 0; kt1 = nkt; slot = -1;
     if (splits >= 2 && vb >= full) {
       const int w = vb - full;
@@ -532,7 +526,7 @@ __global__ __launch_bounds__(256, BN == 128 ? 4 : BN == 192 ? 3 : 2) void k_gemm
   const int total = tiles_m * tiles_n, nk = K / BK, padded = (total + 255) / 256 * 256;
   auto next_tile = [&](int& vb, int& bm0, int& bn0) {      // k_gemm_dlds's order, no split tiles
     for (vb += gridDim.x; vb < padded; vb += gridDim.x) {
-      const int t = tile_index(vb, total);
+      const int t = tile_index(vb, total, spread_round(BM, BN));
       if (t >= total) continue;
       constexpr int gm = kPatchRows;
   const int per_group = gm * tiles_n, group = t / per_group, first_m = group * gm, gsz = min(tiles_m - first_m, gm);
@@ -695,7 +689,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_288(const bf16_t* __restrict__ 
   float* const sbias = (float*)(smem + S * L::kStage);
   float* const sgate = sbias + BN;
 
-  const int total = tiles_m * tiles_n, t = tile_index(blockIdx.x, total);
+  const int total = tiles_m * tiles_n, t = tile_index(blockIdx.x, total, true);
   if (t >= total) return;                                  // k_gemm_dlds's tile order
   constexpr int gm = kPatchRows;
   const int per_group = gm * tiles_n, group = t / per_group, first_m = group * gm, gsz = min(tiles_m - first_m, gm);
@@ -1008,7 +1002,7 @@ __global__ __launch_bounds__(WR * WC * 64) void k_gemm_f32(const float* __restri
   const int wr = wave / WC, wc = wave % WC;
   const int li = lane & 31, lh = lane >> 5;
   // workgroup -> tile as in k_gemm_dlds
-  const int t = tile_index(blockIdx.x, tiles_m * tiles_n);
+  const int t = tile_index(blockIdx.x, tiles_m * tiles_n, true);
   if (t >= tiles_m * tiles_n) return;
   constexpr int gm = kPatchRows;
   const int per_group = gm * tiles_n, group = t / per_group, first_m = group * gm, gsz = min(tiles_m - first_m, gm);
@@ -1164,7 +1158,7 @@ __global__ __launch_bounds__(WR * WC * 64, PER_SIMD) void k_gemm_f32_parts(const
   const int wr = wave / WC, wc = wave % WC;
   const int li = lane & 31, lh = lane >> 5;
   // workgroup -> tile as in k_gemm_dlds
-  const int t = tile_index(blockIdx.x, tiles_m * tiles_n);
+  const int t = tile_index(blockIdx.x, tiles_m * tiles_n, true);
   if (t >= tiles_m * tiles_n) return;
   constexpr int gm = kPatchRows;
   const int per_group = gm * tiles_n, group = t / per_group, first_m = group * gm, gsz = min(tiles_m - first_m, gm);

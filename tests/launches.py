@@ -38,13 +38,19 @@ int main() {
 """
 
 
+def program(folder, source):
+    """Compiles a host program against the library's headers and links the library."""
+    src, exe = str(folder / "program.hip"), str(folder / "program")
+    with open(src, "w") as f:
+        f.write(source)
+    subprocess.run([build.HIPCC, "-std=c++17", "-O1", "-w", "--offload-host-only", "-I" + build.CSRC, "-c", src, "-o", exe + ".o"], check=True)
+    subprocess.run([build.HIPCC, "-rdynamic", exe + ".o", build.LIB_PATH, "-Wl,-rpath," + os.path.dirname(build.LIB_PATH), "-ldl", "-o", exe], check=True)
+    return exe
+
+
 class Launches:
     def __init__(self, folder):
-        src, self.exe = str(folder / "launches.hip"), str(folder / "launches")
-        with open(src, "w") as f:
-            f.write(SOURCE)
-        subprocess.run([build.HIPCC, "-std=c++17", "-O1", "-w", "--offload-host-only", "-I" + build.CSRC, "-c", src, "-o", self.exe + ".o"], check=True)
-        subprocess.run([build.HIPCC, "-rdynamic", self.exe + ".o", build.LIB_PATH, "-Wl,-rpath," + os.path.dirname(build.LIB_PATH), "-ldl", "-o", self.exe], check=True)
+        self.exe = program(folder, SOURCE)
 
     def __call__(self, products):
         """products: (mode, M, N, K, packed weights, bytes of scratch memory).  For each: status, bf16_form, [(kernel, tile rows, columns)]."""
