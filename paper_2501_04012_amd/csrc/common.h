@@ -329,7 +329,7 @@ bool packs_weights(int N, int K);
 // k_gemm_288
 enum Bf16Form : int { F128, F192, F256, F384, P128, P256, W288 };
 Bf16Form bf16_form(int M, int N, int K, bool packed, const void* scratch, size_t scratch_bytes);
-bool packed_weights_serve(int M, int N, int K, bool lent);          // whether a product of M rows takes them, with scratch lent or without
+bool packed_weights_serve(int M, int N, int K, size_t lent);        // whether a product of M rows takes them, lent so many bytes of scratch memory
 hipError_t launch_pack_weights(const void* W, void* out, int N, int K, hipStream_t s);
 size_t split_weights_bytes(int N, int K);
 hipError_t launch_split_weights(const float* Wt, void* out, int N, int K, hipStream_t s);

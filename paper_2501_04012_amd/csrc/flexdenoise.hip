@@ -9,6 +9,7 @@
 #include <cstring>
 #include <map>
 #include <string>
+#include <tuple>
 #include <vector>
 
 using namespace fc;
@@ -192,13 +193,12 @@ struct Carver {          // bump allocator over a byte range, 256-byte aligned p
   }
 };
 
-// Whether a product of the model's rows takes packed weights at any number of samples: past 2^17 rows the rounds that packed
-// tiles save are less than what they cost.  All products over token rows are lent scratch memory but the queries of the cross attention.
-bool rows_take_packed(const fc_model* m, int in, int out) {
+// Whether a product of the model's rows, lent `lent` bytes of scratch memory a row, takes packed weights at any number of samples: past 2^17
+// rows the rounds that packed tiles save are less than what they cost.
+bool rows_take_packed(const fc_model* m, int in, int out, size_t lent) {
   if (!packs_weights(out, in)) return false;
-  const bool queries = m->cfg.attn_mode == FC_ATTN_FACTORIZED_CROSS && in == m->cfg.hidden && out == m->cfg.hidden;
   for (long long rows = m->Ns; rows == m->Ns || rows <= 1 << 17; rows += m->Ns)
-    if (packed_weights_serve((int)rows, out, in, true) || (queries && packed_weights_serve((int)rows, out, in, false))) return true;
+    if (packed_weights_serve((int)rows, out, in, rows * lent)) return true;
   return false;
 }
 
@@ -208,21 +208,21 @@ WeightBytes layout_weights(fc_model* m, unsigned char* base, unsigned char* copi
   const fc_model_config& c = m->cfg;
   const size_t D = c.hidden, M = c.mlp_dim, es = m->esz;
   Carver cv(base), cc(copies);
-  std::map<std::pair<int, int>, bool> packed;
+  std::map<std::tuple<int, int, size_t>, bool> packed;
   auto lin = [&](Linear& L, int in, int out) {
     L.in = in; L.out = out;
     L.wt = cv.take((size_t)in * out * es);
     L.b = (float*)cv.take((size_t)out * 4);
   };
-  // the products over all token rows
-  auto lin_rows = [&](Linear& L, int in, int out) {
+  // the products over all token rows; lent: scratch memory that a call lends them, bytes a row
+  auto lin_rows = [&](Linear& L, int in, int out, size_t lent) {
     lin(L, in, out);
     L.parts = nullptr;
     if (m->chain_shape) L.parts = cv.take((size_t)in * out * es);
     else if (!m->bf16) L.parts = cc.take(split_weights_bytes(out, in));
     else {
-      const auto known = packed.find({in, out});
-      const bool take = known != packed.end() ? known->second : packed.emplace(std::make_pair(in, out), rows_take_packed(m, in, out)).first->second;
+      const auto known = packed.find({in, out, lent});
+      const bool take = known != packed.end() ? known->second : packed.emplace(std::make_tuple(in, out, lent), rows_take_packed(m, in, out, lent)).first->second;
       if (take) L.parts = cc.take((size_t)in * out * es);
     }
   };
@@ -235,21 +235,22 @@ WeightBytes layout_weights(fc_model* m, unsigned char* base, unsigned char* copi
   m->mod_b = (float*)cv.take((size_t)c.depth * m->nmod * D * 4);
   m->blocks.resize(c.depth);
   if (c.attn_mode == FC_ATTN_FACTORIZED_CROSS) lin(m->xkv, D, c.depth * 2 * D);
+  const size_t act = D * es, hid = M * es;               // a row of k, of the MLP's hidden layer
   for (int l = 0; l < c.depth; ++l) {
     Block& b = m->blocks[l];
-    lin_rows(b.qkv[0], D, 3 * D);
-    lin_rows(b.proj[0], D, D);
+    lin_rows(b.qkv[0], D, 3 * D, hid);
+    lin_rows(b.proj[0], D, D, act);
     if (c.attn_mode == FC_ATTN_FACTORIZED_CROSS) {
-      lin_rows(b.qkv[1], D, 3 * D);
-      lin_rows(b.proj[1], D, D);
-      lin_rows(b.xq, D, D);
+      lin_rows(b.qkv[1], D, 3 * D, hid);
+      lin_rows(b.proj[1], D, D, act);
+      lin_rows(b.xq, D, D, 0);
       b.xkv.in = D; b.xkv.out = 2 * D;                   // its rows of the product that serves all blocks
       b.xkv.wt = base ? (unsigned char*)m->xkv.wt + (size_t)l * 2 * D * D * es : nullptr;
       b.xkv.b = base ? m->xkv.b + (size_t)l * 2 * D : nullptr;
-      lin_rows(b.xproj, D, D);
+      lin_rows(b.xproj, D, D, act);
     }
-    lin_rows(b.fc1, D, M);
-    lin_rows(b.fc2, M, D);
+    lin_rows(b.fc1, D, M, act);
+    lin_rows(b.fc2, M, D, act);
   }
   lin(m->fmod, D, 2 * D);
   lin(m->fout, D, m->pd);

@@ -1760,9 +1760,9 @@ Bf16Form bf16_form(int M, int N, int K, bool packed, const void* scratch, size_t
   return form;
 }
 
-bool packed_weights_serve(int M, int N, int K, bool lent) {
+bool packed_weights_serve(int M, int N, int K, size_t lent) {
   if ((long long)ceil_div(M, 128) * ceil_div(N, 128) < 32 || N < 32) return false;      // k_gemm_skinny
-  const Bf16Form form = lent ? bf16_form(M, N, K, true, (const void*)16, ~(size_t)0) : bf16_form(M, N, K, true, nullptr, 0);
+  const Bf16Form form = bf16_form(M, N, K, true, lent ? (const void*)16 : nullptr, lent);
   return form == P128 || form == P256;
 }
 

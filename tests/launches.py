@@ -5,21 +5,32 @@ import subprocess
 
 from paper_2501_04012_amd import build
 
-SOURCE = r"""
+# the runtime calls of the library: launches are noted, memory is an address
+STUBS = r"""
 #include <dlfcn.h>
 #include <cstdio>
 #include <string>
 #include "common.h"
+#define STUB extern "C" __attribute__((visibility("default"))) hipError_t
 static std::string seen;
-extern "C" __attribute__((visibility("default"))) hipError_t hipLaunchKernel(const void* f, dim3, dim3, void**, size_t, hipStream_t) {
+static size_t address = 1 << 20;
+STUB hipLaunchKernel(const void* f, dim3, dim3, void**, size_t, hipStream_t) {
   Dl_info info;
   seen += std::string(" ") + (dladdr(f, &info) && info.dli_sname ? info.dli_sname : "unknown");
   return hipSuccess;
 }
-extern "C" __attribute__((visibility("default"))) hipError_t __hipPushCallConfiguration(dim3, dim3, size_t, hipStream_t) { return hipSuccess; }
-extern "C" __attribute__((visibility("default"))) hipError_t __hipPopCallConfiguration(dim3*, dim3*, size_t*, hipStream_t*) { return hipSuccess; }
-extern "C" __attribute__((visibility("default"))) hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) { return hipSuccess; }
-extern "C" __attribute__((visibility("default"))) hipError_t hipGetLastError() { return hipSuccess; }
+STUB __hipPushCallConfiguration(dim3, dim3, size_t, hipStream_t) { return hipSuccess; }
+STUB __hipPopCallConfiguration(dim3*, dim3*, size_t*, hipStream_t*) { return hipSuccess; }
+STUB hipFuncSetAttribute(const void*, hipFuncAttribute, int) { return hipSuccess; }
+STUB hipGetLastError() { return hipSuccess; }
+STUB hipMalloc(void** p, size_t n) { *p = (void*)address; address += (n + 4095) / 4096 * 4096; return hipSuccess; }
+STUB hipFree(void*) { return hipSuccess; }
+STUB hipMemcpy(void*, const void*, size_t, hipMemcpyKind) { return hipSuccess; }
+STUB hipMemGetInfo(size_t* free, size_t* total) { *free = *total = (size_t)288 << 30; return hipSuccess; }
+STUB hipDeviceSynchronize() { return hipSuccess; }
+STUB hipGetDevice(int* d) { *d = 0; return hipSuccess; }
+"""
+SOURCE = STUBS + r"""
 int main() {
   using namespace fc;
   int mode, M, N, K, packed;
@@ -43,9 +54,15 @@ def program(folder, source):
     src, exe = str(folder / "program.hip"), str(folder / "program")
     with open(src, "w") as f:
         f.write(source)
-    subprocess.run([build.HIPCC, "-std=c++17", "-O1", "-w", "--offload-host-only", "-I" + build.CSRC, "-c", src, "-o", exe + ".o"], check=True)
+    subprocess.run([build.HIPCC, "-std=c++17", "-O1", "-w", "--offload-host-only", "-I" + build.CSRC, "-I" + os.path.join(build.HERE, "..", "include"), "-c", src, "-o", exe + ".o"], check=True)
     subprocess.run([build.HIPCC, "-rdynamic", exe + ".o", build.LIB_PATH, "-Wl,-rpath," + os.path.dirname(build.LIB_PATH), "-ldl", "-o", exe], check=True)
     return exe
+
+
+def kernels(symbols):
+    """[(kernel, first two of its numbers: rows and columns of a tile)]"""
+    parts = [re.match(r"_ZN2fc\d+(k_[a-z0-9_]+?)(?:ILi(\d+)ELi(\d+)E|I|E)", n).groups() for n in symbols]
+    return [(k, int(a or 0), int(b or 0)) for k, a, b in parts]
 
 
 class Launches:
@@ -60,6 +77,5 @@ class Launches:
         found = []
         for line in out:
             status, form, *names = line.split()
-            kernels = [re.match(r"_ZN2fc\d+(k_[a-z0-9_]+?)(?:ILi(\d+)ELi(\d+)E|I|E)", n).groups() for n in names]
-            found.append((int(status), int(form), [(k, int(a or 0), int(b or 0)) for k, a, b in kernels]))
+            found.append((int(status), int(form), kernels(names)))
         return found
