@@ -48,7 +48,8 @@ template <int N> __device__ __forceinline__ void wait_vm() {
 // acc += x * y, 16x16x32.  An instruction of its own in asm for one reason: its sum has to stay in its registers.  The compiler ties the
 // sums of 32x32 instructions to their inputs but not those of four registers, moves them about between the two halves of a K
 // tile and then spills (50 registers of the 256x256 tile).  What the compiler would see to otherwise: nothing but other
-// such instructions touches a sum before settled().
+// such instructions on the same registers touches a sum before settled(), and no vector instruction writes an operand, a copied fragment or a
+// zeroed sum, within two issue slots in front.  The source does not force either; both are read off the built code in a test.
 __device__ __forceinline__ void mfma_into(f32x4& acc, const bf16x8& x, const bf16x8& y) {
 #if defined(__HIP_DEVICE_COMPILE__)
   asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(__builtin_bit_cast(f32x4, x)), "v"(__builtin_bit_cast(f32x4, y)));
