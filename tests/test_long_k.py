@@ -1,4 +1,5 @@
-"""Products along a very long K: tiles of 128x128 as long as their rows lie within 32-bit offsets, not the plain kernel."""
+"""Products along a very long K, in tiles of 128x128 as long as their rows lie within 32-bit offsets and not in the plain kernel, and of
+operands of more than 4 GB in every other tile of the product kernel."""
 import pytest
 
 from launches import Launches
@@ -33,5 +34,36 @@ def test_linear_bf16_along_a_long_k(fc, M, N, K):
     fc.fc_op_linear(fc.FC_BF16, A, W, None, None, out, M, N, K, 0)
     err = float((out.double() - want).norm() / want.norm())
     record(rel_l2=err)
-    # rounding of the result to bf16: at most 2^-9 of it; K / 32 fp32 additions one after the other: 2^-24 sqrt(K / 32) in the mean
+    # rounding of normal values to bf16: 1.66e-3 of them in the root mean square; K / 32 fp32 additions one after the other: 2^-24 sqrt(K / 32) in the mean
     assert err < 2.0 ** -9 + 2.0 ** -24 * (K / 32) ** 0.5
+
+
+BEYOND = [(65600 + 37, 1152, 32768, (256, 192)), (65600 + 37, 2048, 32768, (256, 256)), (2048 + 1, 65640, 32768, (256, 256))]       # M, N, K, tile
+
+
+@pytest.mark.parametrize("M,N,K,tile", BEYOND)
+def test_tiles_of_the_large_operands(tmp_path, M, N, K, tile):
+    assert max(M, N) * K * 2 >= 2 ** 32
+    (status, _, launched), = Launches(tmp_path)([(STORE, M, N, K, False, 0)])
+    assert status == 0 and launched == [("k_gemm_dlds", *tile)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,N,K", [b[:3] for b in BEYOND])
+def test_linear_bf16_of_large_operands_in_three_stages(fc, M, N, K):
+    """Rows and columns at the ends and around 2^31 and 2^32 bytes against the float64 product, the rest for finiteness."""
+    import torch
+    g = torch.Generator(device="cuda:0").manual_seed(M)
+    A = torch.empty((M, K), dtype=torch.bfloat16, device="cuda:0").normal_(generator=g)
+    W = torch.empty((N, K), dtype=torch.bfloat16, device="cuda:0").normal_(std=K ** -0.5, generator=g)
+    out = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda:0")
+    fc.fc_op_linear(fc.FC_BF16, A, W, None, None, out, M, N, K, 0)
+    assert bool(torch.isfinite(out).all())
+    pick = lambda n: torch.tensor(sorted({x for e in (0, 256, 32768, 65536, n) for x in range(e - 3, e + 3) if 0 <= x < n} | set(range(0, n, 997))), device="cuda:0")
+    m, n = pick(M), pick(N)
+    want = A[m].double() @ W.double().t().contiguous() if N < M else (W[n].double() @ A.double().t().contiguous()).t()
+    got = out[m].double() if N < M else out[:, n].double()
+    err = float((got - want).norm() / want.norm())
+    record(rel_l2=err)
+    # rounding as above; element by element half an ulp of the bf16 result, and fp32 sums of 1024 instructions one after the other
+    assert err < 2.0 ** -9 and bool(((got - want).abs() <= 2.0 ** -8 * want.abs() + 1e-4).all())
