@@ -218,7 +218,7 @@ struct Epilogue {
     }
   }
 
-  // Four consecutive rows m0..m0+3 of column c (the unit of the 32x32 MFMA accumulator).
+  // Four consecutive rows m0..m0+3 of column c (what a lane of an MFMA accumulator holds one after the other).
   __device__ __forceinline__ void store4(const Col& c, int m0, const float (&acc)[4]) const {
     if (!c.valid || m0 >= Mvalid) return;
 #pragma unroll

@@ -20,9 +20,9 @@ namespace fc {
 // sums per product, holds a higher clock there (random operands out of registers 2040 TFLOP/s against 1835, with the
 // fragments read from LDS 1845 against 1665), and its sums are those of two 32x32x16 bit for bit.
 // The operand tiles go from global memory straight into LDS (buffer_load ... lds: lane l's 16 bytes land at
-// base + 16 l), two stages, with no register staging and no ds_write.
+// base + 16 l), two or three stages of A's rows and, behind them, two of B's (DldsStages), with no register staging and no ds_write.
 //
-// LDS layout of a stage: BM rows of A then BN rows of B, 128 bytes each, unpadded.
+// LDS layout of a stage: its rows, 128 bytes each, unpadded.
 // A 256-byte LDS line holds 2 rows; chunk kc (16 bytes) of row r sits at
 //   line r/2, slot (r % 2) * 8 + (kc ^ ((r/2) % 8)),
 // so that the 16 rows a ds_read_b128 touches at one kc fall into 16 distinct slots
@@ -132,7 +132,7 @@ struct TileVectors {
 #pragma unroll
     for (int x = 0; x < NV; ++x) {
       const int c = x * 64 + lane;
-      // (WTN is a multiple of 32: lanes of one load may belong to bias and to gate)
+      // (WTN is 32, 48, 64, 96 or 128: lanes of one load may belong to bias and to gate)
       if (x * 64 + 63 < WTN || !Epi::kHasGate)
         v[x] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rb, (n0 + c) * 4, 0, 0));
       else if (x * 64 >= WTN)
@@ -277,7 +277,7 @@ template <int N> __device__ __forceinline__ void counted_wait_lgkm0() {
 // A K tile is 2 TN columns of products (two halves of K, 32 each), TM matrix instructions a column.  The fragment of
 // a column is read AHEAD columns before it is multiplied; the row fragments of the second half are read
 // during the first.  The barrier that publishes K tile g + 1 sits TAIL columns before the end of g, whose
-// fragments are all in registers by then.  After it a wave requests K tile g + 2 into the stage it
+// fragments are all in registers by then.  After it a wave requests K tile g + 2 (of A's rows, where they have three stages, g + 3) into the stages it
 // has just stopped reading, reads the first fragments of g + 1, and only then multiplies g's
 // last columns: neither the requests nor the LDS latency of the first fragments find the matrix
 // pipe empty, and a DMA still has a whole K tile of matrix work to land.
@@ -290,6 +290,7 @@ template <int N> __device__ __forceinline__ void counted_wait_lgkm0() {
 template <int BM, int BN, int NW> struct DldsStages {
   static constexpr int A = BM * 128, B = BN * 128, SA = NW == 8 && 3 * A + 2 * B <= 160 * 1024 ? 3 : 2, BYTES = SA * A + 2 * B;
 };
+constexpr int kUnitKTiles = 2;                             // K tiles of the shortest unit of work of a tile with three stages (the dispatch and split_ranges)
 template <int BM, int BN, int BK, int WR, int WC, typename Epi>
 __global__ __launch_bounds__(WR * WC * 64) void k_gemm_dlds(const bf16_t* A, const bf16_t* Wt,
                                                            int M, int N, int K, int tiles_m, int tiles_n, Epi epi,
@@ -305,9 +306,11 @@ __global__ __launch_bounds__(WR * WC * 64) void k_gemm_dlds(const bf16_t* A, con
   constexpr int LA = BM / RW / NW, LB = BN / RW / NW;      // wave-loads per wave and K tile: rows of A, rows of Wt
   static_assert(BM % (RW * NW) == 0 && BN % (RW * NW) == 0, "loads must divide among waves");
   static_assert(LB <= LA, "B shares A's lane offsets");
+  static_assert(TAIL * TM >= LB + LA && TAIL * TM >= TM + AHEAD, "requests and first fragments go between the last columns' products");
   static_assert((NW * 4) % CPR == 0 && (BM / RW * 4) % CPR == 0, "the swizzle must not depend on the load index");
   using L = DldsStages<BM, BN, NW>;
   constexpr int SA = L::SA, B_REGION = SA * L::A;
+  static_assert(SA - 1 <= kUnitKTiles, "a unit's requests reach at most into the next one");
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -530,7 +533,7 @@ __global__ __launch_bounds__(256, BN == 128 ? 4 : BN == 192 ? 3 : 2) void k_gemm
       const int t = tile_index(vb, total, spread_round(BM, BN));
       if (t >= total) continue;
       constexpr int gm = kPatchRows;
-  const int per_group = gm * tiles_n, group = t / per_group, first_m = group * gm, gsz = min(tiles_m - first_m, gm);
+      const int per_group = gm * tiles_n, group = t / per_group, first_m = group * gm, gsz = min(tiles_m - first_m, gm);
       bm0 = (first_m + (t % per_group) % gsz) * BM;
       bn0 = ((t % per_group) / gsz) * BN;
       return true;
@@ -1497,7 +1500,7 @@ static int split_ranges(long long total, long long slots, int K, const void* scr
   if (total / 256 > 8 || rem == 0 || rem > slots / 2 || (slots != 256 && full != 0) || !scratch || ((uintptr_t)scratch & 15) != 0) return 1;
   long long sp = slots / rem;
   sp = sp > 4 ? 4 : sp;
-  sp = sp > K / 128 ? K / 128 : sp;
+  sp = sp > K / (64 * kUnitKTiles) ? K / (64 * kUnitKTiles) : sp;
   if (sp < 2 || (long long)K * (sp - 1) / sp < 1536 || (size_t)(rem * sp) * BM * BN * sizeof(float) > scratch_bytes) return 1;
   return (int)sp;
 }
@@ -1622,7 +1625,7 @@ static hipError_t dispatch_f32(const void* A, const void* Wt, const void* w_part
 constexpr int kTileMaxK = 1 << 22, kNarrowMaxK = 1 << 24;
 // The tile of a product of k_gemm_dlds.
 static Bf16Form bf16_tile(bool unpatch, int M, int N, int K) {
-  if (K < 128 || K >= kTileMaxK) return F128;            // (K < 128: three stages of A take at least two K tiles)
+  if (K < 64 * kUnitKTiles || K >= kTileMaxK) return F128;           // (128x128 tiles have two stages)
   // Tile choice.  256x256 (8 waves, one workgroup per CU) has the best operand reuse but
   // needs several rounds of tiles per CU and wastes the ragged part of N; 256x192 takes
   // over where N is a multiple of 192 that 256 would pad by more than 5 % (N = 1152:

@@ -26,7 +26,7 @@ LIN_SHAPES = [
     (2500, 48, 192),         # narrow N, many rows (the output head's shape class), ragged both ways
     (8209, 2048, 128),       # enough tiles for the 256x256 configuration, ragged M
     (8200, 1152, 128),       # N a multiple of 192 that 256 would pad: the 256x192 configuration, ragged M
-    (8209, 2048, 192),       # an odd number of K tiles: the general form of the tile kernel, 256x256
+    (8209, 2048, 192),       # an odd number of K tiles, 256x256
     (8200, 1152, 320),       # the same, 256x192
     (8209, 2304, 384),       # six K tiles, 256x256, ragged M
     (250, 160, 72),          # K not a multiple of 64: plain kernel
@@ -122,8 +122,8 @@ def test_linear_bf16_split_k_remainder(fc, M, N, K, epilogue):
 
 
 def test_linear_bf16_operand_beyond_32_bit_offsets(fc):
-    """An activation matrix of more than 4 GB: the tile kernel's buffer-addressed form covers
-    32-bit ranges only, so the dispatcher must hand this product to the general form.  The
+    """An activation matrix of more than 4 GB, in 128x128 tiles: the tile kernel's buffer resources cover
+    32-bit ranges, a tile's rows each.  The
     operand is drawn on the device (it is 4.3 GB) with a seeded generator; the float64 product
     is checked on sampled rows copied back to the host, the rest for finiteness."""
     torch = _torch()
