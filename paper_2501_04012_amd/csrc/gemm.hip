@@ -291,7 +291,7 @@ template <int BM, int BN, int NW> struct DldsStages {
   static constexpr int A = BM * 128, B = BN * 128, SA = NW == 8 && 3 * A + 2 * B <= 160 * 1024 ? 3 : 2, BYTES = SA * A + 2 * B;
 };
 constexpr int kUnitKTiles = 2;                             // K tiles of the shortest unit of work of a tile with three stages (the dispatch and split_ranges)
-template <int BM, int BN, int BK, int WR, int WC, typename Epi>
+template <int BM, int BN, int WR, int WC, typename Epi>
 __global__ __launch_bounds__(WR * WC * 64) void k_gemm_dlds(const bf16_t* A, const bf16_t* Wt,
                                                            int M, int N, int K, int tiles_m, int tiles_n, Epi epi,
                                                            int splits, float* partial) {
@@ -300,9 +300,8 @@ __global__ __launch_bounds__(WR * WC * 64) void k_gemm_dlds(const bf16_t* A, con
   constexpr int WTM = BM / WR, WTN = BN / WC;
   constexpr int TM = WTM / 16, TN = WTN / 16;
   constexpr int AHEAD = TN < 5 ? TN : 5, TAIL = AHEAD - 1, COLS = 2 * TN;
-  static_assert(BK == 64, "128-byte rows, two halves of 32");
   static_assert(TN >= 4 && TM <= 2 * TN, "fragments of the second half are read during the first");
-  constexpr int CPR = BK / 8, RPL = 16 / CPR, RW = 4 * RPL;
+  constexpr int BK = 64, CPR = BK / 8, RPL = 16 / CPR, RW = 4 * RPL;      // 128-byte rows, two halves of 32
   constexpr int LA = BM / RW / NW, LB = BN / RW / NW;      // wave-loads per wave and K tile: rows of A, rows of Wt
   static_assert(BM % (RW * NW) == 0 && BN % (RW * NW) == 0, "loads must divide among waves");
   static_assert(LB <= LA, "B shares A's lane offsets");
@@ -1505,13 +1504,13 @@ static int split_ranges(long long total, long long slots, int K, const void* scr
   return (int)sp;
 }
 
-template <int BM, int BN, int BK, int WR, int WC, int MODE>
+template <int BM, int BN, int WR, int WC, int MODE>
 static hipError_t run_dlds(const void* A, const void* Wt, int M, int N, int K, const EpiParams& ep, void* scratch,
                            size_t scratch_bytes, hipStream_t s) {
   using Epi = Epilogue<bf16_t, MODE>;
   Epi epi = Epi::make(ep, M, N);
   constexpr size_t smem = DldsStages<BM, BN, WR * WC>::BYTES;
-  auto kern = k_gemm_dlds<BM, BN, BK, WR, WC, Epi>;
+  auto kern = k_gemm_dlds<BM, BN, WR, WC, Epi>;
   static bool attr_set = false;
   if (!attr_set) {
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
@@ -1796,13 +1795,13 @@ static hipError_t dispatch_mode(int bf16, const void* A, const void* Wt, int M, 
   if constexpr (MODE == EPI_HEADS || MODE == EPI_GATE || MODE == EPI_GELU)           // a model's products over token rows
     form = bf16_form(M, N, K, w_parts && ((uintptr_t)w_parts & 15) == 0, scratch, scratch_bytes);
   switch (form) {
-    case F256: return run_dlds<256, 256, 64, 4, 2, MODE>(A, Wt, M, N, K, ep, scratch, scratch_bytes, s);
-    case F192: return run_dlds<256, 192, 64, 4, 2, MODE>(A, Wt, M, N, K, ep, scratch, scratch_bytes, s);
-    case F128: return run_dlds<128, 128, 64, 2, 2, MODE>(A, Wt, M, N, K, ep, scratch, scratch_bytes, s);
+    case F256: return run_dlds<256, 256, 4, 2, MODE>(A, Wt, M, N, K, ep, scratch, scratch_bytes, s);
+    case F192: return run_dlds<256, 192, 4, 2, MODE>(A, Wt, M, N, K, ep, scratch, scratch_bytes, s);
+    case F128: return run_dlds<128, 128, 2, 2, MODE>(A, Wt, M, N, K, ep, scratch, scratch_bytes, s);
     default: break;
   }
   if constexpr (MODE != EPI_UNPATCH)
-    if (form == F384) return run_dlds<384, 192, 64, 4, 2, MODE>(A, Wt, M, N, K, ep, scratch, scratch_bytes, s);
+    if (form == F384) return run_dlds<384, 192, 4, 2, MODE>(A, Wt, M, N, K, ep, scratch, scratch_bytes, s);
   if constexpr (MODE == EPI_HEADS || MODE == EPI_GATE || MODE == EPI_GELU) {
     if (form == P256) return run_packed<128, 256, 2, MODE>(A, w_parts, M, N, K, ep, s);
     if (form == P128 && narrow_is_192(M, N, K)) return run_packed<128, 192, 3, MODE>(A, w_parts, M, N, K, ep, s);
