@@ -265,8 +265,8 @@ def hbm_ops_bench(args):
 
 def mfma_ceiling_bench(args):
     """Secondary measurement (--mfma-ceiling): what the part at hand sustains.
-    (1) The library's pipe-rate microbenchmark: independent bf16 32x32x16 MFMA chains on random
-    and on constant operands, v_exp_f32 streams, both in one wave, and MFMA waves beside
+    (1) The library's pipe-rate microbenchmark: independent bf16 MFMA chains, of 32x32x16 (the
+    attention kernels) and of 16x16x32 (the products), on random and on constant operands, v_exp_f32 streams, both in one wave, and MFMA waves beside
     exponential waves on the same SIMDs, each with the shader clock it ran at.
     (2) Yardsticks, not on the product path: torch.matmul (bf16, the vendor's GEMM library) on
     the four GEMM shapes of the full-3D configuration and torch's fused attention on its
@@ -293,8 +293,10 @@ def mfma_ceiling_bench(args):
     pipes = {}
     for label, ops, ma, mb, blocks in (
             ("mfma_random_operands_2_waves_per_simd", rnd, 1, 1, 256),
+            ("mfma_16x16x32_random_operands_2_waves_per_simd", rnd, 4, 4, 256),
             ("mfma_random_operands_4_waves_per_simd", rnd, 1, 1, 512),
             ("mfma_constant_operands_2_waves_per_simd", const, 1, 1, 256),
+            ("mfma_16x16x32_constant_operands_2_waves_per_simd", const, 4, 4, 256),
             ("exp_only_2_waves_per_simd", rnd, 2, 2, 256),
             ("mfma_and_exp_in_one_wave", rnd, 3, 3, 256),
             ("mfma_waves_beside_exp_waves", rnd, 1, 2, 256)):
@@ -302,8 +304,8 @@ def mfma_ceiling_bench(args):
         clocks = torch.zeros(blocks * 16, dtype=torch.int64, device="cuda")
         ms = timed(lambda: fc.fc_bench_pipe_rates(ops, iters, ma, mb, blocks, sink, clocks), 3)
         c = clocks.cpu().numpy().reshape(-1, 2).astype(np.float64)
-        mfma_waves = blocks * (4 * (ma & 1) + 4 * (mb & 1))
-        exp_waves = blocks * (4 * ((ma >> 1) & 1) + 4 * ((mb >> 1) & 1))
+        mfma_waves = blocks * (4 * (ma in (1, 3, 4)) + 4 * (mb in (1, 3, 4)))
+        exp_waves = blocks * (4 * (ma in (2, 3)) + 4 * (mb in (2, 3)))
         r = {"ms": ms, "shader_clock_ghz": float(np.median(c[:, 0] / np.maximum(c[:, 1], 1.0)) * 0.1)}
         if mfma_waves:
             r["mfma_tflops"] = mfma_waves * iters * 4 * 32768.0 / (ms * 1e-3) / 1e12

@@ -17,8 +17,8 @@ namespace fc {
 //   B: column i of the 16-col tile, k = 8h .. 8h+7
 //   D: column i, rows 4h + e in register e
 // 16x16x32 and not 32x32x16: the matrix pipe runs at the power limit, and 16x16x32, which reads and writes half as many
-// sums per product, holds a higher clock there (random operands out of registers 2040 TFLOP/s against 1835, with the
-// fragments read from LDS 1845 against 1665), and its sums are those of two 32x32x16 bit for bit.
+// sums per product, holds a higher clock there (fc_bench_pipe_rates, random operands out of registers: 1926 TFLOP/s at 1.99 GHz against
+// 1716 at 1.72), and its sums are those of two 32x32x16 bit for bit.
 // The operand tiles go from global memory straight into LDS (buffer_load ... lds: lane l's 16 bytes land at
 // base + 16 l), two or three stages of A's rows and, behind them, two of B's (DldsStages), with no register staging and no ds_write.
 //

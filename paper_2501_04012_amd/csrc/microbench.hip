@@ -1,13 +1,13 @@
-// Microbenchmarks of the matrix pipe and the vector pipe of a compute unit, as the
-// attention and GEMM kernels of a step load them: independent v_mfma_f32_32x32x16_bf16
-// chains, v_exp_f32 streams, and the two together (in one wave, or in different waves of a
-// workgroup).  They give the rates the step's kernels are to be read against on the part at
+// Microbenchmarks of the matrix pipe and the vector pipe of a compute unit: independent chains of
+// v_mfma_f32_32x32x16_bf16, as the attention kernels issue them, or of v_mfma_f32_16x16x32_bf16, as the
+// bf16 products do, v_exp_f32 streams, and 32x32x16 chains and exponentials together (in one wave, or in
+// different waves of a workgroup).  They give the rates the step's kernels are to be read against on the part at
 // hand (sustained clock under matrix load included) and are not part of a step.
 #include "common.h"
 
 namespace fc {
 
-// mode bits: 1 = this wave issues MFMAs, 2 = this wave issues exponentials.
+// mode bits: 1 = this wave issues MFMAs of 32x32x16, 2 = this wave issues exponentials; mode 4: MFMAs of 16x16x32, twice as many, half as long each.
 // split != 0: waves 0..3 of the workgroup take `mode_a`, waves 4..7 take `mode_b`.
 // clocks[2 * wave_global] = shader-clock cycles of the loop, [2 * wave_global + 1] = the same
 // interval on the constant-rate counter (100 MHz): their ratio is the shader clock.
@@ -28,6 +28,9 @@ __global__ __launch_bounds__(512, 1) void k_pipe_rates(const bf16_t* __restrict_
   for (int j = 0; j < 4; ++j)
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[j][r] = 0.0f;
+  f32x4 acc16[8];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) acc16[j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
   float e[4 * EXP_PER_MFMA];
 #pragma unroll
   for (int i = 0; i < 4 * EXP_PER_MFMA; ++i) e[i] = 0.01f * (float)(lane + i);
@@ -52,6 +55,11 @@ __global__ __launch_bounds__(512, 1) void k_pipe_rates(const bf16_t* __restrict_
         for (int i = 0; i < EXP_PER_MFMA; ++i) e[j * EXP_PER_MFMA + i] = __builtin_amdgcn_exp2f(-e[j * EXP_PER_MFMA + i]);
       }
     }
+  } else if (mode == 4) {
+    for (int it = 0; it < iters; ++it) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) acc16[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[j & 3], b[j >> 1], acc16[j], 0, 0, 0);
+    }
   }
   const long long c1 = clock64(), w1 = wall_clock64();
 
@@ -60,6 +68,10 @@ __global__ __launch_bounds__(512, 1) void k_pipe_rates(const bf16_t* __restrict_
   for (int j = 0; j < 4; ++j)
 #pragma unroll
     for (int r = 0; r < 16; ++r) s += acc[j][r];
+#pragma unroll
+  for (int j = 0; j < 8; ++j)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) s += acc16[j][r];
 #pragma unroll
   for (int i = 0; i < 4 * EXP_PER_MFMA; ++i) s += e[i];
   const size_t wg = (size_t)blockIdx.x * 8 + wave;
