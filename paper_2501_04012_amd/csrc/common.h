@@ -309,19 +309,18 @@ hipError_t launch_cfg_ddim_noise(float* x, const float* eps_c, const float* eps_
 hipError_t launch_gemm(int bf16, int mode, const void* A, const void* Wt, int M, int N, int K,
                        const EpiParams& ep, hipStream_t s, void* scratch = nullptr, size_t scratch_bytes = 0,
                        const void* w_parts = nullptr);
-// Tile of workgroup id `vb` of a product (total or more: none).  32 workgroups running together on one XCD hold 32 consecutive tiles; `spread`: of a last
-// round of fewer than 256 each XCD has an eighth, so that all their L2s and ways to memory serve it.  us, 32 to an XCD until there are none left, and
-// spread: 8192 x 1152 x 1152 in 192 tiles of 256x192 26.4, 23.1; 8192 x 1152 x 4608 90, 85; 9326 x 2048 x 2048 in packed 128x256 72, 67; fp32 step of a
-// 1152-wide block 1489, 1418.
-__host__ __device__ inline int tile_index(int vb, int total, bool spread) {
-  const int round = vb & ~255, xcd = vb & 7, slot = (vb >> 3) & 31, left = total - round, per = !spread || left >= 256 ? 32 : (left + 7) >> 3;
+// Tile of workgroup id `vb` of a product (total or more: none).  32 workgroups running together on one XCD hold 32 consecutive tiles.  Of a last round of
+// fewer than 256 each XCD has an eighth, so that all their L2s and ways to memory serve it: us, 32 to an XCD until there are none left, and an eighth each:
+// 8192 x 1152 x 1152 in 192 tiles of 256x192 26.4, 23.1; 8192 x 1152 x 4608 90, 85; 9326 x 2048 x 2048 in packed 128x256 72, 67; fp32 step of a 1152-wide
+// block 1489, 1418; and with 128x128 tiles alone dealt out the one way and the other, 72 bf16 steps of 150 to 1100 us 0.989 of the time in the mean (0.96 to
+// 1.005; 17 x 32 x 14, 768 wide, four blocks 769, 736).  The price: an eighth of a round straddles the patches of 8 x 4 tiles, whose panels just fit an L2,
+// which tells where the operands lie in the L2s already (the same product again and again, 128x128 tiles: 3600 x 1024 x 1152 13.0, 15.8, 5000 x 512 x 1152
+// 12.8, 15.3; operands by turns 16.0, 16.4 and 15.7, 15.8).
+__host__ __device__ inline int tile_index(int vb, int total) {
+  const int round = vb & ~255, xcd = vb & 7, slot = (vb >> 3) & 31, left = total - round, per = left >= 256 ? 32 : (left + 7) >> 3;
   const int t = round + xcd * per + slot;
   return slot < per && t < total ? t : total;
 }
-// bf16 tiles larger than 128x128.  Those, two or four to a CU, gain nothing (30 products of 500 to 6500 rows, operands by turns: 1.00 of the time, staged
-// and packed) and lose where the operands are in the L2s: an eighth of a round straddles the patches of 8 x 4 tiles, whose panels just fit one (3600 x 1024 x
-// 1152 in 232 tiles 13.0 us, 15.8 spread; packed 11.2, 12.8; 5000 x 512 x 1152 12.8, 15.3).
-constexpr bool spread_round(int bm, int bn) { return bm * bn > 128 * 128; }
 // w_parts (optional): the weights once more, fp32 split into bf16 parts (launch_split_weights, split_weights_bytes), bf16 in
 // fragment order (launch_pack_weights, N * K elements, where packs_weights)
 bool packs_weights(int N, int K);

@@ -330,7 +330,7 @@ __global__ __launch_bounds__(WR * WC * 64) void k_gemm_dlds(const bf16_t* A, con
   // virtual ids run over the whole rounds and, behind them, the units of the last one
   const int padded = splits >= 2 ? ((full + rem * splits + 7) & ~7) : (total + 255) / 256 * 256;
   auto tile_of = [&](int vb, int& bm0, int& bn0, int& kt0, int& kt1, int& slot) {
-    int t = tile_index(vb, total, spread_round(BM, BN));
+    int t = tile_index(vb, total);
     kt0 = 0; kt1 = nkt; slot = -1;
     if (splits >= 2 && vb >= full) {
       const int w = vb - full;
@@ -529,7 +529,7 @@ __global__ __launch_bounds__(256, BN == 128 ? 4 : BN == 192 ? 3 : 2) void k_gemm
   const int total = tiles_m * tiles_n, nk = K / BK, padded = (total + 255) / 256 * 256;
   auto next_tile = [&](int& vb, int& bm0, int& bn0) {      // k_gemm_dlds's order, no split tiles
     for (vb += gridDim.x; vb < padded; vb += gridDim.x) {
-      const int t = tile_index(vb, total, spread_round(BM, BN));
+      const int t = tile_index(vb, total);
       if (t >= total) continue;
       constexpr int gm = kPatchRows;
       const int per_group = gm * tiles_n, group = t / per_group, first_m = group * gm, gsz = min(tiles_m - first_m, gm);
@@ -692,7 +692,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_288(const bf16_t* __restrict__ 
   float* const sbias = (float*)(smem + S * L::kStage);
   float* const sgate = sbias + BN;
 
-  const int total = tiles_m * tiles_n, t = tile_index(blockIdx.x, total, true);
+  const int total = tiles_m * tiles_n, t = tile_index(blockIdx.x, total);
   if (t >= total) return;                                  // k_gemm_dlds's tile order
   constexpr int gm = kPatchRows;
   const int per_group = gm * tiles_n, group = t / per_group, first_m = group * gm, gsz = min(tiles_m - first_m, gm);
@@ -1005,7 +1005,7 @@ __global__ __launch_bounds__(WR * WC * 64) void k_gemm_f32(const float* __restri
   const int wr = wave / WC, wc = wave % WC;
   const int li = lane & 31, lh = lane >> 5;
   // workgroup -> tile as in k_gemm_dlds
-  const int t = tile_index(blockIdx.x, tiles_m * tiles_n, true);
+  const int t = tile_index(blockIdx.x, tiles_m * tiles_n);
   if (t >= tiles_m * tiles_n) return;
   constexpr int gm = kPatchRows;
   const int per_group = gm * tiles_n, group = t / per_group, first_m = group * gm, gsz = min(tiles_m - first_m, gm);
@@ -1161,7 +1161,7 @@ __global__ __launch_bounds__(WR * WC * 64, PER_SIMD) void k_gemm_f32_parts(const
   const int wr = wave / WC, wc = wave % WC;
   const int li = lane & 31, lh = lane >> 5;
   // workgroup -> tile as in k_gemm_dlds
-  const int t = tile_index(blockIdx.x, tiles_m * tiles_n, true);
+  const int t = tile_index(blockIdx.x, tiles_m * tiles_n);
   if (t >= tiles_m * tiles_n) return;
   constexpr int gm = kPatchRows;
   const int per_group = gm * tiles_n, group = t / per_group, first_m = group * gm, gsz = min(tiles_m - first_m, gm);
